@@ -82,6 +82,18 @@ __device__ __forceinline__ int64_t eff_n(int64_t n, const int64_t* dn) {
   return dn ? min(n, *dn) : n;
 }
 
+// a / b correctly rounded to binary32, given inv_b = 1.0 / (double)b: the product
+// a inv_b is within 2^-52 of the quotient, and the quotient of two 24-bit
+// significands is at least 2^-49 away from every midpoint of binary32 (a
+// midpoint's 25 bits times b's never make a 24-bit a exactly), so rounding the
+// product gives the rounded quotient.  Results near the subnormal range, where
+// midpoints have fewer bits, take the division.
+__device__ __forceinline__ float quot_rn(float a, double inv_b, float b) {
+  const double q = (double)a * inv_b;
+  if (fabs(q) >= 0x1p-120) return (float)q;
+  return (float)((double)a / (double)b);
+}
+
 __device__ __forceinline__ int64_t floordiv_i64(int64_t a, int64_t b) {
   int64_t q = a / b;
   return (a % b != 0 && ((a < 0) != (b < 0))) ? q - 1 : q;
