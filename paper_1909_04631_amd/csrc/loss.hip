@@ -12,9 +12,9 @@
 //
 // Rows and queries are bucketed in cells slightly larger than l, so a point's
 // support lies in its own cell and the 26 around it.  Kernel weights are
-// recomputed in the backward pass; nothing per pair is stored.  Each query (or
-// training row) is owned by one lane; scalar gradients are reduced in double
-// in a fixed order (deterministic, no floating-point atomics).
+// recomputed in the backward pass; nothing per pair is stored.  A query is
+// owned by one wavefront, whose lanes take its rows, a training row by one lane;
+// every sum is taken in a fixed order (deterministic, no floating-point atomics).
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -182,92 +182,257 @@ __global__ void __launch_bounds__(256) k_validate(const float* __restrict__ txyz
   }
 }
 
-// alpha at each query, in query order.
-__global__ void k_alpha_q(LossArgs a, const float* __restrict__ qxyz, float* __restrict__ alpha_q) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= a.H) return;
-  float* A = alpha_q + h * a.K;
-  for (int k = 0; k < a.K; ++k) A[k] = a.alpha0;
-  for_neighbours(a, qxyz[3 * h], qxyz[3 * h + 1], qxyz[3 * h + 2],
-                 [&](const float4& p, float, float, float, float d2, int32_t) {
-                   const float d = __builtin_sqrtf(d2);
-                   const float s = fmaxf(fmaf(-d, a.inv_l, 1.0f), 0.0f);
-                   A[__float_as_int(p.w)] += kernel_weight(a.coef, s);
-                 });
+// ---------------------------------------------------------------------------
+// Query side: one wavefront per query, lanes over the rows around it.  A query
+// meets 10^2 to 10^4 rows and every row is one 16-byte record, so what bounds
+// these kernels is the latency of dependent loads: one lane per query, as
+// before, walked them one after the other with a read-modify-write of global
+// memory for each (room scene, 380 queries: 4.4 ms forward, now 0.02; LiDAR
+// scan, 2.4e4 queries: 1.8 ms).
+//
+// The 27 cells are nine columns along z, each one run of sorted rows per block
+// that it crosses: lanes 0..17 look the runs up together.  Lane i then takes
+// rows i, i + 64, ... of the runs' concatenation.
+// ---------------------------------------------------------------------------
+constexpr int kRuns = 32;   // at most 18 used; a power of two for the search
+struct RunTable {
+  float4 at[kRuns];       // the point relative to the run's block centre; .w: first row minus
+                          // the rows of the runs before it (as bits)
+  int32_t incl[kRuns];    // rows up to and including the run; INT32_MAX past the last run
+};
+
+// Fills the table for point (x, y, z) (all 64 lanes); returns the rows in all runs.
+__device__ __forceinline__ int32_t find_runs(const LossArgs& a, float x, float y, float z,
+                                             RunTable& t) {
+  const BucketGeom& g = a.g;
+  const int lane = threadIdx.x;
+  const int cx = cell_of(x, g.res), cy = cell_of(y, g.res), cz = cell_of(z, g.res);
+  const int col = lane >> 1, part = lane & 1;
+  const int vx = cx + col / 3 - 1, vy = cy + col % 3 - 1;
+  const int bx = vx >> LLOG2B, by = vy >> LLOG2B, b0 = (cz - 1) >> LLOG2B, b1 = (cz + 1) >> LLOG2B;
+  const int bz = part ? b1 : b0;
+  const int z0 = part ? b1 * LB : cz - 1, z1 = part || b0 == b1 ? cz + 1 : b0 * LB + LB - 1;
+  const int px = bx - g.blo[0], py = by - g.blo[1], pz = bz - g.blo[2];
+  int32_t first = 0, n = 0;
+  if (lane < 18 && !(part && b0 == b1) && px >= 0 && py >= 0 && pz >= 0 && px < g.nb[0] &&
+      py < g.nb[1] && pz < g.nb[2]) {
+    const int32_t slot = a.dense[((int64_t)px * g.nb[1] + py) * g.nb[2] + pz];
+    if (slot >= 0) {
+      const int32_t c0 = ((vx - bx * LB) * LB + (vy - by * LB)) * LB - bz * LB;
+      const int32_t* P = a.prefix + (int64_t)slot * (LB * LB * LB + 1);
+      first = P[c0 + z0];
+      n = P[c0 + z1 + 1] - first;
+    }
+  }
+  int32_t inc = n;
+#pragma unroll
+  for (int o = 1; o < 32; o <<= 1) {
+    const int32_t v = __shfl_up(inc, o, SMKI_WAVE);
+    if (lane >= o) inc += v;
+  }
+  const uint64_t some = __ballot(n > 0);
+  __syncthreads();   // (the previous point's table is no longer read)
+  if (lane < kRuns && lane >= __popcll(some)) t.incl[lane] = INT32_MAX;
+  if (n > 0) {
+    const int k = __popcll(some & ((1ull << lane) - 1ull));
+    const double h = (double)g.res;
+    t.incl[k] = inc;
+    // the point relative to the exact centre of block (bx, by, bz)
+    t.at[k] = make_float4((float)((double)x - ((double)(bx * LB) + 0.5 * LB) * h),
+                          (float)((double)y - ((double)(by * LB) + 0.5 * LB) * h),
+                          (float)((double)z - ((double)(bz * LB) + 0.5 * LB) * h),
+                          __int_as_float(first - (inc - n)));
+  }
+  __syncthreads();
+  return __builtin_amdgcn_readlane(inc, 17);
 }
 
-// loss = -(1/H) sum_h log(alpha[h][y_h] / S_h), double accumulation, fixed order
-__global__ void __launch_bounds__(256) k_loss_value(const float* __restrict__ alpha_q,
-                                                    const int32_t* __restrict__ qlab, int64_t H,
-                                                    int32_t K, float* __restrict__ loss) {
-  __shared__ double part[256];
-  double s = 0.0;
-  for (int64_t h = threadIdx.x; h < H; h += 256) {
-    const float* A = alpha_q + h * K;
-    double S = 0.0;
-    for (int k = 0; k < K; ++k) S += (double)A[k];
-    s += log((double)A[qlab[h]] / S);
+// Visits the rows of the table, 64 at a time: fn(in, record, dx, dy, dz, d2) is
+// called by every lane, in = this lane holds a row within the search cut.
+template <typename Fn>
+__device__ __forceinline__ void for_rows(const LossArgs& a, const RunTable& t, int32_t total, Fn fn) {
+  for (int32_t b = 0; b < total; b += SMKI_WAVE) {
+    const int32_t i = b + (int32_t)threadIdx.x;
+    const bool live = i < total;
+    int k = 0;   // the run of row i: the first whose inclusive count exceeds it
+#pragma unroll
+    for (int st = kRuns / 2; st > 0; st >>= 1)
+      if (t.incl[k + st - 1] <= i) k += st;
+    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
+    float dx = 0.f, dy = 0.f, dz = 0.f;
+    if (live) {
+      const float4 q = t.at[k];
+      p = a.pts[__float_as_int(q.w) + i];
+      dx = p.x - q.x;
+      dy = p.y - q.y;
+      dz = p.z - q.z;
+    }
+    const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+    fn(live && d2 < a.l2, p, dx, dy, dz, d2);
   }
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
+}
+
+template <typename T>
+__device__ __forceinline__ T wave_sum(T v) {
+#pragma unroll
+  for (int o = SMKI_WAVE / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, SMKI_WAVE);
+  return v;
+}
+
+// Sums per class in LDS, spread over COLS columns: lanes l, l + COLS, ... share
+// column l % COLS and take turns (a barrier of the one-wavefront workgroup
+// between them), so each sum has one order.
+template <typename T, int COLS>
+__device__ __forceinline__ void class_add(T* bins, bool in, int32_t c, T v) {
+  const int lane = threadIdx.x;
+  if constexpr (COLS == SMKI_WAVE) {
+    if (in) bins[c * COLS + lane] += v;
+  } else {
+#pragma unroll
+    for (int r = 0; r < SMKI_WAVE / COLS; ++r) {
+      if (in && lane / COLS == r) bins[c * COLS + lane % COLS] += v;
+      __syncthreads();
+    }
+  }
+}
+
+// Sum of class c's columns in double (callers' lanes hold consecutive classes:
+// the rotated order keeps their reads in different banks).
+template <typename T, int COLS>
+__device__ __forceinline__ double class_total(const T* bins, int32_t c) {
+  double s = 0.0;
+  for (int j = 0; j < COLS; ++j) s += (double)bins[c * COLS + ((j + c) & (COLS - 1))];
+  return s;
+}
+
+// alpha at each query, in query order, and the query's term of the loss,
+// log(alpha[h][y_h] / S_h).  PC: per-class kernels.
+template <bool PC, int COLS>
+__global__ void __launch_bounds__(SMKI_WAVE) k_alpha_q(LossArgs a, const float* __restrict__ qxyz,
+                                                       const int32_t* __restrict__ qlab,
+                                                       float* __restrict__ alpha_q,
+                                                       double* __restrict__ term) {
+  __shared__ RunTable t;
+  extern __shared__ float bins[];   // [K][COLS]
+  const int lane = threadIdx.x;
+  for (int64_t h = blockIdx.x; h < a.H; h += gridDim.x) {
+    for (int i = lane; i < a.K * COLS; i += SMKI_WAVE) bins[i] = 0.0f;
+    const int32_t total = find_runs(a, qxyz[3 * h], qxyz[3 * h + 1], qxyz[3 * h + 2], t);
+    for_rows(a, t, total, [&](bool in, const float4& p, float, float, float, float d2) {
+      const int32_t y = __float_as_int(p.w);
+      float v;
+      if constexpr (PC) {
+        const float4 c = a.cls[in ? y : 0];
+        in = in && d2 < c.x;
+        const float s = fmaxf(fmaf(-__builtin_sqrtf(d2), c.y, 1.0f), 0.0f);
+        v = c.z * kernel_weight(a.coef, s);
+      } else {
+        const float s = fmaxf(fmaf(-__builtin_sqrtf(d2), a.inv_l, 1.0f), 0.0f);
+        v = kernel_weight(a.coef, s);
+      }
+      class_add<float, COLS>(bins, in, y, v);
+    });
+    __syncthreads();
+    const int32_t yh = qlab[h];
+    double S = 0.0, ay = 0.0;
+    for (int32_t k = lane; k < a.K; k += SMKI_WAVE) {
+      const float v = (float)((double)a.alpha0 + class_total<float, COLS>(bins, k));
+      alpha_q[h * a.K + k] = v;
+      S += (double)v;
+      if (k == yh) ay = (double)v;
+    }
+    S = wave_sum(S);
+    ay = wave_sum(ay);   // (one lane holds it)
+    if (lane == 0) term[h] = log(ay / S);
     __syncthreads();
   }
-  if (threadIdx.x == 0) *loss = (float)(-part[0] / (double)H);
 }
 
-// Per query: 1/S, 1/alpha_y, and its closed-form dloss/dsigma0 share
-//   sum_k G_hk (alpha_hk - alpha0) / sigma0 = -(g/(H sigma0)) (K alpha0/S - alpha0/alpha_y).
-__global__ void k_prep(const float* __restrict__ alpha_q, const int32_t* __restrict__ qlab, int64_t H,
-                       int32_t K, float alpha0, float sigma0, const float* __restrict__ gscale,
-                       float* __restrict__ inv_s, float* __restrict__ inv_ay,
-                       double* __restrict__ dsig) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= H) return;
-  const float* A = alpha_q + h * K;
-  double S = 0.0;
-  for (int k = 0; k < K; ++k) S += (double)A[k];
-  const double ay = (double)A[qlab[h]];
-  inv_s[h] = (float)(1.0 / S);
-  inv_ay[h] = (float)(1.0 / ay);
-  const double g = (double)gscale[0];
-  dsig[h] = -(g / ((double)H * (double)sigma0)) * ((double)K * alpha0 / S - (double)alpha0 / ay);
-}
-
-// Query-side adjoint: dloss/dx_h and the per-query share of dloss/dl.
-__global__ void k_query_grad(LossArgs a, const float* __restrict__ qxyz,
-                             const int32_t* __restrict__ qlab, const float* __restrict__ inv_s,
-                             const float* __restrict__ inv_ay, const float* __restrict__ gscale,
-                             float* __restrict__ grad_q, double* __restrict__ dl_part) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= a.H) return;
+// Query-side adjoint: dloss/dx_h, 1/S_h and 1/alpha_y (for the training side), and
+// the query's shares of the scalar gradients: dl_part[h] and, in closed form,
+//   sum_k G_hk (alpha_hk - alpha0) / sigma0 = -(g/(H sigma0)) (K alpha0/S - alpha0/alpha_y),
+// or (PC) dl[h][k] and ds[h][k] per class.
+template <bool PC, int COLS>
+__global__ void __launch_bounds__(SMKI_WAVE) k_query_grad(
+    LossArgs a, const float* __restrict__ qxyz, const int32_t* __restrict__ qlab,
+    const float* __restrict__ alpha_q, const float* __restrict__ gscale,
+    float* __restrict__ inv_s, float* __restrict__ inv_ay, float* __restrict__ grad_q,
+    double* __restrict__ dl_part, double* __restrict__ dsig, double* __restrict__ dl,
+    double* __restrict__ ds) {
+  __shared__ RunTable t;
+  extern __shared__ double dbins[];   // PC: [2][K][COLS]
+  const int lane = threadIdx.x;
   const float gH = gscale[0] / (float)a.H;
-  const int32_t yh = qlab[h];
-  const float is = inv_s[h], ia = inv_ay[h];
-  float gx = 0.f, gy = 0.f, gz = 0.f;
-  double dl = 0.0;
-  const float il2 = a.inv_l * a.inv_l;
-  for_neighbours(a, qxyz[3 * h], qxyz[3 * h + 1], qxyz[3 * h + 2],
-                 [&](const float4& p, float dx, float dy, float dz, float d2, int32_t) {
-                   const int32_t yt = __float_as_int(p.w);
-                   const float G = -gH * ((yt == yh ? ia : 0.0f) - is);
-                   const float d = __builtin_sqrtf(d2);
-                   const float r = d * a.inv_l;
-                   const float s = fmaxf(1.0f - r, 0.0f);
-                   const float gr = a.sigma0 * dfdr_over_r(s);      // sigma0 f'(r)/r
-                   const float c = G * gr * il2;                    // coefficient of (x_t - x_h)
-                   gx -= c * dx;
-                   gy -= c * dy;
-                   gz -= c * dz;
-                   dl += (double)(-G * gr * r * r * a.inv_l);       // G sigma0 f'(r) (-r/l)
-                 });
-  if (grad_q) {
-    grad_q[3 * h] = gx;
-    grad_q[3 * h + 1] = gy;
-    grad_q[3 * h + 2] = gz;
+  for (int64_t h = blockIdx.x; h < a.H; h += gridDim.x) {
+    const int32_t yh = qlab[h];
+    double S = 0.0;
+    for (int32_t k = lane; k < a.K; k += SMKI_WAVE) S += (double)alpha_q[h * a.K + k];
+    S = wave_sum(S);
+    const double ay = (double)alpha_q[h * a.K + yh];
+    const float is = (float)(1.0 / S), ia = (float)(1.0 / ay);
+    double* DL = dbins;
+    double* DS = dbins + (PC ? a.K * COLS : 0);
+    if constexpr (PC)
+      for (int i = lane; i < 2 * a.K * COLS; i += SMKI_WAVE) dbins[i] = 0.0;
+    const int32_t total = find_runs(a, qxyz[3 * h], qxyz[3 * h + 1], qxyz[3 * h + 2], t);
+    float gx = 0.f, gy = 0.f, gz = 0.f;
+    double dlh = 0.0;
+    for_rows(a, t, total, [&](bool in, const float4& p, float dx, float dy, float dz, float d2) {
+      const int32_t yt = __float_as_int(p.w);
+      float inv_l = a.inv_l, s0 = a.sigma0;
+      if constexpr (PC) {
+        const float4 c = a.cls[in ? yt : 0];
+        in = in && d2 < c.x;
+        inv_l = c.y;
+        s0 = c.z;
+      }
+      const float G = -gH * ((yt == yh ? ia : 0.0f) - is);
+      const float r = __builtin_sqrtf(d2) * inv_l;
+      const float s = fmaxf(1.0f - r, 0.0f);
+      const float gr = s0 * dfdr_over_r(s);                // sigma0 f'(r)/r
+      if (in) {
+        const float c = G * gr * (inv_l * inv_l);          // coefficient of (x_t - x_h)
+        gx -= c * dx;
+        gy -= c * dy;
+        gz -= c * dz;
+      }
+      const double vl = (double)(-G * gr * r * r * inv_l);   // G sigma0 f'(r) (-r/l)
+      if constexpr (PC) {
+        class_add<double, COLS>(DL, in, yt, vl);
+        class_add<double, COLS>(DS, in, yt, (double)(G * kernel_weight(a.coef, s)));
+      } else if (in) {
+        dlh += vl;
+      }
+    });
+    gx = wave_sum(gx);
+    gy = wave_sum(gy);
+    gz = wave_sum(gz);
+    if constexpr (PC) {
+      __syncthreads();
+      for (int32_t k = lane; k < a.K; k += SMKI_WAVE) {
+        dl[h * a.K + k] = class_total<double, COLS>(DL, k);
+        ds[h * a.K + k] = class_total<double, COLS>(DS, k);
+      }
+      __syncthreads();
+    } else {
+      dlh = wave_sum(dlh);
+    }
+    if (lane == 0) {
+      inv_s[h] = is;
+      inv_ay[h] = ia;
+      if (grad_q) {
+        grad_q[3 * h] = gx;
+        grad_q[3 * h + 1] = gy;
+        grad_q[3 * h + 2] = gz;
+      }
+      if constexpr (!PC) {
+        const double g = (double)gscale[0];
+        dl_part[h] = dlh;
+        dsig[h] = -(g / ((double)a.H * (double)a.sigma0)) *
+                  ((double)a.K * a.alpha0 / S - (double)a.alpha0 / ay);
+      }
+    }
   }
-  dl_part[h] = dl;
 }
 
 // Training-side adjoint: dloss/dx_t, walking the bucketed queries around each row.
@@ -306,64 +471,6 @@ __global__ void k_train_grad(LossArgs a, const float* __restrict__ txyz,
 //   dloss/dsigma0_k = sum over pairs with y_t = k  G_{h,k} f(r)
 // per query into dl[h][k], ds[h][k] (double), then summed per class in a fixed order.
 // ---------------------------------------------------------------------------
-__global__ void k_alpha_q_pc(LossArgs a, const float* __restrict__ qxyz,
-                             float* __restrict__ alpha_q) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= a.H) return;
-  float* A = alpha_q + h * a.K;
-  for (int k = 0; k < a.K; ++k) A[k] = a.alpha0;
-  for_neighbours(a, qxyz[3 * h], qxyz[3 * h + 1], qxyz[3 * h + 2],
-                 [&](const float4& p, float, float, float, float d2, int32_t) {
-                   const int32_t y = __float_as_int(p.w);
-                   const float4 c = a.cls[y];
-                   if (!(d2 < c.x)) return;
-                   const float d = __builtin_sqrtf(d2);
-                   const float s = fmaxf(fmaf(-d, c.y, 1.0f), 0.0f);
-                   A[y] += c.z * kernel_weight(a.coef, s);
-                 });
-}
-
-__global__ void k_query_grad_pc(LossArgs a, const float* __restrict__ qxyz,
-                                const int32_t* __restrict__ qlab, const float* __restrict__ inv_s,
-                                const float* __restrict__ inv_ay, const float* __restrict__ gscale,
-                                float* __restrict__ grad_q, double* __restrict__ dl,
-                                double* __restrict__ ds) {
-  const int64_t h = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= a.H) return;
-  const float gH = gscale[0] / (float)a.H;
-  const int32_t yh = qlab[h];
-  const float is = inv_s[h], ia = inv_ay[h];
-  double* DL = dl + h * a.K;
-  double* DS = ds + h * a.K;
-  for (int k = 0; k < a.K; ++k) {
-    DL[k] = 0.0;
-    DS[k] = 0.0;
-  }
-  float gx = 0.f, gy = 0.f, gz = 0.f;
-  for_neighbours(a, qxyz[3 * h], qxyz[3 * h + 1], qxyz[3 * h + 2],
-                 [&](const float4& p, float dx, float dy, float dz, float d2, int32_t) {
-                   const int32_t yt = __float_as_int(p.w);
-                   const float4 c = a.cls[yt];
-                   if (!(d2 < c.x)) return;
-                   const float G = -gH * ((yt == yh ? ia : 0.0f) - is);
-                   const float d = __builtin_sqrtf(d2);
-                   const float r = d * c.y;
-                   const float s = fmaxf(1.0f - r, 0.0f);
-                   const float gr = c.z * dfdr_over_r(s);          // sigma0_k f'(r)/r
-                   const float cc = G * gr * (c.y * c.y);          // coefficient of (x_t - x_h)
-                   gx -= cc * dx;
-                   gy -= cc * dy;
-                   gz -= cc * dz;
-                   DL[yt] += (double)(-G * gr * r * r * c.y);     // G sigma0_k f'(r) (-r/l_k)
-                   DS[yt] += (double)(G * kernel_weight(a.coef, s));
-                 });
-  if (grad_q) {
-    grad_q[3 * h] = gx;
-    grad_q[3 * h + 1] = gy;
-    grad_q[3 * h + 2] = gz;
-  }
-}
-
 __global__ void k_train_grad_pc(LossArgs a, const float* __restrict__ txyz,
                                 const int32_t* __restrict__ tlab, int64_t n_train,
                                 const int32_t* __restrict__ qlab, const float* __restrict__ inv_s,
@@ -393,34 +500,45 @@ __global__ void k_train_grad_pc(LossArgs a, const float* __restrict__ txyz,
   grad_t[3 * t + 2] = gz;
 }
 
-// out[k] = sum_h v[h][k] (one workgroup per class, fixed order)
-__global__ void __launch_bounds__(256) k_colsum_f64(const double* __restrict__ v, int64_t H,
-                                                    int32_t K, float* __restrict__ out) {
-  __shared__ double part[256];
-  const int32_t k = blockIdx.x;
-  double s = 0.0;
-  for (int64_t h = threadIdx.x; h < H; h += 256) s += v[h * K + k];
+// Sums over queries in a fixed order (one workgroup each): thread t adds entries
+// t, t + 1024, ..., then a tree over the threads.
+constexpr int kSumThreads = 1024;
+__device__ __forceinline__ double block_sum(double s) {
+  __shared__ double part[kSumThreads];
   part[threadIdx.x] = s;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
+  for (int o = kSumThreads / 2; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[k] = (float)part[0];
+  return part[0];
 }
 
-__global__ void __launch_bounds__(256) k_sum_f64(const double* __restrict__ v, int64_t n,
-                                                 float* __restrict__ out) {
-  __shared__ double part[256];
+// loss = -(1/H) sum_h term[h]
+__global__ void __launch_bounds__(kSumThreads) k_loss_value(const double* __restrict__ term,
+                                                            int64_t H, float* __restrict__ loss) {
   double s = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) s += v[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = (float)part[0];
+  for (int64_t h = threadIdx.x; h < H; h += kSumThreads) s += term[h];
+  s = block_sum(s);
+  if (threadIdx.x == 0) *loss = (float)(-s / (double)H);
+}
+
+// out[k] = sum_h v[h][k], one workgroup per class: workgroups [0, K) sum v0, the
+// next K sum v1 (a null output is skipped)
+__global__ void __launch_bounds__(kSumThreads) k_colsum2(const double* __restrict__ v0,
+                                                         float* __restrict__ out0,
+                                                         const double* __restrict__ v1,
+                                                         float* __restrict__ out1, int64_t H,
+                                                         int32_t K) {
+  const bool second = (int32_t)blockIdx.x >= K;
+  const double* v = second ? v1 : v0;
+  float* out = second ? out1 : out0;
+  if (!out) return;   // (the whole workgroup)
+  const int32_t k = (int32_t)blockIdx.x - (second ? K : 0);
+  double s = 0.0;
+  for (int64_t h = threadIdx.x; h < H; h += kSumThreads) s += v[h * K + k];
+  s = block_sum(s);
+  if (threadIdx.x == 0) out[k] = (float)s;
 }
 
 inline unsigned nblk(int64_t n, int t) { return (unsigned)ceil_div_i64(n > 0 ? n : 1, t); }
@@ -507,6 +625,44 @@ smki_status err_status(uint32_t e) {
 }
 
 constexpr int kValidateGrid = 1024;   // workgroups per set in the validation
+
+constexpr int64_t kQueryGrid = 1 << 20;   // workgroups of the query-side kernels (they stride)
+
+// The query-side kernels; few classes take a column per lane (float) or 16
+// columns (double), many take fewer columns, so that the sums stay within 33 KB.
+void launch_alpha_q(bool pc, const LossArgs& a, const float* qxyz, const int32_t* qlab, float* A,
+                    double* term, hipStream_t st) {
+  const dim3 grid((unsigned)std::min<int64_t>(a.H, kQueryGrid)), block(SMKI_WAVE);
+  const bool few = a.K <= 64;
+  const unsigned lds = (unsigned)(sizeof(float) * a.K * (few ? 64 : 16));
+  if (pc && few)
+    hipLaunchKernelGGL((k_alpha_q<true, 64>), grid, block, lds, st, a, qxyz, qlab, A, term);
+  else if (pc)
+    hipLaunchKernelGGL((k_alpha_q<true, 16>), grid, block, lds, st, a, qxyz, qlab, A, term);
+  else if (few)
+    hipLaunchKernelGGL((k_alpha_q<false, 64>), grid, block, lds, st, a, qxyz, qlab, A, term);
+  else
+    hipLaunchKernelGGL((k_alpha_q<false, 16>), grid, block, lds, st, a, qxyz, qlab, A, term);
+}
+
+void launch_query_grad(bool pc, const LossArgs& a, const float* qxyz, const int32_t* qlab,
+                       const float* alpha_q, const float* gscale, const LossBufs& b, float* grad_q,
+                       hipStream_t st) {
+  const dim3 grid((unsigned)std::min<int64_t>(a.H, kQueryGrid)), block(SMKI_WAVE);
+  if (!pc) {
+    hipLaunchKernelGGL((k_query_grad<false, 16>), grid, block, 0, st, a, qxyz, qlab, alpha_q, gscale,
+                       b.inv_s, b.inv_ay, grad_q, b.dl, b.dsig, b.dlk, b.dsk);
+    return;
+  }
+  const bool few = a.K <= 64;
+  const unsigned lds = (unsigned)(2 * sizeof(double) * a.K * (few ? 16 : 8));
+  if (few)
+    hipLaunchKernelGGL((k_query_grad<true, 16>), grid, block, lds, st, a, qxyz, qlab, alpha_q,
+                       gscale, b.inv_s, b.inv_ay, grad_q, b.dl, b.dsig, b.dlk, b.dsk);
+  else
+    hipLaunchKernelGGL((k_query_grad<true, 8>), grid, block, lds, st, a, qxyz, qlab, alpha_q,
+                       gscale, b.inv_s, b.inv_ay, grad_q, b.dl, b.dsig, b.dlk, b.dsk);
+}
 
 char* align_up(char* p) { return (char*)(((uintptr_t)p + kAl - 1) / kAl * kAl); }
 
@@ -643,8 +799,9 @@ extern "C" smki_status smki_loss_forward(const float* txyz, const int32_t* tlab,
   if (rc == SMKI_OK) {
     const LossArgs a = make_args(g, b.tr, l, sigma0, alpha0, K, nq);
     float* A = alpha_q ? alpha_q : b.alpha_q;
-    hipLaunchKernelGGL(k_alpha_q, dim3(nblk(nq, 64)), dim3(64), 0, st, a, qxyz, A);
-    hipLaunchKernelGGL(k_loss_value, dim3(1), dim3(256), 0, st, (const float*)A, qlab, nq, K, loss);
+    launch_alpha_q(false, a, qxyz, qlab, A, b.dl, st);
+    hipLaunchKernelGGL(k_loss_value, dim3(1), dim3(kSumThreads), 0, st, (const double*)b.dl, nq,
+                       loss);
     if (hipGetLastError() != hipSuccess) rc = SMKI_E_DEVICE;
   }
   release(own, st);
@@ -668,16 +825,11 @@ extern "C" smki_status smki_loss_backward(const float* txyz, const int32_t* tlab
   smki_status rc = prepare(txyz, tlab, nt, qxyz, qlab, nq, l, K, grad_train != nullptr,
                            (char*)workspace, ws_bytes, own, b, g, st);
   if (rc == SMKI_OK) {
-    hipLaunchKernelGGL(k_prep, dim3(nblk(nq, 256)), dim3(256), 0, st, alpha_q, qlab, nq, K, alpha0,
-                       sigma0, grad_loss, b.inv_s, b.inv_ay, b.dsig);
-    if (grad_sigma0)
-      hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(256), 0, st, (const double*)b.dsig, nq,
-                         grad_sigma0);
     const LossArgs aq = make_args(g, b.tr, l, sigma0, alpha0, K, nq);
-    hipLaunchKernelGGL(k_query_grad, dim3(nblk(nq, 64)), dim3(64), 0, st, aq, qxyz, qlab,
-                       (const float*)b.inv_s, (const float*)b.inv_ay, grad_loss, grad_query, b.dl);
-    if (grad_l)
-      hipLaunchKernelGGL(k_sum_f64, dim3(1), dim3(256), 0, st, (const double*)b.dl, nq, grad_l);
+    launch_query_grad(false, aq, qxyz, qlab, alpha_q, grad_loss, b, grad_query, st);
+    if (grad_l || grad_sigma0)
+      hipLaunchKernelGGL(k_colsum2, dim3(2), dim3(kSumThreads), 0, st, (const double*)b.dl, grad_l,
+                         (const double*)b.dsig, grad_sigma0, nq, 1);
     if (grad_train && nt > 0) {
       const LossArgs at = make_args(g, b.qu, l, sigma0, alpha0, K, nq);
       hipLaunchKernelGGL(k_train_grad, dim3(nblk(nt, 64)), dim3(64), 0, st, at, txyz, tlab, nt,
@@ -737,8 +889,9 @@ extern "C" smki_status smki_loss_forward_classes(const float* txyz, const int32_
   if (rc == SMKI_OK) {
     const LossArgs a = make_args_pc(g, b.tr, lmax, b.cls, alpha0, K, nq);
     float* A = alpha_q ? alpha_q : b.alpha_q;
-    hipLaunchKernelGGL(k_alpha_q_pc, dim3(nblk(nq, 64)), dim3(64), 0, st, a, qxyz, A);
-    hipLaunchKernelGGL(k_loss_value, dim3(1), dim3(256), 0, st, (const float*)A, qlab, nq, K, loss);
+    launch_alpha_q(true, a, qxyz, qlab, A, b.dl, st);
+    hipLaunchKernelGGL(k_loss_value, dim3(1), dim3(kSumThreads), 0, st, (const double*)b.dl, nq,
+                       loss);
     if (hipGetLastError() != hipSuccess) rc = SMKI_E_DEVICE;
   }
   release(own, st);
@@ -762,19 +915,11 @@ extern "C" smki_status smki_loss_backward_classes(
   smki_status rc = prepare(txyz, tlab, nt, qxyz, qlab, nq, lmax, K, grad_train != nullptr,
                            (char*)workspace, ws_bytes, own, b, g, st, tab);
   if (rc == SMKI_OK) {
-    // 1/S and 1/alpha_y per query (the single-kernel sigma0 share is not used here)
-    hipLaunchKernelGGL(k_prep, dim3(nblk(nq, 256)), dim3(256), 0, st, alpha_q, qlab, nq, K, alpha0,
-                       1.0f, grad_loss, b.inv_s, b.inv_ay, b.dsig);
     const LossArgs aq = make_args_pc(g, b.tr, lmax, b.cls, alpha0, K, nq);
-    hipLaunchKernelGGL(k_query_grad_pc, dim3(nblk(nq, 64)), dim3(64), 0, st, aq, qxyz, qlab,
-                       (const float*)b.inv_s, (const float*)b.inv_ay, grad_loss, grad_query,
-                       b.dlk, b.dsk);
-    if (grad_l)
-      hipLaunchKernelGGL(k_colsum_f64, dim3(K), dim3(256), 0, st, (const double*)b.dlk, nq, K,
-                         grad_l);
-    if (grad_sigma0)
-      hipLaunchKernelGGL(k_colsum_f64, dim3(K), dim3(256), 0, st, (const double*)b.dsk, nq, K,
-                         grad_sigma0);
+    launch_query_grad(true, aq, qxyz, qlab, alpha_q, grad_loss, b, grad_query, st);
+    if (grad_l || grad_sigma0)
+      hipLaunchKernelGGL(k_colsum2, dim3(2 * K), dim3(kSumThreads), 0, st, (const double*)b.dlk,
+                         grad_l, (const double*)b.dsk, grad_sigma0, nq, K);
     if (grad_train && nt > 0) {
       const LossArgs at = make_args_pc(g, b.qu, lmax, b.cls, alpha0, K, nq);
       hipLaunchKernelGGL(k_train_grad_pc, dim3(nblk(nt, 64)), dim3(64), 0, st, at, txyz, tlab, nt,

@@ -36,3 +36,41 @@ def test_last_bad_row_is_an_error(n, q, bad):
         with pytest.raises(SmkiError) as e:
             loss_forward(*[cuda(v) for v in args], float(L), float(S0), float(A0), 4)
         assert e.value.status == (-6 if bad == "range" else -5)
+
+
+@pytest.mark.parametrize("per_class", [False, True])
+@pytest.mark.parametrize("n,q,K", [(1, 1, 2), (63, 3, 64), (64, 64, 65), (65, 130, 4),
+                                   (2_000, 129, 255), (3_000, 65, 20)])
+def test_rows_around_a_wavefront_and_many_classes(n, q, K, per_class):
+    # 64 rows at a time per query, in up to 18 runs of sorted rows; sums per class
+    # in 64, 16 or 8 columns; the box spans the origin so that blocks of either
+    # sign meet, and one query lies away from every row
+    from paper_1909_04631_amd import (loss_backward, loss_backward_classes, loss_forward,
+                                      loss_forward_classes)
+    print(f"[case] loss rows={n} queries={q} K={K} per_class={per_class}", flush=True)
+    tx, ty = _rows(n, K, n + K, 0.4 if n < 100 else 0.9)
+    qx, qy = _rows(q, K, q + K + 1, 0.4 if n < 100 else 0.9)
+    qx[-1] = 3.0
+    g = np.ones(1, np.float32)
+    a = [cuda(v) for v in (tx, ty, qx, qy)]
+    if per_class:
+        rng = np.random.default_rng(K)
+        lk = rng.choice(np.array([0.2, 0.25, 0.3], np.float32), K).astype(np.float64)
+        sk = rng.choice(np.array([0.25, 0.5], np.float32), K).astype(np.float64)
+        ref = oracle.loss_classes(tx, ty, qx, qy, K, lk, sk, float(A0))
+        loss, aq = loss_forward_classes(*a, lk, sk, float(A0), K)
+        gl, gs, gt, gq = loss_backward_classes(*a, lk, sk, float(A0), K, aq, cuda(g))
+    else:
+        lk, sk = np.array([float(L)]), np.array([float(S0)])
+        ref = oracle.loss(tx, ty, qx, qy, K, float(L), float(S0), float(A0))
+        loss, aq = loss_forward(*a, float(L), float(S0), float(A0), K)
+        gl, gs, gt, gq = loss_backward(*a, float(L), float(S0), float(A0), K, aq, cuda(g))
+    f = lambda t: t.cpu().numpy().astype(np.float64)  # noqa: E731
+    assert np.max(np.abs(f(aq) - ref["alpha_q"]) / ref["alpha_q"]) <= 1e-5
+    assert abs(float(loss.cpu()) - ref["loss"]) <= 1e-5 * abs(ref["loss"])
+    # one scale for the scalar gradients: they are compared in log parameters
+    got = np.concatenate([lk * f(gl).reshape(-1), sk * f(gs).reshape(-1)])
+    want = np.concatenate([lk * np.reshape(ref["grad_l"], -1), sk * np.reshape(ref["grad_sigma0"], -1)])
+    assert np.linalg.norm(got - want) <= 1e-4 * np.linalg.norm(want)
+    for x, r in ((gt, ref["grad_train"]), (gq, ref["grad_query"])):
+        assert np.linalg.norm(f(x) - r) <= 1e-4 * np.linalg.norm(r)
