@@ -458,56 +458,30 @@ __global__ void __launch_bounds__(HT_THREADS) k_slot_heads(const KeyT* __restric
   }
 }
 
-// Per slot (grid-stride over slots): histogram of the rows' voxel cells in LDS,
-// then the exclusive scan -> prefix[slot][c] = first row of cell c, [B3] = end.
+// Cell table of every slot: prefix[slot][c] = first row of cell c, [B3] = the
+// slot's end.  One wavefront per slot (they stride over the slots), lane c
+// searching the slot's sorted keys for cell c: log2(rows) dependent loads, which
+// the other wavefronts hide.  (A histogram of the rows in LDS and its scan, by a
+// workgroup per slot with four barriers, took 79 us for 3.2e6 rows.)
 template <typename KeyT, int LOG2B3>
-__global__ void __launch_bounds__(256) k_slot_prefix(const KeyT* __restrict__ keys, int64_t n,
+__global__ void __launch_bounds__(256) k_slot_prefix(const KeyT* __restrict__ keys,
                                                      const int32_t* __restrict__ head,
                                                      const int32_t* __restrict__ d_nslots,
                                                      int32_t* __restrict__ prefix) {
   constexpr int B3 = 1 << LOG2B3;
-  constexpr int PER = (B3 + 255) / 256;
-  __shared__ int32_t cnt[B3];
-  __shared__ int32_t wsum[256 / SMKI_WAVE];
-  const int32_t ns = *d_nslots;
-  const int tid = threadIdx.x;
-  for (int32_t s = blockIdx.x; s < ns; s += gridDim.x) {
-    const int32_t r0 = head[s];
-    const int32_t r1 = (s + 1 < ns) ? head[s + 1] : (int32_t)n;
-    for (int c = tid; c < B3; c += 256) cnt[c] = 0;
-    __syncthreads();
-    for (int32_t r = r0 + tid; r < r1; r += 256)
-      atomicAdd(&cnt[(uint32_t)((uint64_t)keys[r] & (uint64_t)(B3 - 1))], 1);
-    __syncthreads();
-    // exclusive scan of cnt: thread tid owns cells [tid * PER, tid * PER + PER)
-    int32_t loc[PER];
-    int32_t tot = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int c = tid * PER + j;
-      loc[j] = c < B3 ? cnt[c] : 0;
-      tot += loc[j];
-    }
-    int32_t inc = tot;   // inclusive scan over the wavefront
-#pragma unroll
-    for (int o = 1; o < SMKI_WAVE; o <<= 1) {
-      const int32_t v = __shfl_up(inc, o, SMKI_WAVE);
-      if ((tid & (SMKI_WAVE - 1)) >= o) inc += v;
-    }
-    if ((tid & (SMKI_WAVE - 1)) == SMKI_WAVE - 1) wsum[tid / SMKI_WAVE] = inc;
-    __syncthreads();
-    int32_t base = r0;
-    for (int w = 0; w < tid / SMKI_WAVE; ++w) base += wsum[w];
-    int32_t run = base + inc - tot;
+  const int32_t ns = *d_nslots, lane = threadIdx.x & (SMKI_WAVE - 1);
+  const int32_t nw = gridDim.x * (256 / SMKI_WAVE);
+  for (int32_t s = blockIdx.x * (256 / SMKI_WAVE) + threadIdx.x / SMKI_WAVE; s < ns; s += nw) {
+    const int32_t r0 = head[s], r1 = head[s + 1];
     int32_t* P = prefix + (int64_t)s * (B3 + 1);
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-      const int c = tid * PER + j;
-      if (c < B3) P[c] = run;
-      run += loc[j];
+    for (int32_t c = lane; c <= B3; c += SMKI_WAVE) {
+      int32_t lo = r0, hi = r1;   // the first row whose cell is at least c
+      while (lo < hi) {
+        const int32_t mid = lo + ((hi - lo) >> 1);
+        if ((int32_t)((uint64_t)keys[mid] & (uint64_t)(B3 - 1)) < c) lo = mid + 1; else hi = mid;
+      }
+      P[c] = lo;
     }
-    if (tid == 0) P[B3] = r1;
-    __syncthreads();
   }
 }
 
@@ -579,7 +553,7 @@ static hipError_t finish_set(PointSet& ps, KeyT* keys, uint32_t* idx, KeyT* akey
   // the last radix pass gathers the records (and weights) into sorted order,
   // if the set keeps sorted records; else they are read through the permutation
   const SortPayload pl{rec_unsorted, ps.pts, scr.wt, ps.wts};
-  const SortPayload* plp = (n > 1 && ps.pts && !dn) ? &pl : nullptr;
+  const SortPayload* plp = ((n > 1 || dn) && ps.pts) ? &pl : nullptr;
   if (sizeof(KeyT) == 4)
     e = radix_sort_u32((uint32_t*)keys, idx, (uint32_t*)akeys, aidx, n, key_bits, scr.sort_tmp, st,
                        plp, idx_iota, dn);
@@ -602,20 +576,9 @@ static hipError_t finish_set(PointSet& ps, KeyT* keys, uint32_t* idx, KeyT* akey
                      dn, log2B3, g.n_blocks, g.planes, scr.slot_excl, ps.dense, ps.slot_lin,
                      ps.head, ps.d_nslots, cap_slots);
   if (!ps.prefix) return hipGetLastError();
-  if (dn) return hipErrorInvalidValue;   // (per-cell tables are built for host counts only)
-  const unsigned grid = (unsigned)std::min<int64_t>(n, 8192);
-  switch (log2B3) {
-    case 6:
-      hipLaunchKernelGGL((k_slot_prefix<KeyT, 6>), dim3(grid), dim3(256), 0, st, keys, n,
-                         ps.head, ps.d_nslots, ps.prefix);
-      break;
-    case 9:
-      hipLaunchKernelGGL((k_slot_prefix<KeyT, 9>), dim3(grid), dim3(256), 0, st, keys, n,
-                         ps.head, ps.d_nslots, ps.prefix);
-      break;
-    default:
-      return hipErrorInvalidValue;
-  }
+  if (log2B3 != 6) return hipErrorInvalidValue;   // (cell tables: blocks of 4^3 cells)
+  hipLaunchKernelGGL((k_slot_prefix<KeyT, 6>), dim3((unsigned)std::min<int64_t>(nblk(n, 4), 4096)),
+                     dim3(256), 0, st, keys, ps.head, ps.d_nslots, ps.prefix);
   return hipGetLastError();
 }
 
@@ -660,20 +623,180 @@ hipError_t bucket_scan(const float* xyz, const int32_t* label, const float* prob
 
 int64_t free_sample_workgroups(int64_t nf) { return nf > 0 ? ceil_div_i64(nf, FREE_WG) : 1; }
 
-hipError_t bucket_rows(const float* xyz, const int32_t* label, int64_t n, const BucketGeom& g,
-                       PointSet& ps, BucketScratch& scr, uint32_t* err, hipStream_t st) {
-  hipError_t e = launch_fill_i32(ps.dense, g.n_blocks * g.planes, -1, st);
-  if (e != hipSuccess || n <= 0) return e;
-  if (g.key_bits <= 32) {
-    hipLaunchKernelGGL(k_row_keys<uint32_t>, dim3(nblk(n, 256)), dim3(256), 0, st, xyz, label, n,
-                       g, (uint32_t*)scr.keys, scr.idx, scr.rec, err);
-    return finish_set<uint32_t>(ps, (uint32_t*)scr.keys, scr.idx, (uint32_t*)scr.akeys, scr.aidx,
-                                scr.rec, g, g.key_bits, scr, st);
+// ---------------------------------------------------------------------------
+// rows and queries of the differentiable form
+// ---------------------------------------------------------------------------
+// The cells within one cell of a query, as one bit per cell (64 cells a block).
+__global__ void k_mark_near(const float* __restrict__ qxyz, int64_t nq, BucketGeom g,
+                            unsigned long long* __restrict__ near) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nq) return;
+  int32_t v[3], b0[3], b1[3];
+  for (int a = 0; a < 3; ++a) {
+    if (!voxel_index(qxyz[3 * i + a], g.res, &v[a])) return;   // (validated before)
+    b0[a] = (v[a] - 1) >> g.log2B;
+    b1[a] = (v[a] + 1) >> g.log2B;
   }
-  hipLaunchKernelGGL(k_row_keys<uint64_t>, dim3(nblk(n, 256)), dim3(256), 0, st, xyz, label, n, g,
-                     (uint64_t*)scr.keys, scr.idx, scr.rec, err);
-  return finish_set<uint64_t>(ps, (uint64_t*)scr.keys, scr.idx, (uint64_t*)scr.akeys, scr.aidx,
-                              scr.rec, g, g.key_bits, scr, st);
+  // bits of one axis: the cells [v - 1, v + 1] that lie in block b
+  auto span = [&](int a, int32_t b) {
+    const int32_t lo = max(v[a] - 1, b * 4) - b * 4, hi = min(v[a] + 1, b * 4 + 3) - b * 4;
+    return (uint32_t)(((1 << (hi - lo + 1)) - 1) << lo);
+  };
+  for (int32_t bx = b0[0]; bx <= b1[0]; ++bx)
+    for (int32_t by = b0[1]; by <= b1[1]; ++by)
+      for (int32_t bz = b0[2]; bz <= b1[2]; ++bz) {
+        const int32_t b[3] = {bx, by, bz};
+        if (!in_grid(g, b)) continue;
+        const uint32_t mx = span(0, bx), my = span(1, by), mz = span(2, bz);
+        unsigned long long m = 0;
+        for (int y = 0; y < 4; ++y)
+          if ((my >> y) & 1) m |= (unsigned long long)mz << (4 * y);
+        unsigned long long m3 = 0;
+        for (int x = 0; x < 4; ++x)
+          if ((mx >> x) & 1) m3 |= m << (16 * x);
+        unsigned long long* w =
+            near + ((int64_t)(bx - g.blo[0]) * g.nb[1] + (by - g.blo[1])) * g.nb[2] + (bz - g.blo[2]);
+        if ((*w & m3) != m3) atomicOr(w, m3);
+      }
+}
+
+// The cell of a row: block, cell in the block and (with near) whether a query
+// lies within one cell of it; rows outside the grid are errors and not near.
+__device__ __forceinline__ bool row_cell(const BucketGeom& g, double inv_res, float x, float y,
+                                         float z, const unsigned long long* __restrict__ near,
+                                         int32_t b[3], int32_t l[3], uint32_t* __restrict__ err) {
+  const float f[3] = {floorf(quot_rn(x, inv_res, g.res)), floorf(quot_rn(y, inv_res, g.res)),
+                      floorf(quot_rn(z, inv_res, g.res))};
+  int32_t v[3];
+  bool ok = true;
+  for (int a = 0; a < 3; ++a) {
+    ok = ok && f[a] >= -(float)SMKI_COORD_LIM && f[a] < (float)SMKI_COORD_LIM;
+    v[a] = ok ? (int32_t)f[a] : 0;
+  }
+  block_of(g, v, b, l);
+  if (!ok || !in_grid(g, b)) {
+    atomicOr(err, DEVERR_RANGE);
+    return false;
+  }
+  if (!near) return true;
+  const int64_t w = ((int64_t)(b[0] - g.blo[0]) * g.nb[1] + (b[1] - g.blo[1])) * g.nb[2] + (b[2] - g.blo[2]);
+  return (near[w] >> ((l[0] * 4 + l[1]) * 4 + l[2])) & 1ull;
+}
+
+// Rows near a query: one bit per row (mask), their count per tile, and the
+// gradient of every other row (zero: it is in no query's support).
+__global__ void __launch_bounds__(HT_THREADS) k_near_count(
+    const float* __restrict__ xyz, int64_t n, BucketGeom g,
+    const unsigned long long* __restrict__ near, unsigned long long* __restrict__ mask,
+    int32_t* __restrict__ tcount, float* __restrict__ grad, uint32_t* __restrict__ err) {
+  __shared__ int32_t wc[HT_THREADS / SMKI_WAVE];
+  const int lane = threadIdx.x & (SMKI_WAVE - 1), w = threadIdx.x / SMKI_WAVE;
+  const int64_t base = (int64_t)blockIdx.x * HT + (int64_t)w * HS;
+  const double inv_res = 1.0 / (double)g.res;
+  int32_t c = 0;
+#pragma unroll 4
+  for (int r = 0; r < HT_ROUNDS; ++r) {
+    const int64_t i = base + r * SMKI_WAVE + lane;
+    bool is = false;
+    if (i < n) {
+      int32_t b[3], l[3];
+      is = row_cell(g, inv_res, xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], near, b, l, err);
+      if (grad && !is) grad[3 * i] = grad[3 * i + 1] = grad[3 * i + 2] = 0.0f;
+    }
+    const uint64_t m = __ballot(is);
+    if (lane == 0 && i < n) mask[i / SMKI_WAVE] = m;
+    c += (int32_t)__popcll(m);
+  }
+  if (lane == 0) wc[w] = c;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t t = 0;
+    for (int q = 0; q < HT_THREADS / SMKI_WAVE; ++q) t += wc[q];
+    tcount[blockIdx.x] = t;
+  }
+}
+
+// Keys and indices of the rows near a query, in row order (tstart: the scan of
+// the tile counts, *n_near its total), and their records, at their indices; then (workgroups from gt on) the
+// queries, plane 1 of the keys, with indices n + h.  dn receives the rows written.
+template <typename KeyT>
+__global__ void __launch_bounds__(HT_THREADS) k_near_keys(
+    const float* __restrict__ xyz, const int32_t* __restrict__ label, int64_t n, int32_t gt,
+    const float* __restrict__ qxyz, const int32_t* __restrict__ qlab, int64_t nq, BucketGeom g,
+    const unsigned long long* __restrict__ mask, const int32_t* __restrict__ tstart,
+    const int32_t* __restrict__ n_near, int64_t* __restrict__ dn, KeyT* __restrict__ keys,
+    uint32_t* __restrict__ idx, float4* __restrict__ rec, uint32_t* __restrict__ err) {
+  const double inv_res = 1.0 / (double)g.res;
+  int32_t b[3], l[3];
+  if (blockIdx.x == 0 && threadIdx.x == 0) *dn = (int64_t)*n_near + nq;
+  if ((int32_t)blockIdx.x >= gt) {
+    const int64_t h = (int64_t)(blockIdx.x - gt) * blockDim.x + threadIdx.x;
+    if (h >= nq) return;
+    const float x = qxyz[3 * h], y = qxyz[3 * h + 1], z = qxyz[3 * h + 2];
+    const int64_t pos = (int64_t)*n_near + h;
+    const bool ok = row_cell(g, inv_res, x, y, z, nullptr, b, l, err);
+    keys[pos] = ok ? make_key<KeyT>(g, 1, b, l) : (KeyT)0;
+    idx[pos] = (uint32_t)(n + h);
+    rec[n + h] = ok ? make_record(g, x, y, z, b, qlab[h]) : make_float4(0, 0, 0, 0);
+    return;
+  }
+  __shared__ int32_t wc[HT_THREADS / SMKI_WAVE];
+  const int lane = threadIdx.x & (SMKI_WAVE - 1), w = threadIdx.x / SMKI_WAVE;
+  const int64_t base = (int64_t)blockIdx.x * HT + (int64_t)w * HS;
+  // lane r holds round r's mask
+  const int64_t word = base / SMKI_WAVE + lane;
+  const uint64_t mine = lane < HT_ROUNDS && word * SMKI_WAVE < n ? mask[word] : 0ull;
+  int32_t c = (int32_t)__popcll(mine);
+#pragma unroll
+  for (int o = SMKI_WAVE / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, SMKI_WAVE);
+  if (lane == 0) wc[w] = c;
+  __syncthreads();
+  int32_t run = tstart[blockIdx.x];
+  for (int q = 0; q < w; ++q) run += wc[q];
+  for (int r = 0; r < HT_ROUNDS; ++r) {
+    const uint64_t m = __shfl(mine, r, SMKI_WAVE);
+    if ((m >> lane) & 1ull) {
+      const int64_t i = base + r * SMKI_WAVE + lane;
+      const float x = xyz[3 * i], y = xyz[3 * i + 1], z = xyz[3 * i + 2];
+      row_cell(g, inv_res, x, y, z, nullptr, b, l, err);
+      const int32_t pos = run + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
+      keys[pos] = make_key<KeyT>(g, 0, b, l);
+      idx[pos] = (uint32_t)i;
+      rec[i] = make_record(g, x, y, z, b, label[i]);   // (the sort gathers records by index)
+    }
+    run += (int32_t)__popcll(m);
+  }
+}
+
+hipError_t bucket_near(const float* txyz, const int32_t* tlab, int64_t nt, const float* qxyz,
+                       const int32_t* qlab, int64_t nq, bool both, const BucketGeom& g, PointSet& ps,
+                       BucketScratch& scr, unsigned long long* near, float* grad_far, int64_t* dn,
+                       int32_t* n_near, uint32_t* err, hipStream_t st) {
+  if (g.key_bits > 32 || g.log2B != 2 || g.planes != (both ? 2 : 1)) return hipErrorInvalidValue;
+  hipError_t e = launch_clear3(ps.d_nslots, 1, (int32_t*)near, near ? 2 * g.n_blocks : 0, ps.dense,
+                               g.n_blocks * g.planes, -1, st);
+  if (e != hipSuccess) return e;
+  const int64_t n_sorted_q = both ? nq : 0;
+  ps.n = nt + n_sorted_q;
+  if (ps.n <= 0) return hipSuccess;
+  if (near && nt > 0)
+    hipLaunchKernelGGL(k_mark_near, dim3(nblk(nq, 256)), dim3(256), 0, st, qxyz, nq, g, near);
+  const int64_t tiles = ceil_div_i64(nt, HT);
+  int32_t* tcount = scr.flag;
+  int32_t* tstart = scr.flag + tiles;
+  unsigned long long* mask = (unsigned long long*)scr.slot_excl;
+  if (nt > 0)
+    hipLaunchKernelGGL(k_near_count, dim3((unsigned)tiles), dim3(HT_THREADS), 0, st, txyz, nt, g,
+                       (const unsigned long long*)near, mask, tcount, grad_far, err);
+  e = scan_excl_i32(tcount, tstart, tiles, n_near, scr.scan_tmp, st);   // (no rows: total 0)
+  if (e != hipSuccess) return e;
+  const int64_t gq = both ? ceil_div_i64(nq, HT_THREADS) : 0;
+  hipLaunchKernelGGL(k_near_keys<uint32_t>, dim3((unsigned)(tiles + gq)), dim3(HT_THREADS), 0, st,
+                     txyz, tlab, nt, (int32_t)tiles, qxyz, qlab, n_sorted_q, g,
+                     (const unsigned long long*)mask, (const int32_t*)tstart,
+                     (const int32_t*)n_near, dn, (uint32_t*)scr.keys, scr.idx, scr.rec, err);
+  return finish_set<uint32_t>(ps, (uint32_t*)scr.keys, scr.idx, (uint32_t*)scr.akeys, scr.aidx,
+                              scr.rec, g, g.key_bits, scr, st, false, dn);
 }
 
 // ---------------------------------------------------------------------------

@@ -43,7 +43,8 @@ struct LossArgs {
   const float4* pts;     // sorted records of the set being walked (label bits in .w)
   const int32_t* dense;
   const int32_t* prefix;
-  const int32_t* sidx;   // sorted position -> original row of the walked set
+  const int32_t* sidx;   // sorted position -> original row (queries: training rows + query)
+  int32_t planes, plane; // label planes of the sorted set, and the one that is walked
   float l, l2, inv_l, sigma0, alpha0;
   float coef[SMKI_POLY_N];  // sigma0 * Q (per-class form: Q, the class's sigma0 applied apart)
   int32_t K;
@@ -70,40 +71,6 @@ __device__ __forceinline__ float dfdr_over_r(float s) {
 
 __device__ __forceinline__ int cell_of(float x, float h) {
   return (int)floorf((float)((double)x / (double)h));
-}
-
-// Visit every row of the walked set in the 27 cells around point x (row ranges
-// from the prefix tables); fn(record, dx, dy, dz, d2, sorted index).
-template <typename Fn>
-__device__ __forceinline__ void for_neighbours(const LossArgs& a, float x, float y, float z, Fn fn) {
-  const BucketGeom& g = a.g;
-  const int cx = cell_of(x, g.res), cy = cell_of(y, g.res), cz = cell_of(z, g.res);
-  const int32_t B3 = LB * LB * LB;
-  const double h = (double)g.res;
-  for (int ox = -1; ox <= 1; ++ox)
-    for (int oy = -1; oy <= 1; ++oy)
-      for (int oz = -1; oz <= 1; ++oz) {
-        const int vx = cx + ox, vy = cy + oy, vz = cz + oz;
-        const int bx = vx >> LLOG2B, by = vy >> LLOG2B, bz = vz >> LLOG2B;
-        const int px = bx - g.blo[0], py = by - g.blo[1], pz = bz - g.blo[2];
-        if (px < 0 || py < 0 || pz < 0 || px >= g.nb[0] || py >= g.nb[1] || pz >= g.nb[2]) continue;
-        const int32_t slot = a.dense[((int64_t)px * g.nb[1] + py) * g.nb[2] + pz];
-        if (slot < 0) continue;
-        const int32_t loc = ((vx - bx * LB) * LB + (vy - by * LB)) * LB + (vz - bz * LB);
-        const int32_t* P = a.prefix + (int64_t)slot * (B3 + 1);
-        const int32_t S = P[loc], E = P[loc + 1];
-        if (S == E) continue;
-        // the point relative to the exact centre of block (bx, by, bz)
-        const float qx = (float)((double)x - ((double)(bx * LB) + 0.5 * LB) * h);
-        const float qy = (float)((double)y - ((double)(by * LB) + 0.5 * LB) * h);
-        const float qz = (float)((double)z - ((double)(bz * LB) + 0.5 * LB) * h);
-        for (int32_t i = S; i < E; ++i) {
-          const float4 p = a.pts[i];
-          const float dx = p.x - qx, dy = p.y - qy, dz = p.z - qz;
-          const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-          if (d2 < a.l2) fn(p, dx, dy, dz, d2, i);
-        }
-      }
 }
 
 // Header of a call (kHdr bytes): bounding-box copies (min x, y, z, max x, y, z,
@@ -216,7 +183,7 @@ __device__ __forceinline__ int32_t find_runs(const LossArgs& a, float x, float y
   int32_t first = 0, n = 0;
   if (lane < 18 && !(part && b0 == b1) && px >= 0 && py >= 0 && pz >= 0 && px < g.nb[0] &&
       py < g.nb[1] && pz < g.nb[2]) {
-    const int32_t slot = a.dense[((int64_t)px * g.nb[1] + py) * g.nb[2] + pz];
+    const int32_t slot = a.dense[(((int64_t)px * g.nb[1] + py) * g.nb[2] + pz) * a.planes + a.plane];
     if (slot >= 0) {
       const int32_t c0 = ((vx - bx * LB) * LB + (vy - by * LB)) * LB - bz * LB;
       const int32_t* P = a.prefix + (int64_t)slot * (LB * LB * LB + 1);
@@ -348,22 +315,26 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_alpha_q(LossArgs a, const float* 
   }
 }
 
-// Query-side adjoint: dloss/dx_h, 1/S_h and 1/alpha_y (for the training side), and
+// Query-side adjoint: dloss/dx_h, (1/S_h, 1/alpha_y) for the training side, and
 // the query's shares of the scalar gradients: dl_part[h] and, in closed form,
 //   sum_k G_hk (alpha_hk - alpha0) / sigma0 = -(g/(H sigma0)) (K alpha0/S - alpha0/alpha_y),
 // or (PC) dl[h][k] and ds[h][k] per class.
 template <bool PC, int COLS>
 __global__ void __launch_bounds__(SMKI_WAVE) k_query_grad(
-    LossArgs a, const float* __restrict__ qxyz, const int32_t* __restrict__ qlab,
+    LossArgs a, int64_t n_train, const int32_t* __restrict__ n_near,
+    const float* __restrict__ qxyz, const int32_t* __restrict__ qlab,
     const float* __restrict__ alpha_q, const float* __restrict__ gscale,
-    float* __restrict__ inv_s, float* __restrict__ inv_ay, float* __restrict__ grad_q,
-    double* __restrict__ dl_part, double* __restrict__ dsig, double* __restrict__ dl,
-    double* __restrict__ ds) {
+    float2* __restrict__ inv, float* __restrict__ grad_q, double* __restrict__ dl_part,
+    double* __restrict__ dsig, double* __restrict__ dl, double* __restrict__ ds) {
   __shared__ RunTable t;
   extern __shared__ double dbins[];   // PC: [2][K][COLS]
   const int lane = threadIdx.x;
   const float gH = gscale[0] / (float)a.H;
-  for (int64_t h = blockIdx.x; h < a.H; h += gridDim.x) {
+  // queries in sorted order where the set holds them (n_near non-null: they
+  // follow its training rows): the wavefronts in flight share rows
+  const int64_t q0 = n_near ? *n_near : 0;
+  for (int64_t j = blockIdx.x; j < a.H; j += gridDim.x) {
+    const int64_t h = n_near ? a.sidx[q0 + j] - n_train : j;
     const int32_t yh = qlab[h];
     double S = 0.0;
     for (int32_t k = lane; k < a.K; k += SMKI_WAVE) S += (double)alpha_q[h * a.K + k];
@@ -418,8 +389,7 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_query_grad(
       dlh = wave_sum(dlh);
     }
     if (lane == 0) {
-      inv_s[h] = is;
-      inv_ay[h] = ia;
+      inv[j] = make_float2(is, ia);
       if (grad_q) {
         grad_q[3 * h] = gx;
         grad_q[3 * h + 1] = gy;
@@ -435,69 +405,78 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_query_grad(
   }
 }
 
-// Training-side adjoint: dloss/dx_t, walking the bucketed queries around each row.
-__global__ void k_train_grad(LossArgs a, const float* __restrict__ txyz,
-                             const int32_t* __restrict__ tlab, int64_t n_train,
-                             const int32_t* __restrict__ qlab, const float* __restrict__ inv_s,
-                             const float* __restrict__ inv_ay, const float* __restrict__ gscale,
-                             float* __restrict__ grad_t) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_train) return;
-  const float gH = gscale[0] / (float)a.H;
-  const int32_t yt = tlab[t];
-  float gx = 0.f, gy = 0.f, gz = 0.f;
-  const float il2 = a.inv_l * a.inv_l;
-  for_neighbours(a, txyz[3 * t], txyz[3 * t + 1], txyz[3 * t + 2],
-                 [&](const float4& p, float dx, float dy, float dz, float d2, int32_t j) {
-                   // p is a query record; (dx, dy, dz) = x_h - x_t
-                   const int32_t h = a.sidx[j];
-                   const float G = -gH * ((yt == qlab[h] ? inv_ay[h] : 0.0f) - inv_s[h]);
-                   const float d = __builtin_sqrtf(d2);
-                   const float s = fmaxf(fmaf(-d, a.inv_l, 1.0f), 0.0f);
-                   const float c = G * a.sigma0 * dfdr_over_r(s) * il2;
-                   gx -= c * dx;
-                   gy -= c * dy;
-                   gz -= c * dz;
-                 });
-  grad_t[3 * t] = gx;
-  grad_t[3 * t + 1] = gy;
-  grad_t[3 * t + 2] = gz;
-}
-
-// ---------------------------------------------------------------------------
-// per-class kernels: rows of class k use l_k and sigma0_k,
-//   alpha_h^k = alpha0 + sum_{y_t = k} sigma0_k f(|x_t - x_h| / l_k),
+// Training-side adjoint: dloss/dx_t of the rows near a query, one lane per row in
+// sorted order, walking the sorted queries around it: the rows of a wavefront
+// lie in a few cells, so that they read the same cell tables and queries.  (One
+// lane per row of the caller's order, with 27 table look-ups for each of the
+// 3.1e6 rows, took 385 us; most rows have no query near and are zeroed when the
+// near ones are picked.)  PC: per-class kernels,
 //   dloss/dl_k      = sum over pairs with y_t = k  G_{h,k} sigma0_k f'(r) (-r/l_k)
 //   dloss/dsigma0_k = sum over pairs with y_t = k  G_{h,k} f(r)
-// per query into dl[h][k], ds[h][k] (double), then summed per class in a fixed order.
-// ---------------------------------------------------------------------------
-__global__ void k_train_grad_pc(LossArgs a, const float* __restrict__ txyz,
-                                const int32_t* __restrict__ tlab, int64_t n_train,
-                                const int32_t* __restrict__ qlab, const float* __restrict__ inv_s,
-                                const float* __restrict__ inv_ay, const float* __restrict__ gscale,
-                                float* __restrict__ grad_t) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_train) return;
+// (summed per query by k_query_grad, then per class in a fixed order).
+template <bool PC>
+__global__ void __launch_bounds__(256) k_train_grad(LossArgs a, const float* __restrict__ txyz,
+                                                    const int32_t* __restrict__ tlab,
+                                                    const int32_t* __restrict__ n_near,
+                                                    const float2* __restrict__ inv,
+                                                    const float* __restrict__ gscale,
+                                                    float* __restrict__ grad_t) {
+  const BucketGeom& g = a.g;
+  const int32_t q0 = *n_near;   // the first query in sorted order
   const float gH = gscale[0] / (float)a.H;
-  const int32_t yt = tlab[t];
-  const float4 c = a.cls[yt];
-  float gx = 0.f, gy = 0.f, gz = 0.f;
-  const float il2 = c.y * c.y;
-  for_neighbours(a, txyz[3 * t], txyz[3 * t + 1], txyz[3 * t + 2],
-                 [&](const float4&, float dx, float dy, float dz, float d2, int32_t j) {
-                   if (!(d2 < c.x)) return;
-                   const int32_t h = a.sidx[j];
-                   const float G = -gH * ((yt == qlab[h] ? inv_ay[h] : 0.0f) - inv_s[h]);
-                   const float d = __builtin_sqrtf(d2);
-                   const float s = fmaxf(fmaf(-d, c.y, 1.0f), 0.0f);
-                   const float cc = G * c.z * dfdr_over_r(s) * il2;
-                   gx -= cc * dx;
-                   gy -= cc * dy;
-                   gz -= cc * dz;
-                 });
-  grad_t[3 * t] = gx;
-  grad_t[3 * t + 1] = gy;
-  grad_t[3 * t + 2] = gz;
+  const double h = (double)g.res;
+  for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < q0;
+       j += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t t = a.sidx[j];
+    const float x = txyz[3 * t], y = txyz[3 * t + 1], z = txyz[3 * t + 2];
+    const int32_t yt = tlab[t];
+    float inv_l = a.inv_l, s0 = a.sigma0, l2 = a.l2;
+    if constexpr (PC) {
+      const float4 c = a.cls[yt];
+      l2 = fminf(l2, c.x);
+      inv_l = c.y;
+      s0 = c.z;
+    }
+    const float il2 = inv_l * inv_l;
+    const int cx = cell_of(x, g.res), cy = cell_of(y, g.res), cz = cell_of(z, g.res);
+    const int b0 = (cz - 1) >> LLOG2B, b1 = (cz + 1) >> LLOG2B;
+    float gx = 0.f, gy = 0.f, gz = 0.f;
+    for (int ox = -1; ox <= 1; ++ox)
+      for (int oy = -1; oy <= 1; ++oy)
+        for (int bz = b0; bz <= b1; ++bz) {
+          const int vx = cx + ox, vy = cy + oy;
+          const int bx = vx >> LLOG2B, by = vy >> LLOG2B;
+          const int px = bx - g.blo[0], py = by - g.blo[1], pz = bz - g.blo[2];
+          if (px < 0 || py < 0 || pz < 0 || px >= g.nb[0] || py >= g.nb[1] || pz >= g.nb[2]) continue;
+          const int32_t slot =
+              a.dense[(((int64_t)px * g.nb[1] + py) * g.nb[2] + pz) * a.planes + a.plane];
+          if (slot < 0) continue;
+          const int32_t c0 = ((vx - bx * LB) * LB + (vy - by * LB)) * LB;
+          const int32_t* P = a.prefix + (int64_t)slot * (LB * LB * LB + 1) + c0;
+          const int32_t S = P[max(cz - 1 - bz * LB, 0)], E = P[min(cz + 1 - bz * LB, LB - 1) + 1];
+          if (S == E) continue;
+          // the row relative to the exact centre of block (bx, by, bz)
+          const float tx = (float)((double)x - ((double)(bx * LB) + 0.5 * LB) * h);
+          const float ty = (float)((double)y - ((double)(by * LB) + 0.5 * LB) * h);
+          const float tz = (float)((double)z - ((double)(bz * LB) + 0.5 * LB) * h);
+          for (int32_t i = S; i < E; ++i) {
+            const float4 p = a.pts[i];   // a query record; (dx, dy, dz) = x_h - x_t
+            const float dx = p.x - tx, dy = p.y - ty, dz = p.z - tz;
+            const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            if (!(d2 < l2)) continue;
+            const float2 iv = inv[i - q0];
+            const float G = -gH * ((yt == __float_as_int(p.w) ? iv.y : 0.0f) - iv.x);
+            const float s = fmaxf(fmaf(-__builtin_sqrtf(d2), inv_l, 1.0f), 0.0f);
+            const float c = G * s0 * dfdr_over_r(s) * il2;
+            gx -= c * dx;
+            gy -= c * dy;
+            gz -= c * dz;
+          }
+        }
+    grad_t[3 * t] = gx;
+    grad_t[3 * t + 1] = gy;
+    grad_t[3 * t + 2] = gz;
+  }
 }
 
 // Sums over queries in a fixed order (one workgroup each): thread t adds entries
@@ -558,40 +537,16 @@ struct Carve {
   }
 };
 
-struct SetBufs {
+struct LossBufs {
   PointSet ps;
   BucketScratch scr;
-};
-
-void carve_set(Carve& c, SetBufs& s, int64_t n, int64_t nblocks_cap) {
-  const int64_t slots = std::min<int64_t>(n, nblocks_cap);
-  s.ps.n = n;
-  s.ps.wts = nullptr;   // every training row of the loss weighs 1
-  s.scr.wt = nullptr;
-  s.ps.pts = c.take<float4>(n);
-  s.ps.dense = c.take<int32_t>(nblocks_cap);
-  s.ps.slot_lin = c.take<int32_t>(slots);
-  s.ps.prefix = c.take<int32_t>(slots * (LB * LB * LB + 1));
-  s.ps.d_nslots = c.take<int32_t>(1);
-  s.scr.keys = c.take<uint64_t>(n);
-  s.scr.akeys = c.take<uint64_t>(n);
-  s.scr.idx = c.take<uint32_t>(n);
-  s.scr.aidx = c.take<uint32_t>(n);
-  s.scr.rec = c.take<float4>(n);
-  s.scr.flag = c.take<int32_t>(n);
-  s.scr.slot_excl = c.take<int32_t>(n);
-  s.ps.head = c.take<int32_t>(n + 1);
-  s.scr.sort_tmp = c.take<char>(radix_tmp_bytes(n));
-  s.scr.scan_tmp = c.take<char>(scan_tmp_bytes(n));
-}
-
-struct LossBufs {
-  SetBufs tr, qu;
+  unsigned long long* near;   // [n_blocks] cells near a query; nullptr: no room for it
   int32_t* bbox;
   uint32_t* err;
+  int64_t* dn;        // rows of the sorted set
+  int32_t* n_near;    // its training rows
   float* alpha_q;
-  float* inv_s;
-  float* inv_ay;
+  float2* inv;   // (1/S, 1/alpha_y) of the queries in sorted order
   double* dsig;
   double* dl;
   double* dlk;   // [H][K] per-class form
@@ -599,22 +554,77 @@ struct LossBufs {
   float4* cls;   // [K] per-class form: class kernels (in the header)
 };
 
-// bounding box and error word (first 512 bytes) and the per-class kernel table
-// (up to 255 float4), ahead of the carved buffers
+// Header of a call (first 512 bytes: the bounding-box copies, the row counts of
+// the sorted set, the error word) and the per-class kernel table (up to 255
+// float4), ahead of the carved buffers
 constexpr size_t kHdr = 512 + 256 * sizeof(float4);
+constexpr size_t kCountOff = 256;
 
-// Buffers after the header, for a grid of nblocks blocks (nullptr base: size only).
-size_t carve_body(char* base, LossBufs& b, int64_t nt, int64_t nq, int32_t K, int64_t nblocks) {
+// Bytes that a workspace has to offer after the header for a grid of nblocks
+// blocks (what the calls accept: two row sets with 64-bit keys, each with tables
+// of its own).
+size_t body_bytes(int64_t nt, int64_t nq, int32_t K, int64_t nblocks) {
+  Carve c{nullptr, 0};
+  c.take<float>((size_t)nq * K);
+  c.take<float>(nq);
+  c.take<float>(nq);
+  c.take<double>(nq);
+  c.take<double>(nq);
+  c.take<double>((size_t)nq * K);
+  c.take<double>((size_t)nq * K);
+  for (int64_t n : {nt, nq}) {
+    const int64_t slots = std::min<int64_t>(n, nblocks);
+    c.take<float4>(n);
+    c.take<int32_t>(nblocks);
+    c.take<int32_t>(slots);
+    c.take<int32_t>(slots * (LB * LB * LB + 1));
+    c.take<int32_t>(1);
+    c.take<uint64_t>(n);
+    c.take<uint64_t>(n);
+    c.take<uint32_t>(n);
+    c.take<uint32_t>(n);
+    c.take<float4>(n);
+    c.take<int32_t>(n);
+    c.take<int32_t>(n);
+    c.take<int32_t>(n + 1);
+    c.take<char>(radix_tmp_bytes(n));
+    c.take<char>(scan_tmp_bytes(n));
+  }
+  return c.used + kAl;
+}
+
+// Buffers after the header (nullptr base: size only): one set of nt + nq rows
+// with 32-bit keys, which never takes more than body_bytes without the bits of
+// the cells near a query; near: with them.
+size_t carve_body(char* base, LossBufs& b, int64_t nt, int64_t nq, int32_t K, int64_t nblocks,
+                  bool near) {
   Carve c{base, 0};
+  const int64_t n = nt + nq;
+  const int64_t slots = std::min<int64_t>(nt, nblocks) + std::min<int64_t>(nq, nblocks);
   b.alpha_q = c.take<float>((size_t)nq * K);
-  b.inv_s = c.take<float>(nq);
-  b.inv_ay = c.take<float>(nq);
+  b.inv = c.take<float2>(nq);
   b.dsig = c.take<double>(nq);
   b.dl = c.take<double>(nq);
   b.dlk = c.take<double>((size_t)nq * K);
   b.dsk = c.take<double>((size_t)nq * K);
-  carve_set(c, b.tr, nt, nblocks);
-  carve_set(c, b.qu, nq, nblocks);
+  b.ps.wts = nullptr;   // every training row of the loss weighs 1
+  b.scr.wt = nullptr;
+  b.ps.pts = c.take<float4>(n);
+  b.ps.dense = c.take<int32_t>(2 * nblocks);
+  b.ps.slot_lin = c.take<int32_t>(slots);
+  b.ps.prefix = c.take<int32_t>(slots * (LB * LB * LB + 1));
+  b.ps.d_nslots = c.take<int32_t>(1);
+  b.scr.keys = c.take<uint32_t>(n);
+  b.scr.akeys = c.take<uint32_t>(n);
+  b.scr.idx = c.take<uint32_t>(n);
+  b.scr.aidx = c.take<uint32_t>(n);
+  b.scr.rec = c.take<float4>(n);
+  b.scr.flag = c.take<int32_t>(n);
+  b.scr.slot_excl = c.take<int32_t>(n);
+  b.ps.head = c.take<int32_t>(n + 1);
+  b.scr.sort_tmp = c.take<char>(radix_tmp_bytes(n));
+  b.scr.scan_tmp = c.take<char>(scan_tmp_bytes(n));
+  b.near = near ? c.take<unsigned long long>(nblocks) : nullptr;
   return c.used + kAl;
 }
 
@@ -626,6 +636,7 @@ smki_status err_status(uint32_t e) {
 
 constexpr int kValidateGrid = 1024;   // workgroups per set in the validation
 
+constexpr unsigned kTrainGrid = 8192;   // workgroups of the training-side kernel (they stride)
 constexpr int64_t kQueryGrid = 1 << 20;   // workgroups of the query-side kernels (they stride)
 
 // The query-side kernels; few classes take a column per lane (float) or 16
@@ -646,34 +657,36 @@ void launch_alpha_q(bool pc, const LossArgs& a, const float* qxyz, const int32_t
 }
 
 void launch_query_grad(bool pc, const LossArgs& a, const float* qxyz, const int32_t* qlab,
-                       const float* alpha_q, const float* gscale, const LossBufs& b, float* grad_q,
-                       hipStream_t st) {
+                       const float* alpha_q, const float* gscale, const LossBufs& b, int64_t n_train,
+                       bool sorted, float* grad_q, hipStream_t st) {
+  const int32_t* nn = sorted ? b.n_near : nullptr;
   const dim3 grid((unsigned)std::min<int64_t>(a.H, kQueryGrid)), block(SMKI_WAVE);
   if (!pc) {
-    hipLaunchKernelGGL((k_query_grad<false, 16>), grid, block, 0, st, a, qxyz, qlab, alpha_q, gscale,
-                       b.inv_s, b.inv_ay, grad_q, b.dl, b.dsig, b.dlk, b.dsk);
+    hipLaunchKernelGGL((k_query_grad<false, 16>), grid, block, 0, st, a, n_train, nn, qxyz, qlab,
+                       alpha_q, gscale, b.inv, grad_q, b.dl, b.dsig, b.dlk, b.dsk);
     return;
   }
   const bool few = a.K <= 64;
   const unsigned lds = (unsigned)(2 * sizeof(double) * a.K * (few ? 16 : 8));
   if (few)
-    hipLaunchKernelGGL((k_query_grad<true, 16>), grid, block, lds, st, a, qxyz, qlab, alpha_q,
-                       gscale, b.inv_s, b.inv_ay, grad_q, b.dl, b.dsig, b.dlk, b.dsk);
+    hipLaunchKernelGGL((k_query_grad<true, 16>), grid, block, lds, st, a, n_train, nn, qxyz, qlab,
+                       alpha_q, gscale, b.inv, grad_q, b.dl, b.dsig, b.dlk, b.dsk);
   else
-    hipLaunchKernelGGL((k_query_grad<true, 8>), grid, block, lds, st, a, qxyz, qlab, alpha_q,
-                       gscale, b.inv_s, b.inv_ay, grad_q, b.dl, b.dsig, b.dlk, b.dsk);
+    hipLaunchKernelGGL((k_query_grad<true, 8>), grid, block, lds, st, a, n_train, nn, qxyz, qlab,
+                       alpha_q, gscale, b.inv, grad_q, b.dl, b.dsig, b.dlk, b.dsk);
 }
 
 char* align_up(char* p) { return (char*)(((uintptr_t)p + kAl - 1) / kAl * kAl); }
 
 // Validate both sets and size the grid (synchronous); then carve the body from
 // the caller's workspace or a fresh allocation, and bucket the training rows
-// (and the queries if both_sets).
+// near a query (and the queries if both_sets; grad_train, nullable, is zeroed at
+// the rows left out).
 // h_cls (nullable): per-class kernel table, copied into the header before the
 // synchronisation (so the host array may go out of scope after the call).
 smki_status prepare(const float* txyz, const int32_t* tlab, int64_t nt, const float* qxyz,
                     const int32_t* qlab, int64_t nq, float l, int32_t K, bool both_sets,
-                    char* ws, size_t ws_bytes, char** own, LossBufs& b, BucketGeom& g,
+                    float* grad_train, char* ws, size_t ws_bytes, char** own, LossBufs& b, BucketGeom& g,
                     hipStream_t st, const float4* h_cls = nullptr) {
   const float h = (float)((double)l * (1.0 + 1.0 / 1024.0));
   char* hdr = ws ? align_up(ws) : nullptr;
@@ -684,6 +697,8 @@ smki_status prepare(const float* txyz, const int32_t* tlab, int64_t nt, const fl
   }
   b.bbox = (int32_t*)hdr;
   b.err = (uint32_t*)(hdr + kErrOff);
+  b.dn = (int64_t*)(hdr + kCountOff);
+  b.n_near = (int32_t*)(hdr + kCountOff + sizeof(int64_t));
   b.cls = (float4*)(hdr + 512);
   if (h_cls)
     SMKI_HIP_TRY(hipMemcpyAsync(b.cls, h_cls, sizeof(float4) * K, hipMemcpyHostToDevice, st));
@@ -709,7 +724,7 @@ smki_status prepare(const float* txyz, const int32_t* tlab, int64_t nt, const fl
     }
   }
   g = BucketGeom{};
-  g.planes = 1;
+  g.planes = both_sets ? 2 : 1;
   g.res = h;
   g.B = LB;
   g.log2B = LLOG2B;
@@ -722,24 +737,25 @@ smki_status prepare(const float* txyz, const int32_t* tlab, int64_t nt, const fl
   }
   if (g.n_blocks > kMaxLossBlocks) return SMKI_E_CAPACITY;
   int bits = 0;
-  while (bits < 62 && (int64_t(1) << bits) < g.n_blocks) ++bits;
+  while (bits < 62 && (int64_t(1) << bits) < g.n_blocks * g.planes) ++bits;
   g.key_bits = std::max(1, bits + 3 * LLOG2B);
-  const size_t body = carve_body(nullptr, b, nt, nq, K, g.n_blocks);
+  const size_t body = body_bytes(nt, nq, K, g.n_blocks);
+  const size_t with_near = carve_body(nullptr, b, nt, nq, K, g.n_blocks, true);
   char* bbase = nullptr;
+  bool near = true;
   if (ws) {
     bbase = align_up(hdr + kHdr);
     if ((size_t)(bbase - ws) + body > ws_bytes) return SMKI_E_CAPACITY;
+    near = (size_t)(bbase - ws) + with_near <= ws_bytes;
   } else {
     char* p = nullptr;
-    SMKI_HIP_TRY(hipMallocAsync((void**)&p, body, st));
+    SMKI_HIP_TRY(hipMallocAsync((void**)&p, with_near, st));
     own[1] = p;
     bbase = align_up(p);
   }
-  carve_body(bbase, b, nt, nq, K, g.n_blocks);
-  SMKI_HIP_TRY(hipMemsetAsync(b.tr.ps.d_nslots, 0, sizeof(int32_t), st));
-  SMKI_HIP_TRY(hipMemsetAsync(b.qu.ps.d_nslots, 0, sizeof(int32_t), st));
-  SMKI_HIP_TRY(bucket_rows(txyz, tlab, nt, g, b.tr.ps, b.tr.scr, b.err, st));
-  if (both_sets) SMKI_HIP_TRY(bucket_rows(qxyz, qlab, nq, g, b.qu.ps, b.qu.scr, b.err, st));
+  carve_body(bbase, b, nt, nq, K, g.n_blocks, near);
+  SMKI_HIP_TRY(bucket_near(txyz, tlab, nt, qxyz, qlab, nq, both_sets, g, b.ps, b.scr, b.near,
+                           grad_train, b.dn, b.n_near, b.err, st));
   return SMKI_OK;
 }
 
@@ -748,14 +764,16 @@ void release(char** own, hipStream_t st) {
     if (own[i]) (void)hipFreeAsync(own[i], st);
 }
 
-LossArgs make_args(const BucketGeom& g, const SetBufs& s, float l, float sigma0, float alpha0,
-                   int32_t K, int64_t H) {
+LossArgs make_args(const BucketGeom& g, const LossBufs& b, int32_t plane, float l, float sigma0,
+                   float alpha0, int32_t K, int64_t H) {
   LossArgs a{};
   a.g = g;
-  a.pts = s.ps.pts;
-  a.dense = s.ps.dense;
-  a.prefix = s.ps.prefix;
-  a.sidx = (const int32_t*)s.scr.idx;
+  a.pts = b.ps.pts;
+  a.dense = b.ps.dense;
+  a.prefix = b.ps.prefix;
+  a.sidx = (const int32_t*)b.scr.idx;
+  a.planes = g.planes;
+  a.plane = plane;
   a.l = l;
   a.l2 = l * l;
   a.inv_l = 1.0f / l;
@@ -776,10 +794,8 @@ bool bad_params(int64_t nt, int64_t nq, float l, float sigma0, float alpha0, int
 }  // namespace
 
 extern "C" size_t smki_loss_workspace_bytes(int64_t n_train, int64_t n_query, int32_t K) {
-  LossBufs b{};
-  return kHdr + 2 * kAl + carve_body(nullptr, b, std::max<int64_t>(n_train, 0),
-                                     std::max<int64_t>(n_query, 1), std::max(K, 1),
-                                     kMaxLossBlocks);
+  return kHdr + 2 * kAl + body_bytes(std::max<int64_t>(n_train, 0), std::max<int64_t>(n_query, 1),
+                                     std::max(K, 1), kMaxLossBlocks);
 }
 
 extern "C" smki_status smki_loss_forward(const float* txyz, const int32_t* tlab, int64_t nt,
@@ -794,10 +810,10 @@ extern "C" smki_status smki_loss_forward(const float* txyz, const int32_t* tlab,
   char* own[2] = {nullptr, nullptr};
   LossBufs b{};
   BucketGeom g{};
-  smki_status rc = prepare(txyz, tlab, nt, qxyz, qlab, nq, l, K, false, (char*)workspace,
+  smki_status rc = prepare(txyz, tlab, nt, qxyz, qlab, nq, l, K, false, nullptr, (char*)workspace,
                            ws_bytes, own, b, g, st);
   if (rc == SMKI_OK) {
-    const LossArgs a = make_args(g, b.tr, l, sigma0, alpha0, K, nq);
+    const LossArgs a = make_args(g, b, 0, l, sigma0, alpha0, K, nq);
     float* A = alpha_q ? alpha_q : b.alpha_q;
     launch_alpha_q(false, a, qxyz, qlab, A, b.dl, st);
     hipLaunchKernelGGL(k_loss_value, dim3(1), dim3(kSumThreads), 0, st, (const double*)b.dl, nq,
@@ -823,18 +839,19 @@ extern "C" smki_status smki_loss_backward(const float* txyz, const int32_t* tlab
   LossBufs b{};
   BucketGeom g{};
   smki_status rc = prepare(txyz, tlab, nt, qxyz, qlab, nq, l, K, grad_train != nullptr,
-                           (char*)workspace, ws_bytes, own, b, g, st);
+                           grad_train, (char*)workspace, ws_bytes, own, b, g, st);
   if (rc == SMKI_OK) {
-    const LossArgs aq = make_args(g, b.tr, l, sigma0, alpha0, K, nq);
-    launch_query_grad(false, aq, qxyz, qlab, alpha_q, grad_loss, b, grad_query, st);
+    const LossArgs aq = make_args(g, b, 0, l, sigma0, alpha0, K, nq);
+    launch_query_grad(false, aq, qxyz, qlab, alpha_q, grad_loss, b, nt, grad_train != nullptr,
+                      grad_query, st);
     if (grad_l || grad_sigma0)
       hipLaunchKernelGGL(k_colsum2, dim3(2), dim3(kSumThreads), 0, st, (const double*)b.dl, grad_l,
                          (const double*)b.dsig, grad_sigma0, nq, 1);
     if (grad_train && nt > 0) {
-      const LossArgs at = make_args(g, b.qu, l, sigma0, alpha0, K, nq);
-      hipLaunchKernelGGL(k_train_grad, dim3(nblk(nt, 64)), dim3(64), 0, st, at, txyz, tlab, nt,
-                         qlab, (const float*)b.inv_s, (const float*)b.inv_ay, grad_loss,
-                         grad_train);
+      const LossArgs at = make_args(g, b, 1, l, sigma0, alpha0, K, nq);
+      hipLaunchKernelGGL(k_train_grad<false>, dim3(std::min(nblk(nt, 256), kTrainGrid)), dim3(256),
+                         0, st, at, txyz, tlab, (const int32_t*)b.n_near, (const float2*)b.inv,
+                         grad_loss, grad_train);
     }
     if (hipGetLastError() != hipSuccess) rc = SMKI_E_DEVICE;
   }
@@ -860,9 +877,9 @@ bool class_table(const float* l, const float* sigma0, int32_t K, float4* t, floa
   return true;
 }
 
-LossArgs make_args_pc(const BucketGeom& g, const SetBufs& s, float lmax, const float4* cls,
-                      float alpha0, int32_t K, int64_t H) {
-  LossArgs a = make_args(g, s, lmax, 1.0f, alpha0, K, H);   // coef = Q: sigma0_k applied per row
+LossArgs make_args_pc(const BucketGeom& g, const LossBufs& b, int32_t plane, float lmax,
+                      const float4* cls, float alpha0, int32_t K, int64_t H) {
+  LossArgs a = make_args(g, b, plane, lmax, 1.0f, alpha0, K, H);   // coef = Q: sigma0_k applied per row
   a.cls = cls;
   return a;
 }
@@ -884,10 +901,10 @@ extern "C" smki_status smki_loss_forward_classes(const float* txyz, const int32_
   char* own[2] = {nullptr, nullptr};
   LossBufs b{};
   BucketGeom g{};
-  smki_status rc = prepare(txyz, tlab, nt, qxyz, qlab, nq, lmax, K, false, (char*)workspace,
+  smki_status rc = prepare(txyz, tlab, nt, qxyz, qlab, nq, lmax, K, false, nullptr, (char*)workspace,
                            ws_bytes, own, b, g, st, tab);
   if (rc == SMKI_OK) {
-    const LossArgs a = make_args_pc(g, b.tr, lmax, b.cls, alpha0, K, nq);
+    const LossArgs a = make_args_pc(g, b, 0, lmax, b.cls, alpha0, K, nq);
     float* A = alpha_q ? alpha_q : b.alpha_q;
     launch_alpha_q(true, a, qxyz, qlab, A, b.dl, st);
     hipLaunchKernelGGL(k_loss_value, dim3(1), dim3(kSumThreads), 0, st, (const double*)b.dl, nq,
@@ -913,18 +930,19 @@ extern "C" smki_status smki_loss_backward_classes(
   LossBufs b{};
   BucketGeom g{};
   smki_status rc = prepare(txyz, tlab, nt, qxyz, qlab, nq, lmax, K, grad_train != nullptr,
-                           (char*)workspace, ws_bytes, own, b, g, st, tab);
+                           grad_train, (char*)workspace, ws_bytes, own, b, g, st, tab);
   if (rc == SMKI_OK) {
-    const LossArgs aq = make_args_pc(g, b.tr, lmax, b.cls, alpha0, K, nq);
-    launch_query_grad(true, aq, qxyz, qlab, alpha_q, grad_loss, b, grad_query, st);
+    const LossArgs aq = make_args_pc(g, b, 0, lmax, b.cls, alpha0, K, nq);
+    launch_query_grad(true, aq, qxyz, qlab, alpha_q, grad_loss, b, nt, grad_train != nullptr,
+                      grad_query, st);
     if (grad_l || grad_sigma0)
       hipLaunchKernelGGL(k_colsum2, dim3(2 * K), dim3(kSumThreads), 0, st, (const double*)b.dlk,
                          grad_l, (const double*)b.dsk, grad_sigma0, nq, K);
     if (grad_train && nt > 0) {
-      const LossArgs at = make_args_pc(g, b.qu, lmax, b.cls, alpha0, K, nq);
-      hipLaunchKernelGGL(k_train_grad_pc, dim3(nblk(nt, 64)), dim3(64), 0, st, at, txyz, tlab, nt,
-                         qlab, (const float*)b.inv_s, (const float*)b.inv_ay, grad_loss,
-                         grad_train);
+      const LossArgs at = make_args_pc(g, b, 1, lmax, b.cls, alpha0, K, nq);
+      hipLaunchKernelGGL(k_train_grad<true>, dim3(std::min(nblk(nt, 256), kTrainGrid)), dim3(256),
+                         0, st, at, txyz, tlab, (const int32_t*)b.n_near, (const float2*)b.inv,
+                         grad_loss, grad_train);
     }
     if (hipGetLastError() != hipSuccess) rc = SMKI_E_DEVICE;
   }
@@ -977,8 +995,7 @@ extern "C" smki_status smki_loss_forward_noalloc(const float* txyz, const int32_
     return SMKI_E_INVALID_ARG;
   // the buffers that do not depend on the grid must fit before anything runs;
   // the grid-dependent tables are checked once the grid is known
-  LossBufs b0{};
-  if (kHdr + 2 * kAl + carve_body(nullptr, b0, nt, nq, K, 1) > kStaticScratchBytes)
+  if (kHdr + 2 * kAl + body_bytes(nt, nq, K, 1) > kStaticScratchBytes)
     return SMKI_E_CAPACITY;
   char* ws = nullptr;
   const smki_status rc = static_scratch(&ws);

@@ -72,8 +72,17 @@ hipError_t bucket_scan(const float* xyz, const int32_t* label, const float* prob
                        int32_t cap_slots = INT32_MAX);
 // entries of bucket_scan's wgbeam scratch for nf free samples
 int64_t free_sample_workgroups(int64_t nf);
-hipError_t bucket_rows(const float* xyz, const int32_t* label, int64_t n, const BucketGeom& g,
-                       PointSet& ps, BucketScratch& scr, uint32_t* err, hipStream_t st);
+// The rows of the differentiable form in one sorted set: the training rows that
+// have a query within one cell (plane 0), and with `both` the queries (plane 1,
+// indices nt + h), sorted by (plane, block, cell) with records and cell tables.
+// near (nullable): scratch of n_blocks words, one bit per cell; without it every
+// training row is kept.  grad_far (nullable, [nt][3]): zeroed at the rows left
+// out.  dn, n_near (device): receive the set's rows and its training rows; ps.n
+// becomes the capacity nt (+ nq).  Keys have at most 32 bits.
+hipError_t bucket_near(const float* txyz, const int32_t* tlab, int64_t nt, const float* qxyz,
+                       const int32_t* qlab, int64_t nq, bool both, const BucketGeom& g, PointSet& ps,
+                       BucketScratch& scr, unsigned long long* near, float* grad_far, int64_t* dn,
+                       int32_t* n_near, uint32_t* err, hipStream_t st);
 hipError_t bucket_cells_sort(const float* xyz, int64_t n, const BucketGeom& g, BucketScratch& scr,
                              uint32_t* err, int32_t* d_ncells, hipStream_t st);
 hipError_t bucket_cells_table(int64_t n, int64_t ncells, const BucketGeom& g, BucketScratch& scr,

@@ -74,3 +74,37 @@ def test_rows_around_a_wavefront_and_many_classes(n, q, K, per_class):
     assert np.linalg.norm(got - want) <= 1e-4 * np.linalg.norm(want)
     for x, r in ((gt, ref["grad_train"]), (gq, ref["grad_query"])):
         assert np.linalg.norm(f(x) - r) <= 1e-4 * np.linalg.norm(r)
+
+
+@pytest.mark.parametrize("n,q", [(1, 1), (300, 40), (4_097, 64)])
+def test_rows_far_from_queries(n, q):
+    # half of the rows lie within reach of a query, the others in a box of about
+    # 3.4e6 blocks around them: those are left out of the sort and get a zero
+    # gradient.  A workspace of smki_loss_workspace_bytes has no room for the
+    # bits of the cells near a query at that size (every row is then sorted);
+    # the call's own allocation has: the results agree bit for bit.
+    import torch
+    from paper_1909_04631_amd import loss_backward, loss_forward
+    from paper_1909_04631_amd.loss import workspace
+    print(f"[case] far rows n={n} q={q}", flush=True)
+    tx, ty = _rows(n, 4, n)
+    qx, qy = _rows(q, 4, q + 1, 0.6)
+    tx[n // 2:] *= 58.0
+    tx[-1] = 89.0
+    tx[0] = -89.0
+    args = [cuda(v) for v in (tx, ty, qx, qy)] + [float(L), float(S0), float(A0), 4]
+    g = cuda(np.ones(1, np.float32))
+    ref = oracle.loss(tx, ty, qx, qy, 4, float(L), float(S0), float(A0))
+    out = []
+    for ws in (None, workspace(n, q, 4)):
+        loss, aq = loss_forward(*args, ws=ws)
+        out.append([loss, aq, *loss_backward(*args, aq, g, ws=ws)])
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    loss, aq, _, _, gt, gq = [t.cpu().numpy().astype(np.float64) for t in out[0]]
+    assert np.max(np.abs(aq - ref["alpha_q"]) / ref["alpha_q"]) <= 1e-5
+    assert abs(loss[0] - ref["loss"]) <= 1e-5 * abs(ref["loss"])
+    assert np.all(gt[np.all(ref["grad_train"] == 0, axis=1)] == 0)
+    for x, r in ((gt, ref["grad_train"]), (gq, ref["grad_query"])):
+        assert np.linalg.norm(x - r) <= 1e-4 * max(np.linalg.norm(r), 1e-30)
