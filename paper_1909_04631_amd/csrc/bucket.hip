@@ -626,38 +626,39 @@ int64_t free_sample_workgroups(int64_t nf) { return nf > 0 ? ceil_div_i64(nf, FR
 // ---------------------------------------------------------------------------
 // rows and queries of the differentiable form
 // ---------------------------------------------------------------------------
-// The cells within one cell of a query, as one bit per cell (64 cells a block).
-__global__ void k_mark_near(const float* __restrict__ qxyz, int64_t nq, BucketGeom g,
-                            unsigned long long* __restrict__ near) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// The cells within one cell of a query, as one bit per cell (64 cells a block):
+// eight threads per query, one for each of the at most 2 x 2 x 2 blocks.
+__global__ void __launch_bounds__(256) k_mark_near(const float* __restrict__ qxyz, int64_t nq,
+                                                   BucketGeom g,
+                                                   unsigned long long* __restrict__ near) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = t >> 3;
   if (i >= nq) return;
-  int32_t v[3], b0[3], b1[3];
+  const double inv_res = 1.0 / (double)g.res;
+  int32_t b[3];
+  uint32_t m[3];   // the cells [v - 1, v + 1] of each axis that lie in block b
+#pragma unroll
   for (int a = 0; a < 3; ++a) {
-    if (!voxel_index(qxyz[3 * i + a], g.res, &v[a])) return;   // (validated before)
-    b0[a] = (v[a] - 1) >> g.log2B;
-    b1[a] = (v[a] + 1) >> g.log2B;
+    // (validated before: the voxel index is in range)
+    const int32_t v = (int32_t)floorf(quot_rn(qxyz[3 * i + a], inv_res, g.res));
+    const int32_t b0 = (v - 1) >> 2, b1 = (v + 1) >> 2;
+    const bool second = (t >> a) & 1;
+    if (second && b0 == b1) return;
+    b[a] = second ? b1 : b0;
+    const int32_t lo = max(v - 1 - b[a] * 4, 0), hi = min(v + 1 - b[a] * 4, 3);
+    m[a] = ((1u << (hi - lo + 1)) - 1u) << lo;
   }
-  // bits of one axis: the cells [v - 1, v + 1] that lie in block b
-  auto span = [&](int a, int32_t b) {
-    const int32_t lo = max(v[a] - 1, b * 4) - b * 4, hi = min(v[a] + 1, b * 4 + 3) - b * 4;
-    return (uint32_t)(((1 << (hi - lo + 1)) - 1) << lo);
-  };
-  for (int32_t bx = b0[0]; bx <= b1[0]; ++bx)
-    for (int32_t by = b0[1]; by <= b1[1]; ++by)
-      for (int32_t bz = b0[2]; bz <= b1[2]; ++bz) {
-        const int32_t b[3] = {bx, by, bz};
-        if (!in_grid(g, b)) continue;
-        const uint32_t mx = span(0, bx), my = span(1, by), mz = span(2, bz);
-        unsigned long long m = 0;
-        for (int y = 0; y < 4; ++y)
-          if ((my >> y) & 1) m |= (unsigned long long)mz << (4 * y);
-        unsigned long long m3 = 0;
-        for (int x = 0; x < 4; ++x)
-          if ((mx >> x) & 1) m3 |= m << (16 * x);
-        unsigned long long* w =
-            near + ((int64_t)(bx - g.blo[0]) * g.nb[1] + (by - g.blo[1])) * g.nb[2] + (bz - g.blo[2]);
-        if ((*w & m3) != m3) atomicOr(w, m3);
-      }
+  if (!in_grid(g, b)) return;
+  unsigned long long m2 = 0, m3 = 0;   // bits of one x layer, of the block
+#pragma unroll
+  for (int y = 0; y < 4; ++y)
+    if ((m[1] >> y) & 1) m2 |= (unsigned long long)m[2] << (4 * y);
+#pragma unroll
+  for (int x = 0; x < 4; ++x)
+    if ((m[0] >> x) & 1) m3 |= m2 << (16 * x);
+  unsigned long long* w =
+      near + ((int64_t)(b[0] - g.blo[0]) * g.nb[1] + (b[1] - g.blo[1])) * g.nb[2] + (b[2] - g.blo[2]);
+  if ((*w & m3) != m3) atomicOr(w, m3);
 }
 
 // The cell of a row: block, cell in the block and (with near) whether a query
@@ -683,6 +684,12 @@ __device__ __forceinline__ bool row_cell(const BucketGeom& g, double inv_res, fl
   return (near[w] >> ((l[0] * 4 + l[1]) * 4 + l[2])) & 1ull;
 }
 
+// Tiles of the two passes over the rows: NT rows, four per thread, loaded before
+// any is used (sixteen, as in the slot passes, left 25,000 rows to seven workgroups).
+constexpr int NR = 4;
+constexpr int NS = NR * SMKI_WAVE;       // rows per wavefront
+constexpr int NT = HT_THREADS * NR;      // rows per tile
+
 // Rows near a query: one bit per row (mask), their count per tile, and the
 // gradient of every other row (zero: it is in no query's support).
 __global__ void __launch_bounds__(HT_THREADS) k_near_count(
@@ -691,16 +698,24 @@ __global__ void __launch_bounds__(HT_THREADS) k_near_count(
     int32_t* __restrict__ tcount, float* __restrict__ grad, uint32_t* __restrict__ err) {
   __shared__ int32_t wc[HT_THREADS / SMKI_WAVE];
   const int lane = threadIdx.x & (SMKI_WAVE - 1), w = threadIdx.x / SMKI_WAVE;
-  const int64_t base = (int64_t)blockIdx.x * HT + (int64_t)w * HS;
+  const int64_t base = (int64_t)blockIdx.x * NT + (int64_t)w * NS;
   const double inv_res = 1.0 / (double)g.res;
   int32_t c = 0;
-#pragma unroll 4
-  for (int r = 0; r < HT_ROUNDS; ++r) {
+  float v[NR][3];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int64_t i = min(base + r * SMKI_WAVE + lane, n - 1);
+    v[r][0] = xyz[3 * i];
+    v[r][1] = xyz[3 * i + 1];
+    v[r][2] = xyz[3 * i + 2];
+  }
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
     const int64_t i = base + r * SMKI_WAVE + lane;
     bool is = false;
     if (i < n) {
       int32_t b[3], l[3];
-      is = row_cell(g, inv_res, xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], near, b, l, err);
+      is = row_cell(g, inv_res, v[r][0], v[r][1], v[r][2], near, b, l, err);
       if (grad && !is) grad[3 * i] = grad[3 * i + 1] = grad[3 * i + 2] = 0.0f;
     }
     const uint64_t m = __ballot(is);
@@ -742,10 +757,10 @@ __global__ void __launch_bounds__(HT_THREADS) k_near_keys(
   }
   __shared__ int32_t wc[HT_THREADS / SMKI_WAVE];
   const int lane = threadIdx.x & (SMKI_WAVE - 1), w = threadIdx.x / SMKI_WAVE;
-  const int64_t base = (int64_t)blockIdx.x * HT + (int64_t)w * HS;
+  const int64_t base = (int64_t)blockIdx.x * NT + (int64_t)w * NS;
   // lane r holds round r's mask
   const int64_t word = base / SMKI_WAVE + lane;
-  const uint64_t mine = lane < HT_ROUNDS && word * SMKI_WAVE < n ? mask[word] : 0ull;
+  const uint64_t mine = lane < NR && word * SMKI_WAVE < n ? mask[word] : 0ull;
   int32_t c = (int32_t)__popcll(mine);
 #pragma unroll
   for (int o = SMKI_WAVE / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, SMKI_WAVE);
@@ -753,7 +768,8 @@ __global__ void __launch_bounds__(HT_THREADS) k_near_keys(
   __syncthreads();
   int32_t run = tstart[blockIdx.x];
   for (int q = 0; q < w; ++q) run += wc[q];
-  for (int r = 0; r < HT_ROUNDS; ++r) {
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
     const uint64_t m = __shfl(mine, r, SMKI_WAVE);
     if ((m >> lane) & 1ull) {
       const int64_t i = base + r * SMKI_WAVE + lane;
@@ -780,8 +796,8 @@ hipError_t bucket_near(const float* txyz, const int32_t* tlab, int64_t nt, const
   ps.n = nt + n_sorted_q;
   if (ps.n <= 0) return hipSuccess;
   if (near && nt > 0)
-    hipLaunchKernelGGL(k_mark_near, dim3(nblk(nq, 256)), dim3(256), 0, st, qxyz, nq, g, near);
-  const int64_t tiles = ceil_div_i64(nt, HT);
+    hipLaunchKernelGGL(k_mark_near, dim3(nblk(8 * nq, 256)), dim3(256), 0, st, qxyz, nq, g, near);
+  const int64_t tiles = ceil_div_i64(nt, NT);
   int32_t* tcount = scr.flag;
   int32_t* tstart = scr.flag + tiles;
   unsigned long long* mask = (unsigned long long*)scr.slot_excl;

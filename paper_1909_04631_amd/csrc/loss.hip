@@ -69,8 +69,28 @@ __device__ __forceinline__ float dfdr_over_r(float s) {
   return (s2 * s2) * p;
 }
 
-__device__ __forceinline__ int cell_of(float x, float h) {
-  return (int)floorf((float)((double)x / (double)h));
+// The cell of a coordinate, and how far (in cells, squared) the cells below and
+// above it are: less a margin for the rounding of the cell index, which grows
+// with it.  A cell edge is a little over l, so a cell at a squared distance of 1
+// or more holds no row in the support: of the 27 cells around a point that
+// leaves 21 on average.
+struct Axis {
+  int c;
+  float lo2, hi2;
+};
+__device__ __forceinline__ Axis axis_of(float x, double inv_h, float h) {
+  Axis a;
+  const float f = floorf(quot_rn(x, inv_h, h));
+  a.c = (int)f;
+  const float u = (float)((double)x * inv_h - (double)f);   // in [0, 1], up to rounding
+  const float m = 1e-3f + fabsf(f) * 0x1p-20f;
+  const float lo = fmaxf(u - m, 0.0f), hi = fmaxf(1.0f - u - m, 0.0f);
+  a.lo2 = lo * lo;
+  a.hi2 = hi * hi;
+  return a;
+}
+__device__ __forceinline__ float axis_dist2(const Axis& a, int o) {
+  return o < 0 ? a.lo2 : (o > 0 ? a.hi2 : 0.0f);
 }
 
 // Header of a call (kHdr bytes): bounding-box copies (min x, y, z, max x, y, z,
@@ -104,27 +124,38 @@ __global__ void __launch_bounds__(256) k_validate(const float* __restrict__ txyz
   const double inv_h = 1.0 / (double)h;
   int32_t box[6] = {INT32_MAX, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, INT32_MIN};
   uint32_t e = 0;
-  for (int64_t i = b * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const float x = xyz[3 * i], y = xyz[3 * i + 1], z = xyz[3 * i + 2];
-    if (lab[i] < 0 || lab[i] >= K) e |= DEVERR_LABEL;
-    if (!isfinite(x) || !isfinite(y) || !isfinite(z)) {
-      e |= DEVERR_NONFINITE;
-      continue;
-    }
-    const float c[3] = {floorf(quot_rn(x, inv_h, h)), floorf(quot_rn(y, inv_h, h)),
-                        floorf(quot_rn(z, inv_h, h))};
-    bool in = true;
+  constexpr int U = 4;   // rows in flight per thread
+  for (int64_t i0 = b * blockDim.x + threadIdx.x; i0 < n; i0 += U * stride) {
+    float v[U][3];
+    int32_t y[U];
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-      in = in && c[a] >= -(float)SMKI_COORD_LIM && c[a] < (float)SMKI_COORD_LIM;
-    if (!in) {
-      e |= DEVERR_RANGE;
-      continue;
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = min(i0 + u * stride, n - 1);   // (past the end: the last row again)
+      v[u][0] = xyz[3 * i];
+      v[u][1] = xyz[3 * i + 1];
+      v[u][2] = xyz[3 * i + 2];
+      y[u] = lab[i];
     }
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      box[a] = min(box[a], (int32_t)c[a]);
-      box[3 + a] = max(box[3 + a], (int32_t)c[a]);
+    for (int u = 0; u < U; ++u) {
+      if (y[u] < 0 || y[u] >= K) e |= DEVERR_LABEL;
+      const bool fin = isfinite(v[u][0]) && isfinite(v[u][1]) && isfinite(v[u][2]);
+      if (!fin) e |= DEVERR_NONFINITE;
+      float c[3];
+      bool in = fin;
+#pragma unroll
+      for (int a = 0; a < 3; ++a) {
+        c[a] = floorf(quot_rn(v[u][a], inv_h, h));
+        in = in && c[a] >= -(float)SMKI_COORD_LIM && c[a] < (float)SMKI_COORD_LIM;
+      }
+      if (fin && !in) e |= DEVERR_RANGE;
+      if (in) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          box[a] = min(box[a], (int32_t)c[a]);
+          box[3 + a] = max(box[3 + a], (int32_t)c[a]);
+        }
+      }
     }
   }
   if (e) atomicOr(err, e);
@@ -173,15 +204,21 @@ __device__ __forceinline__ int32_t find_runs(const LossArgs& a, float x, float y
                                              RunTable& t) {
   const BucketGeom& g = a.g;
   const int lane = threadIdx.x;
-  const int cx = cell_of(x, g.res), cy = cell_of(y, g.res), cz = cell_of(z, g.res);
+  const double inv_h = 1.0 / (double)g.res;
+  const Axis ax = axis_of(x, inv_h, g.res), ay = axis_of(y, inv_h, g.res),
+             az = axis_of(z, inv_h, g.res);
+  const int cx = ax.c, cy = ay.c, cz = az.c;
   const int col = lane >> 1, part = lane & 1;
+  // the column's cells along z that the support reaches
+  const float r2 = 1.0f - axis_dist2(ax, col / 3 - 1) - axis_dist2(ay, col % 3 - 1);
+  const int zlo = az.lo2 < r2 ? cz - 1 : cz, zhi = az.hi2 < r2 ? cz + 1 : cz;
   const int vx = cx + col / 3 - 1, vy = cy + col % 3 - 1;
-  const int bx = vx >> LLOG2B, by = vy >> LLOG2B, b0 = (cz - 1) >> LLOG2B, b1 = (cz + 1) >> LLOG2B;
+  const int bx = vx >> LLOG2B, by = vy >> LLOG2B, b0 = zlo >> LLOG2B, b1 = zhi >> LLOG2B;
   const int bz = part ? b1 : b0;
-  const int z0 = part ? b1 * LB : cz - 1, z1 = part || b0 == b1 ? cz + 1 : b0 * LB + LB - 1;
+  const int z0 = part ? b1 * LB : zlo, z1 = part || b0 == b1 ? zhi : b0 * LB + LB - 1;
   const int px = bx - g.blo[0], py = by - g.blo[1], pz = bz - g.blo[2];
   int32_t first = 0, n = 0;
-  if (lane < 18 && !(part && b0 == b1) && px >= 0 && py >= 0 && pz >= 0 && px < g.nb[0] &&
+  if (lane < 18 && r2 > 0.0f && !(part && b0 == b1) && px >= 0 && py >= 0 && pz >= 0 && px < g.nb[0] &&
       py < g.nb[1] && pz < g.nb[2]) {
     const int32_t slot = a.dense[(((int64_t)px * g.nb[1] + py) * g.nb[2] + pz) * a.planes + a.plane];
     if (slot >= 0) {
@@ -215,27 +252,41 @@ __device__ __forceinline__ int32_t find_runs(const LossArgs& a, float x, float y
 }
 
 // Visits the rows of the table, 64 at a time: fn(in, record, dx, dy, dz, d2) is
-// called by every lane, in = this lane holds a row within the search cut.
+// called by every lane, in = this lane holds a row within the search cut.  The
+// searches and loads of kAhead sets of 64 go out together: one set at a time,
+// each waited for its chain of five LDS reads and a load (1.4 us a set where a
+// query meets thousands of rows and few wavefronts run).
+constexpr int kAhead = 4;
 template <typename Fn>
 __device__ __forceinline__ void for_rows(const LossArgs& a, const RunTable& t, int32_t total, Fn fn) {
-  for (int32_t b = 0; b < total; b += SMKI_WAVE) {
-    const int32_t i = b + (int32_t)threadIdx.x;
-    const bool live = i < total;
-    int k = 0;   // the run of row i: the first whose inclusive count exceeds it
+  for (int32_t b = 0; b < total; b += kAhead * SMKI_WAVE) {
+    int k[kAhead];
+    float4 p[kAhead], q[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) k[u] = 0;
+    // the run of row i: the first whose inclusive count exceeds it
 #pragma unroll
     for (int st = kRuns / 2; st > 0; st >>= 1)
-      if (t.incl[k + st - 1] <= i) k += st;
-    float4 p = make_float4(0.f, 0.f, 0.f, 0.f);
-    float dx = 0.f, dy = 0.f, dz = 0.f;
-    if (live) {
-      const float4 q = t.at[k];
-      p = a.pts[__float_as_int(q.w) + i];
-      dx = p.x - q.x;
-      dy = p.y - q.y;
-      dz = p.z - q.z;
+#pragma unroll
+      for (int u = 0; u < kAhead; ++u)
+        if (t.incl[k[u] + st - 1] <= b + u * SMKI_WAVE + (int32_t)threadIdx.x) k[u] += st;
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int32_t i = b + u * SMKI_WAVE + (int32_t)threadIdx.x;
+      p[u] = q[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (i < total) {
+        q[u] = t.at[k[u]];
+        p[u] = a.pts[__float_as_int(q[u].w) + i];
+      }
     }
-    const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    fn(live && d2 < a.l2, p, dx, dy, dz, d2);
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      if (b + u * SMKI_WAVE >= total) break;   // (uniform)
+      const bool live = b + u * SMKI_WAVE + (int32_t)threadIdx.x < total;
+      const float dx = p[u].x - q[u].x, dy = p[u].y - q[u].y, dz = p[u].z - q[u].z;
+      const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+      fn(live && d2 < a.l2, p[u], dx, dy, dz, d2);
+    }
   }
 }
 
@@ -424,7 +475,7 @@ __global__ void __launch_bounds__(256) k_train_grad(LossArgs a, const float* __r
   const BucketGeom& g = a.g;
   const int32_t q0 = *n_near;   // the first query in sorted order
   const float gH = gscale[0] / (float)a.H;
-  const double h = (double)g.res;
+  const double h = (double)g.res, inv_h = 1.0 / h;
   for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < q0;
        j += (int64_t)gridDim.x * blockDim.x) {
     const int64_t t = a.sidx[j];
@@ -438,41 +489,60 @@ __global__ void __launch_bounds__(256) k_train_grad(LossArgs a, const float* __r
       s0 = c.z;
     }
     const float il2 = inv_l * inv_l;
-    const int cx = cell_of(x, g.res), cy = cell_of(y, g.res), cz = cell_of(z, g.res);
-    const int b0 = (cz - 1) >> LLOG2B, b1 = (cz + 1) >> LLOG2B;
+    const Axis ax = axis_of(x, inv_h, g.res), ay = axis_of(y, inv_h, g.res),
+               az = axis_of(z, inv_h, g.res);
+    const int cx = ax.c, cy = ay.c, cz = az.c;
     float gx = 0.f, gy = 0.f, gz = 0.f;
-    for (int ox = -1; ox <= 1; ++ox)
-      for (int oy = -1; oy <= 1; ++oy)
-        for (int bz = b0; bz <= b1; ++bz) {
-          const int vx = cx + ox, vy = cy + oy;
-          const int bx = vx >> LLOG2B, by = vy >> LLOG2B;
-          const int px = bx - g.blo[0], py = by - g.blo[1], pz = bz - g.blo[2];
-          if (px < 0 || py < 0 || pz < 0 || px >= g.nb[0] || py >= g.nb[1] || pz >= g.nb[2]) continue;
-          const int32_t slot =
-              a.dense[(((int64_t)px * g.nb[1] + py) * g.nb[2] + pz) * a.planes + a.plane];
-          if (slot < 0) continue;
-          const int32_t c0 = ((vx - bx * LB) * LB + (vy - by * LB)) * LB;
-          const int32_t* P = a.prefix + (int64_t)slot * (LB * LB * LB + 1) + c0;
-          const int32_t S = P[max(cz - 1 - bz * LB, 0)], E = P[min(cz + 1 - bz * LB, LB - 1) + 1];
-          if (S == E) continue;
-          // the row relative to the exact centre of block (bx, by, bz)
-          const float tx = (float)((double)x - ((double)(bx * LB) + 0.5 * LB) * h);
-          const float ty = (float)((double)y - ((double)(by * LB) + 0.5 * LB) * h);
-          const float tz = (float)((double)z - ((double)(bz * LB) + 0.5 * LB) * h);
-          for (int32_t i = S; i < E; ++i) {
-            const float4 p = a.pts[i];   // a query record; (dx, dy, dz) = x_h - x_t
-            const float dx = p.x - tx, dy = p.y - ty, dz = p.z - tz;
-            const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-            if (!(d2 < l2)) continue;
-            const float2 iv = inv[i - q0];
-            const float G = -gH * ((yt == __float_as_int(p.w) ? iv.y : 0.0f) - iv.x);
-            const float s = fmaxf(fmaf(-__builtin_sqrtf(d2), inv_l, 1.0f), 0.0f);
-            const float c = G * s0 * dfdr_over_r(s) * il2;
-            gx -= c * dx;
-            gy -= c * dy;
-            gz -= c * dz;
-          }
+    for (int ox = -1; ox <= 1; ++ox) {
+      // the runs of three columns, two blocks each: all look-ups in flight together
+      const int vx = cx + ox, bx = vx >> LLOG2B, px = bx - g.blo[0];
+      int32_t slot[6], S[6], E[6];
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const int oy = k / 2 - 1, vy = cy + oy;
+        const float r2 = 1.0f - axis_dist2(ax, ox) - axis_dist2(ay, oy);
+        const int b0 = (az.lo2 < r2 ? cz - 1 : cz) >> LLOG2B, b1 = (az.hi2 < r2 ? cz + 1 : cz) >> LLOG2B;
+        const int py = (vy >> LLOG2B) - g.blo[1], pz = (k & 1 ? b1 : b0) - g.blo[2];
+        const bool in = r2 > 0.0f && px >= 0 && py >= 0 && pz >= 0 && px < g.nb[0] && py < g.nb[1] &&
+                        pz < g.nb[2] && !((k & 1) && b0 == b1);
+        slot[k] = in ? a.dense[(((int64_t)px * g.nb[1] + py) * g.nb[2] + pz) * a.planes + a.plane] : -1;
+      }
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const int oy = k / 2 - 1, vy = cy + oy;
+        const float r2 = 1.0f - axis_dist2(ax, ox) - axis_dist2(ay, oy);
+        const int zlo = az.lo2 < r2 ? cz - 1 : cz, zhi = az.hi2 < r2 ? cz + 1 : cz;
+        const int z0 = (k & 1 ? zhi : zlo) & ~(LB - 1);   // the block's first cell
+        const int32_t c0 = ((vx - bx * LB) * LB + (vy & (LB - 1))) * LB;
+        const int32_t* P = a.prefix + (int64_t)max(slot[k], 0) * (LB * LB * LB + 1) + c0;
+        S[k] = P[max(zlo - z0, 0)];
+        E[k] = slot[k] >= 0 ? P[min(zhi - z0, LB - 1) + 1] : S[k];
+      }
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        if (S[k] >= E[k]) continue;
+        const int oy = k / 2 - 1, by = (cy + oy) >> LLOG2B;
+        const float r2 = 1.0f - axis_dist2(ax, ox) - axis_dist2(ay, oy);
+        const int bz = ((k & 1) ? (az.hi2 < r2 ? cz + 1 : cz) : (az.lo2 < r2 ? cz - 1 : cz)) >> LLOG2B;
+        // the row relative to the exact centre of block (bx, by, bz)
+        const float tx = (float)((double)x - ((double)(bx * LB) + 0.5 * LB) * h);
+        const float ty = (float)((double)y - ((double)(by * LB) + 0.5 * LB) * h);
+        const float tz = (float)((double)z - ((double)(bz * LB) + 0.5 * LB) * h);
+        for (int32_t i = S[k]; i < E[k]; ++i) {
+          const float4 p = a.pts[i];   // a query record; (dx, dy, dz) = x_h - x_t
+          const float dx = p.x - tx, dy = p.y - ty, dz = p.z - tz;
+          const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+          if (!(d2 < l2)) continue;
+          const float2 iv = inv[i - q0];
+          const float G = -gH * ((yt == __float_as_int(p.w) ? iv.y : 0.0f) - iv.x);
+          const float s = fmaxf(fmaf(-__builtin_sqrtf(d2), inv_l, 1.0f), 0.0f);
+          const float c = G * s0 * dfdr_over_r(s) * il2;
+          gx -= c * dx;
+          gy -= c * dy;
+          gz -= c * dz;
         }
+      }
+    }
     grad_t[3 * t] = gx;
     grad_t[3 * t + 1] = gy;
     grad_t[3 * t + 2] = gz;
