@@ -1,0 +1,35 @@
+"""Kernels at the sizes where they can go wrong: the edges of their tiles, the
+smallest inputs, and the class counts at which their layout changes."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+import oracle
+import scenes
+from gpu_cases import cuda, gpu_map_of, oracle_map_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K", [2, 20, 32, 33, 64, 65, 128, 129, 255])
+def test_readout_of_any_number_of_voxels(K):
+    # a workgroup serves 64, 32, 16 or 8 voxels by class count and writes their
+    # rows together; every subset of the outputs has the same values
+    sc = scenes.random_points_scene(seed=K, n=400, K=K, extent=0.8)
+    om, gm = oracle_map_of(sc, scsm=True), gpu_map_of(sc, model="scsm")
+    rng = np.random.default_rng(K)
+    q = rng.integers(-9, 9, size=(131, 3)).astype(np.int32)
+    ref = oracle.readout(om.lookup(q), free_class=0)
+    a_ref = om.lookup(q)
+    for M in (1, 7, 8, 9, 63, 64, 65, 131):
+        print(f"[case] readout K={K} M={M}", flush=True)
+        out = {k: v.cpu().numpy() for k, v in gm.query(cuda(q[:M])).items()}
+        assert np.array_equal(out["alpha"], (a_ref[:M]).astype(np.float32))
+        np.testing.assert_allclose(out["mean"], ref["mean"][:M], rtol=1e-6)
+        np.testing.assert_allclose(out["var"], ref["var"][:M], rtol=1e-6)
+        np.testing.assert_allclose(out["p_occ"], ref["p_occ"][:M], rtol=1e-6, atol=1e-7)
+        assert np.array_equal(out["label"], ref["label"][:M])
+        for k in out:
+            one = gm.query(cuda(q[:M]), **{n: n == k for n in out})
+            assert list(one) == [k] and np.array_equal(one[k].cpu().numpy(), out[k])
