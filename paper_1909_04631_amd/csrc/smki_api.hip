@@ -156,7 +156,8 @@ struct Stencil {
 struct smki_map {
   float res, l, sigma0, alpha0;
   int32_t K, B, log2B, free_class;
-  int32_t chunk;  // rows per splat work unit
+  int32_t budget;   // rows per splat work unit as asked for (0: chosen per insert, chunk_for)
+  int32_t chunk;    // rows per splat work unit of the last insert
   int32_t model;      // SMKI_MODEL_SBKI or SMKI_MODEL_SCSM
   int32_t selection;  // SMKI_SELECT_EXACT or SMKI_SELECT_FACE_BLOCKS
   int32_t flags;      // SMKI_FLAG_*
@@ -253,6 +254,19 @@ Stencil make_stencil(double lv, double margin) {
 // 64 KiB for all of them.
 bool sbki_shape_ok(int32_t B, int32_t R) {
   return (B == 2 || B == 4 || B == 8 || B == 16) && R <= B && R <= SMKI_MAX_REACH;
+}
+
+// Rows per splat work unit of an insert of nt rows: as asked for at creation,
+// else so many that about 4,096 units (16 wavefronts on each of 256 CUs) share
+// the rows, in whole batches of 64, between 128 and SMKI_CHUNK.  One wavefront takes
+// a unit's rows one after the other (0.29 us each at reach 3), so a small scan
+// whose rows lie in few blocks lasts as long as its longest unit, while every
+// unit adds a region to write and merge.  2,000 hits with 28,000 free samples,
+// splat + merge: 512 rows a unit 150 + 15 us, 128 rows 47 + 25, 64 rows 30 + 41.
+int32_t chunk_for(const smki_map* m, int64_t nt) {
+  if (m->budget > 0) return m->budget;
+  const int64_t c = ceil_div_i64(ceil_div_i64(nt, 4096), SMKI_WAVE) * SMKI_WAVE;
+  return (int32_t)std::min<int64_t>(std::max<int64_t>(c, 2 * SMKI_WAVE), SMKI_CHUNK);
 }
 
 hipError_t sync_read(smki_map* m, const void* dev, size_t bytes, void* host) {
@@ -644,6 +658,7 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
 
   // ---- phase B: bucket all rows (class-major keys), mark target blocks ----
   const int64_t nt = nk + nf;
+  m->chunk = chunk_for(m, nt);
   const int64_t max_slots = std::min<int64_t>(nt, g.n_blocks * m->K);
   Sizer zb;
   zb.add<int32_t>(g.n_blocks * m->K);
@@ -921,6 +936,7 @@ struct smki_batch {
   int32_t eblo[3] = {0, 0, 0}, enb[3] = {0, 0, 0};
   int64_t n_ext = 0;
   Stencil sten;
+  int32_t chunk = 0;         // rows per work unit (the sizing insert's)
   int64_t cap_rows = 0, cap_slots = 0, cap_units = 0;
   int64_t pool_cap = 0, cpool_cap = 0, hcap = 0;
   size_t in_bytes = 0;
@@ -1064,7 +1080,7 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
                            ps, scr, d.err, q, d.pc, (int32_t)b->cap_slots));
   SMKI_HIP_TRY(launch_mark_targets(ps.slot_lin, ps.d_nslots, (int32_t)b->cap_slots, g, b->eblo,
                                    b->enb, 1, d.mark, q));
-  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)b->cap_slots, m->chunk, d.nun, q));
+  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)b->cap_slots, b->chunk, d.nun, q));
   SMKI_HIP_TRY(scan_excl_pair_i32(d.mark, d.mpos, ne, d.si + 1, d.nun, d.ust, b->cap_slots,
                                   d.si + 2, d.scan_tmp, q, ps.d_nslots));
   SMKI_HIP_TRY(launch_batch_units(d.si, b->cap_slots, b->cap_units, d.err, q));
@@ -1079,7 +1095,7 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   sa.cls = m->d_cls;
   for (int i = 0; i < SMKI_POLY_N; ++i) sa.mcoef[i] = (float)(kSmkiQ[i] / kSmkiQ[0]);
   sa.K = m->K;
-  sa.chunk = m->chunk;
+  sa.chunk = b->chunk;
   sa.piece_mask = 0;
   for (int p = 0; p < 27; ++p) {
     const int nz = (p / 9 != 1) + ((p / 3) % 3 != 1) + (p % 3 != 1);
@@ -1116,7 +1132,7 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   sa.dn_units = d.si + 2;
   sa.abort_word = d.err;
   sa.cap_units = (int32_t)b->cap_units;
-  SMKI_HIP_TRY(launch_unit_table(d.nun, d.ust, d.head, d.slot_lin, g.n_blocks, m->chunk,
+  SMKI_HIP_TRY(launch_unit_table(d.nun, d.ust, d.head, d.slot_lin, g.n_blocks, b->chunk,
                                  (int32_t)b->cap_slots, ps.d_nslots, d.si + 2, d.units, d.uorder,
                                  q, (int32_t)b->cap_units));
   SMKI_HIP_TRY(launch_splat(sa, b->cap_units, q));
@@ -1216,7 +1232,8 @@ smki_status smki_create_map(float res, int32_t block_size, float l, float sigma0
   m->B = block_size;
   m->log2B = ilog2(block_size);
   m->free_class = free_class;
-  m->chunk = (opt && opt->unit_budget > 0) ? opt->unit_budget : SMKI_CHUNK;
+  m->budget = opt ? opt->unit_budget : 0;
+  m->chunk = SMKI_CHUNK;
   m->model = opt ? opt->model : SMKI_MODEL_SBKI;
   m->selection = opt ? opt->selection : SMKI_SELECT_EXACT;
   m->flags = opt ? opt->flags : 0;
@@ -1741,6 +1758,7 @@ smki_status smki_batch_capture(smki_map* m, const float* xyz, const int32_t* lab
   b->n = n;
   b->S = S;
   b->step = free_step;
+  b->chunk = m->chunk;
   const double grow = 1.0 + (double)margin;
   // 2. the window: the voxel box of that insert grown by margin of its extent per
   // side (at least two blocks), narrowed while that would widen the row keys

@@ -33,3 +33,19 @@ def test_readout_of_any_number_of_voxels(K):
         for k in out:
             one = gm.query(cuda(q[:M]), **{n: n == k for n in out})
             assert list(one) == [k] and np.array_equal(one[k].cpu().numpy(), out[k])
+
+
+@pytest.mark.parametrize("n", [1, 127, 129, 700_000])
+def test_unit_sizes_chosen_per_insert(n):
+    # no free samples: n rows, all of one class in a few blocks, so that a unit's
+    # rows (128 at least, 192 for the largest) decide how many units there are
+    sc = scenes.random_points_scene(seed=3, n=n, K=2, extent=0.35, centre=(0.4, 0.4, 0.4), l=0.15)
+    sc.scans[0].label[:] = 1
+    print(f"[case] unit size n={n}", flush=True)
+    om, gm = oracle_map_of(sc), gpu_map_of(sc)
+    st = gm.stats()
+    chunk = 192 if n == 700_000 else 128
+    assert st["n_units"] >= -(-n // chunk) and st["n_units"] <= n // chunk + st["n_point_blocks"]
+    ijk, a_ref, _, _ = om.export()
+    a = gm.query(cuda(ijk.astype(np.int32)))["alpha"].cpu().numpy()
+    assert np.max(np.abs(a - a_ref) / a_ref) <= 1e-5
