@@ -657,7 +657,7 @@ size_t body_bytes(int64_t nt, int64_t nq, int32_t K, int64_t nblocks) {
     c.take<int32_t>(n);
     c.take<int32_t>(n);
     c.take<int32_t>(n + 1);
-    c.take<char>(radix_tmp_bytes(n));
+    c.take<char>(sizeof(uint32_t) * 512 * (ceil_div_i64(std::max<int64_t>(n, 1), 4096) + 1) + 256);
     c.take<char>(scan_tmp_bytes(n));
   }
   return c.used + kAl;

@@ -3,8 +3,8 @@
 // One pass per digit of up to 9 bits: (1) per-tile digit histograms, (2) per
 // digit, an exclusive scan of its tile counts and its total, (3) a stable
 // scatter, which adds the totals of the smaller digits itself.  In the
-// scatter a wavefront takes 1024 consecutive elements of its tile and groups
-// equal digits with wave ballots (the peers of a lane are the lanes whose
+// scatter a wavefront takes consecutive elements of its tile and groups equal
+// digits with wave ballots (the peers of a lane are the lanes whose
 // digit agrees on every bit); its running digit counts live in its own LDS
 // row, so rounds need no barrier.  Integer work only: bit-exact and
 // run-to-run deterministic.
@@ -14,9 +14,15 @@ namespace {
 
 constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / SMKI_WAVE;
-constexpr int RS_ROUNDS = 16;
-constexpr int RS_SPAN = RS_ROUNDS * SMKI_WAVE;   // 1024 consecutive elements per wavefront
-constexpr int RS_TILE = RS_THREADS * RS_ROUNDS;  // 4096 elements per tile
+// Elements per thread: 16 (tiles of 4096) keep the tile counts, which every digit
+// scans, few; up to kSmallN elements 4 (tiles of 1024), since a tile's rounds run
+// one after the other and the larger tiles would leave most CUs idle: 26,000
+// elements 12 us a scatter with tiles of 4096, 8 with tiles of 1024 (their counts included).
+constexpr int kRounds = 16, kSmallRounds = 4;
+constexpr int64_t kSmallN = int64_t(1) << 18;
+// Up to this many tiles the scatter adds the earlier tiles' counts itself (64
+// counts a thread, about what the launch of their scan costs).
+constexpr int64_t kFewTiles = 64;
 constexpr int RS_MAXBITS = 9;                   // digits of up to 9 bits
 constexpr int RS_MAXBINS = 1 << RS_MAXBITS;
 
@@ -36,11 +42,12 @@ __device__ __forceinline__ uint64_t digit_peers(uint32_t d, bool valid, int dbit
   return peers;
 }
 
-// Element layout of a tile: wavefront w holds elements [w RS_SPAN, (w+1) RS_SPAN),
-// round r of it the 64 elements from w RS_SPAN + 64 r, lane i the i-th of them;
-// so (wavefront, round, lane) is element order.
+// Element layout of a tile of RD rounds: wavefront w holds its 64 RD consecutive
+// elements, round r of it the 64 from 64 r, lane i the i-th of them; so
+// (wavefront, round, lane) is element order.
+template <int RD>
 __device__ __forceinline__ int64_t elem_index(int64_t tile_base, int w, int r, int lane) {
-  return tile_base + (int64_t)w * RS_SPAN + (int64_t)r * SMKI_WAVE + lane;
+  return tile_base + (int64_t)w * (RD * SMKI_WAVE) + (int64_t)r * SMKI_WAVE + lane;
 }
 
 // Per-tile digit counts: every element adds 1 to its digit's counter with an
@@ -48,7 +55,9 @@ __device__ __forceinline__ int64_t elem_index(int64_t tile_base, int w, int r, i
 // uses copy l % NC of the counters, rows padded by one word, so that the lanes
 // of one wavefront with equal digits neither hit one address nor one bank;
 // the copies are summed at the end.
-template <typename K, int NB>
+// FEW: the counts go to the table tile by tile (the scatter's threads read one
+// digit each), else digit by digit (each digit's row is scanned).
+template <typename K, int NB, int RD, bool FEW>
 __global__ void __launch_bounds__(RS_THREADS) k_hist(const K* __restrict__ keys, int64_t ncap,
                                                      const int64_t* __restrict__ dn, int shift,
                                                      int dbits, int64_t ntiles,
@@ -60,21 +69,21 @@ __global__ void __launch_bounds__(RS_THREADS) k_hist(const K* __restrict__ keys,
   __shared__ uint32_t h[NC * STR];
   const int tid = threadIdx.x, lane = tid & (SMKI_WAVE - 1), w = tid / SMKI_WAVE;
   const uint32_t mask = (1u << dbits) - 1u;
-  const int64_t tile_base = (int64_t)blockIdx.x * RS_TILE;
+  const int64_t tile_base = (int64_t)blockIdx.x * (RS_THREADS * RD);
   for (int i = tid; i < NC * STR; i += RS_THREADS) h[i] = 0;
-  K key[RS_ROUNDS];
+  K key[RD];
 #pragma unroll
-  for (int r = 0; r < RS_ROUNDS; ++r) {
-    const int64_t i = elem_index(tile_base, w, r, lane);
+  for (int r = 0; r < RD; ++r) {
+    const int64_t i = elem_index<RD>(tile_base, w, r, lane);
     key[r] = i < n ? keys[i] : (K)0;
   }
   __syncthreads();
   uint32_t* hc = h + (lane % NC) * STR;
 #pragma unroll
-  for (int r = 0; r < RS_ROUNDS; ++r)
-    if (elem_index(tile_base, w, r, lane) < n) atomicAdd(&hc[digit_of(key[r], shift, mask)], 1u);
+  for (int r = 0; r < RD; ++r)
+    if (elem_index<RD>(tile_base, w, r, lane) < n) atomicAdd(&hc[digit_of(key[r], shift, mask)], 1u);
   __syncthreads();
-  // digit-major layout: all tiles of digit 0, then digit 1, ...
+  // digit-major layout: all tiles of digit 0, then digit 1, ... (FEW: tile-major)
 #pragma unroll
   for (int j = 0; j < DPT; ++j) {
     const int d = tid * DPT + j;
@@ -82,7 +91,7 @@ __global__ void __launch_bounds__(RS_THREADS) k_hist(const K* __restrict__ keys,
     uint32_t c = 0;
 #pragma unroll
     for (int q = 0; q < NC; ++q) c += h[q * STR + d];
-    hist[(int64_t)d * ntiles + blockIdx.x] = c;
+    hist[FEW ? (int64_t)blockIdx.x * NB + d : (int64_t)d * ntiles + blockIdx.x] = c;
   }
 }
 
@@ -143,16 +152,16 @@ __global__ void __launch_bounds__(RS_THREADS) k_digit_scan(uint32_t* __restrict_
 
 // Last pass with records: a thread gathers the records (and weights) of eight
 // of the tile's sorted elements before storing any of them.
-template <typename K, bool WT>
+template <typename K, bool WT, int RD>
 __device__ __forceinline__ void write_records(const K* skey, const uint32_t* sval,
                                               const uint32_t* gbase, const uint32_t* lstart,
                                               int tile_n, int shift, uint32_t mask,
                                               K* __restrict__ okeys, uint32_t* __restrict__ ovals,
                                               const SortPayload& pl) {
-  constexpr int G = 8;
+  constexpr int G = RD < 8 ? RD : 8, TILE = RS_THREADS * RD;
   const int tid = threadIdx.x;
 #pragma unroll
-  for (int j0 = 0; j0 < RS_TILE; j0 += G * RS_THREADS) {
+  for (int j0 = 0; j0 < TILE; j0 += G * RS_THREADS) {
     // Unconditional: a thread past the tile's end takes its last element again
     // and stores the same values to the same place.
     float rx[G], ry[G], rz[G], rw[G], wv[G];   // (component arrays stay in registers)
@@ -182,17 +191,18 @@ __device__ __forceinline__ void write_records(const K* skey, const uint32_t* sva
   }
 }
 
-// Stable scatter of one tile (RS_TILE elements, one workgroup):
+// Stable scatter of one tile (256 RD elements, one workgroup):
 //   1. every wavefront loads its span and ranks each element among the equal
 //      digits of its span (wave ballots; per-wavefront running counts in LDS,
 //      no barrier between rounds);
 //   2. per digit, the tile's count and each wavefront's first index inside the
 //      tile (exclusive scans over wavefronts, then over digits); the scanned
-//      histogram table gives the digit's first global position;
+//      histogram table (FEW: the counts of the earlier tiles) gives the digit's
+//      first global position;
 //   3. the elements are placed in LDS in digit order, then written out by
 //      consecutive threads, so the stores of each digit's run are contiguous.
 // pl.rec_in (last pass only, optional): also gather the records by value.
-template <typename K, int NB>
+template <typename K, int NB, int RD, bool FEW>
 __global__ void __launch_bounds__(RS_THREADS) k_scatter(const K* __restrict__ keys,
                                                         const uint32_t* __restrict__ vals,
                                                         K* __restrict__ okeys,
@@ -202,45 +212,58 @@ __global__ void __launch_bounds__(RS_THREADS) k_scatter(const K* __restrict__ ke
                                                         const uint32_t* __restrict__ offs,
                                                         const uint32_t* __restrict__ total,
                                                         SortPayload pl, int vals_iota) {
+  constexpr int TILE = RS_THREADS * RD;
   const int64_t n = eff_n(ncap, dn);
-  if ((int64_t)blockIdx.x * RS_TILE >= n) return;   // a tile past the count (capacity launch)
+  if ((int64_t)blockIdx.x * TILE >= n) return;   // a tile past the count (capacity launch)
   constexpr int DPT = NB / RS_THREADS;   // digits per thread: tid * DPT + j
   __shared__ uint32_t gbase[NB];    // first global position of the tile's digit-d elements
   __shared__ uint32_t lstart[NB];   // first index of digit d inside the tile
   __shared__ uint32_t wh[RS_WAVES][NB];   // per wavefront: digit counts, then first index
   __shared__ uint32_t wsum[2][RS_WAVES];
-  __shared__ K skey[RS_TILE];
-  __shared__ uint32_t sval[RS_TILE];
+  __shared__ K skey[TILE];
+  __shared__ uint32_t sval[TILE];
   const int tid = threadIdx.x, lane = tid & (SMKI_WAVE - 1), w = tid / SMKI_WAVE;
   const uint32_t mask = (1u << dbits) - 1u;
   const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (SMKI_WAVE - lane));
-  const int64_t tile_base = (int64_t)blockIdx.x * RS_TILE;
+  const int64_t tile_base = (int64_t)blockIdx.x * TILE;
   uint32_t in_digit[DPT], dtot[DPT];   // earlier tiles' count of the digit, its total
 #pragma unroll
   for (int j = 0; j < DPT; ++j) {
     const int d = tid * DPT + j;
     const bool real = d <= (int)mask;
-    in_digit[j] = real ? offs[(int64_t)d * ntiles + blockIdx.x] : 0u;
-    dtot[j] = real ? total[d] : 0u;
+    if constexpr (FEW) {
+      uint32_t before = 0, all = 0;
+#pragma unroll 8
+      for (int t = 0; t < (int)ntiles; ++t) {
+        const uint32_t c = real ? offs[t * NB + d] : 0u;
+        before += t < (int)blockIdx.x ? c : 0u;
+        all += c;
+      }
+      in_digit[j] = before;
+      dtot[j] = all;
+    } else {
+      in_digit[j] = real ? offs[(int64_t)d * ntiles + blockIdx.x] : 0u;
+      dtot[j] = real ? total[d] : 0u;
+    }
   }
 #pragma unroll
   for (int q = 0; q < RS_WAVES; ++q)
 #pragma unroll
     for (int j = 0; j < DPT; ++j) wh[q][tid * DPT + j] = 0;
-  K key[RS_ROUNDS];
-  uint32_t val[RS_ROUNDS];
+  K key[RD];
+  uint32_t val[RD];
 #pragma unroll
-  for (int r = 0; r < RS_ROUNDS; ++r) {
-    const int64_t i = elem_index(tile_base, w, r, lane);
+  for (int r = 0; r < RD; ++r) {
+    const int64_t i = elem_index<RD>(tile_base, w, r, lane);
     key[r] = i < n ? keys[i] : (K)0;
     val[r] = vals_iota ? (uint32_t)i : (i < n ? vals[i] : 0u);
   }
   __syncthreads();
   // 1. rank inside the wavefront's span
-  uint32_t lrank[RS_ROUNDS];
+  uint32_t lrank[RD];
 #pragma unroll
-  for (int r = 0; r < RS_ROUNDS; ++r) {
-    const bool valid = elem_index(tile_base, w, r, lane) < n;
+  for (int r = 0; r < RD; ++r) {
+    const bool valid = elem_index<RD>(tile_base, w, r, lane) < n;
     const uint32_t d = digit_of(key[r], shift, mask);
     const uint64_t peers = digit_peers(d, valid, dbits);
     const uint32_t before = wh[w][d];
@@ -301,15 +324,15 @@ __global__ void __launch_bounds__(RS_THREADS) k_scatter(const K* __restrict__ ke
   __syncthreads();
   // 3. place in digit order, then write out contiguously
 #pragma unroll
-  for (int r = 0; r < RS_ROUNDS; ++r) {
-    if (elem_index(tile_base, w, r, lane) < n) {
+  for (int r = 0; r < RD; ++r) {
+    if (elem_index<RD>(tile_base, w, r, lane) < n) {
       const uint32_t p = wh[w][digit_of(key[r], shift, mask)] + lrank[r];
       skey[p] = key[r];
       sval[p] = val[r];
     }
   }
   __syncthreads();
-  const int tile_n = (int)min((int64_t)RS_TILE, n - tile_base);
+  const int tile_n = (int)min((int64_t)TILE, n - tile_base);
   if (!pl.rec_in) {
 #pragma unroll 4
     for (int j = tid; j < tile_n; j += RS_THREADS) {
@@ -322,22 +345,38 @@ __global__ void __launch_bounds__(RS_THREADS) k_scatter(const K* __restrict__ ke
     return;
   }
   if (pl.w_in)
-    write_records<K, true>(skey, sval, gbase, lstart, tile_n, shift, mask, okeys, ovals, pl);
+    write_records<K, true, RD>(skey, sval, gbase, lstart, tile_n, shift, mask, okeys, ovals, pl);
   else
-    write_records<K, false>(skey, sval, gbase, lstart, tile_n, shift, mask, okeys, ovals, pl);
+    write_records<K, false, RD>(skey, sval, gbase, lstart, tile_n, shift, mask, okeys, ovals, pl);
 }
 
-template <typename K, int NB>
-void launch_pass(const K* sk, const uint32_t* sv, K* dk, uint32_t* dv, int64_t n,
-                 const int64_t* dn, int shift, int dbits, int64_t ntiles, uint32_t* hist,
-                 uint32_t* total, const SortPayload& pl, int vals_iota, hipStream_t st) {
-  hipLaunchKernelGGL((k_hist<K, NB>), dim3((unsigned)ntiles), dim3(RS_THREADS), 0, st, sk, n, dn,
-                     shift, dbits, ntiles, hist);
-  hipLaunchKernelGGL(k_digit_scan, dim3(1u << dbits), dim3(RS_THREADS), 0, st, hist, ntiles,
-                     total);
-  hipLaunchKernelGGL((k_scatter<K, NB>), dim3((unsigned)ntiles), dim3(RS_THREADS), 0, st, sk, sv,
-                     dk, dv, n, dn, shift, dbits, ntiles, (const uint32_t*)hist,
+template <typename K, int NB, int RD, bool FEW>
+void launch_pass_of(const K* sk, const uint32_t* sv, K* dk, uint32_t* dv, int64_t n,
+                    const int64_t* dn, int shift, int dbits, int64_t ntiles, uint32_t* hist,
+                    uint32_t* total, const SortPayload& pl, int vals_iota, hipStream_t st) {
+  hipLaunchKernelGGL((k_hist<K, NB, RD, FEW>), dim3((unsigned)ntiles), dim3(RS_THREADS), 0, st, sk,
+                     n, dn, shift, dbits, ntiles, hist);
+  if (!FEW)
+    hipLaunchKernelGGL(k_digit_scan, dim3(1u << dbits), dim3(RS_THREADS), 0, st, hist, ntiles,
+                       total);
+  hipLaunchKernelGGL((k_scatter<K, NB, RD, FEW>), dim3((unsigned)ntiles), dim3(RS_THREADS), 0, st,
+                     sk, sv, dk, dv, n, dn, shift, dbits, ntiles, (const uint32_t*)hist,
                      (const uint32_t*)total, pl, vals_iota);
+}
+
+template <typename K, int NB, typename... A>
+void launch_pass(bool small, int64_t ntiles, A... args) {
+  if (!small)
+    launch_pass_of<K, NB, kRounds, false>(args...);
+  else if (ntiles <= kFewTiles)
+    launch_pass_of<K, NB, kSmallRounds, true>(args...);
+  else
+    launch_pass_of<K, NB, kSmallRounds, false>(args...);
+}
+
+// Tiles of n elements (n: the capacity where the count is on the device).
+int64_t tiles_of(int64_t n) {
+  return ceil_div_i64(n, RS_THREADS * (n <= kSmallN ? kSmallRounds : kRounds));
 }
 
 template <typename K>
@@ -348,7 +387,8 @@ hipError_t sort_impl(K* keys, uint32_t* vals, K* akeys, uint32_t* avals, int64_t
   // without one, one element or none needs no pass
   if (n <= 0 || (!dn && n <= 1)) return hipSuccess;
   if (bits <= 0) bits = 1;
-  const int64_t ntiles = ceil_div_i64(n, RS_TILE);
+  const int64_t ntiles = tiles_of(n);
+  const bool small = n <= kSmallN;
   uint32_t* hist = (uint32_t*)tmp;
   uint32_t* total = hist + RS_MAXBINS * ntiles;   // digit totals
   // fewest passes of at most 9 bits, the bits spread evenly over them; digits
@@ -365,10 +405,10 @@ hipError_t sort_impl(K* keys, uint32_t* vals, K* akeys, uint32_t* avals, int64_t
     const SortPayload& pp = (p == passes - 1 && pl) ? *pl : none;
     const int iota = (p == 0 && vals_iota) ? 1 : 0;
     if (dbits <= 8)
-      launch_pass<K, 256>(src_k, src_v, dst_k, dst_v, n, dn, shift, dbits, ntiles, hist, total,
+      launch_pass<K, 256>(small, ntiles, src_k, src_v, dst_k, dst_v, n, dn, shift, dbits, ntiles, hist, total,
                           pp, iota, st);
     else
-      launch_pass<K, 512>(src_k, src_v, dst_k, dst_v, n, dn, shift, dbits, ntiles, hist, total,
+      launch_pass<K, 512>(small, ntiles, src_k, src_v, dst_k, dst_v, n, dn, shift, dbits, ntiles, hist, total,
                           pp, iota, st);
     K* tk = src_k; src_k = dst_k; dst_k = tk;
     uint32_t* tv = src_v; src_v = dst_v; dst_v = tv;
@@ -385,7 +425,7 @@ hipError_t sort_impl(K* keys, uint32_t* vals, K* akeys, uint32_t* avals, int64_t
 }  // namespace
 
 size_t radix_tmp_bytes(int64_t n) {
-  const int64_t ntiles = ceil_div_i64(n > 0 ? n : 1, RS_TILE);
+  const int64_t ntiles = tiles_of(n > 0 ? n : 1);
   return sizeof(uint32_t) * RS_MAXBINS * (ntiles + 1) + 256;   // tile counts, digit totals
 }
 

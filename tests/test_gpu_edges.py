@@ -49,3 +49,27 @@ def test_unit_sizes_chosen_per_insert(n):
     ijk, a_ref, _, _ = om.export()
     a = gm.query(cuda(ijk.astype(np.int32)))["alpha"].cpu().numpy()
     assert np.max(np.abs(a - a_ref) / a_ref) <= 1e-5
+
+
+@pytest.mark.parametrize("n", [1, 2, 1_023, 1_025, 65_536, 65_537, 262_144, 262_145])
+@pytest.mark.parametrize("extent,res", [(2.0, 0.1), (700.0, 0.3)])
+def test_sorted_cells_at_tile_edges(n, extent, res):
+    # the radix sort's tiles (1,024 elements up to 2^18, 4,096 beyond), its passes
+    # without a scan of the counts (up to 64 tiles), 32- and 64-bit keys
+    from paper_1909_04631_amd import bucket_cells
+    rng = np.random.default_rng(n)
+    xyz = rng.uniform(-extent, extent, size=(n, 3)).astype(np.float32)
+    if extent > 100:
+        xyz[:, 2] *= 0.05
+    print(f"[case] cells n={n} extent={extent}", flush=True)
+    keys, start, count, order = [t.cpu().numpy() for t in bucket_cells(cuda(xyz), res, 4)]
+    ref = oracle.pack_keys(oracle.voxel_coords(xyz, np.float32(res)))
+    uk, inv, cnt = np.unique(ref, return_inverse=True, return_counts=True)
+    by_key = np.argsort(keys.view(np.uint64))
+    assert np.array_equal(keys.view(np.uint64)[by_key], uk)
+    assert np.array_equal(count[by_key], cnt)
+    # the rows of a cell in input order: a stable sort by key gives the same order
+    want = np.argsort(inv, kind="stable")
+    first = np.concatenate([[0], np.cumsum(cnt)])
+    got = np.concatenate([order[s:s + c] for s, c in zip(start[by_key], count[by_key])])
+    assert np.array_equal(got, want) and first[-1] == n
