@@ -368,36 +368,49 @@ __global__ void k_permute_rec(const float4* __restrict__ rec, const float* __res
 
 // Slots: the runs of sorted rows that share (plane, block) = key >> log2B3.
 // A row heads a slot when its block differs from the previous row's.  Tiles of
-// HT rows (one workgroup; wavefront w takes rows [w HS, (w+1) HS) of it, 64 per
-// round) first count their heads; after the scan of the counts, they give
-// their heads consecutive slot numbers in row order with wave ballots.
+// 256 RD rows (one workgroup; wavefront w takes its 64 RD consecutive rows, 64 per
+// round) first mark their heads, one bit per row, and count them; after the scan
+// of the counts they give their heads consecutive slot numbers in row order.
+// The second pass reads the bits and the heads' keys only (reading every key and
+// its predecessor twice took 492 us of the 1.7e8 rows of a town, now 234).
+// Few rows take tiles of four rounds, which run one after the other, instead of
+// sixteen (26,000 rows: 16 us, now 7).
 constexpr int HT_THREADS = 256;
-constexpr int HT_ROUNDS = 16;
-constexpr int HS = HT_ROUNDS * SMKI_WAVE;      // rows per wavefront
-constexpr int HT = HT_THREADS * HT_ROUNDS;     // rows per tile
+constexpr int kHeadRounds = 16, kHeadSmallRounds = 4;
+constexpr int64_t kHeadSmallN = int64_t(1) << 18;
 
-template <typename KeyT>
-__device__ __forceinline__ bool heads_slot(const KeyT* __restrict__ keys, int64_t i, int64_t n,
-                                           int shift) {
-  // (n is the row count; launches past it see no heads)
-  if (i >= n) return false;
-  return i == 0 || (uint64_t)(keys[i] >> shift) != (uint64_t)(keys[i - 1] >> shift);
-}
-
-template <typename KeyT>
+template <typename KeyT, int RD>
 __global__ void __launch_bounds__(HT_THREADS) k_head_counts(const KeyT* __restrict__ keys,
                                                             int64_t ncap,
                                                             const int64_t* __restrict__ dn,
                                                             int shift,
+                                                            unsigned long long* __restrict__ heads,
                                                             int32_t* __restrict__ tcount) {
-  const int64_t n = eff_n(ncap, dn);
+  const int64_t n = eff_n(ncap, dn);   // (rows past the count head nothing)
   __shared__ int32_t wc[HT_THREADS / SMKI_WAVE];
   const int lane = threadIdx.x & (SMKI_WAVE - 1), w = threadIdx.x / SMKI_WAVE;
-  const int64_t base = (int64_t)blockIdx.x * HT + (int64_t)w * HS + lane;
+  const int64_t first = ((int64_t)blockIdx.x * (HT_THREADS / SMKI_WAVE) + w) * (RD * SMKI_WAVE);
+  KeyT k[RD];
+#pragma unroll
+  for (int r = 0; r < RD; ++r) {
+    const int64_t i = first + r * SMKI_WAVE + lane;
+    k[r] = i < n ? keys[i] : (KeyT)0;
+  }
+  // the block before the wavefront's rows, then the last of each round (row 0
+  // heads a slot whatever came before)
+  uint64_t prev = first > 0 && first < n ? (uint64_t)(keys[first - 1] >> shift) : 0ull;
   int32_t c = 0;
-#pragma unroll 4
-  for (int r = 0; r < HT_ROUNDS; ++r)
-    c += (int32_t)__popcll(__ballot(heads_slot(keys, base + r * SMKI_WAVE, n, shift)));
+#pragma unroll
+  for (int r = 0; r < RD; ++r) {
+    const int64_t i = first + r * SMKI_WAVE + lane;
+    const uint64_t b = (uint64_t)(k[r] >> shift);
+    const uint64_t up = __shfl_up(b, 1, SMKI_WAVE);
+    const bool head = i < n && (i == 0 || b != (lane == 0 ? prev : up));
+    prev = __shfl(b, SMKI_WAVE - 1, SMKI_WAVE);
+    const uint64_t m = __ballot(head);
+    if (lane == 0 && i < ncap) heads[i / SMKI_WAVE] = m;
+    c += (int32_t)__popcll(m);
+  }
   if (lane == 0) wc[w] = c;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -411,50 +424,43 @@ __global__ void __launch_bounds__(HT_THREADS) k_head_counts(const KeyT* __restri
 // row of every slot, the dense grid -> slot index and each slot's grid
 // position.  The dense table is block-major: entry (block * planes + plane),
 // so the classes of one block share a cache line.
-template <typename KeyT>
-__global__ void __launch_bounds__(HT_THREADS) k_slot_heads(const KeyT* __restrict__ keys,
-                                                           int64_t ncap,
-                                                           const int64_t* __restrict__ dn,
-                                                           int log2B3, int64_t n_blocks,
-                                                           int32_t planes,
-                                                           const int32_t* __restrict__ tstart,
-                                                           int32_t* __restrict__ dense,
-                                                           int32_t* __restrict__ slot_lin,
-                                                           int32_t* __restrict__ head,
-                                                           const int32_t* __restrict__ d_nslots,
-                                                           int32_t cap_slots) {
+template <typename KeyT, int RD>
+__global__ void __launch_bounds__(HT_THREADS) k_slot_heads(
+    const KeyT* __restrict__ keys, int64_t ncap, const int64_t* __restrict__ dn, int log2B3,
+    int64_t n_blocks, int32_t planes, const unsigned long long* __restrict__ heads,
+    const int32_t* __restrict__ tstart, int32_t* __restrict__ dense, int32_t* __restrict__ slot_lin,
+    int32_t* __restrict__ head, const int32_t* __restrict__ d_nslots, int32_t cap_slots) {
   // (slots past cap_slots are not stored: a captured insert whose rows make
   // more slots than it was sized for is failed by its capacity check)
   const int64_t n = eff_n(ncap, dn);
   __shared__ int32_t wc[HT_THREADS / SMKI_WAVE];
   const int lane = threadIdx.x & (SMKI_WAVE - 1), w = threadIdx.x / SMKI_WAVE;
-  const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (SMKI_WAVE - lane));
-  const int64_t base = (int64_t)blockIdx.x * HT + (int64_t)w * HS + lane;
+  const int64_t first = ((int64_t)blockIdx.x * (HT_THREADS / SMKI_WAVE) + w) * (RD * SMKI_WAVE);
   if (blockIdx.x == 0 && threadIdx.x == 0 && *d_nslots <= cap_slots) head[*d_nslots] = (int32_t)n;
-  uint64_t hb[HT_ROUNDS];
-  int32_t c = 0;
+  // lane r holds the bits of round r
+  const uint64_t mine = lane < RD && first + lane * SMKI_WAVE < n ? heads[first / SMKI_WAVE + lane] : 0ull;
+  int32_t c = (int32_t)__popcll(mine);
 #pragma unroll
-  for (int r = 0; r < HT_ROUNDS; ++r) {
-    hb[r] = __ballot(heads_slot(keys, base + r * SMKI_WAVE, n, log2B3));
-    c += (int32_t)__popcll(hb[r]);
-  }
+  for (int o = SMKI_WAVE / 2; o > 0; o >>= 1) c += __shfl_xor(c, o, SMKI_WAVE);
   if (lane == 0) wc[w] = c;
   __syncthreads();
   int32_t slot = tstart[blockIdx.x];
   for (int q = 0; q < w; ++q) slot += wc[q];
 #pragma unroll
-  for (int r = 0; r < HT_ROUNDS; ++r) {
-    if ((hb[r] >> lane) & 1ull) {
-      const int64_t i = base + r * SMKI_WAVE;
-      const int64_t blk = (int64_t)((uint64_t)keys[i] >> log2B3);   // plane * n_blocks + block
-      const int32_t sl = slot + (int32_t)__popcll(hb[r] & lt_mask);
+  for (int r = 0; r < RD; ++r) {
+    const uint64_t m = __shfl(mine, r, SMKI_WAVE);
+    if ((m >> lane) & 1ull) {
+      const int64_t i = first + r * SMKI_WAVE + lane;
+      // plane * n_blocks + block, below 2^30
+      const uint32_t blk = (uint32_t)((uint64_t)keys[i] >> log2B3), nb = (uint32_t)n_blocks;
+      const int32_t sl = slot + (int32_t)__popcll(m & ((1ull << lane) - 1ull));
       if (sl < cap_slots) {
-        dense[(blk % n_blocks) * planes + blk / n_blocks] = sl;
+        dense[(int64_t)(blk % nb) * planes + blk / nb] = sl;
         slot_lin[sl] = (int32_t)blk;
         head[sl] = (int32_t)i;
       }
     }
-    slot += (int32_t)__popcll(hb[r]);
+    slot += (int32_t)__popcll(m);
   }
 }
 
@@ -566,15 +572,29 @@ static hipError_t finish_set(PointSet& ps, KeyT* keys, uint32_t* idx, KeyT* akey
                        (const float*)scr.wt, idx, n, ps.pts, ps.wts);
   ps.perm = idx;
   const int log2B3 = 3 * g.log2B;
-  // slot heads: per-tile counts (in scr.flag), their scan (scr.slot_excl), numbering
-  const int64_t ntiles = ceil_div_i64(n, HT);
-  hipLaunchKernelGGL(k_head_counts<KeyT>, dim3((unsigned)ntiles), dim3(HT_THREADS), 0, st, keys, n,
-                     dn, log2B3, scr.flag);
+  // slot heads: their bits and per-tile counts (both in scr.flag), the scan of
+  // the counts (scr.slot_excl), numbering
+  const bool few = n <= kHeadSmallN;
+  const int64_t ntiles =
+      ceil_div_i64(n, HT_THREADS * (few ? kHeadSmallRounds : kHeadRounds));
+  unsigned long long* heads = (unsigned long long*)(scr.flag + (ntiles + 1) / 2 * 2);
+  const dim3 grid((unsigned)ntiles), block(HT_THREADS);
+  if (few)
+    hipLaunchKernelGGL((k_head_counts<KeyT, kHeadSmallRounds>), grid, block, 0, st, keys, n, dn,
+                       log2B3, heads, scr.flag);
+  else
+    hipLaunchKernelGGL((k_head_counts<KeyT, kHeadRounds>), grid, block, 0, st, keys, n, dn, log2B3,
+                       heads, scr.flag);
   e = scan_excl_i32(scr.flag, scr.slot_excl, ntiles, ps.d_nslots, scr.scan_tmp, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_slot_heads<KeyT>, dim3((unsigned)ntiles), dim3(HT_THREADS), 0, st, keys, n,
-                     dn, log2B3, g.n_blocks, g.planes, scr.slot_excl, ps.dense, ps.slot_lin,
-                     ps.head, ps.d_nslots, cap_slots);
+  if (few)
+    hipLaunchKernelGGL((k_slot_heads<KeyT, kHeadSmallRounds>), grid, block, 0, st, keys, n, dn,
+                       log2B3, g.n_blocks, g.planes, (const unsigned long long*)heads, scr.slot_excl,
+                       ps.dense, ps.slot_lin, ps.head, ps.d_nslots, cap_slots);
+  else
+    hipLaunchKernelGGL((k_slot_heads<KeyT, kHeadRounds>), grid, block, 0, st, keys, n, dn, log2B3,
+                       g.n_blocks, g.planes, (const unsigned long long*)heads, scr.slot_excl,
+                       ps.dense, ps.slot_lin, ps.head, ps.d_nslots, cap_slots);
   if (!ps.prefix) return hipGetLastError();
   if (log2B3 != 6) return hipErrorInvalidValue;   // (cell tables: blocks of 4^3 cells)
   hipLaunchKernelGGL((k_slot_prefix<KeyT, 6>), dim3((unsigned)std::min<int64_t>(nblk(n, 4), 4096)),
@@ -685,7 +705,7 @@ __device__ __forceinline__ bool row_cell(const BucketGeom& g, double inv_res, fl
 }
 
 // Tiles of the two passes over the rows: NT rows, four per thread, loaded before
-// any is used (sixteen, as in the slot passes, left 25,000 rows to seven workgroups).
+// any is used (sixteen left 25,000 rows to seven workgroups).
 constexpr int NR = 4;
 constexpr int NS = NR * SMKI_WAVE;       // rows per wavefront
 constexpr int NT = HT_THREADS * NR;      // rows per tile

@@ -42,7 +42,7 @@ struct BucketScratch {
   uint32_t* aidx;
   float4* rec;        // unsorted records
   float* wt;          // unsorted row weights, or nullptr (then PointSet::wts is not written)
-  int32_t* flag;
+  int32_t* flag;      // tile counts and slot-head bits (rows, and at least 64 entries)
   int32_t* slot_excl;
   void* sort_tmp;
   void* scan_tmp;
