@@ -37,9 +37,8 @@ __device__ __forceinline__ float beam_len(float px, float py, float pz, float ox
   return sqrt_rn(L2);
 }
 
-__device__ __forceinline__ int voxel_index(float x, float res, int32_t* out) {
-  float q = div_rn(x, res);
-  float f = floorf(q);
+__device__ __forceinline__ int voxel_index(float x, double inv_res, float res, int32_t* out) {
+  const float f = floorf(quot_rn(x, inv_res, res));
   if (!(f >= -(float)SMKI_COORD_LIM && f < (float)SMKI_COORD_LIM)) return 0;
   *out = (int32_t)f;
   return 1;
@@ -59,20 +58,36 @@ __device__ __forceinline__ int32_t scan_of(const int64_t* scan_off, int32_t S, i
   return lo;
 }
 
+// Scan offsets in LDS (up to kScanLds scans; else they stay in global memory).
+constexpr int kScanLds = 512;
+__device__ __forceinline__ const int64_t* stage_scans(const int64_t* __restrict__ scan_off, int32_t S,
+                                                      int64_t* lds) {
+  if (S > kScanLds) return scan_off;
+  for (int32_t s = threadIdx.x; s <= S; s += blockDim.x) lds[s] = scan_off[s];
+  __syncthreads();
+  return lds;
+}
+
 // Per hit: validation, hit rows (kept: 1 for a labelled hit; for soft weights
 // the number of classes with a positive weight), number of free samples of a
 // kept hit, voxel bounding box.  probs (nullable) replaces label: [n][K]
 // weights, each finite and >= 0; all zero drops the hit and its beam.
-__global__ void k_count(const float* __restrict__ xyz, const int32_t* __restrict__ label,
-                        const float* __restrict__ probs, int64_t n,
-                        const int64_t* __restrict__ scan_off, const float* __restrict__ origins,
-                        int32_t S, float res, float step, int32_t K, int64_t* __restrict__ nfree,
-                        int32_t* __restrict__ kept, int32_t* __restrict__ bbox,
-                        uint32_t* __restrict__ err) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// Threads stride over the hits in a capped grid, so that the box copies meet few
+// atomics (a workgroup per 256 hits of 4.5e6: 159 us, now 40).
+__global__ void __launch_bounds__(256) k_count(
+    const float* __restrict__ xyz, const int32_t* __restrict__ label,
+    const float* __restrict__ probs, int64_t n, const int64_t* __restrict__ scan_off,
+    const float* __restrict__ origins, int32_t S, float res, float step, int32_t K,
+    int64_t* __restrict__ nfree, int32_t* __restrict__ kept, int32_t* __restrict__ bbox,
+    uint32_t* __restrict__ err) {
+  __shared__ int64_t so[kScanLds + 1];
+  const int64_t* soff = stage_scans(scan_off, S, so);
+  const double inv_res = 1.0 / (double)res, inv_step = 1.0 / (double)step;
   int32_t lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX};
   int32_t hi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
-  if (i < n) {
+  uint32_t err_all = 0;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x) {
     const float px = xyz[3 * i], py = xyz[3 * i + 1], pz = xyz[3 * i + 2];
     uint32_t e = 0;
     int64_t c = 0;
@@ -91,26 +106,26 @@ __global__ void k_count(const float* __restrict__ xyz, const int32_t* __restrict
     if (!finite3(px, py, pz)) e |= DEVERR_NONFINITE;
     if (e == 0 && k > 0) {
       int32_t v[3];
-      if (!voxel_index(px, res, &v[0]) || !voxel_index(py, res, &v[1]) ||
-          !voxel_index(pz, res, &v[2])) {
+      if (!voxel_index(px, inv_res, res, &v[0]) || !voxel_index(py, inv_res, res, &v[1]) ||
+          !voxel_index(pz, inv_res, res, &v[2])) {
         e |= DEVERR_RANGE;
       } else {
-        for (int a = 0; a < 3; ++a) { lo[a] = v[a]; hi[a] = v[a]; }
+        for (int a = 0; a < 3; ++a) { lo[a] = min(lo[a], v[a]); hi[a] = max(hi[a], v[a]); }
       }
       if (step > 0.0f) {
-        const int32_t s = scan_of(scan_off, S, i);
+        const int32_t s = scan_of(soff, S, i);
         const float ox = origins[3 * s], oy = origins[3 * s + 1], oz = origins[3 * s + 2];
         float vx, vy, vz;
         const float L = beam_len(px, py, pz, ox, oy, oz, &vx, &vy, &vz);
         if (L > 0.0f) {
-          const float cf = ceilf(div_rn(L, step));
+          const float cf = ceilf(quot_rn(L, inv_step, step));
           if (!(cf - 1.0f <= (float)SMKI_MAX_SAMPLES_PER_RAY)) e |= DEVERR_RAY;
           else c = (int64_t)cf - 1;
         }
         if (c > 0) {
           int32_t vo[3];
-          if (voxel_index(ox, res, &vo[0]) && voxel_index(oy, res, &vo[1]) &&
-              voxel_index(oz, res, &vo[2])) {
+          if (voxel_index(ox, inv_res, res, &vo[0]) && voxel_index(oy, inv_res, res, &vo[1]) &&
+              voxel_index(oz, inv_res, res, &vo[2])) {
             for (int a = 0; a < 3; ++a) { lo[a] = min(lo[a], vo[a]); hi[a] = max(hi[a], vo[a]); }
           } else {
             e |= DEVERR_RANGE;
@@ -120,27 +135,31 @@ __global__ void k_count(const float* __restrict__ xyz, const int32_t* __restrict
     }
     nfree[i] = e ? 0 : c;
     kept[i] = e ? 0 : k;
-    if (e) atomicOr(err, e);
+    err_all |= e;
   }
+  if (err_all) atomicOr(err, err_all);
   // workgroup reduction of the bounding box, then one atomic per workgroup
-  __shared__ int32_t slo[3][256], shi[3][256];
-  for (int a = 0; a < 3; ++a) { slo[a][threadIdx.x] = lo[a]; shi[a][threadIdx.x] = hi[a]; }
-  __syncthreads();
-  for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      for (int a = 0; a < 3; ++a) {
-        slo[a][threadIdx.x] = min(slo[a][threadIdx.x], slo[a][threadIdx.x + o]);
-        shi[a][threadIdx.x] = max(shi[a][threadIdx.x], shi[a][threadIdx.x + o]);
-      }
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int o = SMKI_WAVE / 2; o > 0; o >>= 1) {
+      lo[a] = min(lo[a], __shfl_xor(lo[a], o, SMKI_WAVE));
+      hi[a] = max(hi[a], __shfl_xor(hi[a], o, SMKI_WAVE));
     }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {   // spread over copies: workgroups rarely contend on one address
-    int32_t* bb = bbox + (blockIdx.x % SMKI_BBOX_COPIES) * 8;
+  __shared__ int32_t part[256 / SMKI_WAVE][6];
+  if ((threadIdx.x & (SMKI_WAVE - 1)) == 0)
     for (int a = 0; a < 3; ++a) {
-      if (slo[a][0] != INT32_MAX) atomicMin(&bb[a], slo[a][0]);
-      if (shi[a][0] != INT32_MIN) atomicMax(&bb[3 + a], shi[a][0]);
+      part[threadIdx.x / SMKI_WAVE][a] = lo[a];
+      part[threadIdx.x / SMKI_WAVE][3 + a] = hi[a];
     }
+  __syncthreads();
+  if (threadIdx.x < 6) {   // spread over copies: workgroups rarely contend on one address
+    const int a = threadIdx.x;
+    int32_t v = part[0][a];
+    for (int w = 1; w < 256 / SMKI_WAVE; ++w) v = a < 3 ? min(v, part[w][a]) : max(v, part[w][a]);
+    int32_t* bb = bbox + (blockIdx.x % SMKI_BBOX_COPIES) * 8 + a;
+    if (a < 3 && v != INT32_MAX) atomicMin(bb, v);
+    if (a >= 3 && v != INT32_MIN) atomicMax(bb, v);
   }
 }
 
@@ -206,16 +225,19 @@ __device__ __forceinline__ bool in_grid(const BucketGeom& g, const int32_t b[3])
 // Kept hits -> (key, index) and records (unsorted), at rows kpos[i]...  With
 // soft weights (probs non-null) a hit gives one row per class of positive
 // weight, in class order, and wt[row] = that weight.  Also, for the free-sample
-// kernel (workgroups of FREE_WG samples): wgbeam[b] = the beam that holds free
-// sample b FREE_WG (each such sample lies in exactly one beam's range).
-constexpr int FREE_WG = 256;
+// kernel (workgroups of wg samples): wgbeam[b] = the beam that holds free
+// sample b wg (each such sample lies in exactly one beam's range).
+// Samples per thread of the free-sample kernel (256 threads a workgroup): four
+// share a beam's set-up, one where four would leave CUs without a workgroup (nf: the
+// capacity of a captured insert).
+static inline int32_t free_per(int64_t nf) { return nf <= (int64_t(1) << 18) ? 1 : 4; }
 // dcnt (device, nullable): row counts [total, hits, free samples] of the
 // insert, read here instead of nf (a capacity then).
 template <typename KeyT>
 __global__ void k_hit_keys(const float* __restrict__ xyz, const int32_t* __restrict__ label,
                            const float* __restrict__ probs, int32_t K, int64_t n,
                            const int32_t* __restrict__ kept, const int32_t* __restrict__ kpos,
-                           const int64_t* __restrict__ off, int64_t nf_cap,
+                           const int64_t* __restrict__ off, int64_t nf_cap, int32_t wg,
                            const int64_t* __restrict__ dcnt,
                            int32_t* __restrict__ wgbeam, BucketGeom g, KeyT* __restrict__ keys,
                            float4* __restrict__ rec,
@@ -226,14 +248,15 @@ __global__ void k_hit_keys(const float* __restrict__ xyz, const int32_t* __restr
   if (nf > 0) {
     // (clamped: a captured insert may hold fewer samples than its beams ask for)
     const int64_t a0 = min(off[i], nf), a1 = min(i + 1 < n ? off[i + 1] : nf, nf);
-    for (int64_t b = (a0 + FREE_WG - 1) / FREE_WG; b * FREE_WG < a1; ++b) wgbeam[b] = (int32_t)i;
+    for (int64_t b = (a0 + wg - 1) / wg; b * wg < a1; ++b) wgbeam[b] = (int32_t)i;
   }
   if (!kept[i]) return;
   const float px = xyz[3 * i], py = xyz[3 * i + 1], pz = xyz[3 * i + 2];
   int32_t v[3], b[3], l[3];
-  voxel_index(px, g.res, &v[0]);
-  voxel_index(py, g.res, &v[1]);
-  voxel_index(pz, g.res, &v[2]);
+  const double inv_res = 1.0 / (double)g.res;
+  voxel_index(px, inv_res, g.res, &v[0]);
+  voxel_index(py, inv_res, g.res, &v[1]);
+  voxel_index(pz, inv_res, g.res, &v[2]);
   block_of(g, v, b, l);
   int32_t w = kpos[i];
   const int32_t rows = kept[i];
@@ -261,75 +284,95 @@ __global__ void k_hit_keys(const float* __restrict__ xyz, const int32_t* __restr
   }
 }
 
-// Free sample f -> its beam (largest i with off[i] <= f), its position, key and record.
+// Free sample f -> its beam (largest i with off[i] <= f), its position, key and
+// record.  The beams of a workgroup's samples lie between the beam of its first
+// sample and the beam of the next workgroup's first sample (wgbeam, written by
+// k_hit_keys).  What the samples of a beam share (its offset, its vector and
+// length, its origin's scan, the reciprocal of the length) is computed once per
+// beam and workgroup, into LDS, where up to MAXB beams fit; else by every sample.
+// Writes 24 bytes a sample; the divisions in double by every sample bound it
+// (1.6e8 samples: 1,777 us, now 1,059; 3.9e6: 29 us, now 27).
+struct Beam {
+  float vx, vy, vz, L;
+  float ox, oy, oz;
+  double inv_l;
+};
+__device__ __forceinline__ Beam beam_of(const float* __restrict__ xyz, int64_t i,
+                                        const float* __restrict__ origins, int32_t s) {
+  Beam b;
+  b.ox = origins[3 * s];
+  b.oy = origins[3 * s + 1];
+  b.oz = origins[3 * s + 2];
+  b.L = beam_len(xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], b.ox, b.oy, b.oz, &b.vx, &b.vy, &b.vz);
+  b.inv_l = 1.0 / (double)b.L;
+  return b;
+}
+
 template <typename KeyT>
-__global__ void k_free_keys(const float* __restrict__ xyz, int64_t n,
-                            const int64_t* __restrict__ off, int64_t nf_cap,
-                            const int64_t* __restrict__ dcnt,
-                            const int64_t* __restrict__ scan_off,
-                            const float* __restrict__ origins, int32_t S, float step,
-                            int32_t free_class, BucketGeom g, int64_t out_base_h,
-                            KeyT* __restrict__ keys, float4* __restrict__ rec, float* __restrict__ wrow,
-                            const int32_t* __restrict__ wgbeam, uint32_t* __restrict__ err) {
-  // The beams of this workgroup's samples lie between the beam of its first
-  // sample and the beam of the next workgroup's first sample (wgbeam, written
-  // by k_hit_keys); every sample searches only between them.
-  // The beam offsets of that range go to LDS first when they fit (one round of
-  // global loads instead of a chain of them per search).
-  constexpr int MAXB = FREE_WG;
+__global__ void __launch_bounds__(256) k_free_keys(
+    const float* __restrict__ xyz, int64_t n, const int64_t* __restrict__ off, int64_t nf_cap,
+    int32_t per, const int64_t* __restrict__ dcnt, const int64_t* __restrict__ scan_off,
+    const float* __restrict__ origins, int32_t S, float step, int32_t free_class, BucketGeom g,
+    int64_t out_base_h, KeyT* __restrict__ keys, float4* __restrict__ rec, float* __restrict__ wrow,
+    const int32_t* __restrict__ wgbeam, uint32_t* __restrict__ err) {
+  constexpr int MAXB = 256;
   __shared__ int64_t soff[MAXB];
+  __shared__ Beam beam[MAXB];
   const int64_t nf = dcnt ? dcnt[2] : nf_cap;             // (launch sized for nf_cap)
   const int64_t out_base = dcnt ? dcnt[1] : out_base_h;   // free samples follow the hits
-  const int64_t nwg = (nf + FREE_WG - 1) / FREE_WG;
+  const int64_t nwg = (nf + 256 * per - 1) / (256 * per);
   if ((int64_t)blockIdx.x >= nwg) return;   // (the whole workgroup)
-  const int64_t f = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int64_t lo = wgbeam[blockIdx.x];
-  int64_t hi = (int64_t)blockIdx.x + 1 < nwg ? wgbeam[blockIdx.x + 1] : n - 1;
-  if (hi - lo < MAXB) {   // (the same range for the whole workgroup)
-    if (threadIdx.x <= hi - lo) soff[threadIdx.x] = off[lo + threadIdx.x];
+  const int64_t b0 = wgbeam[blockIdx.x];
+  const int64_t b1 = (int64_t)blockIdx.x + 1 < nwg ? wgbeam[blockIdx.x + 1] : n - 1;
+  const bool staged = b1 - b0 < MAXB;   // (the same range for the whole workgroup)
+  if (staged) {
+    if (threadIdx.x <= b1 - b0) {
+      const int64_t i = b0 + threadIdx.x;
+      soff[threadIdx.x] = off[i];
+      // (a dropped hit holds no sample: its beam may be anything)
+      beam[threadIdx.x] = beam_of(xyz, i, origins, scan_of(scan_off, S, i));
+    }
     __syncthreads();
-    int32_t a = 0, c = (int32_t)(hi - lo);
-    while (a < c) {
-      const int32_t mid = (a + c + 1) >> 1;
-      if (soff[mid] <= f) a = mid; else c = mid - 1;
+  }
+  const double inv_res = 1.0 / (double)g.res;
+  for (int u = 0; u < per; ++u) {
+    const int64_t f = ((int64_t)blockIdx.x * per + u) * 256 + threadIdx.x;
+    if (f >= nf) break;
+    Beam b;
+    int64_t o;
+    if (staged) {
+      int32_t a = 0, c = (int32_t)(b1 - b0);
+      while (a < c) {
+        const int32_t mid = (a + c + 1) >> 1;
+        if (soff[mid] <= f) a = mid; else c = mid - 1;
+      }
+      b = beam[a];
+      o = soff[a];
+    } else {
+      int64_t lo = b0, hi = b1;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi + 1) >> 1;
+        if (off[mid] <= f) lo = mid; else hi = mid - 1;
+      }
+      b = beam_of(xyz, lo, origins, scan_of(scan_off, S, lo));
+      o = off[lo];
     }
-    lo += a;
-  } else {
-    while (lo < hi) {
-      const int64_t mid = (lo + hi + 1) >> 1;
-      if (off[mid] <= f) lo = mid; else hi = mid - 1;
-    }
+    const int64_t j = f - o + 1;
+    const float t = (float)j * step;
+    const float wt = quot_rn(t, b.inv_l, b.L);
+    const float mx = wt * b.vx, my = wt * b.vy, mz = wt * b.vz;
+    const float qx = b.ox + mx, qy = b.oy + my, qz = b.oz + mz;
+    const int64_t w = out_base + f;
+    int32_t v[3] = {0, 0, 0}, bl[3], l[3];
+    bool ok = voxel_index(qx, inv_res, g.res, &v[0]) && voxel_index(qy, inv_res, g.res, &v[1]) &&
+              voxel_index(qz, inv_res, g.res, &v[2]);
+    block_of(g, v, bl, l);
+    ok = ok && in_grid(g, bl);
+    if (!ok) atomicOr(err, DEVERR_RANGE);
+    keys[w] = ok ? make_key<KeyT>(g, free_class, bl, l) : (KeyT)0;
+    rec[w] = ok ? make_map_record(g, qx, qy, qz, v, l) : make_float4(0, 0, 0, 0);
+    if (wrow) wrow[w] = ok ? 1.0f : 0.0f;
   }
-  if (f >= nf) return;
-  const int64_t i = lo;
-  const int64_t j = f - off[i] + 1;
-  const int32_t s = scan_of(scan_off, S, i);
-  const float ox = origins[3 * s], oy = origins[3 * s + 1], oz = origins[3 * s + 2];
-  float vx, vy, vz;
-  const float L = beam_len(xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], ox, oy, oz, &vx, &vy, &vz);
-  const float t = (float)j * step;
-  const float wt = div_rn(t, L);
-  const float mx = wt * vx, my = wt * vy, mz = wt * vz;
-  const float qx = ox + mx, qy = oy + my, qz = oz + mz;
-  const int64_t w = out_base + f;
-  int32_t v[3], b[3], l[3];
-  if (!voxel_index(qx, g.res, &v[0]) || !voxel_index(qy, g.res, &v[1]) ||
-      !voxel_index(qz, g.res, &v[2])) {
-    atomicOr(err, DEVERR_RANGE);
-    keys[w] = (KeyT)0; rec[w] = make_float4(0, 0, 0, 0);
-    if (wrow) wrow[w] = 0.0f;
-    return;
-  }
-  block_of(g, v, b, l);
-  if (!in_grid(g, b)) {
-    atomicOr(err, DEVERR_RANGE);
-    keys[w] = (KeyT)0; rec[w] = make_float4(0, 0, 0, 0);
-    if (wrow) wrow[w] = 0.0f;
-    return;
-  }
-  keys[w] = make_key<KeyT>(g, free_class, b, l);
-  rec[w] = make_map_record(g, qx, qy, qz, v, l);
-  if (wrow) wrow[w] = 1.0f;
 }
 
 // Explicit training rows (differentiable form, tests): keys and records.
@@ -342,8 +385,9 @@ __global__ void k_row_keys(const float* __restrict__ xyz, const int32_t* __restr
   if (i >= n) return;
   const float px = xyz[3 * i], py = xyz[3 * i + 1], pz = xyz[3 * i + 2];
   int32_t v[3], b[3], l[3];
-  if (!finite3(px, py, pz) || !voxel_index(px, g.res, &v[0]) || !voxel_index(py, g.res, &v[1]) ||
-      !voxel_index(pz, g.res, &v[2])) {
+  const double inv_res = 1.0 / (double)g.res;
+  if (!finite3(px, py, pz) || !voxel_index(px, inv_res, g.res, &v[0]) ||
+      !voxel_index(py, inv_res, g.res, &v[1]) || !voxel_index(pz, inv_res, g.res, &v[2])) {
     atomicOr(err, DEVERR_RANGE);
     keys[i] = (KeyT)0; idx[i] = (uint32_t)i; rec[i] = make_float4(0, 0, 0, 0);
     return;
@@ -501,12 +545,14 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
 // ---------------------------------------------------------------------------
 static inline unsigned nblk(int64_t n, int t) { return (unsigned)ceil_div_i64(n > 0 ? n : 1, t); }
 
+constexpr unsigned kCountGrid = 2048;   // workgroups of the hit validation (they stride)
+
 hipError_t launch_count(const float* xyz, const int32_t* label, const float* probs, int64_t n,
                         const int64_t* scan_off, const float* origins, int32_t S, float res,
                         float step, int32_t K, int64_t* nfree, int32_t* kept, int32_t* bbox,
                         uint32_t* err, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_count, dim3(nblk(n, 256)), dim3(256), 0, st, xyz, label, probs, n,
+  hipLaunchKernelGGL(k_count, dim3(std::min(nblk(n, 256), kCountGrid)), dim3(256), 0, st, xyz, label, probs, n,
                      scan_off, origins, S, res, step, K, nfree, kept, bbox, err);
   return hipGetLastError();
 }
@@ -612,11 +658,11 @@ static hipError_t bucket_scan_t(const float* xyz, const int32_t* label, const fl
                                 const int64_t* dcnt, int32_t cap_slots) {
   if (nk > 0 || dcnt)
     hipLaunchKernelGGL(k_hit_keys<KeyT>, dim3(nblk(n, 256)), dim3(256), 0, st, xyz, label, probs,
-                       K, n, kept, kpos, off, nf, dcnt, wgbeam, g, (KeyT*)scr.keys, scr.rec,
+                       K, n, kept, kpos, off, nf, 256 * free_per(nf), dcnt, wgbeam, g, (KeyT*)scr.keys, scr.rec,
                        scr.wt, err);
   if (nf > 0)
-    hipLaunchKernelGGL(k_free_keys<KeyT>, dim3(nblk(nf, FREE_WG)), dim3(FREE_WG), 0, st, xyz, n,
-                       off, nf, dcnt, scan_off, origins, S, step, free_class, g, nk,
+    hipLaunchKernelGGL(k_free_keys<KeyT>, dim3(nblk(nf, 256 * free_per(nf))), dim3(256), 0,
+                       st, xyz, n, off, nf, free_per(nf), dcnt, scan_off, origins, S, step, free_class, g, nk,
                        (KeyT*)scr.keys, scr.rec, scr.wt, (const int32_t*)wgbeam, err);
   return finish_set<KeyT>(ps, (KeyT*)scr.keys, scr.idx, (KeyT*)scr.akeys, scr.aidx, scr.rec, g,
                           g.key_bits, scr, st, true, dcnt, cap_slots);
@@ -641,7 +687,7 @@ hipError_t bucket_scan(const float* xyz, const int32_t* label, const float* prob
                                  dcnt, cap_slots);
 }
 
-int64_t free_sample_workgroups(int64_t nf) { return nf > 0 ? ceil_div_i64(nf, FREE_WG) : 1; }
+int64_t free_sample_workgroups(int64_t nf) { return nf > 0 ? ceil_div_i64(nf, 256 * free_per(nf)) : 1; }
 
 // ---------------------------------------------------------------------------
 // rows and queries of the differentiable form
