@@ -149,70 +149,184 @@ __global__ void k_hash_insert_slots(MapDev m, int64_t slot0, int64_t n, uint32_t
   atomicOr(err, DEVERR_HASH);
 }
 
+// Export and import move dense [K][B^3] blocks, so the caller's array bounds them.
+// V consecutive voxels per access: 4 (a float4) where B^3 and the caller's array
+// allow it, else 1; four accesses per thread in flight.  6,007 blocks of 20 x 512
+// (246 MB): export 167 us, now 57; import's two passes 100 + 49 us, now 46 + 22.
+template <int V>
+struct VecOf;
+template <>
+struct VecOf<1> { using T = float; };
+template <>
+struct VecOf<4> { using T = float4; };
+
+// class block index -> (block, class): 32-bit arithmetic where it fits
+__device__ __forceinline__ void split_bk(int64_t bk, int32_t K, int64_t* b, int32_t* k) {
+  if (bk < (int64_t(1) << 32)) {
+    const uint32_t q = (uint32_t)bk / (uint32_t)K;
+    *b = q;
+    *k = (int32_t)((uint32_t)bk - q * (uint32_t)K);
+  } else {
+    *b = bk / K;
+    *k = (int32_t)(bk % K);
+  }
+}
+
 // out block b <- pool slot order[b], dense [K][B^3] (alpha0 where a class has no class block)
-__global__ void k_gather_blocks(MapDev m, const uint32_t* __restrict__ order, int64_t n,
-                                float* __restrict__ out) {
-  const int64_t B3 = (int64_t)m.B * m.B * m.B;
-  const int64_t per = (int64_t)m.K * B3;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n * per) return;
-  const int64_t b = i / per, r = i % per, k = r / B3, v = r % B3;
-  const int32_t cb = m.cslot[(int64_t)order[b] * m.K + k];
-  out[i] = cb >= 0 ? m.calpha[cb * B3 + v] : m.alpha0;
+template <int V>
+__global__ void __launch_bounds__(256) k_gather_blocks(MapDev m, const uint32_t* __restrict__ order,
+                                                       int64_t n, float* __restrict__ out) {
+  using T = typename VecOf<V>::T;
+  constexpr int U = 4;
+  const int shift = 3 * m.log2B - (V == 4 ? 2 : 0);   // accesses per class block: 2^shift
+  const int64_t total = (n * m.K) << shift;
+  const int64_t base = (int64_t)blockIdx.x * (256 * U) + threadIdx.x;
+  int32_t cb[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t i = min(base + u * 256, total - 1);
+    int64_t b;
+    int32_t k;
+    split_bk(i >> shift, m.K, &b, &k);
+    cb[u] = m.cslot[(int64_t)order[b] * m.K + k];
+  }
+  T v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t i = min(base + u * 256, total - 1);
+    if constexpr (V == 4)
+      v[u] = make_float4(m.alpha0, m.alpha0, m.alpha0, m.alpha0);
+    else
+      v[u] = m.alpha0;
+    if (cb[u] >= 0) v[u] = ((const T*)m.calpha)[((int64_t)cb[u] << shift) + (i & ((int64_t(1) << shift) - 1))];
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u)
+    if (base + u * 256 < total) ((T*)out)[base + u * 256] = v[u];
 }
 
-// import: flag[b][k] = 1 if any voxel of class k in input block b differs from alpha0
-__global__ void k_import_flags(MapDev m, const float* __restrict__ alpha, int64_t n,
-                               int32_t* __restrict__ flag) {
-  const int64_t B3 = (int64_t)m.B * m.B * m.B;
-  const int64_t bk = blockIdx.x;   // (block, class)
-  if (bk >= n * m.K) return;
-  int any = 0;
-  for (int64_t v = threadIdx.x; v < B3; v += blockDim.x) any |= alpha[bk * B3 + v] != m.alpha0;
-  any = __syncthreads_or(any);
-  if (threadIdx.x == 0) flag[bk] = any ? 1 : 0;
+// import: flag[b][k] = 1 if any voxel of class k in input block b differs from
+// alpha0; one wavefront per class block
+template <int V>
+__global__ void __launch_bounds__(256) k_import_flags(MapDev m, const float* __restrict__ alpha,
+                                                      int64_t nbk, int32_t* __restrict__ flag) {
+  using T = typename VecOf<V>::T;
+  constexpr int U = 4;
+  const int lane = threadIdx.x & (SMKI_WAVE - 1);
+  const int64_t bk = (int64_t)blockIdx.x * (256 / SMKI_WAVE) + threadIdx.x / SMKI_WAVE;
+  if (bk >= nbk) return;
+  const int per = (1 << (3 * m.log2B)) / V;
+  const T* p = (const T*)alpha + bk * per;
+  bool any = false;
+  for (int i0 = 0; i0 < per && !__ballot(any); i0 += U * SMKI_WAVE) {
+    T v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = p[min(i0 + u * SMKI_WAVE + lane, per - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if constexpr (V == 4)
+        any = any || v[u].x != m.alpha0 || v[u].y != m.alpha0 || v[u].z != m.alpha0 || v[u].w != m.alpha0;
+      else
+        any = any || v[u] != m.alpha0;
+    }
+  }
+  const bool set = __ballot(any) != 0;
+  if (lane == 0) flag[bk] = set ? 1 : 0;
 }
 
-// import: (block b, class k) flagged -> class block c0 + pos[b][k]; others alpha0 (no block)
-__global__ void k_import_copy(MapDev m, const float* __restrict__ alpha, int64_t n,
-                              const int32_t* __restrict__ flag, const int32_t* __restrict__ pos,
-                              int64_t c0) {
-  const int64_t B3 = (int64_t)m.B * m.B * m.B;
-  const int64_t bk = blockIdx.x;
-  if (bk >= n * m.K) return;
+// import: (block b, class k) flagged -> class block c0 + pos[b][k]; others alpha0
+// (no block); one wavefront per class block
+template <int V>
+__global__ void __launch_bounds__(256) k_import_copy(MapDev m, const float* __restrict__ alpha,
+                                                     int64_t nbk, const int32_t* __restrict__ flag,
+                                                     const int32_t* __restrict__ pos, int64_t c0) {
+  using T = typename VecOf<V>::T;
+  const int lane = threadIdx.x & (SMKI_WAVE - 1);
+  const int64_t bk = (int64_t)blockIdx.x * (256 / SMKI_WAVE) + threadIdx.x / SMKI_WAVE;
+  if (bk >= nbk) return;
   const int32_t cb = flag[bk] ? (int32_t)(c0 + pos[bk]) : -1;
-  if (threadIdx.x == 0) m.cslot[bk] = cb;
+  if (lane == 0) m.cslot[bk] = cb;
   if (cb < 0) return;
-  for (int64_t v = threadIdx.x; v < B3; v += blockDim.x)
-    m.calpha[(int64_t)cb * B3 + v] = alpha[bk * B3 + v];
+  const int per = (1 << (3 * m.log2B)) / V;
+  const T* p = (const T*)alpha + bk * per;
+  T* q = (T*)m.calpha + (int64_t)cb * per;
+#pragma unroll 4
+  for (int i = lane; i < per; i += SMKI_WAVE) q[i] = p[i];
 }
 
-__global__ void k_keys_to_ijk(const uint64_t* __restrict__ keys, int64_t n, int32_t* ijk) {
+// Blocks of an import that appear twice: their keys go into a table of hcap
+// entries (a power of two, at least twice n, every word ~0 before); a key that
+// is already there is a duplicate.  (A sort of the 63-bit keys took 21 launches.)
+__global__ void k_find_dups(const uint64_t* __restrict__ keys, int64_t n,
+                            unsigned long long* __restrict__ table, int64_t hcap,
+                            uint32_t* __restrict__ err) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const uint64_t k = keys[i];
+  const unsigned long long key = keys[i];
+  uint64_t h = smki_mix64(key) & (uint64_t)(hcap - 1);
+  for (int64_t probe = 0; probe < hcap; ++probe) {
+    const unsigned long long old = atomicCAS(&table[h], ~0ull, key);
+    if (old == ~0ull) return;
+    if (old == key) {
+      atomicOr(err, DEVERR_DUP);
+      return;
+    }
+    h = (h + 1) & (uint64_t)(hcap - 1);
+  }
+}
+
+// Sort keys of the map's blocks relative to a box that holds them (lowest block
+// lo, bits[] bits per axis), in the order of the full keys, and their indices.
+__global__ void k_box_keys(const uint64_t* __restrict__ bkeys, int64_t n, int3 lo, int3 bits,
+                           uint32_t* __restrict__ keys, uint32_t* __restrict__ idx) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const uint64_t k = bkeys[i];
+  const uint32_t x = (uint32_t)((int32_t)((k >> 42) & 0x1FFFFF) - (1 << 20) - lo.x);
+  const uint32_t y = (uint32_t)((int32_t)((k >> 21) & 0x1FFFFF) - (1 << 20) - lo.y);
+  const uint32_t z = (uint32_t)((int32_t)(k & 0x1FFFFF) - (1 << 20) - lo.z);
+  keys[i] = (((x << bits.y) | y) << bits.z) | z;
+  idx[i] = (uint32_t)i;
+}
+
+// block coordinates of pool slots order[0, n)
+__global__ void k_keys_to_ijk(const uint64_t* __restrict__ bkeys, const uint32_t* __restrict__ order,
+                              int64_t n, int32_t* ijk) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const uint64_t k = bkeys[order[i]];
   ijk[3 * i] = (int32_t)((k >> 42) & 0x1FFFFF) - (1 << 20);
   ijk[3 * i + 1] = (int32_t)((k >> 21) & 0x1FFFFF) - (1 << 20);
   ijk[3 * i + 2] = (int32_t)(k & 0x1FFFFF) - (1 << 20);
 }
 
 __global__ void k_ijk_to_keys(const int32_t* __restrict__ ijk, int64_t n, int32_t log2B,
-                              uint64_t* keys, uint32_t* err) {
+                              uint64_t* keys, uint32_t* err, int32_t* __restrict__ box) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const int32_t bx = ijk[3 * i], by = ijk[3 * i + 1], bz = ijk[3 * i + 2];
-  const int32_t lim = (1 << 20) >> log2B;   // the block's voxels stay in [-2^20, 2^20)
-  if (bx < -lim || bx >= lim || by < -lim || by >= lim || bz < -lim || bz >= lim) {
-    atomicOr(err, DEVERR_RANGE);
-    keys[i] = 0;
-    return;
+  int32_t b[3] = {INT32_MAX, INT32_MAX, INT32_MAX}, hi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
+  if (i < n) {
+    const int32_t lim = (1 << 20) >> log2B;   // the block's voxels stay in [-2^20, 2^20)
+    bool ok = true;
+    for (int a = 0; a < 3; ++a) {
+      b[a] = hi[a] = ijk[3 * i + a];
+      ok = ok && b[a] >= -lim && b[a] < lim;
+    }
+    if (!ok) atomicOr(err, DEVERR_RANGE);
+    keys[i] = ok ? smki_block_key(b[0], b[1], b[2]) : 0;
   }
-  keys[i] = smki_block_key(bx, by, bz);
-}
-
-__global__ void k_adjacent_dups(const uint64_t* __restrict__ s, int64_t n, uint32_t* err) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i + 1 < n && s[i] == s[i + 1]) atomicOr(err, DEVERR_DUP);
+  // the box of the blocks (one atomic per wavefront and side)
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+#pragma unroll
+    for (int o = SMKI_WAVE / 2; o > 0; o >>= 1) {
+      b[a] = min(b[a], __shfl_xor(b[a], o, SMKI_WAVE));
+      hi[a] = max(hi[a], __shfl_xor(hi[a], o, SMKI_WAVE));
+    }
+    if ((threadIdx.x & (SMKI_WAVE - 1)) == 0) {
+      atomicMin(&box[a], b[a]);
+      atomicMax(&box[3 + a], hi[a]);
+    }
+  }
 }
 
 __global__ void k_iota(uint32_t* p, int64_t n) {
@@ -376,48 +490,75 @@ hipError_t launch_hash_insert_slots(const MapDev& m, int64_t slot0, int64_t n, u
   return hipGetLastError();
 }
 
+// float4 accesses: whole class blocks of a multiple of four voxels, an aligned array
+static bool vec4_ok(const MapDev& m, const void* p) { return m.B >= 2 && ((uintptr_t)p & 15) == 0; }
+
 hipError_t launch_gather_blocks(const MapDev& m, const uint32_t* order, int64_t n,
                                 float* alpha_out, hipStream_t st) {
   const int64_t tot = n * (int64_t)m.K * m.B * m.B * m.B;
   if (tot <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_blocks, dim3(nblk(tot, 256)), dim3(256), 0, st, m, order, n,
-                     alpha_out);
+  if (vec4_ok(m, alpha_out))
+    hipLaunchKernelGGL(k_gather_blocks<4>, dim3(nblk(tot / 4, 1024)), dim3(256), 0, st, m, order, n,
+                       alpha_out);
+  else
+    hipLaunchKernelGGL(k_gather_blocks<1>, dim3(nblk(tot, 1024)), dim3(256), 0, st, m, order, n,
+                       alpha_out);
   return hipGetLastError();
 }
 
 hipError_t launch_import_flags(const MapDev& m, const float* alpha, int64_t n, int32_t* flag,
                                hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_import_flags, dim3((unsigned)(n * m.K)), dim3(256), 0, st, m, alpha, n,
-                     flag);
+  const int64_t nbk = n * m.K;
+  const dim3 grid(nblk(nbk, 256 / SMKI_WAVE)), block(256);
+  if (vec4_ok(m, alpha))
+    hipLaunchKernelGGL(k_import_flags<4>, grid, block, 0, st, m, alpha, nbk, flag);
+  else
+    hipLaunchKernelGGL(k_import_flags<1>, grid, block, 0, st, m, alpha, nbk, flag);
   return hipGetLastError();
 }
 
 hipError_t launch_import_copy(const MapDev& m, const float* alpha, int64_t n, const int32_t* flag,
                               const int32_t* pos, int64_t c0, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_import_copy, dim3((unsigned)(n * m.K)), dim3(256), 0, st, m, alpha, n,
-                     flag, pos, c0);
+  const int64_t nbk = n * m.K;
+  const dim3 grid(nblk(nbk, 256 / SMKI_WAVE)), block(256);
+  if (vec4_ok(m, alpha))
+    hipLaunchKernelGGL(k_import_copy<4>, grid, block, 0, st, m, alpha, nbk, flag, pos, c0);
+  else
+    hipLaunchKernelGGL(k_import_copy<1>, grid, block, 0, st, m, alpha, nbk, flag, pos, c0);
   return hipGetLastError();
 }
 
-hipError_t launch_block_keys_to_ijk(const uint64_t* keys, int64_t n, int32_t* ijk, hipStream_t st) {
+hipError_t launch_find_dups(const uint64_t* keys, int64_t n, uint64_t* table, int64_t hcap,
+                            uint32_t* err, hipStream_t st) {
+  if (n <= 1) return hipSuccess;
+  hipLaunchKernelGGL(k_hash_clear, dim3(nblk(hcap, 256)), dim3(256), 0, st, table, hcap);
+  hipLaunchKernelGGL(k_find_dups, dim3(nblk(n, 256)), dim3(256), 0, st, keys, n,
+                     (unsigned long long*)table, hcap, err);
+  return hipGetLastError();
+}
+
+hipError_t launch_box_keys(const uint64_t* bkeys, int64_t n, const int32_t lo[3],
+                           const int32_t bits[3], uint32_t* keys, uint32_t* idx, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_keys_to_ijk, dim3(nblk(n, 256)), dim3(256), 0, st, keys, n, ijk);
+  hipLaunchKernelGGL(k_box_keys, dim3(nblk(n, 256)), dim3(256), 0, st, bkeys, n,
+                     make_int3(lo[0], lo[1], lo[2]), make_int3(bits[0], bits[1], bits[2]), keys, idx);
+  return hipGetLastError();
+}
+
+hipError_t launch_block_keys_to_ijk(const uint64_t* bkeys, const uint32_t* order, int64_t n,
+                                    int32_t* ijk, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_keys_to_ijk, dim3(nblk(n, 256)), dim3(256), 0, st, bkeys, order, n, ijk);
   return hipGetLastError();
 }
 
 hipError_t launch_ijk_to_block_keys(const int32_t* ijk, int64_t n, int32_t log2B, uint64_t* keys,
-                                    uint32_t* err, hipStream_t st) {
+                                    uint32_t* err, int32_t* box, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_ijk_to_keys, dim3(nblk(n, 256)), dim3(256), 0, st, ijk, n, log2B, keys,
-                     err);
-  return hipGetLastError();
-}
-
-hipError_t launch_adjacent_dups(const uint64_t* sorted, int64_t n, uint32_t* err, hipStream_t st) {
-  if (n <= 1) return hipSuccess;
-  hipLaunchKernelGGL(k_adjacent_dups, dim3(nblk(n, 256)), dim3(256), 0, st, sorted, n, err);
+                     err, box);
   return hipGetLastError();
 }
 

@@ -206,6 +206,10 @@ struct smki_map {
   // allocator of new growable buffers, and the one that made each current buffer
   Allocator alloc_now, by_hash, by_pool, by_cpool;
   int32_t last_vlo[3] = {0, 0, 0}, last_vhi[3] = {0, 0, 0};   // voxel box of the last insert
+  // a box holding every block of the map (lo > hi: none), from the boxes of the
+  // inserts, replays and imports: an export sorts keys relative to it
+  int32_t box_lo[3] = {INT32_MAX, INT32_MAX, INT32_MAX};
+  int32_t box_hi[3] = {INT32_MIN, INT32_MIN, INT32_MIN};
 };
 
 // ---------------------------------------------------------------------------
@@ -390,6 +394,21 @@ hipError_t timing_begin(smki_map* m, hipStream_t q) {
 
 hipError_t timing_mark(smki_map* m, int i, hipStream_t q) {
   return m->last_timed ? hipEventRecord(m->ev[i], q) : hipSuccess;
+}
+
+// Grow the map's block box by the blocks [lo, lo + n) of an extended grid.
+void add_box(smki_map* m, const int32_t lo[3], const int32_t n[3]) {
+  for (int a = 0; a < 3; ++a) {
+    m->box_lo[a] = std::min(m->box_lo[a], lo[a]);
+    m->box_hi[a] = std::max(m->box_hi[a], lo[a] + n[a] - 1);
+  }
+}
+
+void clear_box(smki_map* m) {
+  for (int a = 0; a < 3; ++a) {
+    m->box_lo[a] = INT32_MAX;
+    m->box_hi[a] = INT32_MIN;
+  }
 }
 
 smki_status take_device_error(smki_map* m) {
@@ -653,6 +672,7 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
     enb[q2] = g.nb[q2] + 2 * DB;
     n_ext *= enb[q2];
   }
+  add_box(m, eblo, enb);
   const int32_t DR = m->B + 2 * sten.R;
   const int64_t DR3 = (int64_t)DR * DR * DR;
 
@@ -1385,11 +1405,22 @@ smki_status smki_export(smki_map* m, int64_t capacity, int64_t* n_blocks, int32_
   uint32_t* o = m->a_misc.take<uint32_t>(n);
   uint32_t* o2 = m->a_misc.take<uint32_t>(n);
   void* tmp = m->a_misc.take<char>(radix_tmp_bytes(n));
-  SMKI_HIP_TRY(hipMemcpyAsync(k, m->dev.bkeys, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice,
-                              m->stream));
-  SMKI_HIP_TRY(launch_iota_u32(o, n, m->stream));
-  SMKI_HIP_TRY(radix_sort_u64(k, o, k2, o2, n, 63, tmp, m->stream));
-  if (block_ijk) SMKI_HIP_TRY(launch_block_keys_to_ijk(k, n, block_ijk, m->stream));
+  // ascending key order: x, then y, then z; relative to the box of the map's
+  // blocks the keys usually take fewer than 32 bits (6,007 blocks of a LiDAR
+  // scan: 2 passes of 32-bit keys instead of 7 of 64)
+  int32_t bits[3];
+  for (int a = 0; a < 3; ++a) bits[a] = bits_for((int64_t)m->box_hi[a] - m->box_lo[a] + 1);
+  const int nbits = bits[0] + bits[1] + bits[2];
+  if (nbits <= 32) {
+    SMKI_HIP_TRY(launch_box_keys(m->dev.bkeys, n, m->box_lo, bits, (uint32_t*)k, o, m->stream));
+    SMKI_HIP_TRY(radix_sort_u32((uint32_t*)k, o, (uint32_t*)k2, o2, n, nbits, tmp, m->stream));
+  } else {
+    SMKI_HIP_TRY(hipMemcpyAsync(k, m->dev.bkeys, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice,
+                                m->stream));
+    SMKI_HIP_TRY(launch_iota_u32(o, n, m->stream));
+    SMKI_HIP_TRY(radix_sort_u64(k, o, k2, o2, n, 63, tmp, m->stream));
+  }
+  if (block_ijk) SMKI_HIP_TRY(launch_block_keys_to_ijk(m->dev.bkeys, o, n, block_ijk, m->stream));
   if (alpha) SMKI_HIP_TRY(launch_gather_blocks(m->dev, o, n, alpha, m->stream));
   SMKI_HIP_TRY(hipStreamSynchronize(m->stream));
   return SMKI_OK;
@@ -1403,6 +1434,7 @@ smki_status smki_import(smki_map* m, int64_t n, const int32_t* block_ijk, const 
     m->n_blocks = 0;
     m->n_cblocks = 0;
     m->host_counts_valid = true;   // (installed on the device by the next replay)
+    clear_box(m);
     return SMKI_OK;
   }
   {
@@ -1412,42 +1444,35 @@ smki_status smki_import(smki_map* m, int64_t n, const int32_t* block_ijk, const 
   const int64_t nk = n * m->K;
   if (nk > (int64_t)INT32_MAX / 2) return SMKI_E_CAPACITY;
   // Validate and size everything in scratch first: the block keys (range
-  // checked), a sorted copy of them (duplicates), and the class blocks to keep
-  // (pairs holding a value other than alpha0).  The map is touched only after
-  // all of that succeeded, so a failed import leaves it unchanged.
+  // checked) and their box, duplicates, and the class blocks to keep (pairs
+  // holding a value other than alpha0).  The map is touched only after all of
+  // that succeeded, so a failed import leaves it unchanged.
+  int64_t hcap = 1024;
+  while (hcap < 2 * n) hcap *= 2;
   Sizer z;
-  z.add<int32_t>(4);
+  z.add<int32_t>(8);
   z.add<uint64_t>(n);
-  z.add<uint64_t>(n);
-  z.add<uint64_t>(n);
-  z.add<uint32_t>(n);
-  z.add<uint32_t>(n);
-  z.add<char>(radix_tmp_bytes(n));
+  z.add<uint64_t>(hcap);
   z.add<int32_t>(nk);
   z.add<int32_t>(nk);
   z.add<char>(scan_tmp_bytes(nk));
   SMKI_HIP_TRY(m->a_misc.reserve(z.total, m->alloc_now));
   Arena& Z = m->a_misc;
-  int32_t* hdr = Z.take<int32_t>(4);   // [0] error word, [1] class blocks
+  int32_t* hdr = Z.take<int32_t>(8);   // [0] error word, [1] class blocks, [2, 8) block box
   uint64_t* keys = Z.take<uint64_t>(n);
-  uint64_t* skeys = Z.take<uint64_t>(n);
-  uint64_t* k2 = Z.take<uint64_t>(n);
-  uint32_t* o = Z.take<uint32_t>(n);
-  uint32_t* o2 = Z.take<uint32_t>(n);
-  void* stmp = Z.take<char>(radix_tmp_bytes(n));
+  uint64_t* table = Z.take<uint64_t>(hcap);
   int32_t* flag = Z.take<int32_t>(nk);
   int32_t* pos = Z.take<int32_t>(nk);
   void* tmp = Z.take<char>(scan_tmp_bytes(nk));
   hipStream_t q = m->stream;
-  SMKI_HIP_TRY(launch_fill_i32(hdr, 4, 0, q));
-  SMKI_HIP_TRY(launch_ijk_to_block_keys(block_ijk, n, m->log2B, keys, (uint32_t*)hdr, q));
-  SMKI_HIP_TRY(hipMemcpyAsync(skeys, keys, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice, q));
-  SMKI_HIP_TRY(launch_iota_u32(o, n, q));
-  SMKI_HIP_TRY(radix_sort_u64(skeys, o, k2, o2, n, 63, stmp, q));
-  SMKI_HIP_TRY(launch_adjacent_dups(skeys, n, (uint32_t*)hdr, q));
+  // (three ranges of the header: error and count 0, box minima, box maxima)
+  SMKI_HIP_TRY(launch_clear3(hdr, 2, hdr, 0, hdr + 2, 3, INT32_MAX, q));
+  SMKI_HIP_TRY(launch_fill_i32(hdr + 5, 3, INT32_MIN, q));
+  SMKI_HIP_TRY(launch_ijk_to_block_keys(block_ijk, n, m->log2B, keys, (uint32_t*)hdr, hdr + 2, q));
+  SMKI_HIP_TRY(launch_find_dups(keys, n, table, hcap, (uint32_t*)hdr, q));
   SMKI_HIP_TRY(launch_import_flags(m->dev, alpha, n, flag, q));
   SMKI_HIP_TRY(scan_excl_i32(flag, pos, nk, hdr + 1, tmp, q));
-  int32_t h[2];
+  int32_t h[8];
   SMKI_HIP_TRY(sync_read(m, hdr, sizeof(h), h));
   if (h[0]) return status_of_err((uint32_t)h[0]);
   const int64_t nc = h[1];
@@ -1467,6 +1492,10 @@ smki_status smki_import(smki_map* m, int64_t n, const int32_t* block_ijk, const 
   SMKI_HIP_TRY(launch_hash_insert_slots(m->dev, 0, n, m->d_err, q));
   m->n_blocks = n;
   m->n_cblocks = nc;
+  for (int a = 0; a < 3; ++a) {
+    m->box_lo[a] = h[2 + a];
+    m->box_hi[a] = h[5 + a];
+  }
   SMKI_HIP_TRY(stream_wait(q));
   return SMKI_OK;
 }
@@ -1882,6 +1911,7 @@ smki_status smki_batch_replay(smki_batch* b, const int64_t* offsets, const float
   // the previous replay has read its header before this one is written
   if (b->launched) SMKI_HIP_TRY(hipEventSynchronize(b->done));
   batch_header(b, offsets, origins);
+  add_box(m, b->eblo, b->enb);
   SMKI_HIP_TRY(hipGraphLaunch(b->exec, m->stream));
   SMKI_HIP_TRY(hipEventRecord(b->done, m->stream));
   b->launched = true;

@@ -190,12 +190,19 @@ hipError_t launch_import_flags(const MapDev& m, const float* alpha, int64_t n, i
                                hipStream_t st);
 hipError_t launch_import_copy(const MapDev& m, const float* alpha, int64_t n, const int32_t* flag,
                               const int32_t* pos, int64_t c0, hipStream_t st);
-hipError_t launch_block_keys_to_ijk(const uint64_t* keys, int64_t n, int32_t* ijk, hipStream_t st);
-// block coordinates -> keys; a block whose voxels leave [-2^20, 2^20) flags DEVERR_RANGE
+// keys of the map's blocks relative to a box holding them (lo, bits per axis, at
+// most 32 in all; same order as the full keys), and their indices
+hipError_t launch_box_keys(const uint64_t* bkeys, int64_t n, const int32_t lo[3],
+                           const int32_t bits[3], uint32_t* keys, uint32_t* idx, hipStream_t st);
+hipError_t launch_block_keys_to_ijk(const uint64_t* bkeys, const uint32_t* order, int64_t n,
+                                    int32_t* ijk, hipStream_t st);
+// block coordinates -> keys; a block whose voxels leave [-2^20, 2^20) flags
+// DEVERR_RANGE; box [6] (min xyz, max xyz) is updated with every block
 hipError_t launch_ijk_to_block_keys(const int32_t* ijk, int64_t n, int32_t log2B, uint64_t* keys,
-                                    uint32_t* err, hipStream_t st);
-// DEVERR_DUP if two adjacent keys of a sorted array are equal
-hipError_t launch_adjacent_dups(const uint64_t* sorted, int64_t n, uint32_t* err, hipStream_t st);
+                                    uint32_t* err, int32_t* box, hipStream_t st);
+// DEVERR_DUP if a key appears twice; table: hcap (a power of two, at least 2 n) words of scratch
+hipError_t launch_find_dups(const uint64_t* keys, int64_t n, uint64_t* table, int64_t hcap,
+                            uint32_t* err, hipStream_t st);
 hipError_t launch_iota_u32(uint32_t* p, int64_t n, hipStream_t st);
 
 __host__ __device__ inline uint64_t smki_block_key(int32_t bx, int32_t by, int32_t bz) {

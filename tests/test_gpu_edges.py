@@ -73,3 +73,79 @@ def test_sorted_cells_at_tile_edges(n, extent, res):
     first = np.concatenate([[0], np.cumsum(cnt)])
     got = np.concatenate([order[s:s + c] for s, c in zip(start[by_key], count[by_key])])
     assert np.array_equal(got, want) and first[-1] == n
+
+
+@pytest.mark.parametrize("B,K,n", [(1, 3, 5), (2, 2, 1), (2, 2, 33), (4, 20, 1_025), (8, 5, 64),
+                                   (32, 2, 3)])
+@pytest.mark.parametrize("spread", ["near", "far"])
+def test_import_export_round_trip(B, K, n, spread):
+    # blocks in random order come back in ascending key order, near ones sorted by
+    # keys relative to their box, far ones (a box of more than 32 bits) by full
+    # keys; arrays that are 4-byte aligned only take scalar accesses
+    import torch
+    from paper_1909_04631_amd import SemanticMap, SmkiError
+    rng = np.random.default_rng(B * 100 + n)
+    lim = (1 << 20) // B
+    half = 12 if spread == "near" else lim
+    ijk = np.unique(rng.integers(-half, half, size=(4 * n + 8, 3)), axis=0)
+    ijk = ijk[rng.permutation(ijk.shape[0])[:n]].astype(np.int32)
+    if spread == "far":
+        ijk[0], ijk[-1] = -lim, lim - 1
+    n = ijk.shape[0]
+    alpha = rng.uniform(0.5, 2.0, size=(n, K, B, B, B)).astype(np.float32)
+    alpha[rng.random((n, K)) < 0.5] = np.float32(1e-3)     # classes without evidence
+    print(f"[case] import/export B={B} K={K} n={n} {spread}", flush=True)
+    order = np.lexsort((ijk[:, 2], ijk[:, 1], ijk[:, 0]))
+    for shift in (0, 1):
+        m = SemanticMap(0.1, B, 0.2, 0.1, K, 1e-3, model="scsm")
+        buf = torch.empty(alpha.size + shift, dtype=torch.float32, device="cuda")
+        a = buf[shift:].view(alpha.shape)
+        a.copy_(cuda(alpha))
+        m.import_(cuda(ijk), a)
+        assert m.num_blocks() == n
+        got_ijk, got = m.export()
+        assert np.array_equal(got_ijk.cpu().numpy(), ijk[order])
+        assert np.array_equal(got.cpu().numpy(), alpha[order])
+        # the same into an array of the caller's that is not 16-byte aligned
+        import ctypes
+        from paper_1909_04631_amd import _lib
+        out = torch.empty(alpha.size + 1, dtype=torch.float32, device="cuda")[1:]
+        k = ctypes.c_int64()
+        assert _lib.lib().smki_export(m._h, n, ctypes.byref(k), None,
+                                      ctypes.c_void_p(out.data_ptr())) == 0
+        assert np.array_equal(out.cpu().numpy(), alpha[order].reshape(-1))
+        # voxels of the first block by query
+        v = ijk[0] * B + rng.integers(0, B, size=(7, 3))
+        q = m.query(cuda(v.astype(np.int32)))["alpha"].cpu().numpy()
+        l = v - ijk[0] * B
+        assert np.array_equal(q, alpha[0][:, l[:, 0], l[:, 1], l[:, 2]].T)
+        if n > 1:   # a duplicate anywhere, and a block out of range, leave the map as it was
+            for bad, status in ((np.concatenate([ijk[1:], ijk[-1:]]), -5),
+                                (np.concatenate([ijk[1:], [[lim, 0, 0]]]).astype(np.int32), -6)):
+                with pytest.raises(SmkiError) as e:
+                    m.import_(cuda(bad), cuda(alpha))
+                assert e.value.status == status
+            assert np.array_equal(m.export()[1].cpu().numpy(), alpha[order])
+
+
+def test_export_after_inserts_and_a_reset():
+    # the box that the export's keys are relative to follows inserts, resets and
+    # imports: blocks in ascending order each time, equal to the map's voxels
+    sc = scenes.make_config(0)
+    p, s = sc.params, sc.scans[0]
+    far = s.xyz + np.float32(150.0)
+    gm = gpu_map_of(sc)
+    for step in ("one scan", "a far scan added", "reset, then the far scan"):
+        print(f"[case] export after {step}", flush=True)
+        if step.startswith("reset"):
+            gm.reset()
+        if "far" in step:
+            gm.insert_scan(cuda(far), cuda(s.label), s.origin + np.float32(150.0), p.free_step)
+        ijk, alpha = [t.cpu().numpy() for t in gm.export()]
+        assert np.array_equal(np.lexsort((ijk[:, 2], ijk[:, 1], ijk[:, 0])), np.arange(ijk.shape[0]))
+        assert np.unique(ijk, axis=0).shape[0] == ijk.shape[0] == gm.num_blocks()
+        for b in range(0, ijk.shape[0], 17):
+            v = ijk[b] * gm.B + np.array([[0, 1, 2], [gm.B - 1, 0, gm.B - 1]])
+            q = gm.query(cuda(v.astype(np.int32)))["alpha"].cpu().numpy()
+            l = v - ijk[b] * gm.B
+            assert np.array_equal(q, alpha[b][:, l[:, 0], l[:, 1], l[:, 2]].T)
