@@ -149,3 +149,32 @@ def test_export_after_inserts_and_a_reset():
             q = gm.query(cuda(v.astype(np.int32)))["alpha"].cpu().numpy()
             l = v - ijk[b] * gm.B
             assert np.array_equal(q, alpha[b][:, l[:, 0], l[:, 1], l[:, 2]].T)
+
+
+@pytest.mark.parametrize("soft", [False, True])
+@pytest.mark.parametrize("n", [1, 64, 65, 4_000])
+def test_counting_model_runs_across_wavefronts(n, soft):
+    # every hit in one of three voxels: runs of equal keys that start before a
+    # wavefront's rows and end inside, or span several wavefronts
+    import torch
+    from paper_1909_04631_amd import SemanticMap
+    rng = np.random.default_rng(n)
+    cell = np.sort(rng.choice(3, size=n, p=[0.9, 0.05, 0.05]))
+    xyz = (0.05 + 0.1 * np.array([[0, 0, 0], [0, 0, 1], [9, 3, 2]])[cell]).astype(np.float32)
+    lab = rng.integers(0, 3, size=n).astype(np.int32)
+    w = rng.uniform(0.0, 1.0, size=(n, 3)).astype(np.float32)
+    w[rng.random((n, 3)) < 0.3] = 0.0
+    print(f"[case] counting runs n={n} soft={soft}", flush=True)
+    m = SemanticMap(0.1, 8, 0.3, 0.1, 3, 1e-3, model="scsm")
+    if soft:
+        m.insert_scan_soft(cuda(xyz), cuda(w), (0, 0, 0), 0.0)
+        add = np.stack([np.bincount(cell, weights=w[:, k].astype(np.float64), minlength=3)
+                        for k in range(3)], 1)
+    else:
+        m.insert_scan(cuda(xyz), cuda(lab), (0, 0, 0), 0.0)
+        add = np.stack([np.bincount(cell[lab == k], minlength=3) for k in range(3)], 1)
+    torch.cuda.synchronize()
+    q = np.array([[0, 0, 0], [0, 0, 1], [9, 3, 2]], np.int32)
+    a = m.query(cuda(q))["alpha"].cpu().numpy()
+    want = np.float32(1e-3) + add.astype(np.float32)
+    assert np.array_equal(a, want.astype(np.float32))
