@@ -174,9 +174,10 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_tile_sums_pair(const TA* __res
                                                                  int64_t ta,
                                                                  const TB* __restrict__ inb,
                                                                  int64_t nb, TB* __restrict__ sb,
+                                                                 const int32_t* dna,
                                                                  const int32_t* dnb) {
   if ((int64_t)blockIdx.x < ta)
-    tile_sum<TA>(ina, na, sa, blockIdx.x);
+    tile_sum<TA>(ina, count_of(na, dna), sa, blockIdx.x);
   else
     tile_sum<TB>(inb, count_of(nb, dnb), sb, (int64_t)blockIdx.x - ta);
 }
@@ -185,9 +186,9 @@ template <typename TA, typename TB>
 __global__ void __launch_bounds__(SCAN_THREADS) k_tile_scan_direct_pair(
     const TA* ina, TA* outa, int64_t na, const TA* __restrict__ sa, TA* tota, int64_t ta,
     const TB* inb, TB* outb, int64_t nb, const TB* __restrict__ sb, TB* totb, int64_t tb,
-    const int32_t* dnb) {
+    const int32_t* dna, const int32_t* dnb) {
   if ((int64_t)blockIdx.x < ta)
-    tile_scan_direct<TA>(ina, outa, na, sa, tota, blockIdx.x, ta);
+    tile_scan_direct<TA>(ina, outa, count_of(na, dna), sa, tota, blockIdx.x, ta);
   else
     tile_scan_direct<TB>(inb, outb, count_of(nb, dnb), sb, totb, (int64_t)blockIdx.x - ta, tb);
 }
@@ -240,20 +241,21 @@ constexpr int64_t kPairTiles = 512;   // per array, for the two-launch pair scan
 
 template <typename TA, typename TB>
 hipError_t scan_pair_impl(const TA* ina, TA* outa, int64_t na, TA* tota, const TB* inb, TB* outb,
-                          int64_t nb, TB* totb, void* tmp, hipStream_t st, const int32_t* dnb) {
+                          int64_t nb, TB* totb, void* tmp, hipStream_t st, const int32_t* dna,
+                          const int32_t* dnb) {
   const int64_t ta = ceil_div_i64(na, SCAN_TILE), tb = ceil_div_i64(nb, SCAN_TILE);
   if (na <= 0 || nb <= 0 || ta > kPairTiles || tb > kPairTiles) {
-    hipError_t e = scan_impl<TA>(ina, outa, na, tota, (TA*)tmp, st);
+    hipError_t e = scan_impl<TA>(ina, outa, na, tota, (TA*)tmp, st, dna);
     if (e != hipSuccess) return e;
     return scan_impl<TB>(inb, outb, nb, totb, (TB*)tmp, st, dnb);
   }
   TA* sa = (TA*)tmp;
   TB* sb = (TB*)((char*)tmp + kPairTiles * sizeof(int64_t));
   hipLaunchKernelGGL((k_tile_sums_pair<TA, TB>), dim3((unsigned)(ta + tb)), dim3(SCAN_THREADS), 0,
-                     st, ina, na, sa, ta, inb, nb, sb, dnb);
+                     st, ina, na, sa, ta, inb, nb, sb, dna, dnb);
   hipLaunchKernelGGL((k_tile_scan_direct_pair<TA, TB>), dim3((unsigned)(ta + tb)),
                      dim3(SCAN_THREADS), 0, st, ina, outa, na, (const TA*)sa, tota, ta, inb, outb,
-                     nb, (const TB*)sb, totb, tb, dnb);
+                     nb, (const TB*)sb, totb, tb, dna, dnb);
   return hipGetLastError();
 }
 
@@ -267,13 +269,15 @@ hipError_t scan_excl_pair_i64_i32(const int64_t* ina, int64_t* outa, int64_t na,
                                   const int32_t* inb, int32_t* outb, int64_t nb, int32_t* totb,
                                   void* tmp, hipStream_t st) {
   return scan_pair_impl<int64_t, int32_t>(ina, outa, na, tota, inb, outb, nb, totb, tmp, st,
-                                          nullptr);
+                                          nullptr, nullptr);
 }
 
 hipError_t scan_excl_pair_i32(const int32_t* ina, int32_t* outa, int64_t na, int32_t* tota,
                               const int32_t* inb, int32_t* outb, int64_t nb, int32_t* totb,
-                              void* tmp, hipStream_t st, const int32_t* dnb) {
-  return scan_pair_impl<int32_t, int32_t>(ina, outa, na, tota, inb, outb, nb, totb, tmp, st, dnb);
+                              void* tmp, hipStream_t st, const int32_t* dnb,
+                              const int32_t* dna) {
+  return scan_pair_impl<int32_t, int32_t>(ina, outa, na, tota, inb, outb, nb, totb, tmp, st, dna,
+                                          dnb);
 }
 
 hipError_t scan_excl_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* total, void* tmp,

@@ -958,6 +958,7 @@ struct smki_batch {
   Stencil sten;
   int32_t chunk = 0;         // rows per work unit (the sizing insert's)
   int64_t cap_rows = 0, cap_slots = 0, cap_units = 0;
+  int64_t tgt_grid = 0;      // targets that launches start workgroups for
   int64_t pool_cap = 0, cpool_cap = 0, hcap = 0;
   size_t in_bytes = 0;
   char* dbuf = nullptr;
@@ -1066,12 +1067,11 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   smki_map* m = b->m;
   const BucketGeom& g = b->g;
   BatchBufs& d = b->d;
-  const int64_t n = b->n, ne = b->n_ext, ntk = ne * m->K;
+  const int64_t n = b->n, ne = b->n_ext;
   SMKI_HIP_TRY(hipMemcpyAsync(d.hdr, b->h_in, b->in_bytes, hipMemcpyHostToDevice, q));
   SMKI_HIP_TRY(launch_batch_start((const int64_t*)d.hdr, m->dev.counts, d.stats, q));
-  SMKI_HIP_TRY(launch_clear3(d.si, (int64_t)(d.mark + ne - d.si), d.cnt,
-                             (int64_t)(d.contrib + ntk - d.cnt), d.dense, g.n_blocks * m->K, -1,
-                             q));
+  // (dense holds -1: from the capture, and each replay puts back what it wrote)
+  SMKI_HIP_TRY(launch_clear3(d.si, (int64_t)(d.mark + ne - d.si), d.si, 0, d.si, 0, 0, q));
   // first phase: validation, free-sample counts, their offsets
   SMKI_HIP_TRY(launch_count(b->xyz, b->label, nullptr, n, d.soff, d.org, b->S, m->res, b->step,
                             m->K, d.nfree, d.kept, d.bbox, d.err, q));
@@ -1152,18 +1152,21 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   sa.dn_units = d.si + 2;
   sa.abort_word = d.err;
   sa.cap_units = (int32_t)b->cap_units;
+  sa.tgt_grid = b->tgt_grid;
   SMKI_HIP_TRY(launch_unit_table(d.nun, d.ust, d.head, d.slot_lin, g.n_blocks, b->chunk,
                                  (int32_t)b->cap_slots, ps.d_nslots, d.si + 2, d.units, d.uorder,
                                  q, (int32_t)b->cap_units));
   SMKI_HIP_TRY(launch_splat(sa, b->cap_units, q));
   SMKI_HIP_TRY(launch_list_targets(d.mark, d.mpos, ne, d.tgt, d.ext2t, q));
+  SMKI_HIP_TRY(launch_clear_targets(sa.dn_targets, (int32_t)ne, b->tgt_grid, m->K, d.cnt, d.active,
+                                    d.contrib, q));
   SMKI_HIP_TRY(launch_slot_info(sa, q));
   SMKI_HIP_TRY(launch_contrib(sa, false, d.contrib, q));
   SMKI_HIP_TRY(launch_map_lookup(m->dev, sa, (int32_t)ne, d.tslot, d.isnew, q));
   SMKI_HIP_TRY(launch_need(m->dev, (int32_t)ne, d.contrib, d.isnew, d.tslot, d.need, d.cpos, q,
-                           d.si + 1));
+                           d.si + 1, b->tgt_grid));
   SMKI_HIP_TRY(scan_excl_pair_i32(d.isnew, d.rank, ne, d.cnt, d.cpos, d.cpos, ne, d.cnt + 1,
-                                  d.ctmp, q));
+                                  d.ctmp, q, sa.dn_targets, sa.dn_targets));
   SMKI_HIP_TRY(launch_batch_alloc_check(d.cnt, m->dev.counts, b->pool_cap, b->cpool_cap, b->hcap,
                                         d.err, q));
   SMKI_HIP_TRY(launch_assign(m->dev, sa, (int32_t)ne, d.isnew, d.rank, 0, d.tslot, d.need, d.cpos,
@@ -1171,6 +1174,7 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   sa.map = m->dev;
   sa.alpha0 = m->alpha0;
   SMKI_HIP_TRY(launch_merge(sa, (int32_t)ne, q));
+  SMKI_HIP_TRY(launch_clear_dense(d.slot_lin, d.si, (int32_t)b->cap_slots, g, d.dense, q));
   SMKI_HIP_TRY(launch_batch_commit(d.cnt, m->dev.counts, d.err, m->d_err, d.pc, d.si, d.out, q));
   SMKI_HIP_TRY(hipMemcpyAsync(b->h_out, d.out, sizeof(int64_t) * (kBOut + 4 * SMKI_STAT_COPIES),
                               hipMemcpyDeviceToHost, q));
@@ -1828,6 +1832,9 @@ smki_status smki_batch_capture(smki_map* m, const float* xyz, const int32_t* lab
   b->cap_slots = std::min<int64_t>(std::min<int64_t>(b->cap_rows, g.n_blocks * m->K),
                                    (int64_t)ceil((double)st.n_point_blocks * grow) + 1024);
   b->cap_units = (int64_t)ceil((double)st.n_units * grow) + 1024;
+  // (a grid, not a capacity: the window may hold more targets, which the kernels
+  // stride over; one workgroup per block of the window cost 0.4 ms of a 2 ms replay)
+  b->tgt_grid = std::min<int64_t>(b->n_ext, (int64_t)ceil((double)st.n_target_blocks * grow) + 256);
   const int64_t DR = m->B + 2 * b->sten.R;
   // keep the partial sums under 4 GiB and 2^24 units (32-bit offsets in the
   // merge) when the sizing insert's fitted
@@ -1877,6 +1884,12 @@ smki_status smki_batch_capture(smki_map* m, const float* xyz, const int32_t* lab
     return smki_hip_error(e);
   }
   carve_batch(b, (char*)(((uintptr_t)b->dbuf + kAlign - 1) / kAlign * kAlign));
+  e = launch_fill_i32(b->d.dense, b->g.n_blocks * m->K, -1, m->stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(m->stream);
+  if (e != hipSuccess) {
+    batch_release(b);
+    return smki_hip_error(e);
+  }
   batch_header(b, offsets, origins);
   // 5. record the insert (nothing runs now)
   e = hipStreamBeginCapture(b->cs, hipStreamCaptureModeThreadLocal);

@@ -94,6 +94,7 @@ struct SplatArgs {
   const uint32_t* abort_word; // non-zero: an error or a capacity overflow; nothing is written
                               // to the map (allocation and merge return at once)
   int32_t cap_units;          // work units the unit table may hold
+  int64_t tgt_grid;           // targets that capacity launches start workgroups for (0: all)
 };
 
 hipError_t launch_mark_targets(const int32_t* slot_lin, const int32_t* d_nslots, int32_t max_slots,
@@ -122,7 +123,15 @@ hipError_t launch_contrib(const SplatArgs& a, bool own_block_only, int32_t* cont
 // target's (0: none); need_t [targets]: their number
 hipError_t launch_need(const MapDev& m, int32_t n_targets, const int32_t* contrib,
                        const int32_t* is_new, const int32_t* tgt_slot, int32_t* need,
-                       int32_t* need_t, hipStream_t st, const int32_t* dn_targets = nullptr);
+                       int32_t* need_t, hipStream_t st, const int32_t* dn_targets = nullptr,
+                       int64_t grid_targets = 0);
+// captured inserts: clear the flags of the targets there are; put the dense
+// entries that an insert wrote back to -1
+hipError_t launch_clear_targets(const int32_t* dn_targets, int32_t cap, int64_t grid_targets,
+                                int32_t K, int32_t* cnt, int32_t* active, int32_t* contrib,
+                                hipStream_t st);
+hipError_t launch_clear_dense(const int32_t* slot_lin, const int32_t* d_nslots, int32_t cap,
+                              const BucketGeom& g, int32_t* dense, hipStream_t st);
 hipError_t launch_slot_info(const SplatArgs& a, hipStream_t st);
 // one launch: clear nclear words from clr, then (independently) the target list
 // of launch_list_targets and the slot summaries of launch_slot_info

@@ -619,8 +619,11 @@ __device__ __forceinline__ float part_at(const float* part, int32_t w, int32_t o
 // by this insert are written alpha0 + sum, older blocks updated in place where
 // the sum is non-zero.  The per-thread state is kept small (packed candidates,
 // slot entries re-read from LDS) so that 8 wavefronts fit per SIMD.
-template <int B, int R, bool WIDE>
-__global__ void __launch_bounds__((B * B * B < 1024 ? B * B * B : 1024), (B == 8 && R <= 3 && !WIDE) ? 8 : 1)
+// STRIDE (captured inserts): the grid is smaller than the window's capacity and
+// the workgroups stride over the targets (a form of its own: the loop's state
+// does not fit the 64 registers).
+template <int B, int R, bool WIDE, bool STRIDE>
+__global__ void __launch_bounds__((B * B * B < 1024 ? B * B * B : 1024), (B == 8 && R <= 3 && !WIDE && !STRIDE) ? 8 : 1)
 k_merge(SplatArgs a, int32_t n_targets) {
   using S = MergeShape<B, R>;
   constexpr int DR = B + 2 * R;
@@ -633,12 +636,17 @@ k_merge(SplatArgs a, int32_t n_targets) {
   __shared__ int2 ent[CPG * 27];
   __shared__ int32_t cflag[CPG], clist[CPG], cblk[CPG], ncls_s;
   __shared__ int32_t red[(NT + SMKI_WAVE - 1) / SMKI_WAVE];
-  const int32_t t = blockIdx.x;
   if (a.dn_targets) n_targets = min(n_targets, *a.dn_targets);
-  if (t >= n_targets || !a.tgt_active[t]) return;
   if (a.abort_word && *a.abort_word) return;   // nothing is written to the map
   const int64_t n_cold = a.dn_targets ? a.map.counts[1] : a.n_cold;
   const int tid = threadIdx.x;
+  int32_t t = blockIdx.x;
+  if (t >= n_targets) return;
+  do {
+  if (!a.tgt_active[t]) {
+    if constexpr (!STRIDE) return;
+    continue;
+  }
   const int32_t mslot = a.tgt_slot[t];
   int32_t bt[3];
   unlin3(a.tgt_elin[t], a.enb, bt);
@@ -805,6 +813,8 @@ k_merge(SplatArgs a, int32_t n_targets) {
     for (int i = 0; i < (NT + SMKI_WAVE - 1) / SMKI_WAVE; ++i) tot += red[i];
     atomicAdd(&a.stats[(blockIdx.x % SMKI_STAT_COPIES) * 4], (unsigned long long)tot);
   }
+  if constexpr (STRIDE) __syncthreads();   // (the next target's tables)
+  } while (STRIDE && (t += gridDim.x) < n_targets);
 }
 
 // (target, class) pairs that receive rows: from each slot's non-zero pieces (or
@@ -842,66 +852,71 @@ __global__ void k_contrib(SplatArgs a, int32_t own_block_only, int32_t* __restri
 // that do (0: no), and the target's number of them in need_t, whose exclusive
 // scan places the target's class blocks.  G lanes per target (G >= K, a power
 // of two up to 64; the ranks from a wave ballot), else one thread per target.
-// (dnt: the device count of targets, n_targets then a capacity whose tail is
-// written 0 for the scan that follows)
+// (dnt: the device count of targets, n_targets then a capacity; the grid may be
+// smaller than the targets)
 template <int G>
 __global__ void k_need(MapDev m, int32_t n_targets, const int32_t* __restrict__ contrib,
                        const int32_t* __restrict__ is_new, const int32_t* __restrict__ tgt_slot,
                        int32_t* __restrict__ need, int32_t* __restrict__ need_t,
                        const int32_t* __restrict__ dnt) {
-  const int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int32_t t = (int32_t)(gi / G), k = (int32_t)(gi % G);
-  const bool in = t < n_targets;                      // (uniform per group of G lanes)
-  const bool live = in && (!dnt || t < *dnt);
-  const bool fresh = live && is_new[t] != 0;
-  const int64_t base = (int64_t)t * m.K;
-  if (G == 1) {
-    if (!in) return;
-    int32_t r = 0;
-    for (int32_t c = 0; c < m.K; ++c) {
-      int32_t v = 0;
-      if (live && contrib[base + c])
-        v = (fresh || m.cslot[(int64_t)tgt_slot[t] * m.K + c] < 0) ? 1 : 0;
-      need[base + c] = v ? r + 1 : 0;
-      r += v;
+  if (dnt) n_targets = min(n_targets, *dnt);
+  // (whole wavefronts stride together: a wavefront's targets are 64 / G in a row)
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+       gi - (threadIdx.x & (SMKI_WAVE - 1)) < (int64_t)n_targets * G; gi += stride) {
+    const int32_t t = (int32_t)(gi / G), k = (int32_t)(gi % G);
+    const bool in = t < n_targets;                      // (uniform per group of G lanes)
+    const bool fresh = in && is_new[t] != 0;
+    const int64_t base = (int64_t)t * m.K;
+    if (G == 1) {
+      if (!in) continue;
+      int32_t r = 0;
+      for (int32_t c = 0; c < m.K; ++c) {
+        int32_t v = 0;
+        if (contrib[base + c])
+          v = (fresh || m.cslot[(int64_t)tgt_slot[t] * m.K + c] < 0) ? 1 : 0;
+        need[base + c] = v ? r + 1 : 0;
+        r += v;
+      }
+      need_t[t] = r;
+      continue;
     }
-    need_t[t] = r;
-    return;
+    bool v = false;
+    if (in && k < m.K && contrib[base + k])
+      v = fresh || m.cslot[(int64_t)tgt_slot[t] * m.K + k] < 0;
+    const int lane = threadIdx.x & (SMKI_WAVE - 1);
+    const uint64_t grp = (G == SMKI_WAVE ? ~0ull : ((1ull << G) - 1ull)) << (lane & ~(G - 1));
+    const uint64_t mk = __ballot(v) & grp;
+    if (!in) continue;
+    if (k < m.K) need[base + k] = v ? __popcll(mk & ((1ull << lane) - 1ull)) + 1 : 0;
+    if (k == 0) need_t[t] = __popcll(mk);
   }
-  bool v = false;
-  if (live && k < m.K && contrib[base + k])
-    v = fresh || m.cslot[(int64_t)tgt_slot[t] * m.K + k] < 0;
-  const int lane = threadIdx.x & (SMKI_WAVE - 1);
-  const uint64_t grp = (G == SMKI_WAVE ? ~0ull : ((1ull << G) - 1ull)) << (lane & ~(G - 1));
-  const uint64_t mk = __ballot(v) & grp;
-  if (!in) return;
-  if (k < m.K) need[base + k] = v ? __popcll(mk & ((1ull << lane) - 1ull)) + 1 : 0;
-  if (k == 0) need_t[t] = __popcll(mk);
 }
 
 // map-slot lookup of the active targets; new blocks are marked for allocation
 __global__ void k_map_lookup(MapDev m, SplatArgs a, int32_t n_targets,
                              int32_t* __restrict__ tgt_slot, int32_t* __restrict__ is_new) {
-  const int32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= n_targets) return;
-  if ((a.dn_targets && t >= *a.dn_targets) || !a.tgt_active[t]) {
-    tgt_slot[t] = -1;
-    is_new[t] = 0;
-    return;
+  if (a.dn_targets) n_targets = min(n_targets, *a.dn_targets);
+  for (int32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n_targets; t += gridDim.x * blockDim.x) {
+    if (!a.tgt_active[t]) {
+      tgt_slot[t] = -1;
+      is_new[t] = 0;
+      continue;
+    }
+    int32_t bt[3];
+    unlin3(a.tgt_elin[t], a.enb, bt);
+    const uint64_t key = smki_block_key(bt[0] + a.eblo[0], bt[1] + a.eblo[1], bt[2] + a.eblo[2]);
+    uint64_t h = smki_mix64(key) & (uint64_t)(m.hcap - 1);
+    int32_t slot = -1;
+    for (int64_t probe = 0; probe < m.hcap; ++probe) {
+      const uint64_t k = m.hkeys[h];
+      if (k == key) { slot = m.hvals[h]; break; }
+      if (k == ~0ull) break;
+      h = (h + 1) & (uint64_t)(m.hcap - 1);
+    }
+    tgt_slot[t] = slot;
+    is_new[t] = slot < 0 ? 1 : 0;
   }
-  int32_t bt[3];
-  unlin3(a.tgt_elin[t], a.enb, bt);
-  const uint64_t key = smki_block_key(bt[0] + a.eblo[0], bt[1] + a.eblo[1], bt[2] + a.eblo[2]);
-  uint64_t h = smki_mix64(key) & (uint64_t)(m.hcap - 1);
-  int32_t slot = -1;
-  for (int64_t probe = 0; probe < m.hcap; ++probe) {
-    const uint64_t k = m.hkeys[h];
-    if (k == key) { slot = m.hvals[h]; break; }
-    if (k == ~0ull) break;
-    h = (h + 1) & (uint64_t)(m.hcap - 1);
-  }
-  tgt_slot[t] = slot;
-  is_new[t] = slot < 0 ? 1 : 0;
 }
 
 // Allocation, one thread per (target, class): a new target block takes map
@@ -915,11 +930,10 @@ __global__ void k_assign(MapDev m, SplatArgs a, int32_t n_targets,
                          const int32_t* __restrict__ need, const int32_t* __restrict__ cpos,
                          int64_t n_cold, uint32_t* __restrict__ err,
                          const int32_t* __restrict__ cnt, int32_t* __restrict__ cnt_copy) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (a.dn_targets) n_targets = min(n_targets, *a.dn_targets);
-  if (i >= (int64_t)n_targets * m.K) return;
   if (a.abort_word && *a.abort_word) return;   // nothing is written to the map
-  if (cnt && i == 0) {   // an ordinary insert: the map's counts after it, on the device
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n = (int64_t)n_targets * m.K;
+  if (cnt && first == 0 && n > 0) {   // an ordinary insert: the map's counts after it, on the device
     m.counts[0] = n_old + cnt[0];
     m.counts[1] = n_cold + cnt[1];
     cnt_copy[0] = cnt[0];
@@ -929,29 +943,63 @@ __global__ void k_assign(MapDev m, SplatArgs a, int32_t n_targets,
     n_old = m.counts[0];
     n_cold = m.counts[1];
   }
-  const int32_t t = (int32_t)(i / m.K), k = (int32_t)(i % m.K);
-  const bool fresh = is_new[t] != 0;
-  const int32_t slot = fresh ? (int32_t)(n_old + rank[t]) : tgt_slot[t];
-  const int32_t nd = need[i];   // 1 + rank among the target's new class blocks, 0: none
-  if (fresh || nd)
-    m.cslot[(int64_t)slot * m.K + k] = nd ? (int32_t)(n_cold + cpos[t] + nd - 1) : -1;
-  if (!fresh || k != 0) return;
-  int32_t bt[3];
-  unlin3(a.tgt_elin[t], a.enb, bt);
-  const uint64_t key = smki_block_key(bt[0] + a.eblo[0], bt[1] + a.eblo[1], bt[2] + a.eblo[2]);
-  tgt_slot[t] = slot;
-  m.bkeys[slot] = key;
-  uint64_t h = smki_mix64(key) & (uint64_t)(m.hcap - 1);
-  for (int64_t probe = 0; probe < m.hcap; ++probe) {
-    const unsigned long long old =
-        atomicCAS((unsigned long long*)&m.hkeys[h], ~0ull, (unsigned long long)key);
-    if (old == ~0ull || old == key) {
-      m.hvals[h] = slot;
-      return;
+  for (int64_t i = first; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const int32_t t = (int32_t)(i / m.K), k = (int32_t)(i % m.K);
+    const bool fresh = is_new[t] != 0;
+    const int32_t slot = fresh ? (int32_t)(n_old + rank[t]) : tgt_slot[t];
+    const int32_t nd = need[i];   // 1 + rank among the target's new class blocks, 0: none
+    if (fresh || nd)
+      m.cslot[(int64_t)slot * m.K + k] = nd ? (int32_t)(n_cold + cpos[t] + nd - 1) : -1;
+    if (!fresh || k != 0) continue;
+    int32_t bt[3];
+    unlin3(a.tgt_elin[t], a.enb, bt);
+    const uint64_t key = smki_block_key(bt[0] + a.eblo[0], bt[1] + a.eblo[1], bt[2] + a.eblo[2]);
+    // (the other classes' threads of this target may still read tgt_slot[t]: a
+    // fresh target's slot does not come from it)
+    tgt_slot[t] = slot;
+    m.bkeys[slot] = key;
+    uint64_t h = smki_mix64(key) & (uint64_t)(m.hcap - 1);
+    bool put = false;
+    for (int64_t probe = 0; probe < m.hcap && !put; ++probe) {
+      const unsigned long long old =
+          atomicCAS((unsigned long long*)&m.hkeys[h], ~0ull, (unsigned long long)key);
+      put = old == ~0ull || old == key;
+      if (put)
+        m.hvals[h] = slot;
+      else
+        h = (h + 1) & (uint64_t)(m.hcap - 1);
     }
-    h = (h + 1) & (uint64_t)(m.hcap - 1);
+    if (!put) atomicOr(err, DEVERR_HASH);
   }
-  atomicOr(err, DEVERR_HASH);
+}
+
+// A captured insert's flags of the targets it has (their number is on the device):
+// cnt[0, 8), active[0, targets), contrib[0, targets * K) = 0.
+__global__ void k_clear_targets(const int32_t* __restrict__ dnt, int32_t cap, int32_t K,
+                                int32_t* __restrict__ cnt, int32_t* __restrict__ active,
+                                int32_t* __restrict__ contrib) {
+  const int64_t n = min(cap, *dnt), first = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  if (first < 8) cnt[first] = 0;
+  for (int64_t i = first; i < n; i += stride) active[i] = 0;
+  for (int64_t i = first; i < n * K; i += stride) contrib[i] = 0;
+}
+
+// dense entries of slots [0, *d_nslots) back to -1 (what the insert wrote)
+__global__ void k_clear_dense(const int32_t* __restrict__ slot_lin,
+                              const int32_t* __restrict__ d_nslots, int32_t cap, int32_t n_blocks,
+                              int32_t K, int32_t* __restrict__ dense) {
+  const int32_t n = min(cap, *d_nslots);
+  for (int32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
+    const int32_t lin = slot_lin[s], y = lin / n_blocks;
+    dense[(int64_t)(lin - y * n_blocks) * K + y] = -1;
+  }
+}
+
+// Targets that a launch sized for a captured insert's capacity (the whole window,
+// millions of blocks) starts workgroups for; the kernels stride over the rest.
+inline int64_t tgt_grid(const SplatArgs& a, int64_t n_targets) {
+  return a.tgt_grid > 0 ? std::min<int64_t>(n_targets, a.tgt_grid) : n_targets;
 }
 
 template <int B, int R, int NSV>
@@ -990,13 +1038,19 @@ hipError_t launch_splat_br(const SplatArgs& a, int64_t n_units, int32_t n_target
   } else {
     if (n_targets > 0) {
       constexpr int64_t DR3 = (int64_t)(B + 2 * R) * (B + 2 * R) * (B + 2 * R);
-      if (!a.wide && a.part_elems * sizeof(float) <= (int64_t(1) << 32) &&
-          (a.part_elems - SMKI_PART_HEAD) / DR3 < (int64_t(1) << 24))
-        hipLaunchKernelGGL((k_merge<B, R, false>), dim3((unsigned)n_targets),
-                           dim3(MergeShape<B, R>::NT), 0, st, a, n_targets);
-      else
-        hipLaunchKernelGGL((k_merge<B, R, true>), dim3((unsigned)n_targets),
-                           dim3(MergeShape<B, R>::NT), 0, st, a, n_targets);
+      const bool narrow = !a.wide && a.part_elems * sizeof(float) <= (int64_t(1) << 32) &&
+                          (a.part_elems - SMKI_PART_HEAD) / DR3 < (int64_t(1) << 24);
+      const dim3 grid((unsigned)tgt_grid(a, n_targets)), block(MergeShape<B, R>::NT);
+      if (a.tgt_grid > 0) {
+        if (narrow)
+          hipLaunchKernelGGL((k_merge<B, R, false, true>), grid, block, 0, st, a, n_targets);
+        else
+          hipLaunchKernelGGL((k_merge<B, R, true, true>), grid, block, 0, st, a, n_targets);
+      } else if (narrow) {
+        hipLaunchKernelGGL((k_merge<B, R, false, false>), grid, block, 0, st, a, n_targets);
+      } else {
+        hipLaunchKernelGGL((k_merge<B, R, true, false>), grid, block, 0, st, a, n_targets);
+      }
     }
   }
   return hipGetLastError();
@@ -1089,7 +1143,7 @@ hipError_t launch_merge(const SplatArgs& a, int32_t n_targets, hipStream_t st) {
 hipError_t launch_map_lookup(const MapDev& m, const SplatArgs& a, int32_t n_targets,
                              int32_t* tgt_slot, int32_t* is_new, hipStream_t st) {
   if (n_targets <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_map_lookup, dim3(nblk(n_targets, 256)), dim3(256), 0, st, m, a, n_targets,
+  hipLaunchKernelGGL(k_map_lookup, dim3(nblk(tgt_grid(a, n_targets), 256)), dim3(256), 0, st, m, a, n_targets,
                      tgt_slot, is_new);
   return hipGetLastError();
 }
@@ -1102,7 +1156,7 @@ hipError_t launch_assign(const MapDev& m, const SplatArgs& a, int32_t n_targets,
   const int64_t n = (int64_t)n_targets * m.K;
   if (n <= 0)
     return cnt ? launch_commit_counts(cnt, m.counts, n_old, n_cold, cnt_copy, st) : hipSuccess;
-  hipLaunchKernelGGL(k_assign, dim3(nblk(n, 256)), dim3(256), 0, st, m, a, n_targets, is_new,
+  hipLaunchKernelGGL(k_assign, dim3(nblk(tgt_grid(a, n_targets) * m.K, 256)), dim3(256), 0, st, m, a, n_targets, is_new,
                      new_rank, n_old, tgt_slot, need, cpos, n_cold, err, cnt, cnt_copy);
   return hipGetLastError();
 }
@@ -1134,17 +1188,34 @@ hipError_t launch_contrib(const SplatArgs& a, bool own_block_only, int32_t* cont
 
 hipError_t launch_need(const MapDev& m, int32_t n_targets, const int32_t* contrib,
                        const int32_t* is_new, const int32_t* tgt_slot, int32_t* need,
-                       int32_t* need_t, hipStream_t st, const int32_t* dn_targets) {
+                       int32_t* need_t, hipStream_t st, const int32_t* dn_targets,
+                       int64_t grid_targets) {
   if (n_targets <= 0 || m.K <= 0) return hipSuccess;
+  const int64_t gt = grid_targets > 0 ? std::min<int64_t>(n_targets, grid_targets) : n_targets;
   if (m.K <= 32)
-    hipLaunchKernelGGL(k_need<32>, dim3(nblk((int64_t)n_targets * 32, 256)), dim3(256), 0, st, m,
-                       n_targets, contrib, is_new, tgt_slot, need, need_t, dn_targets);
+    hipLaunchKernelGGL(k_need<32>, dim3(nblk(gt * 32, 256)), dim3(256), 0, st, m, n_targets, contrib,
+                       is_new, tgt_slot, need, need_t, dn_targets);
   else if (m.K <= 64)
-    hipLaunchKernelGGL(k_need<64>, dim3(nblk((int64_t)n_targets * 64, 256)), dim3(256), 0, st, m,
-                       n_targets, contrib, is_new, tgt_slot, need, need_t, dn_targets);
+    hipLaunchKernelGGL(k_need<64>, dim3(nblk(gt * 64, 256)), dim3(256), 0, st, m, n_targets, contrib,
+                       is_new, tgt_slot, need, need_t, dn_targets);
   else
-    hipLaunchKernelGGL(k_need<1>, dim3(nblk(n_targets, 256)), dim3(256), 0, st, m, n_targets,
-                       contrib, is_new, tgt_slot, need, need_t, dn_targets);
+    hipLaunchKernelGGL(k_need<1>, dim3(nblk(gt, 256)), dim3(256), 0, st, m, n_targets, contrib,
+                       is_new, tgt_slot, need, need_t, dn_targets);
   return hipGetLastError();
 }
 
+hipError_t launch_clear_targets(const int32_t* dn_targets, int32_t cap, int64_t grid_targets,
+                                int32_t K, int32_t* cnt, int32_t* active, int32_t* contrib,
+                                hipStream_t st) {
+  hipLaunchKernelGGL(k_clear_targets, dim3(std::min<unsigned>(nblk(grid_targets * K, 256), 4096)),
+                     dim3(256), 0, st, dn_targets, cap, K, cnt, active, contrib);
+  return hipGetLastError();
+}
+
+hipError_t launch_clear_dense(const int32_t* slot_lin, const int32_t* d_nslots, int32_t cap,
+                              const BucketGeom& g, int32_t* dense, hipStream_t st) {
+  if (cap <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_clear_dense, dim3(std::min<unsigned>(nblk(cap, 256), kSlotGrid)), dim3(256),
+                     0, st, slot_lin, d_nslots, cap, (int32_t)g.n_blocks, g.planes, dense);
+  return hipGetLastError();
+}

@@ -178,3 +178,49 @@ def test_counting_model_runs_across_wavefronts(n, soft):
     a = m.query(cuda(q))["alpha"].cpu().numpy()
     want = np.float32(1e-3) + add.astype(np.float32)
     assert np.array_equal(a, want.astype(np.float32))
+
+
+@pytest.mark.parametrize("B,K", [(4, 5), (8, 70)])
+def test_replay_with_more_targets_than_its_grid(B, K):
+    # captured on hits that fill a few blocks (the window is widened by two of
+    # them), replayed on hits all over the window: many more target blocks than
+    # the launches start workgroups for, then on the first hits again (the slot
+    # table is back as it was), and after a replay that fails
+    import torch
+    from paper_1909_04631_amd import SemanticMap, SmkiError
+    rng = np.random.default_rng(B)
+    n = 700
+    near = rng.uniform(0.0, 0.5, size=(n, 3)).astype(np.float32)
+    near[0], near[1] = -6.0, 6.0
+    wide = rng.uniform(-5.9, 5.9, size=(n, 3)).astype(np.float32)
+    out = wide.copy()
+    out[5] = 400.0
+    lab = rng.integers(0, K, size=n).astype(np.int32)
+    origins = [(0.0, 0.0, 0.0)]
+    m = SemanticMap(0.1, B, 0.2, 0.1, K, 1e-3, initial_blocks=1 << 15)
+    xyz, y = cuda(wide), cuda(lab)
+    m.insert_scan(xyz, y, origins[0], 0.0)     # (room in the map for the wide hits)
+    m.reset()
+    xyz.copy_(cuda(near))
+    g = m.batch_capture(xyz, y, [0, n], origins, 0.0, margin=1.0)
+    q = cuda(np.floor(np.concatenate([near, wide]) / np.float32(0.1)).astype(np.int32))
+    fresh = SemanticMap(0.1, B, 0.2, 0.1, K, 1e-3, initial_blocks=1 << 15)
+    for name, data in (("wide", wide), ("near", near), ("out", out), ("wide", wide)):
+        print(f"[case] replay {name} B={B} K={K}", flush=True)
+        m.reset()
+        xyz.copy_(cuda(data))
+        g.replay([0, n], origins)
+        if name == "out":
+            with pytest.raises(SmkiError):
+                m.sync()
+            assert m.num_blocks() == 0
+            continue
+        m.sync()
+        st = m.stats()
+        fresh.reset()
+        fresh.insert_scan(cuda(data), y, origins[0], 0.0)
+        ref = fresh.stats()
+        assert all(st[k] == ref[k] for k in ("n_updated_voxels", "n_pairs", "n_new_blocks",
+                                             "n_new_class_blocks", "n_target_blocks"))
+        assert torch.equal(m.query(q)["alpha"], fresh.query(q)["alpha"])
+    g.close()
