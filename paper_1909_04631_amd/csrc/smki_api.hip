@@ -151,6 +151,7 @@ constexpr int kPinNew = 512, kPinCounts = 704;
 struct Stencil {
   int32_t R = 0;
   std::vector<StencilOff> offs;
+  FullStencil full{};   // the offsets of all octants together, where they are few
 };
 
 struct smki_map {
@@ -230,17 +231,36 @@ smki_status status_of_err(uint32_t e) {
 // sum_a dist(o_a, [0, 1/2])^2 < (l/res + margin)^2.  The margin covers a point
 // assigned to the neighbouring cell by the rounding of floor(x / res).  A point
 // in another octant uses the mirrored offsets.  Ordered by that distance.
-Stencil make_stencil(double lv, double margin) {
+Stencil make_stencil(double lv, double margin, double res) {
   Stencil s;
   const double L = lv + margin;
   s.R = std::max(0, (int32_t)ceil(lv + 0.5 + margin) - 1);
   auto dist = [](int o) { return o >= 1 ? o - 0.5 : (o == 0 ? 0.0 : -(double)o); };
+  auto dist_all = [](int o) { return std::max(0.0, std::abs((double)o) - 0.5); };
+  std::vector<StencilOff> all;
   for (int dx = -s.R; dx <= s.R; ++dx)
     for (int dy = -s.R; dy <= s.R; ++dy)
       for (int dz = -s.R; dz <= s.R; ++dz) {
         const double ax = dist(dx), ay = dist(dy), az = dist(dz);
         if (ax * ax + ay * ay + az * az < L * L) s.offs.push_back(StencilOff{dx, dy, dz, 0});
+        const double bx = dist_all(dx), by = dist_all(dy), bz = dist_all(dz);
+        if (bx * bx + by * by + bz * bz < L * L) all.push_back(StencilOff{dx, dy, dz, 0});
       }
+  std::stable_sort(all.begin(), all.end(), [&](const StencilOff& a, const StencilOff& b) {
+    return a.dx * a.dx + a.dy * a.dy + a.dz * a.dz < b.dx * b.dx + b.dy * b.dy + b.dz * b.dz;
+  });
+  s.full.n = (int32_t)all.size();
+  for (int32_t n = 0; n < kFullMax + 3; ++n) {
+    const bool real = n < std::min(s.full.n, kFullMax);
+    const StencilOff o = real ? all[n] : StencilOff{0, 0, 0, 0};
+    const double x = o.dx * res, y = o.dy * res, z = o.dz * res;
+    s.full.w[n] = make_float4((float)(-2.0 * x), (float)(-2.0 * y), (float)(-2.0 * z),
+                              real ? (float)(x * x + y * y + z * z) : 1.0e30f);
+    if (!real) continue;
+    s.full.d[n][0] = (int8_t)o.dx;
+    s.full.d[n][1] = (int8_t)o.dy;
+    s.full.d[n][2] = (int8_t)o.dz;
+  }
   // nearest first: the splat's last step then holds the offsets that a row can
   // reach least often, and is skipped for rows that reach none of them
   auto key = [&](const StencilOff& o) {
@@ -656,7 +676,7 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
   const double lv = (double)max_class_l(m) / (double)m->res;   // the stencil of the widest kernel
   const double margin = std::max(1e-4, 4.0 * ldexp((double)maxabs + 1.0, -23));
   if (!csm && (lv != m->sten_lv || margin != m->sten_margin)) {   // (rebuilt when they change)
-    m->sten_cache = make_stencil(lv, margin);
+    m->sten_cache = make_stencil(lv, margin, (double)m->res);
     m->sten_lv = lv;
     m->sten_margin = margin;
   }
@@ -802,6 +822,7 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
     m->dev_R = sten.R;
   }
   sa.offs = (const int4*)m->d_offs;
+  sa.full_stencil = &sten.full;
   sa.cls = m->d_cls;
   for (int i = 0; i < SMKI_POLY_N; ++i) sa.mcoef[i] = (float)(kSmkiQ[i] / kSmkiQ[0]);
   sa.K = m->K;
@@ -1112,6 +1133,7 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   sa.R = sten.R;
   sa.noff = (int32_t)sten.offs.size();
   sa.offs = (const int4*)b->d_offs;
+  sa.full_stencil = &sten.full;
   sa.cls = m->d_cls;
   for (int i = 0; i < SMKI_POLY_N; ++i) sa.mcoef[i] = (float)(kSmkiQ[i] / kSmkiQ[0]);
   sa.K = m->K;
@@ -1826,7 +1848,7 @@ smki_status smki_batch_capture(smki_map* m, const float* xyz, const int32_t* lab
   }
   const double lv = (double)max_class_l(m) / (double)m->res;
   const double smargin = std::max(1e-4, 4.0 * ldexp((double)maxabs + 1.0, -23));
-  b->sten = make_stencil(lv, smargin);
+  b->sten = make_stencil(lv, smargin, (double)m->res);
   // 3. capacities
   b->cap_rows = std::max<int64_t>(n, (int64_t)ceil((double)(st.n_hits + st.n_free) * grow)) + 4096;
   b->cap_slots = std::min<int64_t>(std::min<int64_t>(b->cap_rows, g.n_blocks * m->K),

@@ -41,11 +41,23 @@ struct StencilOff {
   int32_t dx, dy, dz, pad;
 };
 
+// Every voxel offset that a row of a cell can reach, whatever its octant, for the
+// splat of small stencils (n <= kFullMax; larger ones have n > kFullMax and no
+// entries): w = (-2 o res, |o res|^2) of offset o, d = o; the entries past n are
+// out of every support.
+constexpr int kFullMax = 33;   // (a multiple of three)
+struct FullStencil {
+  int32_t n;
+  float4 w[kFullMax + 3];
+  int8_t d[kFullMax][4];
+};
+
 struct SplatArgs {
   BucketGeom g;               // point grid (planes = classes)
   int32_t R;                  // stencil reach in voxels (region = block grown by R)
   int32_t noff;               // voxel offsets in offs
   const int4* offs;           // [noff] StencilOff
+  const FullStencil* full_stencil;   // host: read when a splat is launched
   const float4* cls;          // [K] kernel of each class: (l^2, 1/l, sigma0 * Q's leading
                               // coefficient, l); the stencil covers the largest l
   float mcoef[SMKI_POLY_N];   // Q / Q's leading coefficient (monic), highest degree first

@@ -144,6 +144,93 @@ __global__ void k_unit_table(const int32_t* __restrict__ nunits, const int32_t* 
 // ---------------------------------------------------------------------------
 // splat
 // ---------------------------------------------------------------------------
+// Write out the pieces that received a contribution (and that the selection
+// keeps): per piece, every lane reads its elements into registers, the
+// wavefront votes on any non-zero value, and a non-zero piece is stored
+// contiguously.  Piece geometry is compile-time, so the index arithmetic
+// folds to constants.
+template <int B, int R>
+__device__ __forceinline__ void write_region(const SplatArgs& a, const float* acc, int32_t uid,
+                                             int lane, uint32_t npair) {
+  constexpr int DR = B + 2 * R, DR3 = DR * DR * DR;
+  using PC = Pieces<B, R>;
+  float* out = a.part + SMKI_PART_HEAD + (int64_t)uid * DR3;
+  constexpr int MAXPER = (B * B * B + SMKI_WAVE - 1) / SMKI_WAVE;   // the largest piece is the block
+  uint32_t touched = 0;
+  if constexpr (MAXPER > 8) {
+#pragma unroll
+    for (int p = 0; p < 27; ++p) {
+      if (!((a.piece_mask >> p) & 1u)) continue;
+      const int ey = PC::ext((p / 3) % 3 - 1), ez = PC::ext(p % 3 - 1);
+      const int sx = PC::rstart(p / 9 - 1), sy = PC::rstart((p / 3) % 3 - 1),
+                sz = PC::rstart(p % 3 - 1);
+      const int n = PC::size(p), b = PC::base(p);
+      // large blocks: vote while reading, then read again to store (no
+      // register copy of the piece)
+      bool nz = false;
+      for (int i = lane; i < n; i += SMKI_WAVE) {
+        const int lx = i / (ey * ez), ly = (i / ez) % ey, lz = i % ez;
+        nz = nz || acc[((sx + lx) * DR + (sy + ly)) * DR + (sz + lz)] != 0.0f;
+      }
+      if (__ballot(nz) == 0) continue;
+      touched |= 1u << p;
+      for (int i = lane; i < n; i += SMKI_WAVE) {
+        const int lx = i / (ey * ez), ly = (i / ez) % ey, lz = i % ez;
+        out[b + i] = acc[((sx + lx) * DR + (sy + ly)) * DR + (sz + lz)];
+      }
+    }
+  } else {
+    // Region index of element i = lane + 64 k of a piece, relative to the
+    // piece's first voxel, for each pair of (y, z) extents in {R, B}: computed
+    // once here (the x extent only bounds i).
+    constexpr int KRR = (B * R * R + SMKI_WAVE - 1) / SMKI_WAVE,
+                  KRB = (B * R * B + SMKI_WAVE - 1) / SMKI_WAVE;
+    int32_t lRR[KRR > 0 ? KRR : 1], lRB[KRB > 0 ? KRB : 1], lBR[KRB > 0 ? KRB : 1], lBB[MAXPER];
+    auto rel = [&](int ey, int ez, int i) { return ((i / (ey * ez)) * DR + (i / ez) % ey) * DR + i % ez; };
+#pragma unroll
+    for (int k = 0; k < MAXPER; ++k) {
+      const int i = lane + k * SMKI_WAVE;
+      if (k < KRR) lRR[k] = rel(R, R, i);
+      if (k < KRB) {
+        lRB[k] = rel(R, B, i);
+        lBR[k] = rel(B, R, i);
+      }
+      lBB[k] = rel(B, B, i);
+    }
+#pragma unroll
+    for (int p = 0; p < 27; ++p) {
+      if (!((a.piece_mask >> p) & 1u)) continue;
+      const bool yr = (p / 3) % 3 != 1, zr = p % 3 != 1;   // y / z extent R (else B)
+      const int sx = PC::rstart(p / 9 - 1), sy = PC::rstart((p / 3) % 3 - 1),
+                sz = PC::rstart(p % 3 - 1);
+      const int n = PC::size(p), b = PC::base(p);
+      const int per = (n + SMKI_WAVE - 1) / SMKI_WAVE;
+      const int S = (sx * DR + sy) * DR + sz;
+      float v[MAXPER];
+      bool nz = false;
+#pragma unroll
+      for (int k = 0; k < MAXPER; ++k) {
+        v[k] = 0.0f;
+        if (k < per && lane + k * SMKI_WAVE < n) {
+          const int r = yr ? (zr ? lRR[k < KRR ? k : 0] : lRB[k < KRB ? k : 0])
+                           : (zr ? lBR[k < KRB ? k : 0] : lBB[k]);
+          v[k] = acc[S + r];
+          nz = nz || v[k] != 0.0f;
+        }
+      }
+      if (__ballot(nz) == 0) continue;
+      touched |= 1u << p;
+      float* ob = out + b;
+#pragma unroll
+      for (int k = 0; k < MAXPER; ++k)
+        if (k < per && lane + k * SMKI_WAVE < n) ob[lane + k * SMKI_WAVE] = v[k];
+    }
+  }
+  if (lane == 0) a.umask[uid] = touched;
+  if (lane == 0)
+    atomicAdd(&a.stats[(blockIdx.x % SMKI_STAT_COPIES) * 4 + 1], (unsigned long long)npair);
+}
+
 // NS: steps of 64 voxel offsets, enough for the first-octant stencil of any
 // l / res with reach R (its size is largest at l / res -> R + 1/2: 1, 23, 90,
 // 230, 471 offsets for R = 0..4).
@@ -157,12 +244,9 @@ struct Steps {
 
 // NS = ceil(stencil size / 64), the steps each row takes (compiled per value
 // so that the steps of a row are independent straight-line code).  W: rows carry
-// a weight (soft measurements) that scales their kernel values.  RPS: rows per
-// step; 2 for a stencil of at most 32 offsets (one step), whose two halves of
-// the wavefront then take two rows at once.
-template <int B, int R, int NS, bool W, int RPS>
+// a weight (soft measurements) that scales their kernel values.
+template <int B, int R, int NS, bool W>
 __global__ void __launch_bounds__(SMKI_WAVE) k_splat(SplatArgs a) {
-  static_assert(RPS == 1 || (RPS == 2 && NS == 1), "two rows per step only for a one-step stencil");
   constexpr int DR = B + 2 * R;                 // region edge (voxels)
   constexpr int DR3 = DR * DR * DR;
   constexpr int NACC4 = (DR3 + 3) / 4;
@@ -203,7 +287,7 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat(SplatArgs a) {
   const double res = (double)a.g.res;
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    const int o = s * SMKI_WAVE + (RPS == 2 ? (lane & 31) : lane);
+    const int o = s * SMKI_WAVE + lane;
     pad[s] = o >= a.noff;
     int4 off = a.offs[min(o, a.noff - 1)];   // unconditional load, pad lanes reset below
     if (pad[s]) off = make_int4(0, 0, 0, 0);
@@ -232,7 +316,6 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat(SplatArgs a) {
     sum[s] = 0.0f;
     cw[s] = 0;
   }
-  const int xlane4 = (lane ^ 32) << 2;   // byte address of the other half's lane (RPS == 2)
   // Flush: every lane adds its group sum (0 included) to its voxel of the
   // region, all reads of a flush first, then all writes; pad lanes (no stencil
   // offset) touch nothing.  Within one flush the lanes' addresses are distinct;
@@ -240,17 +323,6 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat(SplatArgs a) {
   // compiler keeps flushes in program order (signal fence), so every voxel
   // sums its groups in processing order: run-to-run identical.
   auto flush = [&]() {
-    if constexpr (RPS == 2) {
-      // both halves hold sums of the same group for the same offsets: the
-      // lower half adds their total
-      const float tot =
-          sum[0] + __int_as_float(__builtin_amdgcn_ds_bpermute(xlane4, __float_as_int(sum[0])));
-      const int32_t fa0 = gcb + cw[0];
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      if (lane < 32 && !pad[0]) acc[fa0] = acc[fa0] + tot;
-      sum[0] = 0.0f;
-      return;
-    }
     int32_t fa[NS];
     float fo[NS];
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -349,50 +421,6 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat(SplatArgs a) {
         sum[s] = fmaf(uu * uu, sv * qq, sum[s]);
     }
   };
-  // Two rows at once (RPS == 2): j in the lower half of the wavefront, jh (-1:
-  // none) in the upper, of one octant, keys klo and khi, their |u| and |u|^2 in
-  // q (per half).  A half's sums join the open group when its row belongs to
-  // it; a pair that spans two groups flushes in between.
-  auto pair = [&](float wp, int j, int jh, int32_t klo, int32_t khi, const float4& q) {
-    const bool hi = lane >= 32;
-    const bool act = !hi || jh >= 0;   // this half has a row
-    float wr = 1.0f;
-    if (W) {
-      const float wlo = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wp), j));
-      const float whi = jh >= 0 ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wp), jh)) : 0.0f;
-      wr = hi ? whi : wlo;
-    }
-    const float d2 = fmaf(q.z, nwz[0], fmaf(q.y, nwy[0], fmaf(q.x, nwx[0], q.w + w2[0])));
-    const bool in = act && d2 < l2;
-    npair += (uint32_t)__popcll(__ballot(in));
-    const float d = __builtin_amdgcn_sqrtf(fabsf(d2));
-    const float sv = __builtin_amdgcn_fmed3f(fmaf(-d, inv_l, 1.0f), 0.0f, 1.0f);
-    const float uu = sv * sv;
-    float qq = fmaf(uu, cq[0], cq[1]);
-#pragma unroll
-    for (int i = 2; i < SMKI_POLY_N; ++i) qq = fmaf(qq, uu, cq[i]);
-    float v = W ? (uu * uu) * ((sv * wr) * qq) : (uu * uu) * (sv * qq);
-    if (!act) v = 0.0f;
-    // (the value is complete before any flush's LDS traffic is issued)
-    asm volatile("" ::"v"(v) : "memory");
-    octant(klo);
-    if (klo != gkey) {
-      if (gkey >= 0) flush();
-      gkey = klo;
-      gcb = cell_base(klo);
-    }
-    if (khi == gkey) {
-      sum[0] += v;
-    } else {
-      sum[0] += hi ? 0.0f : v;
-      if (jh >= 0) {
-        flush();
-        gkey = khi;
-        gcb = cell_base(khi);
-        sum[0] = hi ? v : 0.0f;
-      }
-    }
-  };
   // One batch: its rows go to LDS in octant-major order (each octant's rows in
   // sorted order) and are read back by every lane, one row (or pair) at a time.
   auto process = [&](const Batch& bt, int32_t base) {
@@ -422,34 +450,13 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat(SplatArgs a) {
     if (W) wq[slot] = bt.w;
     const int32_t keyp = keyq[lane];
     const float wp = W ? wq[lane] : 1.0f;
-    if constexpr (RPS == 2) {
-      // pairs of consecutive rows of one octant (a row whose successor lies in
-      // another octant, or the last row, goes alone)
-      int j = 0;
-      while (j < nb) {
-        const int32_t klo = __builtin_amdgcn_readlane(keyp, j);
-        int jh = -1;
-        int32_t khi = -1;
-        if (j + 1 < nb) {
-          const int32_t k1 = __builtin_amdgcn_readlane(keyp, j + 1);
-          if (((k1 ^ klo) & 7) == 0) {
-            jh = j + 1;
-            khi = k1;
-          }
-        }
-        const float4 q = rowq[(lane >= 32 && jh >= 0) ? jh : j];
-        pair(wp, j, jh, klo, khi, q);
-        j = (jh >= 0 ? jh : j) + 1;
-      }
-    } else {
-      // rows in order, through two row registers: the next row is read while
-      // this one is processed
-      float4 qa = rowq[0], qb;
-      for (int j = 0; j < nb; j += 2) {
-        row(keyp, wp, j, qa, min(j + 1, nb - 1), qb);
-        if (j + 1 >= nb) break;
-        row(keyp, wp, j + 1, qb, min(j + 2, nb - 1), qa);
-      }
+    // rows in order, through two row registers: the next row is read while
+    // this one is processed
+    float4 qa = rowq[0], qb;
+    for (int j = 0; j < nb; j += 2) {
+      row(keyp, wp, j, qa, min(j + 1, nb - 1), qb);
+      if (j + 1 >= nb) break;
+      row(keyp, wp, j + 1, qb, min(j + 2, nb - 1), qa);
     }
   };
   Batch ba = load_batch(load_index(r0));
@@ -465,87 +472,148 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat(SplatArgs a) {
   }
   if (gkey >= 0) flush();
   __syncthreads();
-  // Write out the pieces that received a contribution (and that the selection
-  // keeps): per piece, every lane reads its elements into registers, the
-  // wavefront votes on any non-zero value, and a non-zero piece is stored
-  // contiguously.  Piece geometry is compile-time, so the index arithmetic
-  // folds to constants.
-  using PC = Pieces<B, R>;
-  float* out = a.part + SMKI_PART_HEAD + (int64_t)uid * DR3;
-  constexpr int MAXPER = (B * B * B + SMKI_WAVE - 1) / SMKI_WAVE;   // the largest piece is the block
-  uint32_t touched = 0;
-  if constexpr (MAXPER > 8) {
+  write_region<B, R>(a, acc, uid, lane, npair);
+}
+
+// Splat for small stencils (at most 33 voxels around a cell: l / res up to 1.58),
+// where a row meets about 14 voxels and the row-by-row form leaves most lanes of
+// a step idle and pays its row handling (octant order, broadcasts, group
+// changes) for one step.  Here lanes are rows: 64 rows evaluate one voxel offset of the full
+// stencil at a time, its coefficients in scalar registers, into an LDS table
+// [row][offset] (an odd pitch: the rows' writes fall in different banks); then
+// lanes are offsets: rows of one cell are consecutive, and each lane adds its
+// column of every run of rows and adds the sum to its voxel of the region.  Every
+// lane owns distinct region addresses and the LDS runs a wavefront's accesses in
+// order, so the sum order is fixed: by run, rows in sorted order.  The town's
+// 1.7e8 rows: 6.3 ms two rows a step, now 4.7.
+template <int B, int R, bool W>
+__global__ void __launch_bounds__(SMKI_WAVE) k_splat_small(SplatArgs a, FullStencil fs) {
+  constexpr int DR = B + 2 * R, DR3 = DR * DR * DR, NACC4 = (DR3 + 3) / 4;
+  constexpr int FP = kFullMax;   // pitch of the table (odd)
+  __shared__ float4 acc4[NACC4 + SMKI_WAVE / 4];
+  __shared__ float F[SMKI_WAVE * FP + SMKI_WAVE];   // (lanes past the stencil read past a row)
+  float* acc = (float*)acc4;
+  const int lane = threadIdx.x;
+  if (blockIdx.x == 0 && lane < SMKI_PART_HEAD) a.part[lane] = 0.0f;
+  if (a.dn_units && (int32_t)blockIdx.x >= *a.dn_units) return;   // capacity launch
+  if (a.abort_word && *a.abort_word) return;   // (a failed captured insert: the units may be stale)
+  const int32_t uid = a.uorder ? a.uorder[blockIdx.x] : (int32_t)blockIdx.x;
+  const int4 u = a.units[uid];   // (first row, end row, slot, class)
+  const int32_t r0 = u.x, r1 = u.y;
+  const float4 kc = a.cls[u.w];         // the kernel of the unit's class
+  const float l2 = kc.x, inv_l = kc.y, cscale = kc.z;
+  float cq[SMKI_POLY_N];   // sigma0 Q, highest degree first
+  cq[0] = cscale;
 #pragma unroll
-    for (int p = 0; p < 27; ++p) {
-      if (!((a.piece_mask >> p) & 1u)) continue;
-      const int ey = PC::ext((p / 3) % 3 - 1), ez = PC::ext(p % 3 - 1);
-      const int sx = PC::rstart(p / 9 - 1), sy = PC::rstart((p / 3) % 3 - 1),
-                sz = PC::rstart(p % 3 - 1);
-      const int n = PC::size(p), b = PC::base(p);
-      // large blocks: vote while reading, then read again to store (no
-      // register copy of the piece)
-      bool nz = false;
-      for (int i = lane; i < n; i += SMKI_WAVE) {
-        const int lx = i / (ey * ez), ly = (i / ez) % ey, lz = i % ez;
-        nz = nz || acc[((sx + lx) * DR + (sy + ly)) * DR + (sz + lz)] != 0.0f;
+  for (int i = 1; i < SMKI_POLY_N; ++i) cq[i] = cscale * a.mcoef[i];
+  for (int i = lane; i < NACC4; i += SMKI_WAVE) acc4[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  // this lane's offset as a region-index offset
+  const int n = fs.n;
+  const bool mine = lane < n;
+  const int ol = mine ? lane : 0;
+  // (lanes past the stencil add to words of their own past the region)
+  const int32_t wl =
+      mine ? fs.d[ol][0] * DR * DR + fs.d[ol][1] * DR + fs.d[ol][2] : NACC4 * 4 + lane;
+  __syncthreads();
+  uint32_t npair = 0;
+  struct Batch {
+    float4 r;
+    float w;
+  };
+  // rows through the permutation, two batches in registers (as in k_splat)
+  auto load_index = [&](int32_t base) -> int32_t {
+    const int32_t row = min(base + lane, r1 - 1);
+    return a.perm ? (int32_t)a.perm[row] : row;
+  };
+  auto load_batch = [&](int32_t v) {
+    Batch b;
+    b.r = a.pts[v];
+    b.w = W ? a.wts[v] : 1.0f;
+    return b;
+  };
+  auto process = [&](const Batch& bt, int32_t base) {
+    const int nb = min(SMKI_WAVE, r1 - base);
+    const bool valid = lane < nb;
+    const int32_t key = __float_as_int(bt.r.w);
+    // the row relative to its cell's centre, signs from its octant; |q|^2, or
+    // out of everything's support for a lane without a row
+    const float x = (key & 1) ? -bt.r.x : bt.r.x, y = (key & 2) ? -bt.r.y : bt.r.y,
+                z = (key & 4) ? -bt.r.z : bt.r.z;
+    const float q2 = valid ? fmaf(x, x, fmaf(y, y, z * z)) : 1.0e30f;
+    const uint32_t cell = (uint32_t)key >> 3;
+    const int32_t cb =
+        (int32_t)(((cell / (B * B) + R) * DR + ((cell / B) % B + R)) * DR + (cell % B + R));
+    float* Fr = F + lane * FP;
+    // three offsets at a time (the list is padded with offsets out of every
+    // support), the next three's coefficients loaded while these are used
+    float4 w0 = fs.w[0], w1 = fs.w[1], w2 = fs.w[2];
+    for (int k = 0; k < n; k += 3) {
+      const float4 c[3] = {w0, w1, w2};
+      w0 = fs.w[k + 3];
+      w1 = fs.w[k + 4];
+      w2 = fs.w[k + 5];
+      float d2[3], v[3] = {0.0f, 0.0f, 0.0f};
+      uint64_t any = 0;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const float4 w = c[i];   // (uniform: scalar registers)
+        d2[i] = fmaf(z, w.z, fmaf(y, w.y, fmaf(x, w.x, q2 + w.w)));
+        const uint64_t in = __ballot(d2[i] < l2);
+        npair += (uint32_t)__popcll(in);
+        any |= in;
       }
-      if (__ballot(nz) == 0) continue;
-      touched |= 1u << p;
-      for (int i = lane; i < n; i += SMKI_WAVE) {
-        const int lx = i / (ey * ez), ly = (i / ez) % ey, lz = i % ez;
-        out[b + i] = acc[((sx + lx) * DR + (sy + ly)) * DR + (sz + lz)];
-      }
-    }
-  } else {
-    // Region index of element i = lane + 64 k of a piece, relative to the
-    // piece's first voxel, for each pair of (y, z) extents in {R, B}: computed
-    // once here (the x extent only bounds i).
-    constexpr int KRR = (B * R * R + SMKI_WAVE - 1) / SMKI_WAVE,
-                  KRB = (B * R * B + SMKI_WAVE - 1) / SMKI_WAVE;
-    int32_t lRR[KRR > 0 ? KRR : 1], lRB[KRB > 0 ? KRB : 1], lBR[KRB > 0 ? KRB : 1], lBB[MAXPER];
-    auto rel = [&](int ey, int ez, int i) { return ((i / (ey * ez)) * DR + (i / ez) % ey) * DR + i % ez; };
+      if (any) {   // (the offsets are sorted by distance: the last ones are often out of reach)
 #pragma unroll
-    for (int k = 0; k < MAXPER; ++k) {
-      const int i = lane + k * SMKI_WAVE;
-      if (k < KRR) lRR[k] = rel(R, R, i);
-      if (k < KRB) {
-        lRB[k] = rel(R, B, i);
-        lBR[k] = rel(B, R, i);
-      }
-      lBB[k] = rel(B, B, i);
-    }
+        for (int i = 0; i < 3; ++i) {
+          const float d = __builtin_amdgcn_sqrtf(fabsf(d2[i]));
+          const float sv = __builtin_amdgcn_fmed3f(fmaf(-d, inv_l, 1.0f), 0.0f, 1.0f);
+          const float uu = sv * sv;
+          float qq = fmaf(uu, cq[0], cq[1]);
 #pragma unroll
-    for (int p = 0; p < 27; ++p) {
-      if (!((a.piece_mask >> p) & 1u)) continue;
-      const bool yr = (p / 3) % 3 != 1, zr = p % 3 != 1;   // y / z extent R (else B)
-      const int sx = PC::rstart(p / 9 - 1), sy = PC::rstart((p / 3) % 3 - 1),
-                sz = PC::rstart(p % 3 - 1);
-      const int n = PC::size(p), b = PC::base(p);
-      const int per = (n + SMKI_WAVE - 1) / SMKI_WAVE;
-      const int S = (sx * DR + sy) * DR + sz;
-      float v[MAXPER];
-      bool nz = false;
-#pragma unroll
-      for (int k = 0; k < MAXPER; ++k) {
-        v[k] = 0.0f;
-        if (k < per && lane + k * SMKI_WAVE < n) {
-          const int r = yr ? (zr ? lRR[k < KRR ? k : 0] : lRB[k < KRB ? k : 0])
-                           : (zr ? lBR[k < KRB ? k : 0] : lBB[k]);
-          v[k] = acc[S + r];
-          nz = nz || v[k] != 0.0f;
+          for (int q = 2; q < SMKI_POLY_N; ++q) qq = fmaf(qq, uu, cq[q]);
+          v[i] = W ? (uu * uu) * ((sv * bt.w) * qq) : (uu * uu) * (sv * qq);
         }
       }
-      if (__ballot(nz) == 0) continue;
-      touched |= 1u << p;
-      float* ob = out + b;
 #pragma unroll
-      for (int k = 0; k < MAXPER; ++k)
-        if (k < per && lane + k * SMKI_WAVE < n) ob[lane + k * SMKI_WAVE] = v[k];
+      for (int i = 0; i < 3; ++i) Fr[k + i] = v[i];
     }
+    // runs of rows of one cell: bit j set where row j ends one.  Eight rows'
+    // columns are read together.
+    const int32_t after = __shfl_down(cb, 1, SMKI_WAVE);
+    const uint64_t ends = __ballot(valid && (lane == nb - 1 || after != cb));
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (one wavefront: the LDS keeps the order)
+    const float* col = F + lane;
+    float sum = 0.0f;
+    for (int j0 = 0; j0 < nb; j0 += 8) {
+      float f[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f[i] = col[(j0 + i) * FP];
+      const uint32_t e8 = (uint32_t)(ends >> j0) & 0xffu;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        sum += f[i];
+        if ((e8 >> i) & 1u) {   // (uniform)
+          const int32_t at = mine ? __builtin_amdgcn_readlane(cb, j0 + i) + wl : wl;
+          acc[at] += sum;
+          __atomic_signal_fence(__ATOMIC_SEQ_CST);
+          sum = 0.0f;
+        }
+      }
+    }
+  };
+  Batch ba = load_batch(load_index(r0));
+  int32_t vb = load_index(r0 + SMKI_WAVE);
+  for (int32_t base = r0; base < r1; base += 2 * SMKI_WAVE) {
+    const Batch bb = load_batch(vb);
+    const int32_t va = load_index(base + 2 * SMKI_WAVE);
+    process(ba, base);
+    if (base + SMKI_WAVE >= r1) break;
+    ba = load_batch(va);
+    vb = load_index(base + 3 * SMKI_WAVE);
+    process(bb, base + SMKI_WAVE);
   }
-  if (lane == 0) a.umask[uid] = touched;
-  if (lane == 0)
-    atomicAdd(&a.stats[(blockIdx.x % SMKI_STAT_COPIES) * 4 + 1], (unsigned long long)npair);
+  __syncthreads();
+  write_region<B, R>(a, acc, uid, lane, npair);
 }
 
 // ---------------------------------------------------------------------------
@@ -1007,19 +1075,10 @@ hipError_t launch_splat_ns(const SplatArgs& a, int64_t n_units, int ns, hipStrea
   if constexpr (NSV >= Steps<R>::NSMIN) {
     if (ns == NSV) {
       const dim3 grid((unsigned)n_units), block(SMKI_WAVE);
-      if constexpr (NSV == 1) {
-        if (a.noff <= 32) {   // two rows per step
-          if (a.wts)
-            hipLaunchKernelGGL((k_splat<B, R, 1, true, 2>), grid, block, 0, st, a);
-          else
-            hipLaunchKernelGGL((k_splat<B, R, 1, false, 2>), grid, block, 0, st, a);
-          return hipGetLastError();
-        }
-      }
       if (a.wts)
-        hipLaunchKernelGGL((k_splat<B, R, NSV, true, 1>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((k_splat<B, R, NSV, true>), grid, block, 0, st, a);
       else
-        hipLaunchKernelGGL((k_splat<B, R, NSV, false, 1>), grid, block, 0, st, a);
+        hipLaunchKernelGGL((k_splat<B, R, NSV, false>), grid, block, 0, st, a);
       return hipGetLastError();
     }
     return launch_splat_ns<B, R, NSV - 1>(a, n_units, ns, st);
@@ -1032,6 +1091,17 @@ template <int B, int R>
 hipError_t launch_splat_br(const SplatArgs& a, int64_t n_units, int32_t n_targets, bool merge,
                            hipStream_t st) {
   if (!merge) {
+    if constexpr (R <= 2) {
+      // at most kFullMax voxels around a cell: lanes over rows
+      if (n_units > 0 && a.full_stencil->n <= kFullMax) {
+        const dim3 grid((unsigned)n_units), block(SMKI_WAVE);
+        if (a.wts)
+          hipLaunchKernelGGL((k_splat_small<B, R, true>), grid, block, 0, st, a, *a.full_stencil);
+        else
+          hipLaunchKernelGGL((k_splat_small<B, R, false>), grid, block, 0, st, a, *a.full_stencil);
+        return hipGetLastError();
+      }
+    }
     if (n_units > 0)
       return launch_splat_ns<B, R, Steps<R>::NS>(a, n_units, (a.noff + SMKI_WAVE - 1) / SMKI_WAVE,
                                                  st);

@@ -224,3 +224,40 @@ def test_replay_with_more_targets_than_its_grid(B, K):
                                              "n_new_class_blocks", "n_target_blocks"))
         assert torch.equal(m.query(q)["alpha"], fresh.query(q)["alpha"])
     g.close()
+
+
+@pytest.mark.parametrize("soft", [False, True])
+@pytest.mark.parametrize("lv", [0.3, 0.6, 0.8, 0.95, 1.2, 1.45, 1.5, 1.57, 1.65])
+def test_small_stencils_around_unit_edges(lv, soft):
+    # stencils of 1 to 33 voxels around a cell (lanes over rows), and the first
+    # larger one; units of 64 rows and of 96 (a batch and a half)
+    import torch
+    from paper_1909_04631_amd import SemanticMap
+    K, res = 3, 0.2
+    l = float(np.float32(lv) * np.float32(res))
+    rng = np.random.default_rng(int(100 * lv))
+    n = 1_500
+    xyz = rng.uniform(-1.0, 1.0, size=(n, 3)).astype(np.float32)
+    xyz[: n // 2] = np.float32(0.1) + rng.normal(0, 0.03, size=(n // 2, 3)).astype(np.float32)
+    xyz[:40] = np.float32(0.2) * np.round(xyz[:40] / np.float32(0.2))   # on voxel faces
+    lab = rng.integers(0, K, size=n).astype(np.int32)
+    w = rng.uniform(0.0, 1.0, size=(n, K)).astype(np.float32)
+    w[rng.random((n, K)) < 0.4] = 0.0
+    om = oracle.OracleMap(K, float(np.float32(res)), 8, l, 0.5, float(np.float32(1e-3)))
+    if soft:
+        om.insert_scan_soft(xyz, w, (0, 0, 0), 0.0)
+    else:
+        om.insert_scan(xyz, lab, (0, 0, 0), 0.0)
+    ijk, a_ref, nv, nb = om.export()
+    for B, budget in ((2, 64), (4, 64), (8, 96), (16, 96)):
+        print(f"[case] small stencil l/res={lv} B={B} soft={soft}", flush=True)
+        m = SemanticMap(res, B, l, 0.5, K, 1e-3, unit_budget=budget)
+        if soft:
+            m.insert_scan_soft(cuda(xyz), cuda(w), (0, 0, 0), 0.0)
+        else:
+            m.insert_scan(cuda(xyz), cuda(lab), (0, 0, 0), 0.0)
+        a = m.query(cuda(ijk.astype(np.int32)))["alpha"].cpu().numpy()
+        assert np.max(np.abs(a - a_ref) / a_ref) <= 1e-5
+        st = m.stats()
+        assert abs(st["n_pairs"] - int(nv.sum())) <= int(nb.sum())
+        torch.cuda.synchronize()
