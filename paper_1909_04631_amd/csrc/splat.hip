@@ -885,6 +885,176 @@ k_merge(SplatArgs a, int32_t n_targets) {
   } while (STRIDE && (t += gridDim.x) < n_targets);
 }
 
+// Merge where a target block is one wavefront (B = 4): the neighbours whose units
+// wrote a piece of a class in the block are the same for every voxel.  So per class
+// the wavefront walks those that are there, eight at a time with their loads in
+// flight together, and not every candidate of every voxel (up to 27 for 2R > B); a
+// neighbour's unit, piece offset and extents are uniform (one lane each, read
+// across), a voxel that it does not cover reads the zero word.  Later units of
+// multi-unit slots follow, each set of 64 tested at once.  The sums are kept in
+// double, neighbours in order, then later units in order.  Bound by instruction
+// issue (town: 690 vector instructions per target).  Every candidate loaded, as in
+// k_merge, and now: LiDAR scan 238 us and 134, stereo frames 150 and 85 per insert,
+// town 869 and 793, its replay 232 and 208.  (The voxels' offsets from a table in
+// LDS and loads with a range per region: town 767, stereo 91 to 121, replay 250.)
+template <int B, int R, bool WIDE, bool STRIDE>
+__global__ void __launch_bounds__(SMKI_WAVE) k_merge_list(SplatArgs a, int32_t n_targets) {
+  static_assert(B * B * B == SMKI_WAVE, "one wavefront per target");
+  constexpr int DR = B + 2 * R, DR3 = DR * DR * DR;
+  constexpr uint32_t N27 = (1u << 27) - 1u;
+  if (a.dn_targets) n_targets = min(n_targets, *a.dn_targets);
+  if (a.abort_word && *a.abort_word) return;   // nothing is written to the map
+  const int lane = threadIdx.x;
+  int32_t t = blockIdx.x;
+  if (t >= n_targets) return;
+  if (!STRIDE && !a.tgt_active[t]) return;
+  const int64_t n_cold = a.dn_targets ? a.map.counts[1] : a.n_cold;
+  // voxel of this lane, and the neighbours whose regions cover it: bit d = (dx + 1) 9
+  // + (dy + 1) 3 + dz + 1, the and of one mask per axis
+  const int vv[3] = {lane / (B * B), (lane / B) % B, lane % B};
+  const uint32_t cover =
+      ((vv[0] < R ? 0x1ffu : 0u) | 0x1ffu << 9 | (vv[0] >= B - R ? 0x1ffu << 18 : 0u)) &
+      ((vv[1] < R ? 0x7u * 0x40201u : 0u) | 0x38u * 0x40201u | (vv[1] >= B - R ? 0x1c0u * 0x40201u : 0u)) &
+      ((vv[2] < R ? 0x1249249u : 0u) | 0x2492492u | (vv[2] >= B - R ? 0x4924924u : 0u));
+  // neighbour d of lanes d and 27 + d: its piece's offset in its unit's region
+  // less where the voxels' coordinates start there, and the piece's extents (y z, z)
+  const int d = lane < 27 ? lane : lane - 27;
+  const int dx = d / 9 - 1, dy = (d / 3) % 3 - 1, dz = d % 3 - 1;
+  const int ey = dy == 0 ? B : R, ez = dz == 0 ? B : R;
+  const int ext = (ey * ez) << 8 | ez;
+  const int pb = (lane < 54 ? pbase<B, R>(26 - d) : 0) -
+                 (((dx > 0 ? B - R : 0) * ey + (dy > 0 ? B - R : 0)) * ez + (dz > 0 ? B - R : 0));
+  do {
+    if (STRIDE && !a.tgt_active[t]) continue;
+    const int32_t mslot = a.tgt_slot[t];
+    int32_t bt[3];
+    unlin3(a.tgt_elin[t], a.enb, bt);
+    // this lane's neighbour on the point grid: its entries of the slot table
+    const int px = bt[0] + a.eblo[0] - a.g.blo[0] + dx, py = bt[1] + a.eblo[1] - a.g.blo[1] + dy,
+              pz = bt[2] + a.eblo[2] - a.g.blo[2] + dz;
+    const bool near = lane < 54 && px >= 0 && py >= 0 && pz >= 0 && px < a.g.nb[0] &&
+                      py < a.g.nb[1] && pz < a.g.nb[2];
+    const int32_t* slots = a.dense + (((int64_t)px * a.g.nb[1] + py) * a.g.nb[2] + pz) * a.K;
+    bool upd = false;   // the voxel received a non-zero sum
+    for (int y0 = 0; y0 < a.K; y0 += SMKI_WAVE) {
+      // classes whose rows reach this block, and their class blocks
+      int32_t flag = 0, cblk = -1;
+      if (y0 + lane < a.K) {
+        flag = a.contrib[(int64_t)t * a.K + y0 + lane];
+        cblk = a.map.cslot[(int64_t)mslot * a.K + y0 + lane];
+      }
+      uint64_t listed = __ballot(flag != 0);
+      while (listed) {
+        // four classes at a time (two per half of the lanes): the neighbours' units,
+        // (first unit, units) of the neighbour's slot if some unit of it wrote the
+        // piece that lies in this block, else (0, 0); units negated when the first
+        // unit did not write it
+        int yc[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          yc[c] = listed ? __builtin_ctzll(listed) : -1;
+          listed &= listed - 1;
+        }
+        int32_t sl[2];
+        int2 e[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int y = lane < 27 ? yc[2 * h] : yc[2 * h + 1];
+          sl[h] = near && y >= 0 ? slots[y0 + y] : -1;
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          e[h] = make_int2(0, 0);
+          if (sl[h] >= 0) {
+            const int4 si = a.sinfo[sl[h]];
+            if ((si.z >> (26 - d)) & 1) e[h] = make_int2(si.x, ((si.w >> (26 - d)) & 1) ? si.y : -si.y);
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          if (yc[c] < 0) break;   // (uniform)
+          const int2 ec = e[c / 2];
+          const int base = (c & 1) * 27;
+          uint32_t first = (uint32_t)(__ballot(ec.y > 0) >> base) & N27;
+          uint32_t multi = (uint32_t)(__ballot(ec.y > 1 || ec.y < -1) >> base) & N27;
+          double sd = 0.0;
+          // offset of this lane's voxel in the piece of neighbour n (uniform)
+          auto offset = [&](int n) {
+            const int x = __builtin_amdgcn_readlane(ext, n), z = x & 255, yz = x >> 8;
+            return __builtin_amdgcn_readlane(pb, n) + vv[0] * yz + vv[1] * z + vv[2];
+          };
+          while (first) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              const bool has = first != 0;   // (uniform)
+              const int n = has ? __builtin_ctz(first) : 13;
+              first &= first - 1;            // (0 stays 0)
+              const bool ld = has && ((cover >> n) & 1u);
+              v[u] = part_at<DR3, WIDE>(a.part, ld ? __builtin_amdgcn_readlane(ec.x, base + n) : -1,
+                                        offset(n));
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sd += (double)v[u];
+          }
+          // later units, 64 at a time; the masks of the next set are loaded before
+          // the pieces of this one
+          int n = -1;
+          int32_t w0 = 0, w1 = 0;
+          uint32_t mk = 0;
+          auto next_set = [&]() {   // next set of the list: neighbour n, units w0 .. (uniform)
+            w0 += SMKI_WAVE;
+            if (n < 0 || w0 >= w1) {
+              n = -1;
+              if (multi) {
+                n = __builtin_ctz(multi);
+                multi &= multi - 1;
+                const int32_t u0 = __builtin_amdgcn_readlane(ec.x, base + n);
+                w0 = u0 + 1;
+                w1 = u0 + abs(__builtin_amdgcn_readlane(ec.y, base + n));
+              }
+            }
+            mk = n >= 0 && w0 + lane < w1 ? a.umask[w0 + lane] : 0u;
+          };
+          next_set();
+          while (n >= 0) {
+            const int nc = n;
+            const int32_t wc = w0;
+            uint64_t wrote = __ballot((mk >> (26 - nc)) & 1u);
+            next_set();
+            const bool in = (cover >> nc) & 1u;
+            const int32_t off = offset(nc);
+            while (wrote) {
+              float v[8];
+#pragma unroll
+              for (int u = 0; u < 8; ++u) {
+                const bool has = wrote != 0;
+                const int32_t w = has ? wc + (int32_t)__builtin_ctzll(wrote) : -1;
+                wrote &= wrote - 1;
+                v[u] = part_at<DR3, WIDE>(a.part, in ? w : -1, off);
+              }
+#pragma unroll
+              for (int u = 0; u < 8; ++u) sd += (double)v[u];
+            }
+          }
+          const float sm = (float)sd;
+          const int32_t cb = __builtin_amdgcn_readlane(cblk, yc[c]);   // allocated: rows reach here
+          float* dst = a.map.calpha + (int64_t)cb * SMKI_WAVE + lane;
+          if (cb >= n_cold) {
+            *dst = a.alpha0 + sm;   // class block allocated by this insert: written whole
+          } else if (sm != 0.0f) {
+            *dst += sm;
+          }
+          upd = upd || sm != 0.0f;
+        }
+      }
+    }
+    const uint64_t um = __ballot(upd);
+    if (lane == 0)
+      atomicAdd(&a.stats[(blockIdx.x % SMKI_STAT_COPIES) * 4], (unsigned long long)__popcll(um));
+  } while (STRIDE && (t += gridDim.x) < n_targets);
+}
+
 // (target, class) pairs that receive rows: from each slot's non-zero pieces (or
 // the slot's own block for the counting model); idempotent flag stores.  One
 // thread per slot: its block's coordinates once, then the targets of its
@@ -1111,16 +1281,26 @@ hipError_t launch_splat_br(const SplatArgs& a, int64_t n_units, int32_t n_target
       const bool narrow = !a.wide && a.part_elems * sizeof(float) <= (int64_t(1) << 32) &&
                           (a.part_elems - SMKI_PART_HEAD) / DR3 < (int64_t(1) << 24);
       const dim3 grid((unsigned)tgt_grid(a, n_targets)), block(MergeShape<B, R>::NT);
-      if (a.tgt_grid > 0) {
-        if (narrow)
-          hipLaunchKernelGGL((k_merge<B, R, false, true>), grid, block, 0, st, a, n_targets);
-        else
-          hipLaunchKernelGGL((k_merge<B, R, true, true>), grid, block, 0, st, a, n_targets);
-      } else if (narrow) {
-        hipLaunchKernelGGL((k_merge<B, R, false, false>), grid, block, 0, st, a, n_targets);
+      // a target of one wavefront (B = 4): by the list of the neighbours that are
+      // there; smaller blocks leave lanes idle, in larger ones the neighbours
+      // differ between a workgroup's wavefronts
+#define SMKI_MERGE(KERNEL)                                                                \
+  if (a.tgt_grid > 0) {                                                                   \
+    if (narrow)                                                                           \
+      hipLaunchKernelGGL((KERNEL<B, R, false, true>), grid, block, 0, st, a, n_targets);  \
+    else                                                                                  \
+      hipLaunchKernelGGL((KERNEL<B, R, true, true>), grid, block, 0, st, a, n_targets);   \
+  } else if (narrow) {                                                                    \
+    hipLaunchKernelGGL((KERNEL<B, R, false, false>), grid, block, 0, st, a, n_targets);   \
+  } else {                                                                                \
+    hipLaunchKernelGGL((KERNEL<B, R, true, false>), grid, block, 0, st, a, n_targets);    \
+  }
+      if constexpr (B == 4) {
+        SMKI_MERGE(k_merge_list)
       } else {
-        hipLaunchKernelGGL((k_merge<B, R, true, false>), grid, block, 0, st, a, n_targets);
+        SMKI_MERGE(k_merge)
       }
+#undef SMKI_MERGE
     }
   }
   return hipGetLastError();

@@ -261,3 +261,43 @@ def test_small_stencils_around_unit_edges(lv, soft):
         st = m.stats()
         assert abs(st["n_pairs"] - int(nv.sum())) <= int(nb.sum())
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("lv", [0.9, 1.9, 2.9, 3.9])
+@pytest.mark.parametrize("K,budget", [(3, 0), (70, 64)])
+def test_merge_of_small_blocks(lv, K, budget):
+    # blocks of 4^3, reach 1 to 4: classes beyond one wavefront, slots of one unit,
+    # of several and of more than 64, rows at the window's corners, a second insert
+    # on top of the first, and its replay
+    from paper_1909_04631_amd import SemanticMap
+    res = 0.2
+    l = float(np.float32(lv) * np.float32(res))
+    rng = np.random.default_rng(int(10 * lv) + K)
+    n = 9_000
+    xyz = rng.uniform(-3.0, 3.0, size=(n, 3)).astype(np.float32)
+    xyz[: n // 2] = np.float32(0.5) + rng.uniform(0, 0.2, size=(n // 2, 3)).astype(np.float32)
+    lab = rng.integers(0, K, size=n).astype(np.int32)
+    lab[: n // 2] = K - 1
+    om = oracle.OracleMap(K, float(np.float32(res)), 4, l, 0.5, float(np.float32(1e-3)))
+    gm, rm = [SemanticMap(res, 4, l, 0.5, K, 1e-3, unit_budget=budget, initial_blocks=1 << 14)
+              for _ in range(2)]
+    for step, rows in enumerate((slice(0, n), slice(0, n, 3))):
+        print(f"[case] merge B=4 l/res={lv} K={K} budget={budget} insert {step}", flush=True)
+        x, y = np.ascontiguousarray(xyz[rows]), np.ascontiguousarray(lab[rows])
+        om.insert_scan(x, y, (0, 0, 0), 0.0)
+        gm.insert_scan(cuda(x), cuda(y), (0, 0, 0), 0.0)
+        ijk, a_ref, _, _ = om.export()
+        q = cuda(ijk.astype(np.int32))
+        a = gm.query(q)["alpha"].cpu().numpy()
+        assert np.max(np.abs(a - a_ref) / a_ref) <= 1e-5
+        g = rm.batch_capture(cuda(x), cuda(y), [0, x.shape[0]], [(0.0, 0.0, 0.0)], 0.0)
+        rm.reset()      # (the capture inserts once)
+        if step == 1:
+            rm.insert_scan(cuda(xyz), cuda(lab), (0, 0, 0), 0.0)
+        g.replay([0, x.shape[0]], [(0.0, 0.0, 0.0)])
+        rm.sync()
+        ar = rm.query(q)["alpha"].cpu().numpy()
+        assert np.max(np.abs(ar - a_ref) / a_ref) <= 1e-5
+        g.close()
+    if budget:
+        assert gm.stats()["n_units"] > 1_500 // budget
