@@ -885,47 +885,59 @@ k_merge(SplatArgs a, int32_t n_targets) {
   } while (STRIDE && (t += gridDim.x) < n_targets);
 }
 
-// Merge where a target block is one wavefront (B = 4): the neighbours whose units
-// wrote a piece of a class in the block are the same for every voxel.  So per class
-// the wavefront walks those that are there, eight at a time with their loads in
-// flight together, and not every candidate of every voxel (up to 27 for 2R > B); a
-// neighbour's unit, piece offset and extents are uniform (one lane each, read
-// across), a voxel that it does not cover reads the zero word.  Later units of
-// multi-unit slots follow, each set of 64 tested at once.  The sums are kept in
-// double, neighbours in order, then later units in order.  Bound by instruction
-// issue (town: 690 vector instructions per target).  Every candidate loaded, as in
-// k_merge, and now: LiDAR scan 238 us and 134, stereo frames 150 and 85 per insert,
-// town 869 and 793, its replay 232 and 208.  (The voxels' offsets from a table in
-// LDS and loads with a range per region: town 767, stereo 91 to 121, replay 250.)
+// Merge where a target block is one wavefront (B = 4).  The first units of the
+// neighbours: with up to eight candidates per voxel (2R <= B) every lane loads its
+// own, the units read across the lanes that looked them up; with up to 27 the
+// wavefront walks the neighbours that are there, the same ones for every voxel and
+// few of the 26, eight at a time with their loads in flight together (a neighbour's
+// unit, piece offset and extents are uniform; a voxel that it does not cover reads
+// the zero word).  Later units of multi-unit slots follow neighbour by neighbour,
+// each set of 64 tested at once.  The sums are kept in double, neighbours in a fixed
+// order, then later units in order.  Bound by instruction issue (town, walked: 690
+// vector instructions per target).  k_merge's tables and barriers, every candidate
+// loaded, and now: LiDAR scan 238 us and 131, stereo frames 150 and 85 per insert,
+// town 869 and 640 (793 walked), its replay 232 and 195 (208 walked).  Offsets from
+// a table in LDS and loads with a range per region: town 767, stereo 91 to 121.  For
+// blocks of 8^3 the same by x-layers: a room scan 26 us and 20, but soft labels of a
+// LiDAR scan 334 and 398 (each layer looks up the neighbours again): left to k_merge.
+// (2R <= B: at most 64 registers, eight wavefronts per SIMD; town 677 without.)
 template <int B, int R, bool WIDE, bool STRIDE>
-__global__ void __launch_bounds__(SMKI_WAVE) k_merge_list(SplatArgs a, int32_t n_targets) {
+__global__ void __launch_bounds__(SMKI_WAVE, (2 * R > B || WIDE) ? 1 : 8) k_merge_list(SplatArgs a, int32_t n_targets) {
   static_assert(B * B * B == SMKI_WAVE, "one wavefront per target");
   constexpr int DR = B + 2 * R, DR3 = DR * DR * DR;
   constexpr uint32_t N27 = (1u << 27) - 1u;
   if (a.dn_targets) n_targets = min(n_targets, *a.dn_targets);
   if (a.abort_word && *a.abort_word) return;   // nothing is written to the map
-  const int lane = threadIdx.x;
   int32_t t = blockIdx.x;
   if (t >= n_targets) return;
   if (!STRIDE && !a.tgt_active[t]) return;
   const int64_t n_cold = a.dn_targets ? a.map.counts[1] : a.n_cold;
-  // voxel of this lane, and the neighbours whose regions cover it: bit d = (dx + 1) 9
-  // + (dy + 1) 3 + dz + 1, the and of one mask per axis
-  const int vv[3] = {lane / (B * B), (lane / B) % B, lane % B};
-  const uint32_t cover =
-      ((vv[0] < R ? 0x1ffu : 0u) | 0x1ffu << 9 | (vv[0] >= B - R ? 0x1ffu << 18 : 0u)) &
-      ((vv[1] < R ? 0x7u * 0x40201u : 0u) | 0x38u * 0x40201u | (vv[1] >= B - R ? 0x1c0u * 0x40201u : 0u)) &
-      ((vv[2] < R ? 0x1249249u : 0u) | 0x2492492u | (vv[2] >= B - R ? 0x4924924u : 0u));
-  // neighbour d of lanes d and 27 + d: its piece's offset in its unit's region
-  // less where the voxels' coordinates start there, and the piece's extents (y z, z)
-  const int d = lane < 27 ? lane : lane - 27;
-  const int dx = d / 9 - 1, dy = (d / 3) % 3 - 1, dz = d % 3 - 1;
-  const int ey = dy == 0 ? B : R, ez = dz == 0 ? B : R;
-  const int ext = (ey * ez) << 8 | ez;
-  const int pb = (lane < 54 ? pbase<B, R>(26 - d) : 0) -
-                 (((dx > 0 ? B - R : 0) * ey + (dy > 0 ? B - R : 0)) * ez + (dz > 0 ? B - R : 0));
   do {
     if (STRIDE && !a.tgt_active[t]) continue;
+    int lane = threadIdx.x;
+    if constexpr (STRIDE) asm volatile("" : "+v"(lane));   // (nothing of a lane kept over the loop)
+    // voxel of this lane, and the neighbours whose regions cover it: bit d = (dx + 1) 9
+    // + (dy + 1) 3 + dz + 1, the and of one mask per axis
+    const int vv[3] = {lane / (B * B), (lane / B) % B, lane % B};
+    const uint32_t cover =
+        ((vv[0] < R ? 0x1ffu : 0u) | 0x1ffu << 9 | (vv[0] >= B - R ? 0x1ffu << 18 : 0u)) &
+        ((vv[1] < R ? 0x7u * 0x40201u : 0u) | 0x38u * 0x40201u | (vv[1] >= B - R ? 0x1c0u * 0x40201u : 0u)) &
+        ((vv[2] < R ? 0x1249249u : 0u) | 0x2492492u | (vv[2] >= B - R ? 0x4924924u : 0u));
+    // neighbour d of lanes d and 27 + d: its piece's offset in its unit's region
+    // less where the voxels' coordinates start there, and the piece's extents y z, z
+    const int d = lane < 27 ? lane : lane - 27;
+    const int dx = d / 9 - 1, dy = (d / 3) % 3 - 1, dz = d % 3 - 1;
+    const int ey = dy == 0 ? B : R, ez = dz == 0 ? B : R;
+    const int pb = (lane < 54 ? pbase<B, R>(26 - d) : 0) -
+                   (((dx > 0 ? B - R : 0) * ey + (dy > 0 ? B - R : 0)) * ez + (dz > 0 ? B - R : 0));
+    const int pbe = pb * 65536 + ey * ez * 256 + ez;
+    // up to eight candidates per voxel (2R <= B): kept for every voxel
+    constexpr bool CAND = 2 * R <= B;
+    int pk[CAND ? MergeShape<B, R>::MAXC : 1];
+    if constexpr (CAND) {
+#pragma unroll
+      for (int k = 0; k < MergeShape<B, R>::MAXC; ++k) pk[k] = merge_candidate<B, R>(vv, k);
+    }
     const int32_t mslot = a.tgt_slot[t];
     int32_t bt[3];
     unlin3(a.tgt_elin[t], a.enb, bt);
@@ -980,9 +992,22 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_merge_list(SplatArgs a, int32_t n
           double sd = 0.0;
           // offset of this lane's voxel in the piece of neighbour n (uniform)
           auto offset = [&](int n) {
-            const int x = __builtin_amdgcn_readlane(ext, n), z = x & 255, yz = x >> 8;
-            return __builtin_amdgcn_readlane(pb, n) + vv[0] * yz + vv[1] * z + vv[2];
+            const int x = __builtin_amdgcn_readlane(pbe, n), z = x & 255, yz = (x >> 8) & 255;
+            return (x >> 16) + vv[0] * yz + vv[1] * z + vv[2];
           };
+          if constexpr (CAND) {
+            constexpr int MAXC = MergeShape<B, R>::MAXC;
+            const int32_t u0 = ec.y > 0 ? ec.x : -1;
+            float v[MAXC];
+#pragma unroll
+            for (int k = 0; k < MAXC; ++k) {
+              const int32_t w = __shfl(u0, base + (pk[k] >= 0 ? pk[k] >> 16 : 13));
+              v[k] = part_at<DR3, WIDE>(a.part, pk[k] >= 0 ? w : -1, pk[k] & 0xffff);
+            }
+#pragma unroll
+            for (int k = 0; k < MAXC; ++k) sd += (double)v[k];
+            first = 0;
+          }
           while (first) {
             float v[8];
 #pragma unroll
@@ -1282,8 +1307,7 @@ hipError_t launch_splat_br(const SplatArgs& a, int64_t n_units, int32_t n_target
                           (a.part_elems - SMKI_PART_HEAD) / DR3 < (int64_t(1) << 24);
       const dim3 grid((unsigned)tgt_grid(a, n_targets)), block(MergeShape<B, R>::NT);
       // a target of one wavefront (B = 4): by the list of the neighbours that are
-      // there; smaller blocks leave lanes idle, in larger ones the neighbours
-      // differ between a workgroup's wavefronts
+      // there; smaller blocks leave lanes idle, larger ones share their look-ups
 #define SMKI_MERGE(KERNEL)                                                                \
   if (a.tgt_grid > 0) {                                                                   \
     if (narrow)                                                                           \
