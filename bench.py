@@ -670,7 +670,7 @@ def kernel_table(st, p, copy_bw):
     }
     out = {}
     for k, b in alg.items():
-        us = dur.get(k)
+        us = dur.get(k) or dur.get(k + "_list")             # (k_merge_list: the merge at B = 4)
         if us:
             out[k] = {"algorithmic_bytes": b, "mean_us": us, "GBps": b / (us * 1e-6) / 1e9,
                       "frac_of_peak": b / (us * 1e-6) / HBM_PEAK,
