@@ -268,7 +268,7 @@ def test_small_stencils_around_unit_edges(lv, soft):
 def test_merge_of_small_blocks(lv, K, budget):
     # blocks of 4^3, reach 1 to 4: classes beyond one wavefront, slots of one unit,
     # of several and of more than 64, rows at the window's corners, a second insert
-    # on top of the first, and its replay
+    # on top of the first, its replay, and 64-bit offsets of partial sums
     from paper_1909_04631_amd import SemanticMap
     res = 0.2
     l = float(np.float32(lv) * np.float32(res))
@@ -279,8 +279,9 @@ def test_merge_of_small_blocks(lv, K, budget):
     lab = rng.integers(0, K, size=n).astype(np.int32)
     lab[: n // 2] = K - 1
     om = oracle.OracleMap(K, float(np.float32(res)), 4, l, 0.5, float(np.float32(1e-3)))
-    gm, rm = [SemanticMap(res, 4, l, 0.5, K, 1e-3, unit_budget=budget, initial_blocks=1 << 14)
-              for _ in range(2)]
+    gm, rm, wm, wr = [SemanticMap(res, 4, l, 0.5, K, 1e-3, unit_budget=budget,
+                                  initial_blocks=1 << 14, wide_offsets=w)
+                      for w in (False, False, True, True)]
     for step, rows in enumerate((slice(0, n), slice(0, n, 3))):
         print(f"[case] merge B=4 l/res={lv} K={K} budget={budget} insert {step}", flush=True)
         x, y = np.ascontiguousarray(xyz[rows]), np.ascontiguousarray(lab[rows])
@@ -290,14 +291,17 @@ def test_merge_of_small_blocks(lv, K, budget):
         q = cuda(ijk.astype(np.int32))
         a = gm.query(q)["alpha"].cpu().numpy()
         assert np.max(np.abs(a - a_ref) / a_ref) <= 1e-5
-        g = rm.batch_capture(cuda(x), cuda(y), [0, x.shape[0]], [(0.0, 0.0, 0.0)], 0.0)
-        rm.reset()      # (the capture inserts once)
-        if step == 1:
-            rm.insert_scan(cuda(xyz), cuda(lab), (0, 0, 0), 0.0)
-        g.replay([0, x.shape[0]], [(0.0, 0.0, 0.0)])
-        rm.sync()
-        ar = rm.query(q)["alpha"].cpu().numpy()
-        assert np.max(np.abs(ar - a_ref) / a_ref) <= 1e-5
-        g.close()
+        # 64-bit offsets of partial sums, and the replays, give the same bits
+        wm.insert_scan(cuda(x), cuda(y), (0, 0, 0), 0.0)
+        assert np.array_equal(wm.query(q)["alpha"].cpu().numpy(), a)
+        for m in (rm, wr):
+            g = m.batch_capture(cuda(x), cuda(y), [0, x.shape[0]], [(0.0, 0.0, 0.0)], 0.0)
+            m.reset()      # (the capture inserts once)
+            if step == 1:
+                m.insert_scan(cuda(xyz), cuda(lab), (0, 0, 0), 0.0)
+            g.replay([0, x.shape[0]], [(0.0, 0.0, 0.0)])
+            m.sync()
+            assert np.array_equal(m.query(q)["alpha"].cpu().numpy(), a)
+            g.close()
     if budget:
         assert gm.stats()["n_units"] > 1_500 // budget
