@@ -607,11 +607,11 @@ static hipError_t finish_set(PointSet& ps, KeyT* keys, uint32_t* idx, KeyT* akey
   const SortPayload pl{rec_unsorted, ps.pts, scr.wt, ps.wts};
   const SortPayload* plp = ((n > 1 || dn) && ps.pts) ? &pl : nullptr;
   if (sizeof(KeyT) == 4)
-    e = radix_sort_u32((uint32_t*)keys, idx, (uint32_t*)akeys, aidx, n, key_bits, scr.sort_tmp, st,
-                       plp, idx_iota, dn);
+    e = radix_sort_u32((uint32_t*)keys, idx, (uint32_t*)akeys, aidx, n, key_bits, scr.sort_tmp,
+                       scr.sort_tmp_bytes, st, plp, idx_iota, dn);
   else
-    e = radix_sort_u64((uint64_t*)keys, idx, (uint64_t*)akeys, aidx, n, key_bits, scr.sort_tmp, st,
-                       plp, idx_iota, dn);
+    e = radix_sort_u64((uint64_t*)keys, idx, (uint64_t*)akeys, aidx, n, key_bits, scr.sort_tmp,
+                       scr.sort_tmp_bytes, st, plp, idx_iota, dn);
   if (e != hipSuccess) return e;
   if (!plp && ps.pts)
     hipLaunchKernelGGL(k_permute_rec, dim3(nblk(n, 256)), dim3(256), 0, st, rec_unsorted,
@@ -937,7 +937,7 @@ hipError_t bucket_cells_sort(const float* xyz, int64_t n, const BucketGeom& g, B
     hipLaunchKernelGGL(k_row_keys<uint32_t>, dim3(nblk(n, 256)), dim3(256), 0, st, xyz,
                        (const int32_t*)nullptr, n, g, (uint32_t*)scr.keys, scr.idx, scr.rec, err);
     e = radix_sort_u32((uint32_t*)scr.keys, scr.idx, (uint32_t*)scr.akeys, scr.aidx, n, g.key_bits,
-                       scr.sort_tmp, st);
+                       scr.sort_tmp, scr.sort_tmp_bytes, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_cell_flags<uint32_t>, dim3(nblk(n, 256)), dim3(256), 0, st,
                        (const uint32_t*)scr.keys, n, scr.flag);
@@ -945,7 +945,7 @@ hipError_t bucket_cells_sort(const float* xyz, int64_t n, const BucketGeom& g, B
     hipLaunchKernelGGL(k_row_keys<uint64_t>, dim3(nblk(n, 256)), dim3(256), 0, st, xyz,
                        (const int32_t*)nullptr, n, g, (uint64_t*)scr.keys, scr.idx, scr.rec, err);
     e = radix_sort_u64((uint64_t*)scr.keys, scr.idx, (uint64_t*)scr.akeys, scr.aidx, n, g.key_bits,
-                       scr.sort_tmp, st);
+                       scr.sort_tmp, scr.sort_tmp_bytes, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_cell_flags<uint64_t>, dim3(nblk(n, 256)), dim3(256), 0, st,
                        (const uint64_t*)scr.keys, n, scr.flag);

@@ -8,23 +8,14 @@
 // digit agrees on every bit); its running digit counts live in its own LDS
 // row, so rounds need no barrier.  Integer work only: bit-exact and
 // run-to-run deterministic.
-#include "smki_internal.h"
+#include "smki_plan.h"
 
 namespace {
 
-constexpr int RS_THREADS = 256;
 constexpr int RS_WAVES = RS_THREADS / SMKI_WAVE;
-// Elements per thread: 16 (tiles of 4096) keep the tile counts, which every digit
-// scans, few; up to kSmallN elements 4 (tiles of 1024), since a tile's rounds run
-// one after the other and the larger tiles would leave most CUs idle: 26,000
-// elements 12 us a scatter with tiles of 4096, 8 with tiles of 1024 (their counts included).
-constexpr int kRounds = 16, kSmallRounds = 4;
-constexpr int64_t kSmallN = int64_t(1) << 18;
 // Up to this many tiles the scatter adds the earlier tiles' counts itself (64
 // counts a thread, about what the launch of their scan costs).
 constexpr int64_t kFewTiles = 64;
-constexpr int RS_MAXBITS = 9;                   // digits of up to 9 bits
-constexpr int RS_MAXBINS = 1 << RS_MAXBITS;
 
 template <typename K>
 __device__ __forceinline__ uint32_t digit_of(K key, int shift, uint32_t mask) {
@@ -384,20 +375,16 @@ void launch_pass(bool small, int64_t ntiles, A... args) {
     launch_pass_of<K, NB, kSmallRounds, false>(args...);
 }
 
-// Tiles of n elements (n: the capacity where the count is on the device).
-int64_t tiles_of(int64_t n) {
-  return ceil_div_i64(n, RS_THREADS * (n <= kSmallN ? kSmallRounds : kRounds));
-}
-
 template <typename K>
 hipError_t sort_impl(K* keys, uint32_t* vals, K* akeys, uint32_t* avals, int64_t n, int bits,
-                     void* tmp, hipStream_t st, const SortPayload* pl, bool vals_iota,
-                     const int64_t* dn) {
+                     void* tmp, size_t tmp_bytes, hipStream_t st, const SortPayload* pl,
+                     bool vals_iota, const int64_t* dn) {
   // with a device count the passes always run (the count is not known here);
   // without one, one element or none needs no pass
   if (n <= 0 || (!dn && n <= 1)) return hipSuccess;
   if (bits <= 0) bits = 1;
-  const int64_t ntiles = tiles_of(n);
+  if (radix_used_bytes(n) > tmp_bytes) return hipErrorInvalidValue;   // (a caller's mistake)
+  const int64_t ntiles = radix_tiles(n);
   const bool small = n <= kSmallN;
   uint32_t* hist = (uint32_t*)tmp;
   uint32_t* total = hist + RS_MAXBINS * ntiles;   // digit totals
@@ -434,19 +421,14 @@ hipError_t sort_impl(K* keys, uint32_t* vals, K* akeys, uint32_t* avals, int64_t
 
 }  // namespace
 
-size_t radix_tmp_bytes(int64_t n) {
-  const int64_t ntiles = tiles_of(n > 0 ? n : 1);
-  return sizeof(uint32_t) * RS_MAXBINS * (ntiles + 1) + 256;   // tile counts, digit totals
-}
-
 hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* ak, uint32_t* av, int64_t n,
-                          int bits, void* tmp, hipStream_t st, const SortPayload* pl,
-                          bool vals_iota, const int64_t* dn) {
-  return sort_impl<uint32_t>(keys, vals, ak, av, n, bits, tmp, st, pl, vals_iota, dn);
+                          int bits, void* tmp, size_t tmp_bytes, hipStream_t st,
+                          const SortPayload* pl, bool vals_iota, const int64_t* dn) {
+  return sort_impl<uint32_t>(keys, vals, ak, av, n, bits, tmp, tmp_bytes, st, pl, vals_iota, dn);
 }
 
 hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* ak, uint32_t* av, int64_t n,
-                          int bits, void* tmp, hipStream_t st, const SortPayload* pl,
-                          bool vals_iota, const int64_t* dn) {
-  return sort_impl<uint64_t>(keys, vals, ak, av, n, bits, tmp, st, pl, vals_iota, dn);
+                          int bits, void* tmp, size_t tmp_bytes, hipStream_t st,
+                          const SortPayload* pl, bool vals_iota, const int64_t* dn) {
+  return sort_impl<uint64_t>(keys, vals, ak, av, n, bits, tmp, tmp_bytes, st, pl, vals_iota, dn);
 }

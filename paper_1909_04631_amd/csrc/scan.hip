@@ -2,13 +2,9 @@
 // Deterministic: integer sums only.
 #include <algorithm>
 
-#include "smki_internal.h"
+#include "smki_plan.h"
 
 namespace {
-
-constexpr int SCAN_THREADS = 256;
-constexpr int SCAN_ITEMS = 8;
-constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T v) {
@@ -196,17 +192,6 @@ __global__ void __launch_bounds__(SCAN_THREADS) k_tile_scan_direct_pair(
 template <typename T>
 __global__ void k_zero_total(T* total) { *total = 0; }
 
-template <typename T>
-size_t tmp_elems(int64_t n) {
-  size_t e = 0;
-  int64_t m = n;
-  while (m > SCAN_TILE) {
-    m = ceil_div_i64(m, SCAN_TILE);
-    e += (size_t)m + 1;
-  }
-  return e + 1;
-}
-
 // dn (device, nullable): the element count, n then being the capacity
 template <typename T>
 hipError_t scan_impl(const T* in, T* out, int64_t n, T* total, T* tmp, hipStream_t st,
@@ -237,8 +222,6 @@ hipError_t scan_impl(const T* in, T* out, int64_t n, T* total, T* tmp, hipStream
   return hipGetLastError();
 }
 
-constexpr int64_t kPairTiles = 512;   // per array, for the two-launch pair scan
-
 template <typename TA, typename TB>
 hipError_t scan_pair_impl(const TA* ina, TA* outa, int64_t na, TA* tota, const TB* inb, TB* outb,
                           int64_t nb, TB* totb, void* tmp, hipStream_t st, const int32_t* dna,
@@ -260,10 +243,6 @@ hipError_t scan_pair_impl(const TA* ina, TA* outa, int64_t na, TA* tota, const T
 }
 
 }  // namespace
-
-size_t scan_tmp_bytes(int64_t n) {
-  return std::max<size_t>(tmp_elems<int64_t>(n), 2 * kPairTiles) * sizeof(int64_t) + 256;
-}
 
 hipError_t scan_excl_pair_i64_i32(const int64_t* ina, int64_t* outa, int64_t na, int64_t* tota,
                                   const int32_t* inb, int32_t* outb, int64_t nb, int32_t* totb,

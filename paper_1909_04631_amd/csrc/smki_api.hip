@@ -9,6 +9,7 @@
 
 #include "../../include/smki.h"
 #include "smki_gather.h"
+#include "smki_plan.h"
 
 
 int32_t smki_hip_error(hipError_t e) {
@@ -739,7 +740,8 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
   scr.rec = Bz.take<float4>(nt);
   scr.flag = Bz.take<int32_t>(nt);
   scr.slot_excl = Bz.take<int32_t>(nt);
-  scr.sort_tmp = Bz.take<char>(radix_tmp_bytes(nt));
+  scr.sort_tmp_bytes = radix_tmp_bytes(nt);
+  scr.sort_tmp = Bz.take<char>(scr.sort_tmp_bytes);
   scr.scan_tmp = Bz.take<char>(scan_tmp_bytes(std::max(nt, n_ext)));
   int32_t* d_si = Bz.take<int32_t>(8);   // counts; cleared with the target marks below
   int32_t* d_cfirst = Bz.take<int32_t>(m->K);   // first slot of each class (cleared too)
@@ -1115,6 +1117,7 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   scr.flag = d.flag;
   scr.slot_excl = d.slot_excl;
   scr.sort_tmp = d.sort_tmp;
+  scr.sort_tmp_bytes = radix_tmp_bytes(b->cap_rows);
   scr.scan_tmp = d.scan_tmp;
   SMKI_HIP_TRY(bucket_scan(b->xyz, b->label, nullptr, m->K, n, d.kept, d.kpos, n, d.off,
                            b->cap_rows, d.wgbeam, d.soff, d.org, b->S, b->step, m->free_class, g,
@@ -1439,12 +1442,13 @@ smki_status smki_export(smki_map* m, int64_t capacity, int64_t* n_blocks, int32_
   const int nbits = bits[0] + bits[1] + bits[2];
   if (nbits <= 32) {
     SMKI_HIP_TRY(launch_box_keys(m->dev.bkeys, n, m->box_lo, bits, (uint32_t*)k, o, m->stream));
-    SMKI_HIP_TRY(radix_sort_u32((uint32_t*)k, o, (uint32_t*)k2, o2, n, nbits, tmp, m->stream));
+    SMKI_HIP_TRY(radix_sort_u32((uint32_t*)k, o, (uint32_t*)k2, o2, n, nbits, tmp, radix_tmp_bytes(n),
+                                m->stream));
   } else {
     SMKI_HIP_TRY(hipMemcpyAsync(k, m->dev.bkeys, sizeof(uint64_t) * n, hipMemcpyDeviceToDevice,
                                 m->stream));
     SMKI_HIP_TRY(launch_iota_u32(o, n, m->stream));
-    SMKI_HIP_TRY(radix_sort_u64(k, o, k2, o2, n, 63, tmp, m->stream));
+    SMKI_HIP_TRY(radix_sort_u64(k, o, k2, o2, n, 63, tmp, radix_tmp_bytes(n), m->stream));
   }
   if (block_ijk) SMKI_HIP_TRY(launch_block_keys_to_ijk(m->dev.bkeys, o, n, block_ijk, m->stream));
   if (alpha) SMKI_HIP_TRY(launch_gather_blocks(m->dev, o, n, alpha, m->stream));
@@ -1758,7 +1762,8 @@ smki_status smki_bucket_cells(const float* xyz, int64_t n, float res, int32_t bl
   scr.rec = A.take<float4>(n);
   scr.flag = A.take<int32_t>(n);
   scr.slot_excl = A.take<int32_t>(n);
-  scr.sort_tmp = A.take<char>(radix_tmp_bytes(n));
+  scr.sort_tmp_bytes = radix_tmp_bytes(n);
+  scr.sort_tmp = A.take<char>(scr.sort_tmp_bytes);
   scr.scan_tmp = A.take<char>(scan_tmp_bytes(n));
   int32_t* d_nc = A.take<int32_t>(2);
   uint32_t* err2 = A.take<uint32_t>(1);

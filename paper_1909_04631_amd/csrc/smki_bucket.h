@@ -44,7 +44,8 @@ struct BucketScratch {
   float* wt;          // unsorted row weights, or nullptr (then PointSet::wts is not written)
   int32_t* flag;      // tile counts and slot-head bits (rows, and at least 64 entries)
   int32_t* slot_excl;
-  void* sort_tmp;
+  void* sort_tmp;     // radix_tmp_bytes(rows of the set)
+  size_t sort_tmp_bytes;
   void* scan_tmp;
 };
 

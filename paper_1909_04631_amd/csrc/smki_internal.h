@@ -33,8 +33,7 @@ enum : uint32_t {
 // scan / sort primitives (scan.hip, radix_sort.hip)
 // ---------------------------------------------------------------------------
 // exclusive prefix sum of n elements (in may equal out); *total (device,
-// nullable) receives the sum.  tmp must hold scan_tmp_bytes(n) bytes.
-size_t scan_tmp_bytes(int64_t n);
+// nullable) receives the sum.  tmp must hold scan_tmp_bytes(n) bytes (smki_plan.h).
 hipError_t scan_excl_i64(const int64_t* in, int64_t* out, int64_t n, int64_t* total, void* tmp,
                          hipStream_t st);
 hipError_t scan_excl_i32(const int32_t* in, int32_t* out, int64_t n, int32_t* total, void* tmp,
@@ -61,16 +60,17 @@ struct SortPayload {
   const float* w_in;
   float* w_out;
 };
-size_t radix_tmp_bytes(int64_t n);
+// tmp: scratch of tmp_bytes, at least radix_tmp_bytes(n) (smki_plan.h); less than the
+// sort writes is hipErrorInvalidValue.
 // vals_iota: vals holds nothing on entry; element i's value is i.
 // dn (device, nullable): the element count, read by the kernels; n is then a
 // capacity (buffers, tiles and launches are sized for n elements).
 hipError_t radix_sort_u32(uint32_t* keys, uint32_t* vals, uint32_t* alt_keys, uint32_t* alt_vals,
-                          int64_t n, int bits, void* tmp, hipStream_t st,
+                          int64_t n, int bits, void* tmp, size_t tmp_bytes, hipStream_t st,
                           const SortPayload* payload = nullptr, bool vals_iota = false,
                           const int64_t* dn = nullptr);
 hipError_t radix_sort_u64(uint64_t* keys, uint32_t* vals, uint64_t* alt_keys, uint32_t* alt_vals,
-                          int64_t n, int bits, void* tmp, hipStream_t st,
+                          int64_t n, int bits, void* tmp, size_t tmp_bytes, hipStream_t st,
                           const SortPayload* payload = nullptr, bool vals_iota = false,
                           const int64_t* dn = nullptr);
 

@@ -1,0 +1,52 @@
+// Sizes that scratch memory and launches are planned by (host).
+#pragma once
+#include <algorithm>
+
+#include "smki_internal.h"
+
+// ---- radix sort ----
+constexpr int RS_THREADS = 256;
+constexpr int RS_MAXBITS = 9;                   // digits of up to 9 bits
+constexpr int RS_MAXBINS = 1 << RS_MAXBITS;
+// Elements per thread: 16 (tiles of 4096) keep the tile counts, which every digit
+// scans, few; up to kSmallN elements 4 (tiles of 1024), since a tile's rounds run
+// one after the other and the larger tiles would leave most CUs idle: 26,000
+// elements 12 us a scatter with tiles of 4096, 8 with tiles of 1024 (their counts included).
+constexpr int kRounds = 16, kSmallRounds = 4;
+constexpr int64_t kSmallN = int64_t(1) << 18;
+
+// Tiles of n elements (n: the capacity where the count is on the device).
+static inline int64_t radix_tiles(int64_t n) {
+  return ceil_div_i64(n, RS_THREADS * (n <= kSmallN ? kSmallRounds : kRounds));
+}
+// What a sort of n elements writes of its scratch: the tile counts, the digit totals.
+static inline size_t radix_used_bytes(int64_t n) {
+  return sizeof(uint32_t) * RS_MAXBINS * (size_t)(radix_tiles(n) + 1);
+}
+// Scratch for a sort of any number of elements up to n.  2^18 elements make 256
+// tiles and 2^18 + 1 make 65, so the most is not always at n itself: a set of
+// capacity n is sorted with fewer elements where part of it is left out.
+static inline size_t radix_tmp_bytes(int64_t n) {
+  n = std::max<int64_t>(n, 1);
+  return std::max(radix_used_bytes(n), radix_used_bytes(std::min(n, kSmallN))) + 256;
+}
+
+// ---- prefix sums ----
+constexpr int SCAN_THREADS = 256;
+constexpr int SCAN_ITEMS = 8;
+constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
+constexpr int64_t kPairTiles = 512;   // per array, for the two-launch pair scan
+
+template <typename T>
+size_t scan_tmp_elems(int64_t n) {
+  size_t e = 0;
+  int64_t m = n;
+  while (m > SCAN_TILE) {
+    m = ceil_div_i64(m, SCAN_TILE);
+    e += (size_t)m + 1;
+  }
+  return e + 1;
+}
+static inline size_t scan_tmp_bytes(int64_t n) {
+  return std::max<size_t>(scan_tmp_elems<int64_t>(n), 2 * kPairTiles) * sizeof(int64_t) + 256;
+}
