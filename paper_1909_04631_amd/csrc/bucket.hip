@@ -12,6 +12,7 @@
 // own block; label bits).  A per-block prefix table of B^3 + 1 entries maps
 // any voxel range inside a block to a contiguous row range.
 #include "smki_bucket.h"
+#include "smki_plan.h"
 
 #pragma clang fp contract(off)
 
@@ -693,38 +694,41 @@ int64_t free_sample_workgroups(int64_t nf) { return nf > 0 ? ceil_div_i64(nf, 25
 // rows and queries of the differentiable form
 // ---------------------------------------------------------------------------
 // The cells within one cell of a query, as one bit per cell (64 cells a block):
-// eight threads per query, one for each of the at most 2 x 2 x 2 blocks.
+// eight threads per query, one for each of the at most 2 x 2 x 2 blocks (the grid
+// strides over the queries).
 __global__ void __launch_bounds__(256) k_mark_near(const float* __restrict__ qxyz, int64_t nq,
                                                    BucketGeom g,
                                                    unsigned long long* __restrict__ near) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t i = t >> 3;
-  if (i >= nq) return;
   const double inv_res = 1.0 / (double)g.res;
-  int32_t b[3];
-  uint32_t m[3];   // the cells [v - 1, v + 1] of each axis that lie in block b
+  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; (t >> 3) < nq;
+       t += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t i = t >> 3;
+    int32_t b[3];
+    uint32_t m[3];   // the cells [v - 1, v + 1] of each axis that lie in block b
+    bool own = true;   // (no second block along an axis: the first one's thread marks it)
 #pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    // (validated before: the voxel index is in range)
-    const int32_t v = (int32_t)floorf(quot_rn(qxyz[3 * i + a], inv_res, g.res));
-    const int32_t b0 = (v - 1) >> 2, b1 = (v + 1) >> 2;
-    const bool second = (t >> a) & 1;
-    if (second && b0 == b1) return;
-    b[a] = second ? b1 : b0;
-    const int32_t lo = max(v - 1 - b[a] * 4, 0), hi = min(v + 1 - b[a] * 4, 3);
-    m[a] = ((1u << (hi - lo + 1)) - 1u) << lo;
+    for (int a = 0; a < 3; ++a) {
+      // (validated before: the voxel index is in range)
+      const int32_t v = (int32_t)floorf(quot_rn(qxyz[3 * i + a], inv_res, g.res));
+      const int32_t b0 = (v - 1) >> 2, b1 = (v + 1) >> 2;
+      const bool second = (t >> a) & 1;
+      own = own && !(second && b0 == b1);
+      b[a] = second ? b1 : b0;
+      const int32_t lo = max(v - 1 - b[a] * 4, 0), hi = min(v + 1 - b[a] * 4, 3);
+      m[a] = ((1u << (hi - lo + 1)) - 1u) << lo;
+    }
+    if (!own || !in_grid(g, b)) continue;
+    unsigned long long m2 = 0, m3 = 0;   // bits of one x layer, of the block
+#pragma unroll
+    for (int y = 0; y < 4; ++y)
+      if ((m[1] >> y) & 1) m2 |= (unsigned long long)m[2] << (4 * y);
+#pragma unroll
+    for (int x = 0; x < 4; ++x)
+      if ((m[0] >> x) & 1) m3 |= m2 << (16 * x);
+    unsigned long long* w =
+        near + ((int64_t)(b[0] - g.blo[0]) * g.nb[1] + (b[1] - g.blo[1])) * g.nb[2] + (b[2] - g.blo[2]);
+    if ((*w & m3) != m3) atomicOr(w, m3);
   }
-  if (!in_grid(g, b)) return;
-  unsigned long long m2 = 0, m3 = 0;   // bits of one x layer, of the block
-#pragma unroll
-  for (int y = 0; y < 4; ++y)
-    if ((m[1] >> y) & 1) m2 |= (unsigned long long)m[2] << (4 * y);
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-    if ((m[0] >> x) & 1) m3 |= m2 << (16 * x);
-  unsigned long long* w =
-      near + ((int64_t)(b[0] - g.blo[0]) * g.nb[1] + (b[1] - g.blo[1])) * g.nb[2] + (b[2] - g.blo[2]);
-  if ((*w & m3) != m3) atomicOr(w, m3);
 }
 
 // The cell of a row: block, cell in the block and (with near) whether a query
@@ -862,7 +866,7 @@ hipError_t bucket_near(const float* txyz, const int32_t* tlab, int64_t nt, const
   ps.n = nt + n_sorted_q;
   if (ps.n <= 0) return hipSuccess;
   if (near && nt > 0)
-    hipLaunchKernelGGL(k_mark_near, dim3(nblk(8 * nq, 256)), dim3(256), 0, st, qxyz, nq, g, near);
+    hipLaunchKernelGGL(k_mark_near, dim3(near_mark_grid(nq)), dim3(256), 0, st, qxyz, nq, g, near);
   const int64_t tiles = ceil_div_i64(nt, NT);
   int32_t* tcount = scr.flag;
   int32_t* tstart = scr.flag + tiles;

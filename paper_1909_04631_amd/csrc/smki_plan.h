@@ -31,6 +31,14 @@ static inline size_t radix_tmp_bytes(int64_t n) {
   return std::max(radix_used_bytes(n), radix_used_bytes(std::min(n, kSmallN))) + 256;
 }
 
+// ---- marks of the cells near a query ----
+// Workgroups of 256 threads, eight threads a query; beyond 8,192 of them (four times
+// what the card runs at once) they stride: a launch has to stay below 2^32 threads,
+// which eight per query pass from 2^29 queries on.
+static inline unsigned near_mark_grid(int64_t nq) {
+  return (unsigned)std::min<int64_t>(ceil_div_i64(8 * nq, 256), 8192);
+}
+
 // ---- prefix sums ----
 constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 8;

@@ -54,6 +54,15 @@ int main() {
                 (long long)nt, (long long)nq, K, (long long)nb, used, body_bytes(nt, nq, K, nb));
         }
   printf("loss layout: %ld cases\n", cases);
+  // a launch stays below 2^32 threads for as many queries as a call accepts, and
+  // starts eight threads for each of few
+  for (int64_t nq = 1; nq <= INT32_MAX / 2; nq = nq * 2 - (nq > 1000 ? 1 : 0)) {
+    const int64_t threads = 256 * (int64_t)near_mark_grid(nq);
+    CHECK(threads < (int64_t(1) << 32), "%lld queries: %lld threads", (long long)nq, (long long)threads);
+    CHECK(threads >= std::min<int64_t>(8 * nq, 1 << 21), "%lld queries: %lld threads", (long long)nq,
+          (long long)threads);
+  }
+  printf("near marks\n");
   if (bad) return printf("%d wrong\n", bad), 1;
   printf("ok\n");
   return 0;

@@ -1,6 +1,7 @@
 """The differentiable form where the rows and the rows with the queries lie on
 different sides of 2^18, the size at which the sort's tiles change: the calls
-that sort the rows alone share their scratch with those that sort both."""
+that sort the rows alone share their scratch with those that sort both.  Above
+2^18 queries the marks of the cells around them are written in strides."""
 import numpy as np
 import pytest
 
@@ -13,7 +14,8 @@ L, S0, A0, K = np.float32(0.3), np.float32(0.5), np.float32(0.001), 4
 
 
 @pytest.mark.parametrize("own_ws", [False, True])
-@pytest.mark.parametrize("n,q", [(200_000, 70_000), (262_144, 1), (250_000, 25_000), (1_000, 262_144)])
+@pytest.mark.parametrize("n,q", [(200_000, 70_000), (262_144, 1), (250_000, 25_000), (1_000, 262_144),
+                                 (1_000, 262_177)])
 def test_rows_and_queries_around_the_tile_change(n, q, own_ws):
     # 300 rows within reach of the queries, the others in a box of about 8,000
     # blocks away from them: the oracle takes the 300
