@@ -158,8 +158,7 @@ struct Stencil {
 struct smki_map {
   float res, l, sigma0, alpha0;
   int32_t K, B, log2B, free_class;
-  int32_t budget;   // rows per splat work unit as asked for (0: chosen per insert, chunk_for)
-  int32_t chunk;    // rows per splat work unit of the last insert
+  int32_t budget;   // rows per splat work unit as asked for (0: chosen per insert, rows_per_unit)
   int32_t model;      // SMKI_MODEL_SBKI or SMKI_MODEL_SCSM
   int32_t selection;  // SMKI_SELECT_EXACT or SMKI_SELECT_FACE_BLOCKS
   int32_t flags;      // SMKI_FLAG_*
@@ -279,19 +278,6 @@ Stencil make_stencil(double lv, double margin, double res) {
 // 64 KiB for all of them.
 bool sbki_shape_ok(int32_t B, int32_t R) {
   return (B == 2 || B == 4 || B == 8 || B == 16) && R <= B && R <= SMKI_MAX_REACH;
-}
-
-// Rows per splat work unit of an insert of nt rows: as asked for at creation,
-// else so many that about 4,096 units (16 wavefronts on each of 256 CUs) share
-// the rows, in whole batches of 64, between 128 and SMKI_CHUNK.  One wavefront takes
-// a unit's rows one after the other (0.29 us each at reach 3), so a small scan
-// whose rows lie in few blocks lasts as long as its longest unit, while every
-// unit adds a region to write and merge.  2,000 hits with 28,000 free samples,
-// splat + merge: 512 rows a unit 150 + 15 us, 128 rows 47 + 25, 64 rows 30 + 41.
-int32_t chunk_for(const smki_map* m, int64_t nt) {
-  if (m->budget > 0) return m->budget;
-  const int64_t c = ceil_div_i64(ceil_div_i64(nt, 4096), SMKI_WAVE) * SMKI_WAVE;
-  return (int32_t)std::min<int64_t>(std::max<int64_t>(c, 2 * SMKI_WAVE), SMKI_CHUNK);
 }
 
 hipError_t sync_read(smki_map* m, const void* dev, size_t bytes, void* host) {
@@ -699,7 +685,7 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
 
   // ---- phase B: bucket all rows (class-major keys), mark target blocks ----
   const int64_t nt = nk + nf;
-  m->chunk = chunk_for(m, nt);
+  const int32_t chunk = rows_per_unit(m->budget, nt);
   const int64_t max_slots = std::min<int64_t>(nt, g.n_blocks * m->K);
   Sizer zb;
   zb.add<int32_t>(g.n_blocks * m->K);
@@ -768,7 +754,7 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
                            (uint32_t*)(d_si + 3), q));
   SMKI_HIP_TRY(launch_mark_targets(ps.slot_lin, ps.d_nslots, (int32_t)max_slots, g, eblo, enb, DB,
                                    d_mark, q));
-  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)max_slots, m->chunk, d_nun, q,
+  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)max_slots, chunk, d_nun, q,
                                  ps.slot_lin, g.n_blocks, d_cfirst));
   SMKI_HIP_TRY(scan_excl_pair_i32(d_mark, d_mpos, n_ext, d_ntgt, d_nun, d_ust, max_slots, d_nunits,
                                   scr.scan_tmp, q, ps.d_nslots));
@@ -828,7 +814,6 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
   sa.cls = m->d_cls;
   for (int i = 0; i < SMKI_POLY_N; ++i) sa.mcoef[i] = (float)(kSmkiQ[i] / kSmkiQ[0]);
   sa.K = m->K;
-  sa.chunk = m->chunk;
   // piece p = (dx+1)*9 + (dy+1)*3 + (dz+1): all 27, or those with at most one dx, dy, dz != 0
   sa.piece_mask = 0;
   for (int p = 0; p < 27; ++p) {
@@ -896,7 +881,7 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
   sa.contrib = d_contrib;
   // the splat first (its counters were cleared before the bucketing); what
   // only the later kernels read is prepared while it runs
-  SMKI_HIP_TRY(launch_unit_table(d_nun, d_ust, ps.head, ps.slot_lin, g.n_blocks, m->chunk, n_slots,
+  SMKI_HIP_TRY(launch_unit_table(d_nun, d_ust, ps.head, ps.slot_lin, g.n_blocks, chunk, n_slots,
                                  ps.d_nslots, d_nunits, d_units, d_uorder, q));
   SMKI_HIP_TRY(timing_begin(m, q));
   SMKI_HIP_TRY(launch_splat(sa, n_units, q));
@@ -979,7 +964,6 @@ struct smki_batch {
   int32_t eblo[3] = {0, 0, 0}, enb[3] = {0, 0, 0};
   int64_t n_ext = 0;
   Stencil sten;
-  int32_t chunk = 0;         // rows per work unit (the sizing insert's)
   int64_t cap_rows = 0, cap_slots = 0, cap_units = 0;
   int64_t tgt_grid = 0;      // targets that launches start workgroups for
   int64_t pool_cap = 0, cpool_cap = 0, hcap = 0;
@@ -1124,7 +1108,8 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
                            ps, scr, d.err, q, d.pc, (int32_t)b->cap_slots));
   SMKI_HIP_TRY(launch_mark_targets(ps.slot_lin, ps.d_nslots, (int32_t)b->cap_slots, g, b->eblo,
                                    b->enb, 1, d.mark, q));
-  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)b->cap_slots, b->chunk, d.nun, q));
+  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)b->cap_slots, m->budget, d.nun, q,
+                                 nullptr, 1, nullptr, d.pc));
   SMKI_HIP_TRY(scan_excl_pair_i32(d.mark, d.mpos, ne, d.si + 1, d.nun, d.ust, b->cap_slots,
                                   d.si + 2, d.scan_tmp, q, ps.d_nslots));
   SMKI_HIP_TRY(launch_batch_units(d.si, b->cap_slots, b->cap_units, d.err, q));
@@ -1140,7 +1125,6 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   sa.cls = m->d_cls;
   for (int i = 0; i < SMKI_POLY_N; ++i) sa.mcoef[i] = (float)(kSmkiQ[i] / kSmkiQ[0]);
   sa.K = m->K;
-  sa.chunk = b->chunk;
   sa.piece_mask = 0;
   for (int p = 0; p < 27; ++p) {
     const int nz = (p / 9 != 1) + ((p / 3) % 3 != 1) + (p % 3 != 1);
@@ -1178,9 +1162,9 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   sa.abort_word = d.err;
   sa.cap_units = (int32_t)b->cap_units;
   sa.tgt_grid = b->tgt_grid;
-  SMKI_HIP_TRY(launch_unit_table(d.nun, d.ust, d.head, d.slot_lin, g.n_blocks, b->chunk,
+  SMKI_HIP_TRY(launch_unit_table(d.nun, d.ust, d.head, d.slot_lin, g.n_blocks, m->budget,
                                  (int32_t)b->cap_slots, ps.d_nslots, d.si + 2, d.units, d.uorder,
-                                 q, (int32_t)b->cap_units));
+                                 q, (int32_t)b->cap_units, d.pc));
   SMKI_HIP_TRY(launch_splat(sa, b->cap_units, q));
   SMKI_HIP_TRY(launch_list_targets(d.mark, d.mpos, ne, d.tgt, d.ext2t, q));
   SMKI_HIP_TRY(launch_clear_targets(sa.dn_targets, (int32_t)ne, b->tgt_grid, m->K, d.cnt, d.active,
@@ -1282,7 +1266,6 @@ smki_status smki_create_map(float res, int32_t block_size, float l, float sigma0
   m->log2B = ilog2(block_size);
   m->free_class = free_class;
   m->budget = opt ? opt->unit_budget : 0;
-  m->chunk = SMKI_CHUNK;
   m->model = opt ? opt->model : SMKI_MODEL_SBKI;
   m->selection = opt ? opt->selection : SMKI_SELECT_EXACT;
   m->flags = opt ? opt->flags : 0;
@@ -1818,7 +1801,6 @@ smki_status smki_batch_capture(smki_map* m, const float* xyz, const int32_t* lab
   b->n = n;
   b->S = S;
   b->step = free_step;
-  b->chunk = m->chunk;
   const double grow = 1.0 + (double)margin;
   // 2. the window: the voxel box of that insert grown by margin of its extent per
   // side (at least two blocks), narrowed while that would widen the row keys
@@ -1859,6 +1841,11 @@ smki_status smki_batch_capture(smki_map* m, const float* xyz, const int32_t* lab
   b->cap_slots = std::min<int64_t>(std::min<int64_t>(b->cap_rows, g.n_blocks * m->K),
                                    (int64_t)ceil((double)st.n_point_blocks * grow) + 1024);
   b->cap_units = (int64_t)ceil((double)st.n_units * grow) + 1024;
+  const int64_t region = (int64_t)sizeof(float) * (m->B + 2 * b->sten.R) * (m->B + 2 * b->sten.R) *
+                         (m->B + 2 * b->sten.R);
+  // (fewer rows than the sizing insert's may be cut into shorter units)
+  if (m->budget <= 0 && (b->cap_units + kUnitSpread) * region <= (int64_t(64) << 30))
+    b->cap_units += kUnitSpread;
   // (a grid, not a capacity: the window may hold more targets, which the kernels
   // stride over; one workgroup per block of the window cost 0.4 ms of a 2 ms replay)
   b->tgt_grid = std::min<int64_t>(b->n_ext, (int64_t)ceil((double)st.n_target_blocks * grow) + 256);

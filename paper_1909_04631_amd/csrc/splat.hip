@@ -35,6 +35,7 @@
 // sigma0 times that coefficient.
 #include "smki_gather.h"
 #include "smki_pieces.h"
+#include "smki_plan.h"
 
 namespace {
 
@@ -98,7 +99,8 @@ __global__ void k_list_targets(const int32_t* __restrict__ mark, const int32_t* 
 __global__ void k_slot_units(const int32_t* __restrict__ head, const int32_t* __restrict__ d_nslots,
                              int32_t max_slots, int32_t chunk, int32_t* __restrict__ nunits,
                              const int32_t* __restrict__ slot_lin, int64_t n_blocks,
-                             int32_t* __restrict__ cfirst) {
+                             int32_t* __restrict__ cfirst, const int64_t* __restrict__ dn_rows) {
+  if (dn_rows) chunk = rows_per_unit(chunk, *dn_rows);
   const int32_t n = min(max_slots, *d_nslots);
   for (int32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
     nunits[s] = max(0, (head[s + 1] - head[s] + chunk - 1) / chunk);
@@ -119,12 +121,14 @@ __global__ void k_unit_table(const int32_t* __restrict__ nunits, const int32_t* 
                              int64_t n_blocks, int32_t chunk, int32_t max_slots,
                              const int32_t* __restrict__ d_nslots,
                              const int32_t* __restrict__ d_nunits, int4* __restrict__ units,
-                             int32_t* __restrict__ order, int32_t cap_units) {
+                             int32_t* __restrict__ order, int32_t cap_units,
+                             const int64_t* __restrict__ dn_rows) {
   // eight threads per slot, taking its units k = j, j + 8, ...; the grid
   // strides over the slots (a multiple of eight threads)
   // (a captured insert whose slots or units outgrow their tables stores no
   // unit; its abort word is set and the map is left unchanged)
   if (*d_nslots > max_slots || *d_nunits > cap_units || *d_nunits < 0) return;
+  if (dn_rows) chunk = rows_per_unit(chunk, *dn_rows);
   const int32_t ns = *d_nslots;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; (t >> 3) < ns; t += stride) {
@@ -1384,25 +1388,27 @@ hipError_t launch_list_targets(const int32_t* mark, const int32_t* mpos, int64_t
 
 hipError_t launch_slot_units(const int32_t* head, const int32_t* d_nslots, int32_t max_slots,
                              int32_t chunk, int32_t* nunits, hipStream_t st,
-                             const int32_t* slot_lin, int64_t n_blocks, int32_t* cfirst) {
+                             const int32_t* slot_lin, int64_t n_blocks, int32_t* cfirst,
+                             const int64_t* dn_rows) {
   if (max_slots <= 0) return hipSuccess;
-  if (chunk <= 0 || n_blocks <= 0 || (cfirst && !slot_lin)) return hipErrorInvalidValue;
+  if ((chunk <= 0 && !dn_rows) || n_blocks <= 0 || (cfirst && !slot_lin)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_slot_units, dim3(std::min<unsigned>(nblk(max_slots, 256), kSlotGrid)),
                      dim3(256), 0, st, head, d_nslots, max_slots, chunk, nunits, slot_lin,
-                     n_blocks, cfirst);
+                     n_blocks, cfirst, dn_rows);
   return hipGetLastError();
 }
 
 hipError_t launch_unit_table(const int32_t* nunits, const int32_t* ustart, const int32_t* head,
                              const int32_t* slot_lin, int64_t n_blocks, int32_t chunk,
                              int32_t max_slots, const int32_t* d_nslots, const int32_t* d_nunits,
-                             int4* units, int32_t* order, hipStream_t st, int32_t cap_units) {
+                             int4* units, int32_t* order, hipStream_t st, int32_t cap_units,
+                             const int64_t* dn_rows) {
   if (max_slots <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_unit_table,
                      dim3(std::min<unsigned>(nblk((int64_t)max_slots * 8, 256), 8 * kSlotGrid)),
                      dim3(256), 0, st,
                      nunits, ustart, head, slot_lin, n_blocks, chunk, max_slots, d_nslots, d_nunits,
-                     units, order, cap_units);
+                     units, order, cap_units, dn_rows);
   return hipGetLastError();
 }
 

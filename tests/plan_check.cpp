@@ -63,6 +63,19 @@ int main() {
           (long long)threads);
   }
   printf("near marks\n");
+  // rows per unit: whole batches of 64 between 128 and 512, more rows never shorter
+  // units, and never more than kUnitSpread units' worth of rows below 512 a unit
+  int32_t last = 0;
+  for (int64_t n = 1; n <= 3'000'000; n += n % 7 + 1) {
+    const int32_t c = rows_per_unit(0, n);
+    CHECK(c % SMKI_WAVE == 0 && c >= 128 && c <= SMKI_CHUNK && c >= last, "%lld rows: %d a unit",
+          (long long)n, c);
+    CHECK(c == SMKI_CHUNK || n <= kUnitSpread * c, "%lld rows: %d a unit", (long long)n, c);
+    last = c;
+  }
+  CHECK(last == SMKI_CHUNK && rows_per_unit(0, INT32_MAX) == SMKI_CHUNK && rows_per_unit(77, 5) == 77,
+        "rows per unit");
+  printf("unit sizes\n");
   if (bad) return printf("%d wrong\n", bad), 1;
   printf("ok\n");
   return 0;
