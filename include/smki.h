@@ -90,8 +90,10 @@ typedef struct smki_scan_stats {
   int64_t n_units;          /* splat work units launched */
   int64_t n_updated_voxels; /* voxels with at least one row within l */
   int64_t n_pairs;          /* (voxel, row) pairs with distance < l */
-  int64_t n_candidates;     /* (voxel, row) pairs examined: rows x stencil voxels */
-  int64_t n_lane_slots;     /* lane-iterations issued (stencil padded to 64-lane steps);
+  int64_t n_candidates;     /* (voxel, row) pairs examined: rows x stencil voxels (of a
+                               row's octant; up to l / res about 1.58, of its cell) */
+  int64_t n_lane_slots;     /* lane-iterations issued for them (64-lane steps over a row's
+                               stencil, or over up to 64 rows of a work unit);
                                n_candidates / n_lane_slots = lane utilisation */
   double splat_ms;          /* device time of the splat kernel (HIP events recorded on
                                the map's stream around its launch) */

@@ -280,6 +280,21 @@ bool sbki_shape_ok(int32_t B, int32_t R) {
   return (B == 2 || B == 4 || B == 8 || B == 16) && R <= B && R <= SMKI_MAX_REACH;
 }
 
+// Pairs that the splat of `rows` rows examines and the lane-iterations that it issues
+// for them.  Rows on the lanes: every offset around the cell, three at a time, for each
+// set of up to 64 rows (`batches` of them); else every row takes the offsets of its
+// octant, in steps of 64 lanes.
+void splat_work(const Stencil& s, int64_t rows, int64_t batches, smki_scan_stats* st) {
+  if (rows_on_lanes(s.R, s.full)) {
+    st->n_candidates = rows * s.full.n;
+    st->n_lane_slots = batches * SMKI_WAVE * (ceil_div_i64(s.full.n, 3) * 3);
+  } else {
+    const int64_t n = (int64_t)s.offs.size();
+    st->n_candidates = rows * n;
+    st->n_lane_slots = rows * SMKI_WAVE * ceil_div_i64(n, SMKI_WAVE);
+  }
+}
+
 hipError_t sync_read(smki_map* m, const void* dev, size_t bytes, void* host) {
   hipError_t e = hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, m->stream);
   if (e != hipSuccess) return e;
@@ -755,7 +770,8 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
   SMKI_HIP_TRY(launch_mark_targets(ps.slot_lin, ps.d_nslots, (int32_t)max_slots, g, eblo, enb, DB,
                                    d_mark, q));
   SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)max_slots, chunk, d_nun, q,
-                                 ps.slot_lin, g.n_blocks, d_cfirst));
+                                 ps.slot_lin, g.n_blocks, d_cfirst, nullptr,
+                                 csm ? nullptr : m->d_stats));
   SMKI_HIP_TRY(scan_excl_pair_i32(d_mark, d_mpos, n_ext, d_ntgt, d_nun, d_ust, max_slots, d_nunits,
                                   scr.scan_tmp, q, ps.d_nslots));
   // sync 2: slots, targets, work units, the bucketing's error word, each
@@ -771,8 +787,6 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
   m->last.n_target_blocks = n_t;
   m->last.n_units = n_units;
   if ((double)n_units * (double)DR3 * sizeof(float) > 64.0 * (1ull << 30)) return SMKI_E_CAPACITY;
-  m->last.n_candidates = nt * (int64_t)sten.offs.size();
-  m->last.n_lane_slots = nt * (int64_t)SMKI_WAVE * ((int64_t)(sten.offs.size() + SMKI_WAVE - 1) / SMKI_WAVE);
 
   // ---- phase C: splat, allocate, merge ----
   if (csm)
@@ -1109,7 +1123,7 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   SMKI_HIP_TRY(launch_mark_targets(ps.slot_lin, ps.d_nslots, (int32_t)b->cap_slots, g, b->eblo,
                                    b->enb, 1, d.mark, q));
   SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)b->cap_slots, m->budget, d.nun, q,
-                                 nullptr, 1, nullptr, d.pc));
+                                 nullptr, 1, nullptr, d.pc, d.stats));
   SMKI_HIP_TRY(scan_excl_pair_i32(d.mark, d.mpos, ne, d.si + 1, d.nun, d.ust, b->cap_slots,
                                   d.si + 2, d.scan_tmp, q, ps.d_nslots));
   SMKI_HIP_TRY(launch_batch_units(d.si, b->cap_slots, b->cap_units, d.err, q));
@@ -1533,9 +1547,7 @@ smki_status smki_last_scan_stats(smki_map* m, smki_scan_stats* out) {
     st.n_new_class_blocks = o[2];
     st.n_updated_voxels = o[0] ? 0 : (int64_t)s[0];
     st.n_pairs = (int64_t)s[1];
-    st.n_candidates = o[3] * (int64_t)b->sten.offs.size();
-    st.n_lane_slots =
-        o[3] * (int64_t)SMKI_WAVE * ((int64_t)(b->sten.offs.size() + SMKI_WAVE - 1) / SMKI_WAVE);
+    splat_work(b->sten, o[3], (int64_t)s[2], &st);
     m->last = st;
     m->stats_pending = false;
   }
@@ -1548,6 +1560,8 @@ smki_status smki_last_scan_stats(smki_map* m, smki_scan_stats* out) {
       for (int i = 0; i < 4; ++i) s[i] += c[k * 4 + i];
     m->last.n_updated_voxels = (int64_t)s[0];
     m->last.n_pairs = (int64_t)s[1];
+    if (m->model == SMKI_MODEL_SBKI)
+      splat_work(m->sten_cache, m->last.n_hits + m->last.n_free, (int64_t)s[2], &m->last);
     if (m->new_pending) {
       const int32_t* nc = (const int32_t*)(m->h_pin + kPinNew);
       m->last.n_new_blocks = nc[0];

@@ -56,6 +56,11 @@ __host__ __device__ static inline int32_t rows_per_unit(int32_t budget, int64_t 
   const int64_t c = ((rows + 4095) / 4096 + SMKI_WAVE - 1) / SMKI_WAVE * SMKI_WAVE;
   return (int32_t)(c < 2 * SMKI_WAVE ? 2 * SMKI_WAVE : c > SMKI_CHUNK ? SMKI_CHUNK : c);
 }
+// Sets of up to 64 rows that the units of `rows` rows, chunk a unit, are taken in.
+__host__ __device__ static inline int32_t rows_batches(int32_t rows, int32_t chunk) {
+  const int32_t full = rows / chunk, rest = rows - full * chunk;
+  return full * ((chunk + SMKI_WAVE - 1) / SMKI_WAVE) + (rest + SMKI_WAVE - 1) / SMKI_WAVE;
+}
 // Units that a set of fewer rows can have beyond those of more rows in the same slots:
 // shorter units share at most 4,096 times their rows.
 constexpr int64_t kUnitSpread = 4096;

@@ -95,20 +95,30 @@ __global__ void k_list_targets(const int32_t* __restrict__ mark, const int32_t* 
 
 // chunks of every (class, block) slot (entries past the slot count are not
 // written); cfirst (nullable): 1 + the first slot of each class with slots
-// (slots are in class-major order)
+// (slots are in class-major order); stats (nullable): the sets of 64 rows that the
+// units take (insert counter 2)
 __global__ void k_slot_units(const int32_t* __restrict__ head, const int32_t* __restrict__ d_nslots,
                              int32_t max_slots, int32_t chunk, int32_t* __restrict__ nunits,
                              const int32_t* __restrict__ slot_lin, int64_t n_blocks,
-                             int32_t* __restrict__ cfirst, const int64_t* __restrict__ dn_rows) {
+                             int32_t* __restrict__ cfirst, const int64_t* __restrict__ dn_rows,
+                             unsigned long long* __restrict__ stats) {
   if (dn_rows) chunk = rows_per_unit(chunk, *dn_rows);
   const int32_t n = min(max_slots, *d_nslots);
+  int32_t batches = 0;   // (sets of up to 64 rows, at most the rows)
   for (int32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
-    nunits[s] = max(0, (head[s + 1] - head[s] + chunk - 1) / chunk);
+    const int32_t rows = max(0, head[s + 1] - head[s]);
+    nunits[s] = (rows + chunk - 1) / chunk;
+    batches += rows_batches(rows, chunk);
     if (cfirst) {
       const int32_t nb = (int32_t)n_blocks, c = slot_lin[s] / nb;
       if (s == 0 || slot_lin[s - 1] / nb != c) cfirst[c] = s + 1;
     }
   }
+  if (!stats) return;
+#pragma unroll
+  for (int o = SMKI_WAVE / 2; o > 0; o >>= 1) batches += __shfl_xor(batches, o, SMKI_WAVE);
+  if ((threadIdx.x & (SMKI_WAVE - 1)) == 0 && batches)
+    atomicAdd(&stats[(blockIdx.x % SMKI_STAT_COPIES) * 4 + 2], (unsigned long long)batches);
 }
 
 // Work units of every slot: (first row, end row, slot, class), chunk rows each.
@@ -1292,7 +1302,7 @@ hipError_t launch_splat_br(const SplatArgs& a, int64_t n_units, int32_t n_target
   if (!merge) {
     if constexpr (R <= 2) {
       // at most kFullMax voxels around a cell: lanes over rows
-      if (n_units > 0 && a.full_stencil->n <= kFullMax) {
+      if (n_units > 0 && rows_on_lanes(R, *a.full_stencil)) {
         const dim3 grid((unsigned)n_units), block(SMKI_WAVE);
         if (a.wts)
           hipLaunchKernelGGL((k_splat_small<B, R, true>), grid, block, 0, st, a, *a.full_stencil);
@@ -1389,12 +1399,12 @@ hipError_t launch_list_targets(const int32_t* mark, const int32_t* mpos, int64_t
 hipError_t launch_slot_units(const int32_t* head, const int32_t* d_nslots, int32_t max_slots,
                              int32_t chunk, int32_t* nunits, hipStream_t st,
                              const int32_t* slot_lin, int64_t n_blocks, int32_t* cfirst,
-                             const int64_t* dn_rows) {
+                             const int64_t* dn_rows, unsigned long long* stats) {
   if (max_slots <= 0) return hipSuccess;
   if ((chunk <= 0 && !dn_rows) || n_blocks <= 0 || (cfirst && !slot_lin)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_slot_units, dim3(std::min<unsigned>(nblk(max_slots, 256), kSlotGrid)),
                      dim3(256), 0, st, head, d_nslots, max_slots, chunk, nunits, slot_lin,
-                     n_blocks, cfirst, dn_rows);
+                     n_blocks, cfirst, dn_rows, stats);
   return hipGetLastError();
 }
 
