@@ -93,7 +93,8 @@ typedef struct smki_scan_stats {
   int64_t n_candidates;     /* (voxel, row) pairs examined: rows x stencil voxels (of a
                                row's octant; up to l / res about 1.58, of its cell) */
   int64_t n_lane_slots;     /* lane-iterations issued for them (64-lane steps over a row's
-                               stencil, or over up to 64 rows of a work unit);
+                               stencil or, up to l / res about 1.58, over up to 64 rows of
+                               a work unit of more than 16);
                                n_candidates / n_lane_slots = lane utilisation */
   double splat_ms;          /* device time of the splat kernel (HIP events recorded on
                                the map's stream around its launch) */

@@ -281,13 +281,12 @@ bool sbki_shape_ok(int32_t B, int32_t R) {
 }
 
 // Pairs that the splat of `rows` rows examines and the lane-iterations that it issues
-// for them.  Rows on the lanes: every offset around the cell, three at a time, for each
-// set of up to 64 rows (`batches` of them); else every row takes the offsets of its
-// octant, in steps of 64 lanes.
-void splat_work(const Stencil& s, int64_t rows, int64_t batches, smki_scan_stats* st) {
+// for them.  Small stencils: every offset around the cell, in the 64-lane steps counted
+// on the device; else every row takes the offsets of its octant in steps of 64 lanes.
+void splat_work(const Stencil& s, int64_t rows, int64_t steps, smki_scan_stats* st) {
   if (rows_on_lanes(s.R, s.full)) {
     st->n_candidates = rows * s.full.n;
-    st->n_lane_slots = batches * SMKI_WAVE * (ceil_div_i64(s.full.n, 3) * 3);
+    st->n_lane_slots = steps * SMKI_WAVE;
   } else {
     const int64_t n = (int64_t)s.offs.size();
     st->n_candidates = rows * n;
@@ -771,7 +770,8 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
                                    d_mark, q));
   SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)max_slots, chunk, d_nun, q,
                                  ps.slot_lin, g.n_blocks, d_cfirst, nullptr,
-                                 csm ? nullptr : m->d_stats));
+                                 rows_on_lanes(sten.R, sten.full) && !csm ? m->d_stats : nullptr,
+                                 steps_per_set(sten.full)));
   SMKI_HIP_TRY(scan_excl_pair_i32(d_mark, d_mpos, n_ext, d_ntgt, d_nun, d_ust, max_slots, d_nunits,
                                   scr.scan_tmp, q, ps.d_nslots));
   // sync 2: slots, targets, work units, the bucketing's error word, each
@@ -1123,7 +1123,9 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   SMKI_HIP_TRY(launch_mark_targets(ps.slot_lin, ps.d_nslots, (int32_t)b->cap_slots, g, b->eblo,
                                    b->enb, 1, d.mark, q));
   SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)b->cap_slots, m->budget, d.nun, q,
-                                 nullptr, 1, nullptr, d.pc, d.stats));
+                                 nullptr, 1, nullptr, d.pc,
+                                 rows_on_lanes(b->sten.R, b->sten.full) ? d.stats : nullptr,
+                                 steps_per_set(b->sten.full)));
   SMKI_HIP_TRY(scan_excl_pair_i32(d.mark, d.mpos, ne, d.si + 1, d.nun, d.ust, b->cap_slots,
                                   d.si + 2, d.scan_tmp, q, ps.d_nslots));
   SMKI_HIP_TRY(launch_batch_units(d.si, b->cap_slots, b->cap_units, d.err, q));

@@ -51,9 +51,10 @@ struct FullStencil {
   int8_t d[kFullMax][4];
 };
 
-// Whether a splat of reach R takes its rows on the lanes (k_splat_small): small
-// stencils, at most kFullMax voxels around a cell (l / res up to 1.58).
+// Whether a splat of reach R is k_splat_small's (lanes over rows): small stencils, at most kFullMax voxels around a cell (l / res up to 1.58).
 static inline bool rows_on_lanes(int32_t R, const FullStencil& f) { return R <= 2 && f.n <= kFullMax; }
+// Steps for a set of up to 64 rows there: the offsets, three at a time.
+static inline int32_t steps_per_set(const FullStencil& f) { return (f.n + 2) / 3 * 3; }
 
 struct SplatArgs {
   BucketGeom g;               // point grid (planes = classes)
@@ -99,7 +100,7 @@ struct SplatArgs {
   int64_t n_cold;             // class blocks in use before this insert (newer ones are fresh)
   float alpha0;               // prior concentration written to fresh class blocks
   unsigned long long* stats;  // [SMKI_STAT_COPIES][4]: [0] updated voxels, [1] in-support pairs,
-                              // [2] sets of up to 64 rows that the units take;
+                              // [2] 64-lane steps of a small stencil's splat;
                               // workgroup b adds to copy b % SMKI_STAT_COPIES
   // Device-resident counts (captured inserts, whose launches are sized for
   // capacities); all null for an insert sized on the host.
@@ -120,12 +121,12 @@ hipError_t launch_list_targets(const int32_t* mark, const int32_t* mpos, int64_t
 // rows per unit: chunk, or with dn_rows (device, a captured insert's row count)
 // rows_per_unit(chunk, *dn_rows), chunk then being the map's budget
 // cfirst (nullable, [K], zeroed): 1 + the first slot of each class that has one
-// stats (nullable, SplatArgs::stats): counter 2, the sets of 64 rows of all units
+// stats (nullable, SplatArgs::stats): counter 2, the units' steps (lane_steps)
 hipError_t launch_slot_units(const int32_t* head, const int32_t* d_nslots, int32_t max_slots,
                              int32_t chunk, int32_t* nunits, hipStream_t st,
                              const int32_t* slot_lin = nullptr, int64_t n_blocks = 1,
                              int32_t* cfirst = nullptr, const int64_t* dn_rows = nullptr,
-                             unsigned long long* stats = nullptr);
+                             unsigned long long* stats = nullptr, int32_t per_set = 0);
 // units of every slot, and (order, nullable) the splat's launch order
 hipError_t launch_unit_table(const int32_t* nunits, const int32_t* ustart, const int32_t* head,
                              const int32_t* slot_lin, int64_t n_blocks, int32_t chunk,

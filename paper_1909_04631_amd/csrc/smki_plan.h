@@ -56,10 +56,18 @@ __host__ __device__ static inline int32_t rows_per_unit(int32_t budget, int64_t 
   const int64_t c = ((rows + 4095) / 4096 + SMKI_WAVE - 1) / SMKI_WAVE * SMKI_WAVE;
   return (int32_t)(c < 2 * SMKI_WAVE ? 2 * SMKI_WAVE : c > SMKI_CHUNK ? SMKI_CHUNK : c);
 }
-// Sets of up to 64 rows that the units of `rows` rows, chunk a unit, are taken in.
-__host__ __device__ static inline int32_t rows_batches(int32_t rows, int32_t chunk) {
+// Units of at most this many rows are splatted row by row where stencils are small.
+// 2e5 rows at l / res = 1.5, splat in us row by row and with lanes as rows: units of 8
+// rows on average 42 and 51, of 16 rows 32 and 36 (up to 24 rows the same).
+constexpr int kFewRows = 16;
+// 64-lane steps that a small stencil's splat issues for `rows` rows in units of chunk:
+// one a row in a unit of few rows, else per_set for each set of up to 64 rows.
+__host__ __device__ static inline int64_t lane_steps(int32_t rows, int32_t chunk, int32_t per_set) {
   const int32_t full = rows / chunk, rest = rows - full * chunk;
-  return full * ((chunk + SMKI_WAVE - 1) / SMKI_WAVE) + (rest + SMKI_WAVE - 1) / SMKI_WAVE;
+  auto unit = [&](int32_t r) {
+    return r <= kFewRows ? (int64_t)r : (int64_t)((r + SMKI_WAVE - 1) / SMKI_WAVE) * per_set;
+  };
+  return full * unit(chunk) + unit(rest);
 }
 // Units that a set of fewer rows can have beyond those of more rows in the same slots:
 // shorter units share at most 4,096 times their rows.

@@ -95,20 +95,20 @@ __global__ void k_list_targets(const int32_t* __restrict__ mark, const int32_t* 
 
 // chunks of every (class, block) slot (entries past the slot count are not
 // written); cfirst (nullable): 1 + the first slot of each class with slots
-// (slots are in class-major order); stats (nullable): the sets of 64 rows that the
-// units take (insert counter 2)
+// (slots are in class-major order); stats (nullable): the 64-lane steps of the units
+// (insert counter 2, lane_steps)
 __global__ void k_slot_units(const int32_t* __restrict__ head, const int32_t* __restrict__ d_nslots,
                              int32_t max_slots, int32_t chunk, int32_t* __restrict__ nunits,
                              const int32_t* __restrict__ slot_lin, int64_t n_blocks,
                              int32_t* __restrict__ cfirst, const int64_t* __restrict__ dn_rows,
-                             unsigned long long* __restrict__ stats) {
+                             unsigned long long* __restrict__ stats, int32_t per_set) {
   if (dn_rows) chunk = rows_per_unit(chunk, *dn_rows);
   const int32_t n = min(max_slots, *d_nslots);
-  int32_t batches = 0;   // (sets of up to 64 rows, at most the rows)
+  int64_t steps = 0;
   for (int32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
     const int32_t rows = max(0, head[s + 1] - head[s]);
     nunits[s] = (rows + chunk - 1) / chunk;
-    batches += rows_batches(rows, chunk);
+    if (stats) steps += lane_steps(rows, chunk, per_set);
     if (cfirst) {
       const int32_t nb = (int32_t)n_blocks, c = slot_lin[s] / nb;
       if (s == 0 || slot_lin[s - 1] / nb != c) cfirst[c] = s + 1;
@@ -116,9 +116,9 @@ __global__ void k_slot_units(const int32_t* __restrict__ head, const int32_t* __
   }
   if (!stats) return;
 #pragma unroll
-  for (int o = SMKI_WAVE / 2; o > 0; o >>= 1) batches += __shfl_xor(batches, o, SMKI_WAVE);
-  if ((threadIdx.x & (SMKI_WAVE - 1)) == 0 && batches)
-    atomicAdd(&stats[(blockIdx.x % SMKI_STAT_COPIES) * 4 + 2], (unsigned long long)batches);
+  for (int o = SMKI_WAVE / 2; o > 0; o >>= 1) steps += __shfl_xor(steps, o, SMKI_WAVE);
+  if ((threadIdx.x & (SMKI_WAVE - 1)) == 0 && steps)
+    atomicAdd(&stats[(blockIdx.x % SMKI_STAT_COPIES) * 4 + 2], (unsigned long long)steps);
 }
 
 // Work units of every slot: (first row, end row, slot, class), chunk rows each.
@@ -490,22 +490,30 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat(SplatArgs a) {
 }
 
 // Splat for small stencils (at most 33 voxels around a cell: l / res up to 1.58),
-// where a row meets about 14 voxels and the row-by-row form leaves most lanes of
-// a step idle and pays its row handling (octant order, broadcasts, group
-// changes) for one step.  Here lanes are rows: 64 rows evaluate one voxel offset of the full
-// stencil at a time, its coefficients in scalar registers, into an LDS table
-// [row][offset] (an odd pitch: the rows' writes fall in different banks); then
-// lanes are offsets: rows of one cell are consecutive, and each lane adds its
-// column of every run of rows and adds the sum to its voxel of the region.  Every
-// lane owns distinct region addresses and the LDS runs a wavefront's accesses in
-// order, so the sum order is fixed: by run, rows in sorted order.  The town's
-// 1.7e8 rows: 6.3 ms two rows a step, now 4.7.
+// where a row meets about 14 voxels and the row-by-row form of k_splat leaves most
+// lanes of a step idle and pays its row handling (octant order, broadcasts, group
+// changes) for one step.  Here lanes are rows: 64 rows evaluate one voxel offset of the
+// full stencil at a time, its coefficients in scalar registers, into registers; then
+// QR rows at a time pass through an LDS table [row][offset] (an odd pitch: the rows'
+// writes fall in different banks) and lanes are offsets: rows of one cell are
+// consecutive, and each lane adds its column of every run of rows and adds the sum to
+// its voxel of the region.  Every lane owns distinct region addresses and the LDS runs
+// a wavefront's accesses in order, so the sum order is fixed: by run, rows in sorted
+// order.  A unit of few rows waits for its records and for the stores of its region
+// (about 7 us whatever the form), so what counts is how many run at once: a table of
+// all 64 rows took 11 KB a wavefront (14 a CU), one of 16 rows 4.7 KB (28, by the
+// registers).  Splat at l / res = 1.5, k_splat with two rows a step, this kernel with 64
+// rows in the table, and now: the town's 1.7e8 rows 6.3, 4.5 and 4.0 ms; 2e5 rows in
+// 1.3e5 units 121, 247 and 130 us (region stores; the whole call 484, 568 and 428), in
+// 2.7e4 units 41, 67 and 42.  32 rows in the table: 4.1 ms and 188 us, without the
+// form for few rows (16 without it: 4.2 and 170).
 template <int B, int R, bool W>
 __global__ void __launch_bounds__(SMKI_WAVE) k_splat_small(SplatArgs a, FullStencil fs) {
   constexpr int DR = B + 2 * R, DR3 = DR * DR * DR, NACC4 = (DR3 + 3) / 4;
   constexpr int FP = kFullMax;   // pitch of the table (odd)
   __shared__ float4 acc4[NACC4 + SMKI_WAVE / 4];
-  __shared__ float F[SMKI_WAVE * FP + SMKI_WAVE];   // (lanes past the stencil read past a row)
+  constexpr int QR = 16;         // rows in the table at once
+  __shared__ float F[QR * FP + SMKI_WAVE];   // (lanes past the stencil read past a row)
   float* acc = (float*)acc4;
   const int lane = threadIdx.x;
   if (blockIdx.x == 0 && lane < SMKI_PART_HEAD) a.part[lane] = 0.0f;
@@ -545,6 +553,21 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat_small(SplatArgs a, FullSten
     b.w = W ? a.wts[v] : 1.0f;
     return b;
   };
+  // region index of a row's cell
+  auto cell_base = [&](int32_t key) {
+    const uint32_t cell = (uint32_t)key >> 3;
+    return (int32_t)(((cell / (B * B) + R) * DR + ((cell / B) % B + R)) * DR + (cell % B + R));
+  };
+  // kernel value at squared distance d2, times the row's weight
+  auto weight = [&](float d2, float wr) {
+    const float d = __builtin_amdgcn_sqrtf(fabsf(d2));
+    const float sv = __builtin_amdgcn_fmed3f(fmaf(-d, inv_l, 1.0f), 0.0f, 1.0f);
+    const float uu = sv * sv;
+    float qq = fmaf(uu, cq[0], cq[1]);
+#pragma unroll
+    for (int q = 2; q < SMKI_POLY_N; ++q) qq = fmaf(qq, uu, cq[q]);
+    return W ? (uu * uu) * ((sv * wr) * qq) : (uu * uu) * (sv * qq);
+  };
   auto process = [&](const Batch& bt, int32_t base) {
     const int nb = min(SMKI_WAVE, r1 - base);
     const bool valid = lane < nb;
@@ -554,67 +577,96 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat_small(SplatArgs a, FullSten
     const float x = (key & 1) ? -bt.r.x : bt.r.x, y = (key & 2) ? -bt.r.y : bt.r.y,
                 z = (key & 4) ? -bt.r.z : bt.r.z;
     const float q2 = valid ? fmaf(x, x, fmaf(y, y, z * z)) : 1.0e30f;
-    const uint32_t cell = (uint32_t)key >> 3;
-    const int32_t cb =
-        (int32_t)(((cell / (B * B) + R) * DR + ((cell / B) % B + R)) * DR + (cell % B + R));
-    float* Fr = F + lane * FP;
-    // three offsets at a time (the list is padded with offsets out of every
-    // support), the next three's coefficients loaded while these are used
-    float4 w0 = fs.w[0], w1 = fs.w[1], w2 = fs.w[2];
-    for (int k = 0; k < n; k += 3) {
-      const float4 c[3] = {w0, w1, w2};
-      w0 = fs.w[k + 3];
-      w1 = fs.w[k + 4];
-      w2 = fs.w[k + 5];
-      float d2[3], v[3] = {0.0f, 0.0f, 0.0f};
+    const int32_t cb = cell_base(key);
+    // every offset, three at a time (the list is padded with offsets out of every
+    // support): this lane's row of the table, in registers
+    float v[FP];
+#pragma unroll
+    for (int k = 0; k < FP; k += 3) {
+      if (k >= n) break;   // (uniform)
+      float d2[3];
       uint64_t any = 0;
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
-        const float4 w = c[i];   // (uniform: scalar registers)
+        const float4 w = fs.w[k + i];   // (uniform: scalar registers)
         d2[i] = fmaf(z, w.z, fmaf(y, w.y, fmaf(x, w.x, q2 + w.w)));
         const uint64_t in = __ballot(d2[i] < l2);
         npair += (uint32_t)__popcll(in);
         any |= in;
+        v[k + i] = 0.0f;
       }
       if (any) {   // (the offsets are sorted by distance: the last ones are often out of reach)
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-          const float d = __builtin_amdgcn_sqrtf(fabsf(d2[i]));
-          const float sv = __builtin_amdgcn_fmed3f(fmaf(-d, inv_l, 1.0f), 0.0f, 1.0f);
-          const float uu = sv * sv;
-          float qq = fmaf(uu, cq[0], cq[1]);
-#pragma unroll
-          for (int q = 2; q < SMKI_POLY_N; ++q) qq = fmaf(qq, uu, cq[q]);
-          v[i] = W ? (uu * uu) * ((sv * bt.w) * qq) : (uu * uu) * (sv * qq);
-        }
+        for (int i = 0; i < 3; ++i) v[k + i] = weight(d2[i], bt.w);
       }
-#pragma unroll
-      for (int i = 0; i < 3; ++i) Fr[k + i] = v[i];
     }
-    // runs of rows of one cell: bit j set where row j ends one.  Eight rows'
-    // columns are read together.
+    // runs of rows of one cell: bit j set where row j ends one
     const int32_t after = __shfl_down(cb, 1, SMKI_WAVE);
     const uint64_t ends = __ballot(valid && (lane == nb - 1 || after != cb));
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (one wavefront: the LDS keeps the order)
     const float* col = F + lane;
     float sum = 0.0f;
-    for (int j0 = 0; j0 < nb; j0 += 8) {
-      float f[8];
+    for (int h = 0; h < nb; h += QR) {
+      // the rows of QR lanes through the table (one wavefront: the LDS keeps the order)
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      if (lane / QR == h / QR) {
+        float* Fr = F + (lane % QR) * FP;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) f[i] = col[(j0 + i) * FP];
-      const uint32_t e8 = (uint32_t)(ends >> j0) & 0xffu;
+        for (int k = 0; k < FP; k += 3) {
+          if (k >= n) break;   // (uniform)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        sum += f[i];
-        if ((e8 >> i) & 1u) {   // (uniform)
-          const int32_t at = mine ? __builtin_amdgcn_readlane(cb, j0 + i) + wl : wl;
-          acc[at] += sum;
-          __atomic_signal_fence(__ATOMIC_SEQ_CST);
-          sum = 0.0f;
+          for (int i = 0; i < 3; ++i) Fr[k + i] = v[k + i];
+        }
+      }
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      // eight rows' columns are read together
+      for (int j0 = h; j0 < min(nb, h + QR); j0 += 8) {
+        float f[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) f[i] = col[(j0 - h + i) * FP];
+        const uint32_t e8 = (uint32_t)(ends >> j0) & 0xffu;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          sum += f[i];
+          if ((e8 >> i) & 1u) {   // (uniform)
+            const int32_t at = mine ? __builtin_amdgcn_readlane(cb, j0 + i) + wl : wl;
+            acc[at] += sum;
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            sum = 0.0f;
+          }
         }
       }
     }
   };
+  // A unit of few rows: row by row, lanes are offsets, the same products and sums.
+  if (r1 - r0 <= kFewRows) {
+    const float4 w = fs.w[ol];
+    const Batch b = load_batch(load_index(r0));
+    const int nb = r1 - r0;
+    const int32_t key = __float_as_int(b.r.w);
+    const float x = (key & 1) ? -b.r.x : b.r.x, y = (key & 2) ? -b.r.y : b.r.y,
+                z = (key & 4) ? -b.r.z : b.r.z;
+    const float q2 = fmaf(x, x, fmaf(y, y, z * z));
+    const int32_t cb = cell_base(key);
+    auto lane_f = [](float v, int j) {
+      return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), j));
+    };
+    float sum = 0.0f;
+    for (int j = 0; j < nb; ++j) {
+      const float d2 = fmaf(lane_f(z, j), w.z, fmaf(lane_f(y, j), w.y, fmaf(lane_f(x, j), w.x, lane_f(q2, j) + w.w)));
+      npair += (uint32_t)__popcll(__ballot(mine && d2 < l2));
+      const float v = weight(d2, W ? lane_f(b.w, j) : 1.0f);
+      sum += v;
+      const int32_t cj = __builtin_amdgcn_readlane(cb, j);
+      if (j + 1 == nb || __builtin_amdgcn_readlane(cb, j + 1) != cj) {   // (uniform)
+        acc[mine ? cj + wl : wl] += sum;
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        sum = 0.0f;
+      }
+    }
+    __syncthreads();
+    write_region<B, R>(a, acc, uid, lane, npair);
+    return;
+  }
   Batch ba = load_batch(load_index(r0));
   int32_t vb = load_index(r0 + SMKI_WAVE);
   for (int32_t base = r0; base < r1; base += 2 * SMKI_WAVE) {
@@ -1399,12 +1451,12 @@ hipError_t launch_list_targets(const int32_t* mark, const int32_t* mpos, int64_t
 hipError_t launch_slot_units(const int32_t* head, const int32_t* d_nslots, int32_t max_slots,
                              int32_t chunk, int32_t* nunits, hipStream_t st,
                              const int32_t* slot_lin, int64_t n_blocks, int32_t* cfirst,
-                             const int64_t* dn_rows, unsigned long long* stats) {
+                             const int64_t* dn_rows, unsigned long long* stats, int32_t per_set) {
   if (max_slots <= 0) return hipSuccess;
   if ((chunk <= 0 && !dn_rows) || n_blocks <= 0 || (cfirst && !slot_lin)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_slot_units, dim3(std::min<unsigned>(nblk(max_slots, 256), kSlotGrid)),
                      dim3(256), 0, st, head, d_nslots, max_slots, chunk, nunits, slot_lin,
-                     n_blocks, cfirst, dn_rows, stats);
+                     n_blocks, cfirst, dn_rows, stats, per_set);
   return hipGetLastError();
 }
 

@@ -75,6 +75,17 @@ int main() {
   }
   CHECK(last == SMKI_CHUNK && rows_per_unit(0, INT32_MAX) == SMKI_CHUNK && rows_per_unit(77, 5) == 77,
         "rows per unit");
+  // the steps counted for a slot are those of its units, one by one
+  for (int32_t rows = 0; rows < 1300; ++rows)
+    for (int32_t chunk : {1, 7, 16, 17, 64, 100, 128, 512, 2000}) {
+      int64_t want = 0;
+      for (int32_t r = 0; r < rows; r += chunk) {
+        const int32_t u = std::min(chunk, rows - r);
+        want += u <= kFewRows ? u : 33 * ((u + 63) / 64);
+      }
+      CHECK(lane_steps(rows, chunk, 33) == want, "%d rows, %d a unit: %lld steps", rows, chunk,
+            (long long)lane_steps(rows, chunk, 33));
+    }
   printf("unit sizes\n");
   if (bad) return printf("%d wrong\n", bad), 1;
   printf("ok\n");

@@ -40,9 +40,9 @@ def test_pairs_examined_and_lane_iterations(lv, B, budget):
     ceil = lambda a, b: -(-a // b)  # noqa: E731
     assert st["n_units"] == ceil(rows, chunk).sum()
     full = _offsets(lv, False)
-    if full <= 33:   # up to 64 rows of a unit at a time, the offsets three by three
-        sets = (rows // chunk * ceil(chunk, 64) + ceil(rows % chunk, 64)).sum()
-        want = n * full, sets * 64 * ceil(full, 3) * 3
+    if full <= 33:   # 64 rows at a time, the offsets three by three; up to 16 rows one by one
+        unit = lambda r: np.where(r <= 16, r, ceil(r, 64) * ceil(full, 3) * 3)  # noqa: E731
+        want = n * full, 64 * (rows // chunk * unit(chunk) + unit(rows % chunk)).sum()
     else:            # one row at a time, the offsets of its octant in steps of 64 lanes
         octant = _offsets(lv, True)
         want = n * octant, n * ceil(octant, 64) * 64
