@@ -280,6 +280,10 @@ bool sbki_shape_ok(int32_t B, int32_t R) {
   return (B == 2 || B == 4 || B == 8 || B == 16) && R <= B && R <= SMKI_MAX_REACH;
 }
 
+int32_t share_of(const smki_map* m, const Stencil& s) {
+  return unit_share(m->B, rows_on_lanes(s.R, s.full));
+}
+
 // Pairs that the splat of `rows` rows examines and the lane-iterations that it issues
 // for them.  Small stencils: every offset around the cell, in the 64-lane steps counted
 // on the device; else every row takes the offsets of its octant in steps of 64 lanes.
@@ -699,7 +703,7 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
 
   // ---- phase B: bucket all rows (class-major keys), mark target blocks ----
   const int64_t nt = nk + nf;
-  const int32_t chunk = rows_per_unit(m->budget, nt);
+  const UnitRule rule{m->budget, share_of(m, sten), nt, nullptr};
   const int64_t max_slots = std::min<int64_t>(nt, g.n_blocks * m->K);
   Sizer zb;
   zb.add<int32_t>(g.n_blocks * m->K);
@@ -768,8 +772,8 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
                            (uint32_t*)(d_si + 3), q));
   SMKI_HIP_TRY(launch_mark_targets(ps.slot_lin, ps.d_nslots, (int32_t)max_slots, g, eblo, enb, DB,
                                    d_mark, q));
-  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)max_slots, chunk, d_nun, q,
-                                 ps.slot_lin, g.n_blocks, d_cfirst, nullptr,
+  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)max_slots, rule, d_nun, q,
+                                 ps.slot_lin, g.n_blocks, d_cfirst,
                                  rows_on_lanes(sten.R, sten.full) && !csm ? m->d_stats : nullptr,
                                  steps_per_set(sten.full)));
   SMKI_HIP_TRY(scan_excl_pair_i32(d_mark, d_mpos, n_ext, d_ntgt, d_nun, d_ust, max_slots, d_nunits,
@@ -895,7 +899,7 @@ smki_status insert_impl(smki_map* m, const float* xyz, const int32_t* label, con
   sa.contrib = d_contrib;
   // the splat first (its counters were cleared before the bucketing); what
   // only the later kernels read is prepared while it runs
-  SMKI_HIP_TRY(launch_unit_table(d_nun, d_ust, ps.head, ps.slot_lin, g.n_blocks, chunk, n_slots,
+  SMKI_HIP_TRY(launch_unit_table(d_nun, d_ust, ps.head, ps.slot_lin, g.n_blocks, rule, n_slots,
                                  ps.d_nslots, d_nunits, d_units, d_uorder, q));
   SMKI_HIP_TRY(timing_begin(m, q));
   SMKI_HIP_TRY(launch_splat(sa, n_units, q));
@@ -1122,8 +1126,9 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
                            ps, scr, d.err, q, d.pc, (int32_t)b->cap_slots));
   SMKI_HIP_TRY(launch_mark_targets(ps.slot_lin, ps.d_nslots, (int32_t)b->cap_slots, g, b->eblo,
                                    b->enb, 1, d.mark, q));
-  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)b->cap_slots, m->budget, d.nun, q,
-                                 nullptr, 1, nullptr, d.pc,
+  const UnitRule rule{m->budget, share_of(m, b->sten), 0, d.pc};
+  SMKI_HIP_TRY(launch_slot_units(ps.head, ps.d_nslots, (int32_t)b->cap_slots, rule, d.nun, q,
+                                 nullptr, 1, nullptr,
                                  rows_on_lanes(b->sten.R, b->sten.full) ? d.stats : nullptr,
                                  steps_per_set(b->sten.full)));
   SMKI_HIP_TRY(scan_excl_pair_i32(d.mark, d.mpos, ne, d.si + 1, d.nun, d.ust, b->cap_slots,
@@ -1178,9 +1183,9 @@ smki_status batch_enqueue(smki_batch* b, hipStream_t q) {
   sa.abort_word = d.err;
   sa.cap_units = (int32_t)b->cap_units;
   sa.tgt_grid = b->tgt_grid;
-  SMKI_HIP_TRY(launch_unit_table(d.nun, d.ust, d.head, d.slot_lin, g.n_blocks, m->budget,
+  SMKI_HIP_TRY(launch_unit_table(d.nun, d.ust, d.head, d.slot_lin, g.n_blocks, rule,
                                  (int32_t)b->cap_slots, ps.d_nslots, d.si + 2, d.units, d.uorder,
-                                 q, (int32_t)b->cap_units, d.pc));
+                                 q, (int32_t)b->cap_units));
   SMKI_HIP_TRY(launch_splat(sa, b->cap_units, q));
   SMKI_HIP_TRY(launch_list_targets(d.mark, d.mpos, ne, d.tgt, d.ext2t, q));
   SMKI_HIP_TRY(launch_clear_targets(sa.dn_targets, (int32_t)ne, b->tgt_grid, m->K, d.cnt, d.active,
@@ -1859,9 +1864,10 @@ smki_status smki_batch_capture(smki_map* m, const float* xyz, const int32_t* lab
   b->cap_units = (int64_t)ceil((double)st.n_units * grow) + 1024;
   const int64_t region = (int64_t)sizeof(float) * (m->B + 2 * b->sten.R) * (m->B + 2 * b->sten.R) *
                          (m->B + 2 * b->sten.R);
-  // (fewer rows than the sizing insert's may be cut into shorter units)
-  if (m->budget <= 0 && (b->cap_units + kUnitSpread) * region <= (int64_t(64) << 30))
-    b->cap_units += kUnitSpread;
+  // (fewer rows than the sizing insert's may be cut into shorter units: at most so many
+  // more of them as share the rows)
+  const int32_t more = share_of(m, b->sten);
+  if (m->budget <= 0 && (b->cap_units + more) * region <= (int64_t(64) << 30)) b->cap_units += more;
   // (a grid, not a capacity: the window may hold more targets, which the kernels
   // stride over; one workgroup per block of the window cost 0.4 ms of a 2 ms replay)
   b->tgt_grid = std::min<int64_t>(b->n_ext, (int64_t)ceil((double)st.n_target_blocks * grow) + 256);

@@ -1,6 +1,7 @@
 // Map-update structures shared by the HIP translation units (internal).
 #pragma once
 #include "smki_bucket.h"
+#include "smki_plan.h"
 
 #define SMKI_MAX_REACH 4            // largest stencil reach in voxels
 #define SMKI_MAX_OFFS 729           // (2 * SMKI_MAX_REACH + 1)^3
@@ -118,21 +119,19 @@ hipError_t launch_mark_targets(const int32_t* slot_lin, const int32_t* d_nslots,
                                int32_t DB, int32_t* mark, hipStream_t st);
 hipError_t launch_list_targets(const int32_t* mark, const int32_t* mpos, int64_t n_ext,
                                int32_t* tgt_elin, int32_t* ext2t, hipStream_t st);
-// rows per unit: chunk, or with dn_rows (device, a captured insert's row count)
-// rows_per_unit(chunk, *dn_rows), chunk then being the map's budget
 // cfirst (nullable, [K], zeroed): 1 + the first slot of each class that has one
 // stats (nullable, SplatArgs::stats): counter 2, the units' steps (lane_steps)
 hipError_t launch_slot_units(const int32_t* head, const int32_t* d_nslots, int32_t max_slots,
-                             int32_t chunk, int32_t* nunits, hipStream_t st,
+                             const UnitRule& rule, int32_t* nunits, hipStream_t st,
                              const int32_t* slot_lin = nullptr, int64_t n_blocks = 1,
-                             int32_t* cfirst = nullptr, const int64_t* dn_rows = nullptr,
-                             unsigned long long* stats = nullptr, int32_t per_set = 0);
+                             int32_t* cfirst = nullptr, unsigned long long* stats = nullptr,
+                             int32_t per_set = 0);
 // units of every slot, and (order, nullable) the splat's launch order
 hipError_t launch_unit_table(const int32_t* nunits, const int32_t* ustart, const int32_t* head,
-                             const int32_t* slot_lin, int64_t n_blocks, int32_t chunk,
+                             const int32_t* slot_lin, int64_t n_blocks, const UnitRule& rule,
                              int32_t max_slots, const int32_t* d_nslots, const int32_t* d_nunits,
                              int4* units, int32_t* order, hipStream_t st,
-                             int32_t cap_units = INT32_MAX, const int64_t* dn_rows = nullptr);
+                             int32_t cap_units = INT32_MAX);
 hipError_t launch_splat(const SplatArgs& a, int64_t n_units, hipStream_t st);
 hipError_t launch_merge(const SplatArgs& a, int32_t n_targets, hipStream_t st);
 // class blocks: which (target, class) pairs receive rows, which need a new

@@ -41,21 +41,52 @@ static inline unsigned near_mark_grid(int64_t nq) {
 
 // ---- splat work units ----
 #define SMKI_CHUNK 512   // most rows of one (class, block) per unit where no budget was asked for
-// Rows per work unit of an insert of `rows` rows: as asked for at the map's creation
-// (budget > 0), else so many that about 4,096 units (16 wavefronts on each of 256 CUs)
-// share the rows, in whole batches of 64, between 128 and SMKI_CHUNK.  One wavefront
-// takes a unit's rows one after the other (0.29 us each at reach 3), so a small scan
-// whose rows lie in few blocks lasts as long as its longest unit, while every unit adds
-// a region to write and merge.  2,000 hits with 28,000 free samples, splat + merge: 512
-// rows a unit 150 + 15 us, 128 rows 47 + 25, 64 rows 30 + 41.
-// An insert takes it from its row count on the host, a captured one on the device: a
-// replay is cut into the units of the ordinary insert of its rows, whatever rows it was
-// sized by.
-__host__ __device__ static inline int32_t rows_per_unit(int32_t budget, int64_t rows) {
+// Units that an insert's rows are shared by, where no budget was asked for.  One
+// wavefront takes a unit's rows one after the other, so a small scan whose rows lie in
+// few blocks lasts as long as its longest unit (0.29 us a row at reach 3), while every
+// unit adds a region to write and merge.  4,096 is 16 wavefronts on each of 256 CUs.
+// Small stencils take 64 rows at a time: a quarter as many.  A block of 16^3 has regions
+// of 16 to 55 KB, at most 10 on a CU: a tenth as many.  Whole call in us at 128, 256 and
+// 512 rows a unit, of a street's rows in 200 to 50,000 slots:
+//   reach 3, 4^3      60,000 rows 278, 300, 351;  236,000 356, 374, 424;   591,000 480, 476, 523
+//   reach 3, 8^3      60,000 rows 331, 359, 393;  236,000 437, 441, 487;   591,000 542, 558, 580
+//   l/res 1.5, 4^3    60,000 rows 241, 249, 258;  236,000 269, 262, 277;   591,000 312, 313, 316
+//   l/res 1.5, 8^3    60,000 rows 255, 262, 277;  236,000 289, 287, 303;   591,000 396, 371, 368
+//   reach 3, 16^3     60,000 rows 552, 538, 576;  236,000 890, 847, 879;   591,000 1420, 1268, 1249
+//   l/res 1.5, 16^3   14,000 rows 345, 348, 364;  236,000 714, 601, 552;   591,000 1123, 838, 717
+static inline int32_t unit_share(int32_t B, bool small_stencil) {
+  return (B >= 16 ? 384 : 4096) / (small_stencil ? 4 : 1);
+}
+// Units that the rows of one slot are cut into, on average: the merge of a block takes
+// the units of its neighbours one after the other, and where few slots hold the rows
+// there are few blocks to hide it.  The same, of a room's rows in 16 to 280 slots:
+//   reach 3, 4^3      91,000 rows 269, 291, 335;  343,000 369, 351, 381
+//   reach 3, 8^3      91,000 rows 334, 340, 385;  343,000 525, 435, 434
+//   l/res 1.5, 4^3    91,000 rows 223, 217, 227;  343,000 321, 277, 268
+//   l/res 1.5, 8^3    91,000 rows 285, 257, 255;  343,000 513, 383, 331
+//   reach 3, 16^3     91,000 rows 541, 470, 484;  343,000 1347, 874, 644
+constexpr int kSlotUnits = 8;
+// Rows per work unit of an insert of `rows` rows in `slots` (class, block) slots: as
+// asked for at the map's creation (budget > 0), else so many that about `share` units
+// share the rows and a slot has about kSlotUnits at most, in whole batches of 64,
+// between 128 and SMKI_CHUNK.
+// Taken on the device, in an ordinary insert and a captured one alike: a replay is cut
+// into the units of the ordinary insert of its rows, whatever rows it was sized by.
+__host__ __device__ static inline int32_t rows_per_unit(int32_t budget, int32_t share, int64_t rows,
+                                                        int64_t slots) {
   if (budget > 0) return budget;
-  const int64_t c = ((rows + 4095) / 4096 + SMKI_WAVE - 1) / SMKI_WAVE * SMKI_WAVE;
+  const int64_t per_slot = kSlotUnits * (slots > 0 ? slots : 1);
+  const int64_t units = per_slot < share ? per_slot : share;
+  const int64_t c = ((rows + units - 1) / units + SMKI_WAVE - 1) / SMKI_WAVE * SMKI_WAVE;
   return (int32_t)(c < 2 * SMKI_WAVE ? 2 * SMKI_WAVE : c > SMKI_CHUNK ? SMKI_CHUNK : c);
 }
+// What decides the rows per unit: the map's budget, else the share and the rows (their
+// count on the device if dn_rows is set).
+struct UnitRule {
+  int32_t budget, share;
+  int64_t rows;
+  const int64_t* dn_rows;
+};
 // Units of at most this many rows are splatted row by row where stencils are small.
 // 2e5 rows at l / res = 1.5, splat in us row by row and with lanes as rows: units of 8
 // rows on average 42 and 51, of 16 rows 32 and 36 (up to 24 rows the same).
@@ -69,9 +100,6 @@ __host__ __device__ static inline int64_t lane_steps(int32_t rows, int32_t chunk
   };
   return full * unit(chunk) + unit(rest);
 }
-// Units that a set of fewer rows can have beyond those of more rows in the same slots:
-// shorter units share at most 4,096 times their rows.
-constexpr int64_t kUnitSpread = 4096;
 
 // ---- prefix sums ----
 constexpr int SCAN_THREADS = 256;

@@ -93,16 +93,20 @@ __global__ void k_list_targets(const int32_t* __restrict__ mark, const int32_t* 
   if (i < n) list_target(mark, mpos, i, tgt, ext2t);
 }
 
+__device__ __forceinline__ int32_t rule_rows(const UnitRule& r, int32_t slots) {
+  return rows_per_unit(r.budget, r.share, r.dn_rows ? *r.dn_rows : r.rows, slots);
+}
+
 // chunks of every (class, block) slot (entries past the slot count are not
 // written); cfirst (nullable): 1 + the first slot of each class with slots
 // (slots are in class-major order); stats (nullable): the 64-lane steps of the units
 // (insert counter 2, lane_steps)
 __global__ void k_slot_units(const int32_t* __restrict__ head, const int32_t* __restrict__ d_nslots,
-                             int32_t max_slots, int32_t chunk, int32_t* __restrict__ nunits,
+                             int32_t max_slots, UnitRule rule, int32_t* __restrict__ nunits,
                              const int32_t* __restrict__ slot_lin, int64_t n_blocks,
-                             int32_t* __restrict__ cfirst, const int64_t* __restrict__ dn_rows,
-                             unsigned long long* __restrict__ stats, int32_t per_set) {
-  if (dn_rows) chunk = rows_per_unit(chunk, *dn_rows);
+                             int32_t* __restrict__ cfirst, unsigned long long* __restrict__ stats,
+                             int32_t per_set) {
+  const int32_t chunk = rule_rows(rule, *d_nslots);
   const int32_t n = min(max_slots, *d_nslots);
   int64_t steps = 0;
   for (int32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < n; s += gridDim.x * blockDim.x) {
@@ -128,18 +132,17 @@ __global__ void k_slot_units(const int32_t* __restrict__ head, const int32_t* __
 // slots).  A late long unit would leave the rest of the GPU idle at the end.
 __global__ void k_unit_table(const int32_t* __restrict__ nunits, const int32_t* __restrict__ ustart,
                              const int32_t* __restrict__ head, const int32_t* __restrict__ slot_lin,
-                             int64_t n_blocks, int32_t chunk, int32_t max_slots,
+                             int64_t n_blocks, UnitRule rule, int32_t max_slots,
                              const int32_t* __restrict__ d_nslots,
                              const int32_t* __restrict__ d_nunits, int4* __restrict__ units,
-                             int32_t* __restrict__ order, int32_t cap_units,
-                             const int64_t* __restrict__ dn_rows) {
+                             int32_t* __restrict__ order, int32_t cap_units) {
   // eight threads per slot, taking its units k = j, j + 8, ...; the grid
   // strides over the slots (a multiple of eight threads)
   // (a captured insert whose slots or units outgrow their tables stores no
   // unit; its abort word is set and the map is left unchanged)
   if (*d_nslots > max_slots || *d_nunits > cap_units || *d_nunits < 0) return;
-  if (dn_rows) chunk = rows_per_unit(chunk, *dn_rows);
   const int32_t ns = *d_nslots;
+  const int32_t chunk = rule_rows(rule, ns);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; (t >> 3) < ns; t += stride) {
     const int32_t s = (int32_t)(t >> 3);
@@ -1449,28 +1452,28 @@ hipError_t launch_list_targets(const int32_t* mark, const int32_t* mpos, int64_t
 }
 
 hipError_t launch_slot_units(const int32_t* head, const int32_t* d_nslots, int32_t max_slots,
-                             int32_t chunk, int32_t* nunits, hipStream_t st,
+                             const UnitRule& rule, int32_t* nunits, hipStream_t st,
                              const int32_t* slot_lin, int64_t n_blocks, int32_t* cfirst,
-                             const int64_t* dn_rows, unsigned long long* stats, int32_t per_set) {
+                             unsigned long long* stats, int32_t per_set) {
   if (max_slots <= 0) return hipSuccess;
-  if ((chunk <= 0 && !dn_rows) || n_blocks <= 0 || (cfirst && !slot_lin)) return hipErrorInvalidValue;
+  if ((rule.budget <= 0 && rule.share <= 0) || n_blocks <= 0 || (cfirst && !slot_lin))
+    return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_slot_units, dim3(std::min<unsigned>(nblk(max_slots, 256), kSlotGrid)),
-                     dim3(256), 0, st, head, d_nslots, max_slots, chunk, nunits, slot_lin,
-                     n_blocks, cfirst, dn_rows, stats, per_set);
+                     dim3(256), 0, st, head, d_nslots, max_slots, rule, nunits, slot_lin,
+                     n_blocks, cfirst, stats, per_set);
   return hipGetLastError();
 }
 
 hipError_t launch_unit_table(const int32_t* nunits, const int32_t* ustart, const int32_t* head,
-                             const int32_t* slot_lin, int64_t n_blocks, int32_t chunk,
+                             const int32_t* slot_lin, int64_t n_blocks, const UnitRule& rule,
                              int32_t max_slots, const int32_t* d_nslots, const int32_t* d_nunits,
-                             int4* units, int32_t* order, hipStream_t st, int32_t cap_units,
-                             const int64_t* dn_rows) {
+                             int4* units, int32_t* order, hipStream_t st, int32_t cap_units) {
   if (max_slots <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_unit_table,
                      dim3(std::min<unsigned>(nblk((int64_t)max_slots * 8, 256), 8 * kSlotGrid)),
                      dim3(256), 0, st,
-                     nunits, ustart, head, slot_lin, n_blocks, chunk, max_slots, d_nslots, d_nunits,
-                     units, order, cap_units, dn_rows);
+                     nunits, ustart, head, slot_lin, n_blocks, rule, max_slots, d_nslots, d_nunits,
+                     units, order, cap_units);
   return hipGetLastError();
 }
 

@@ -64,17 +64,24 @@ int main() {
   }
   printf("near marks\n");
   // rows per unit: whole batches of 64 between 128 and 512, more rows never shorter
-  // units, and never more than kUnitSpread units' worth of rows below 512 a unit
-  int32_t last = 0;
-  for (int64_t n = 1; n <= 3'000'000; n += n % 7 + 1) {
-    const int32_t c = rows_per_unit(0, n);
-    CHECK(c % SMKI_WAVE == 0 && c >= 128 && c <= SMKI_CHUNK && c >= last, "%lld rows: %d a unit",
-          (long long)n, c);
-    CHECK(c == SMKI_CHUNK || n <= kUnitSpread * c, "%lld rows: %d a unit", (long long)n, c);
-    last = c;
-  }
-  CHECK(last == SMKI_CHUNK && rows_per_unit(0, INT32_MAX) == SMKI_CHUNK && rows_per_unit(77, 5) == 77,
-        "rows per unit");
+  // units nor more slots longer ones, and below 512 a unit never more full units than
+  // share the rows (a replay's tables have room for that many beyond its sizing insert's)
+  for (int32_t B : {2, 8, 16})
+    for (bool few : {false, true})
+      for (int64_t slots : {0, 1, 20, 300, 5000, 1'000'000}) {
+        const int32_t share = unit_share(B, few);
+        int32_t last = 0;
+        for (int64_t n = 1; n <= 3'000'000; n += n % 7 + 1) {
+          const int32_t c = rows_per_unit(0, share, n, slots);
+          CHECK(c % SMKI_WAVE == 0 && c >= 128 && c <= SMKI_CHUNK && c >= last, "%lld rows: %d a unit",
+                (long long)n, c);
+          CHECK(c <= rows_per_unit(0, share, n, slots / 2), "%lld slots", (long long)slots);
+          CHECK(c == SMKI_CHUNK || n <= (int64_t)share * c, "%lld rows: %d a unit", (long long)n, c);
+          last = c;
+        }
+        CHECK(last == SMKI_CHUNK && rows_per_unit(0, share, INT32_MAX, INT32_MAX) == SMKI_CHUNK &&
+                  rows_per_unit(77, share, 5, 5) == 77, "rows per unit");
+      }
   // the steps counted for a slot are those of its units, one by one
   for (int32_t rows = 0; rows < 1300; ++rows)
     for (int32_t chunk : {1, 7, 16, 17, 64, 100, 128, 512, 2000}) {

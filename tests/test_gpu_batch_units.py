@@ -1,6 +1,7 @@
 """Replays whose rows take another work-unit size than the rows they were sized by:
-the size follows the row count (128 rows a unit up to 524,288 rows, 512 from about
-1.8e6 on) in an insert and in a replay alike, so that both sum in one order."""
+the size follows the row count and the slots that the rows lie in (at reach 3, 128 rows a
+unit up to 524,288 rows in many slots, 512 from about 1.8e6 on, or from 3,584 rows a slot
+on) in an insert and in a replay alike, so that both sum in one order."""
 import numpy as np
 import pytest
 
@@ -16,17 +17,19 @@ def _bits(m):
 
 # (rows of the sizing insert, rows of the replays, margin): a step down, a step up,
 # the widest steps, and a step down without margin, where the shorter units of
-# fewer rows outnumber the sizing insert's
+# fewer rows outnumber the sizing insert's; in a small box, whose few slots give longer
+# units, and in a large one
+@pytest.mark.parametrize("edge", [1.5, 9.0])
 @pytest.mark.parametrize("B", [4, 8])
 @pytest.mark.parametrize("n0,n1,margin", [(600_000, 500_000, 0.5), (500_000, 600_000, 0.5),
-                                          (2_000_000, 300_000, 0.5), (530_000, 520_000, 0.0)])
-def test_replays_with_other_row_counts_equal_the_insert(n0, n1, margin, B):
+                                          (2_000_000, 300_000, 0.5), (530_000, 520_000, 0.0),])
+def test_replays_with_other_row_counts_equal_the_insert(n0, n1, margin, B, edge):
     import torch
     from paper_1909_04631_amd import SemanticMap
-    print(f"[case] units B={B} sized by {n0} rows, replayed with {n1}", flush=True)
+    print(f"[case] units B={B} box {edge} sized by {n0} rows, replayed with {n1}", flush=True)
     n, K = max(n0, n1), 3
     rng = np.random.default_rng(n1 + B)
-    xyz = cuda(rng.uniform(0.0, 1.5, size=(n, 3)).astype(np.float32))
+    xyz = cuda(rng.uniform(0.0, edge, size=(n, 3)).astype(np.float32))
     lab = rng.integers(1, K, size=n).astype(np.int32)
 
     def labels(rows):   # (the hits without a label make no row)

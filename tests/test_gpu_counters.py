@@ -36,7 +36,7 @@ def test_pairs_examined_and_lane_iterations(lv, B, budget):
     st = m.stats()
     blocks = np.floor(xyz / RES).astype(np.int64) // B
     _, rows = np.unique(np.column_stack([lab, blocks]), axis=0, return_counts=True)
-    chunk = budget or 128
+    chunk = budget or 128   # (3,000 rows: never longer)
     ceil = lambda a, b: -(-a // b)  # noqa: E731
     assert st["n_units"] == ceil(rows, chunk).sum()
     full = _offsets(lv, False)
