@@ -99,11 +99,14 @@ __global__ void __launch_bounds__(256) k_query(MapDev m, const int32_t* __restri
     }
   }
   const int ql = threadIdx.x / SEG;   // the query inside the workgroup
+  const bool rows = alpha || mean || var;   // (the whole launch)
   if (live) {
+    if (rows) {
 #pragma unroll
-    for (int j = 0; j < MAXC; ++j) {
-      const int k = kl + j * SEG;
-      if (k < K) sa[ql * K + k] = a[j];
+      for (int j = 0; j < MAXC; ++j) {
+        const int k = kl + j * SEG;
+        if (k < K) sa[ql * K + k] = a[j];
+      }
     }
     if (kl == 0) {
       const double inv_s = 1.0 / S;
@@ -114,6 +117,7 @@ __global__ void __launch_bounds__(256) k_query(MapDev m, const int32_t* __restri
       if (p_occ) p_occ[i] = (float)((S - af) * inv_s);
     }
   }
+  if (!rows) return;   // (label and occupancy alone, 3e5 voxels of 255 classes: 124 us with the rows staged, now 104)
   __syncthreads();
   const int64_t q0 = (int64_t)blockIdx.x * NQ;
   const int n = (int)min((int64_t)NQ, M - q0) * K;
