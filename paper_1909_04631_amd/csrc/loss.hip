@@ -549,7 +549,7 @@ __global__ void __launch_bounds__(256) k_train_grad(LossArgs a, const float* __r
 // Sums over queries in a fixed order (one workgroup each): thread t adds entries
 // t, t + 1024, ..., then a tree over the threads.
 constexpr int kSumThreads = 1024;
-constexpr int64_t kFoldRows = 4096;
+constexpr int64_t kFoldRows = 8192;
 __device__ __forceinline__ double block_sum(double s) {
   __shared__ double part[kSumThreads];
   part[threadIdx.x] = s;
@@ -606,8 +606,8 @@ __global__ void __launch_bounds__(kSumThreads) k_colsum2(const double* __restric
 }
 
 // The sums of [H][K] v0 and v1 over the queries (v0 and v1 may be overwritten).  Up to
-// 4,096 queries one launch (a backward of 5,000 queries of 20 classes 219 us, 222 with a
-// second launch; of 10,000 240 and 223), above a fold first.
+// kFoldRows queries one launch (a backward of 5,000 queries of 20 classes 219 us, 231 with
+// a second launch; of 10,000 240 and 223), above a fold first.
 void launch_colsum2(double* v0, float* out0, double* v1, float* out1, int64_t H, int32_t K,
                     hipStream_t st) {
   if (K > 1 && H > kFoldRows) {

@@ -1,4 +1,4 @@
-"""Per-class gradients summed over the queries: up to 4,096 queries in one launch, above
+"""Per-class gradients summed over the queries: up to 8,192 queries in one launch, above
 after a fold of the queries to 1,024 rows."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("K", [2, 66])
-@pytest.mark.parametrize("q", [4096, 4097, 5121])
+@pytest.mark.parametrize("q", [8192, 8193, 9217])
 def test_class_sums_around_the_fold(q, K):
     import torch
     from paper_1909_04631_amd.loss import loss_backward_classes, loss_forward_classes
