@@ -1864,10 +1864,9 @@ smki_status smki_batch_capture(smki_map* m, const float* xyz, const int32_t* lab
   b->cap_units = (int64_t)ceil((double)st.n_units * grow) + 1024;
   const int64_t region = (int64_t)sizeof(float) * (m->B + 2 * b->sten.R) * (m->B + 2 * b->sten.R) *
                          (m->B + 2 * b->sten.R);
-  // (fewer rows than the sizing insert's may be cut into shorter units: at most so many
-  // more of them as share the rows)
-  const int32_t more = share_of(m, b->sten);
-  if (m->budget <= 0 && (b->cap_units + more) * region <= (int64_t(64) << 30)) b->cap_units += more;
+  // (fewer rows than the sizing insert's may be cut into shorter units)
+  if (m->budget <= 0 && (b->cap_units + kMostUnits) * region <= (int64_t(64) << 30))
+    b->cap_units += kMostUnits;
   // (a grid, not a capacity: the window may hold more targets, which the kernels
   // stride over; one workgroup per block of the window cost 0.4 ms of a 2 ms replay)
   b->tgt_grid = std::min<int64_t>(b->n_ext, (int64_t)ceil((double)st.n_target_blocks * grow) + 256);

@@ -41,6 +41,7 @@ static inline unsigned near_mark_grid(int64_t nq) {
 
 // ---- splat work units ----
 #define SMKI_CHUNK 512   // most rows of one (class, block) per unit where no budget was asked for
+constexpr int32_t kMostUnits = 4096;
 // Units that an insert's rows are shared by, where no budget was asked for.  One
 // wavefront takes a unit's rows one after the other, so a small scan whose rows lie in
 // few blocks lasts as long as its longest unit (0.29 us a row at reach 3), while every
@@ -55,7 +56,7 @@ static inline unsigned near_mark_grid(int64_t nq) {
 //   reach 3, 16^3     60,000 rows 552, 538, 576;  236,000 890, 847, 879;   591,000 1420, 1268, 1249
 //   l/res 1.5, 16^3   14,000 rows 345, 348, 364;  236,000 714, 601, 552;   591,000 1123, 838, 717
 static inline int32_t unit_share(int32_t B, bool small_stencil) {
-  return (B >= 16 ? 384 : 4096) / (small_stencil ? 4 : 1);
+  return (B >= 16 ? 384 : kMostUnits) / (small_stencil ? 4 : 1);
 }
 // Units that the rows of one slot are cut into, on average: the merge of a block takes
 // the units of its neighbours one after the other, and where few slots hold the rows
@@ -65,6 +66,9 @@ static inline int32_t unit_share(int32_t B, bool small_stencil) {
 //   l/res 1.5, 4^3    91,000 rows 223, 217, 227;  343,000 321, 277, 268
 //   l/res 1.5, 8^3    91,000 rows 285, 257, 255;  343,000 513, 383, 331
 //   reach 3, 16^3     91,000 rows 541, 470, 484;  343,000 1347, 874, 644
+// (All rows in one slot, in blocks of up to 8^3: kMostUnits whatever the stencil, as
+// before the slots were counted.  7e5 rows of one class in one block of 8^3 at
+// l / res = 1.5 are units of 192 rows and take 929 us; units of 512 would take 487.)
 constexpr int kSlotUnits = 8;
 // Rows per work unit of an insert of `rows` rows in `slots` (class, block) slots: as
 // asked for at the map's creation (budget > 0), else so many that about `share` units
@@ -75,8 +79,11 @@ constexpr int kSlotUnits = 8;
 __host__ __device__ static inline int32_t rows_per_unit(int32_t budget, int32_t share, int64_t rows,
                                                         int64_t slots) {
   if (budget > 0) return budget;
-  const int64_t per_slot = kSlotUnits * (slots > 0 ? slots : 1);
-  const int64_t units = per_slot < share ? per_slot : share;
+  const int64_t per_slot = kSlotUnits * slots;
+  const int64_t units = slots <= 1 && share >= kMostUnits / 4 ? kMostUnits
+                        : slots <= 1                          ? kSlotUnits
+                        : per_slot < share                    ? per_slot
+                                                              : share;
   const int64_t c = ((rows + units - 1) / units + SMKI_WAVE - 1) / SMKI_WAVE * SMKI_WAVE;
   return (int32_t)(c < 2 * SMKI_WAVE ? 2 * SMKI_WAVE : c > SMKI_CHUNK ? SMKI_CHUNK : c);
 }

@@ -64,8 +64,8 @@ int main() {
   }
   printf("near marks\n");
   // rows per unit: whole batches of 64 between 128 and 512, more rows never shorter
-  // units nor more slots longer ones, and below 512 a unit never more full units than
-  // share the rows (a replay's tables have room for that many beyond its sizing insert's)
+  // units nor more slots (from two on) longer ones, and below 512 a unit never more than
+  // 4,096 full units (a replay's tables have room for that many beyond its sizing insert's)
   for (int32_t B : {2, 8, 16})
     for (bool few : {false, true})
       for (int64_t slots : {0, 1, 20, 300, 5000, 1'000'000}) {
@@ -75,8 +75,8 @@ int main() {
           const int32_t c = rows_per_unit(0, share, n, slots);
           CHECK(c % SMKI_WAVE == 0 && c >= 128 && c <= SMKI_CHUNK && c >= last, "%lld rows: %d a unit",
                 (long long)n, c);
-          CHECK(c <= rows_per_unit(0, share, n, slots / 2), "%lld slots", (long long)slots);
-          CHECK(c == SMKI_CHUNK || n <= (int64_t)share * c, "%lld rows: %d a unit", (long long)n, c);
+          CHECK(slots / 2 < 2 || c <= rows_per_unit(0, share, n, slots / 2), "%lld slots", (long long)slots);
+          CHECK(c == SMKI_CHUNK || n <= (int64_t)kMostUnits * c, "%lld rows: %d a unit", (long long)n, c);
           last = c;
         }
         CHECK(last == SMKI_CHUNK && rows_per_unit(0, share, INT32_MAX, INT32_MAX) == SMKI_CHUNK &&
