@@ -376,11 +376,10 @@ __global__ void __launch_bounds__(256) k_free_keys(
   }
 }
 
-// Explicit training rows (differentiable form, tests): keys and records.
+// Rows without labels (the bucketing entry point): keys and records.
 template <typename KeyT>
-__global__ void k_row_keys(const float* __restrict__ xyz, const int32_t* __restrict__ label,
-                           int64_t n, BucketGeom g, KeyT* __restrict__ keys,
-                           uint32_t* __restrict__ idx, float4* __restrict__ rec,
+__global__ void k_row_keys(const float* __restrict__ xyz, int64_t n, BucketGeom g,
+                           KeyT* __restrict__ keys, uint32_t* __restrict__ idx, float4* __restrict__ rec,
                            uint32_t* __restrict__ err) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -397,7 +396,7 @@ __global__ void k_row_keys(const float* __restrict__ xyz, const int32_t* __restr
   if (!in_grid(g, b)) { atomicOr(err, DEVERR_RANGE); keys[i] = (KeyT)0; idx[i] = (uint32_t)i; rec[i] = make_float4(0, 0, 0, 0); return; }
   keys[i] = make_key<KeyT>(g, 0, b, l);
   idx[i] = (uint32_t)i;
-  rec[i] = make_record(g, px, py, pz, b, label ? label[i] : 0);
+  rec[i] = make_record(g, px, py, pz, b, 0);
 }
 
 // Sorted records: out[i] = rec[idx[i]] (and the weights alike when present).
@@ -643,10 +642,15 @@ static hipError_t finish_set(PointSet& ps, KeyT* keys, uint32_t* idx, KeyT* akey
                        g.n_blocks, g.planes, (const unsigned long long*)heads, scr.slot_excl,
                        ps.dense, ps.slot_lin, ps.head, ps.d_nslots, cap_slots);
   if (!ps.prefix) return hipGetLastError();
-  if (log2B3 != 6) return hipErrorInvalidValue;   // (cell tables: blocks of 4^3 cells)
-  hipLaunchKernelGGL((k_slot_prefix<KeyT, 6>), dim3((unsigned)std::min<int64_t>(nblk(n, 4), 4096)),
-                     dim3(256), 0, st, keys, ps.head, ps.d_nslots, ps.prefix);
-  return hipGetLastError();
+  // (cell tables: the differentiable form's, blocks of 4^3 cells and 32-bit keys)
+  if constexpr (sizeof(KeyT) == 4) {
+    if (log2B3 != 6) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_slot_prefix<KeyT, 6>), dim3((unsigned)std::min<int64_t>(nblk(n, 4), 4096)),
+                       dim3(256), 0, st, keys, ps.head, ps.d_nslots, ps.prefix);
+    return hipGetLastError();
+  } else {
+    return hipErrorInvalidValue;
+  }
 }
 
 template <typename KeyT>
@@ -939,7 +943,7 @@ hipError_t bucket_cells_sort(const float* xyz, int64_t n, const BucketGeom& g, B
   hipError_t e;
   if (g.key_bits <= 32) {
     hipLaunchKernelGGL(k_row_keys<uint32_t>, dim3(nblk(n, 256)), dim3(256), 0, st, xyz,
-                       (const int32_t*)nullptr, n, g, (uint32_t*)scr.keys, scr.idx, scr.rec, err);
+                       n, g, (uint32_t*)scr.keys, scr.idx, scr.rec, err);
     e = radix_sort_u32((uint32_t*)scr.keys, scr.idx, (uint32_t*)scr.akeys, scr.aidx, n, g.key_bits,
                        scr.sort_tmp, scr.sort_tmp_bytes, st);
     if (e != hipSuccess) return e;
@@ -947,7 +951,7 @@ hipError_t bucket_cells_sort(const float* xyz, int64_t n, const BucketGeom& g, B
                        (const uint32_t*)scr.keys, n, scr.flag);
   } else {
     hipLaunchKernelGGL(k_row_keys<uint64_t>, dim3(nblk(n, 256)), dim3(256), 0, st, xyz,
-                       (const int32_t*)nullptr, n, g, (uint64_t*)scr.keys, scr.idx, scr.rec, err);
+                       n, g, (uint64_t*)scr.keys, scr.idx, scr.rec, err);
     e = radix_sort_u64((uint64_t*)scr.keys, scr.idx, (uint64_t*)scr.akeys, scr.aidx, n, g.key_bits,
                        scr.sort_tmp, scr.sort_tmp_bytes, st);
     if (e != hipSuccess) return e;

@@ -250,13 +250,13 @@ __device__ __forceinline__ void write_region(const SplatArgs& a, const float* ac
 
 // NS: steps of 64 voxel offsets, enough for the first-octant stencil of any
 // l / res with reach R (its size is largest at l / res -> R + 1/2: 1, 23, 90,
-// 230, 471 offsets for R = 0..4).
+// 230, 471 offsets for R = 0..4; up to reach 1 the small stencils' kernel is used).
 template <int R>
 struct Steps {
   static constexpr int MAXOFF = R == 0 ? 1 : R == 1 ? 23 : R == 2 ? 90 : R == 3 ? 230 : 471;
   static constexpr int NS = (MAXOFF + SMKI_WAVE - 1) / SMKI_WAVE;
   // fewest steps a reach-R stencil can need (its size at l / res -> R - 1/2)
-  static constexpr int NSMIN = R <= 2 ? 1 : R == 3 ? 2 : 4;
+  static constexpr int NSMIN = R == 2 ? 1 : R == 3 ? 2 : 4;
 };
 
 // NS = ceil(stencil size / 64), the steps each row takes (compiled per value
@@ -1356,7 +1356,7 @@ hipError_t launch_splat_br(const SplatArgs& a, int64_t n_units, int32_t n_target
                            hipStream_t st) {
   if (!merge) {
     if constexpr (R <= 2) {
-      // at most kFullMax voxels around a cell: lanes over rows
+      // at most kFullMax voxels around a cell (always, up to reach 1): lanes over rows
       if (n_units > 0 && rows_on_lanes(R, *a.full_stencil)) {
         const dim3 grid((unsigned)n_units), block(SMKI_WAVE);
         if (a.wts)
@@ -1366,9 +1366,12 @@ hipError_t launch_splat_br(const SplatArgs& a, int64_t n_units, int32_t n_target
         return hipGetLastError();
       }
     }
-    if (n_units > 0)
-      return launch_splat_ns<B, R, Steps<R>::NS>(a, n_units, (a.noff + SMKI_WAVE - 1) / SMKI_WAVE,
-                                                 st);
+    static_assert(kFullMax >= 27, "reach 1: 27 voxels");
+    if constexpr (R >= 2) {
+      if (n_units > 0)
+        return launch_splat_ns<B, R, Steps<R>::NS>(a, n_units, (a.noff + SMKI_WAVE - 1) / SMKI_WAVE,
+                                                   st);
+    }
   } else {
     if (n_targets > 0) {
       constexpr int64_t DR3 = (int64_t)(B + 2 * R) * (B + 2 * R) * (B + 2 * R);
