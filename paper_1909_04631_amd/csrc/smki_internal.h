@@ -89,7 +89,7 @@ __device__ __forceinline__ int64_t eff_n(int64_t n, const int64_t* dn) {
 // midpoint's 25 bits times b's never make a 24-bit a exactly), so rounding the
 // product gives the rounded quotient.  Results near the subnormal range, where
 // midpoints have fewer bits, take the division.
-__device__ __forceinline__ float quot_rn(float a, double inv_b, float b) {
+__host__ __device__ __forceinline__ float quot_rn(float a, double inv_b, float b) {
   const double q = (double)a * inv_b;
   if (fabs(q) >= 0x1p-120) return (float)q;
   return (float)((double)a / (double)b);
