@@ -50,6 +50,12 @@ int main() {
     check((float)std::ldexp((double)m * b, -120 + (int)(rng() % 3) - 1), b);
     check((float)std::ldexp((double)m * b, -126 - (int)(rng() % 24)), b);
   }
+  // quotients that are midpoints of subnormals: an inexact product would turn them
+  for (int i = 0; i < 1'000'000; ++i) {
+    const float b = std::ldexp((float)((rng() & 0x7FFu) | 1u), (int)(rng() % 80) + 20);
+    const double q = std::ldexp((double)((rng() & 0xFFFu) | 1u), -150);
+    check((float)(q * b), b);
+  }
   // numerators next to (a midpoint of binary32) x (the divisor)
   for (float b : {0.05f, 0.1f, 0.2f, 0.25f, 0.3f, 1.0f / 3.0f, 0.3002929985523224f, 7.0f})
     for (int i = 0; i < 200'000; ++i) {
