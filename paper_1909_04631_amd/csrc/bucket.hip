@@ -228,10 +228,6 @@ __device__ __forceinline__ bool in_grid(const BucketGeom& g, const int32_t b[3])
 // weight, in class order, and wt[row] = that weight.  Also, for the free-sample
 // kernel (workgroups of wg samples): wgbeam[b] = the beam that holds free
 // sample b wg (each such sample lies in exactly one beam's range).
-// Samples per thread of the free-sample kernel (256 threads a workgroup): four
-// share a beam's set-up, one where four would leave CUs without a workgroup (nf: the
-// capacity of a captured insert).
-static inline int32_t free_per(int64_t nf) { return nf <= (int64_t(1) << 18) ? 1 : 4; }
 // dcnt (device, nullable): row counts [total, hits, free samples] of the
 // insert, read here instead of nf (a capacity then).
 template <typename KeyT>
@@ -284,6 +280,11 @@ __global__ void k_hit_keys(const float* __restrict__ xyz, const int32_t* __restr
     ++w;
   }
 }
+
+// Samples per thread of the free-sample kernel (256 threads a workgroup): four
+// share a beam's set-up, one where four would leave CUs without a workgroup (nf: the
+// capacity of a captured insert).
+static inline int32_t free_per(int64_t nf) { return nf <= (int64_t(1) << 18) ? 1 : 4; }
 
 // Free sample f -> its beam (largest i with off[i] <= f), its position, key and
 // record.  The beams of a workgroup's samples lie between the beam of its first

@@ -15,6 +15,9 @@ namespace {
 
 inline unsigned nblk(int64_t n, int t) { return (unsigned)ceil_div_i64(n > 0 ? n : 1, t); }
 
+// Words of voxel bits per target block.
+constexpr int vbit_words(int B) { return (B * B * B + 31) / 32; }
+
 // One thread per row; the last row of each run of equal keys (one class in one
 // voxel: keys are sorted by (class, block, voxel)) finds the run's first row and
 // adds the run length to that voxel's class.  The first row is found from the
@@ -22,9 +25,6 @@ inline unsigned nblk(int64_t n, int t) { return (unsigned)ceil_div_i64(n > 0 ? n
 // is sought backwards from them in doubling steps, then between the last two.  (A
 // search over all rows before it took 22 dependent loads: 4.0e6 rows 94 us, now
 // 57, the look-ups of the run's block and class.)
-// Words of voxel bits per target block.
-constexpr int vbit_words(int B) { return (B * B * B + 31) / 32; }
-
 template <typename KeyT, int B>
 __global__ void k_csm_counts(SplatArgs a, const KeyT* __restrict__ keys, int64_t n,
                              uint32_t* __restrict__ vbits) {

@@ -13,8 +13,9 @@
 namespace {
 
 constexpr int RS_WAVES = RS_THREADS / SMKI_WAVE;
-// Up to this many tiles the scatter adds the earlier tiles' counts itself (64
-// counts a thread, about what the launch of their scan costs).
+// Up to this many tiles the scatter adds the earlier tiles' counts itself (up to 64
+// counts per digit, one digit a thread with 256 bins and two with 512: about what the
+// launch of their scan costs).
 constexpr int64_t kFewTiles = 64;
 
 template <typename K>

@@ -6,25 +6,29 @@
 // Organisation (deterministic: no floating-point atomics across wavefronts):
 //
 //   splat   Rows are sorted by (class, block, voxel cell).  One wavefront takes
-//           a chunk of at most `chunk` rows of one (class, block) and keeps,
-//           in LDS, the partial sums of the region that those rows can reach:
-//           the block grown by the stencil reach R on every side.  Rows are
-//           taken 64 at a time, octant by octant of their position in their
-//           cell, each octant's rows in sorted order; for each row (uniform
-//           across the wavefront), lane i handles the voxel offsets i, i + 64,
-//           ... of the list of voxels that can lie within l of a point of that
-//           octant of the row's cell.  Lanes accumulate in registers while
-//           consecutive rows share a cell and octant, and add to LDS when it
-//           changes.  Every lane owns distinct LDS addresses and the LDS runs a
+//           a unit, a chunk of the rows of one (class, block), and keeps, in
+//           LDS, the partial sums of the region that those rows can reach: the
+//           block grown by the stencil reach R on every side.  The region is
+//           written out as the unit's partial sums.
+//           k_splat: rows are taken 64 at a time, octant by octant of their
+//           position in their cell, each octant's rows in sorted order; for each
+//           row (uniform across the wavefront), lane i handles the voxel offsets
+//           i, i + 64, ... of the list of voxels that can lie within l of a
+//           point of that octant of the row's cell.  Lanes accumulate in
+//           registers while consecutive rows share a cell and octant, and add to
+//           LDS when it changes.
+//           k_splat_small (at most 33 voxels around a cell): lanes are rows, up
+//           to 64 of them, and then voxel offsets, each summing the rows of one
+//           cell; units of few rows take them one by one.
+//           In both, every lane owns distinct LDS addresses and the LDS runs a
 //           wavefront's adds in issue order, so the sum order of every voxel is
-//           fixed: run-to-run identical.  The region is written out as the
-//           chunk's partial sums.
+//           fixed: run-to-run identical.
 //   merge   One workgroup per target block: for every class, add in double
 //           the partial sums that the neighbouring (class, block) regions
-//           covering a voxel hold for it (first chunks in a fixed neighbour
-//           order, then the later chunks in chunk order), then add the total
-//           to the voxel's concentration: one exclusive write per (voxel,
-//           class).
+//           covering a voxel hold for it (first units in a fixed neighbour
+//           order, then the later units in unit order), then add the total to
+//           the voxel's concentration: one exclusive write per (voxel, class).
+//           k_merge_list: blocks of 4^3, one wavefront each; k_merge: the others.
 //
 // Kernel evaluation: with s = 1 - r, f(1 - s) = s^5 Q(s^2) exactly (the Taylor
 // series of the sparse kernel about r = 1 has only odd powers from s^5 on);
@@ -741,7 +745,6 @@ __device__ __forceinline__ float part_at(const float* part, int32_t w, int32_t o
   return *(const float*)((const char*)part + (w < 0 ? 0u : e));
 }
 
-// (B = 8 up to reach 3: at most 64 registers, eight wavefronts per SIMD)
 // One workgroup per active target block, one thread per voxel (blocks of more
 // than 1024 voxels: several voxels per thread).  Each thread first lists the
 // neighbours whose regions cover its voxel and the offset of its voxel in the
@@ -749,8 +752,8 @@ __device__ __forceinline__ float part_at(const float* part, int32_t w, int32_t o
 // whose rows reach this block and looks up the slots of the 27 neighbouring
 // blocks into LDS (for all classes of the group at once when one round of
 // lookups covers them, else for the listed classes), keeping for each neighbour
-// only whether its units wrote the piece that lies in this block.  For every listed class, each thread adds, in double, the pieces that
-// cover its voxel: the first chunks of all its candidates (loads issued
+// only whether its units wrote the piece that lies in this block.  For every listed
+// class, each thread adds, in double, the pieces that cover its voxel: the first chunks of all its candidates (loads issued
 // together, in the fixed neighbour order; an absent one reads a zero word),
 // then the later chunks of multi-chunk slots eight at a time; blocks allocated
 // by this insert are written alpha0 + sum, older blocks updated in place where
@@ -759,6 +762,7 @@ __device__ __forceinline__ float part_at(const float* part, int32_t w, int32_t o
 // STRIDE (captured inserts): the grid is smaller than the window's capacity and
 // the workgroups stride over the targets (a form of its own: the loop's state
 // does not fit the 64 registers).
+// (B = 8 up to reach 3: at most 64 registers, eight wavefronts per SIMD.)
 template <int B, int R, bool WIDE, bool STRIDE>
 __global__ void __launch_bounds__((B * B * B < 1024 ? B * B * B : 1024), (B == 8 && R <= 3 && !WIDE && !STRIDE) ? 8 : 1)
 k_merge(SplatArgs a, int32_t n_targets) {
