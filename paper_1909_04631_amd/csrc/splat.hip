@@ -662,7 +662,10 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat_small(SplatArgs a, FullSten
       const float d2 = fmaf(lane_f(z, j), w.z, fmaf(lane_f(y, j), w.y, fmaf(lane_f(x, j), w.x, lane_f(q2, j) + w.w)));
       npair += (uint32_t)__popcll(__ballot(mine && d2 < l2));
       const float v = weight(d2, W ? lane_f(b.w, j) : 1.0f);
-      sum += v;
+      {
+#pragma clang fp contract(off)   // (the values are rounded before they are summed, as in the table)
+        sum += v;
+      }
       const int32_t cj = __builtin_amdgcn_readlane(cb, j);
       if (j + 1 == nb || __builtin_amdgcn_readlane(cb, j + 1) != cj) {   // (uniform)
         acc[mine ? cj + wl : wl] += sum;
@@ -966,8 +969,9 @@ k_merge(SplatArgs a, int32_t n_targets) {
 // unit, piece offset and extents are uniform; a voxel that it does not cover reads
 // the zero word).  Later units of multi-unit slots follow neighbour by neighbour,
 // each set of 64 tested at once.  The sums are kept in double, neighbours in a fixed
-// order, then later units in order.  Bound by instruction issue (town, walked: 690
-// vector instructions per target).  k_merge's tables and barriers, every candidate
+// order, then later units in order.  Bound by instruction issue on the town
+// (walked: 690 vector instructions per target), close to memory on the LiDAR scan (its
+// 591 MB in 135 us are 4.4 TB/s, a large copy's rate 4.8).  k_merge's tables and barriers, every candidate
 // loaded, and now: LiDAR scan 238 us and 131, stereo frames 150 and 85 per insert,
 // town 869 and 640 (793 walked), its replay 232 and 195 (208 walked).  Offsets from
 // a table in LDS and loads with a range per region: town 767, stereo 91 to 121.  For

@@ -44,3 +44,32 @@ def test_rows_per_unit(lv, B, soft):
     torch.cuda.synchronize()
     assert m.stats()["n_hits"] == n
     compare_map(m, om, K, rtol=ALPHA_RTOL)
+
+
+@pytest.mark.parametrize("soft", [False, True])
+@pytest.mark.parametrize("lv", [0.4, 1.0, 1.5])
+def test_few_rows_have_the_bits_of_many(lv, soft):
+    # rows in one corner of a block, alone (a unit of few rows) and with 16 rows in the
+    # opposite corner: the voxels around the first corner hold the same bits
+    import torch
+    from paper_1909_04631_amd import SemanticMap
+    print(f"[case] few rows l/res={lv} soft={soft}", flush=True)
+    rng = np.random.default_rng(int(10 * lv))
+    B = 16
+    for n in (1, 2, 5, 9, 16):
+        xyz = np.concatenate([rng.uniform(0.0, 4 * RES, size=(n, 3)),
+                              rng.uniform(11 * RES, 15.9 * RES, size=(16, 3))]).astype(np.float32)
+        ijk = cuda(np.stack(np.meshgrid(*[np.arange(-3, 7)] * 3, indexing="ij"), -1).reshape(-1, 3).astype(np.int32))
+        w = np.zeros((n + 16, K), np.float32)
+        w[:, 1] = rng.uniform(0.1, 1.0, size=n + 16)
+        got = []
+        for rows in (n, n + 16):
+            m = SemanticMap(RES, B, lv * RES, 0.1, K, 1e-3)
+            if soft:
+                m.insert_scan_soft(cuda(xyz[:rows]), cuda(w[:rows]), (0.0, 0.0, 0.0), 0.0)
+            else:
+                m.insert_scan(cuda(xyz[:rows]), cuda(np.ones(rows, np.int32)), (0.0, 0.0, 0.0), 0.0)
+            got.append(m.query(ijk)["alpha"])
+            assert m.stats()["n_hits"] == rows
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], got[1]), n
