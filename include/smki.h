@@ -60,9 +60,9 @@ typedef struct smki_batch smki_batch;   /* a recorded batched insert (smki_batch
 typedef struct smki_options {
   int64_t initial_blocks;   /* initial pool capacity in blocks (0: 4096); grows on demand */
   int32_t unit_budget;      /* rows of one (class, block) that one splat work unit
-                               takes (0: chosen per insert from its rows, 128 to 512; at
-                               most 2^24); a (class, block) holding more rows is split
-                               into several units */
+                               takes (0: chosen per insert from its rows and the pairs
+                               that hold them, 128 to 512; at most 2^24); a (class,
+                               block) holding more rows is split into several units */
   int32_t model;            /* SMKI_MODEL_SBKI (default) or SMKI_MODEL_SCSM; l and sigma0
                                are not used by the counting model */
   int32_t selection;        /* SMKI_SELECT_EXACT (default) or SMKI_SELECT_FACE_BLOCKS

@@ -971,7 +971,7 @@ k_merge(SplatArgs a, int32_t n_targets) {
 // each set of 64 tested at once.  The sums are kept in double, neighbours in a fixed
 // order, then later units in order.  Bound by instruction issue on the town
 // (walked: 690 vector instructions per target), close to memory on the LiDAR scan (its
-// 591 MB in 135 us are 4.4 TB/s, a large copy's rate 4.8).  k_merge's tables and barriers, every candidate
+// 591 MB in 134 us are 4.4 TB/s, a large copy's rate 4.8).  k_merge's tables and barriers, every candidate
 // loaded, and now: LiDAR scan 238 us and 131, stereo frames 150 and 85 per insert,
 // town 869 and 640 (793 walked), its replay 232 and 195 (208 walked).  Offsets from
 // a table in LDS and loads with a range per region: town 767, stereo 91 to 121.  For
