@@ -522,10 +522,11 @@ def bench_face_blocks(torch, m_exact, xyz, lab, vox, s, p, SemanticMap, steps):
             "hit_voxels_label_changed_frac": float((a_face["label"] != a_ex["label"]).float().mean())}
 
 
-def splat_traffic():
-    """HBM bytes per k_splat launch on this workload from the committed counter
-    profile (FETCH_SIZE and WRITE_SIZE, each scaled by a 1 GiB copy measured the
-    same way), or None when the kernel source changed since it was taken."""
+def splat_traffic(field="hbm_bytes_per_launch"):
+    """HBM bytes per k_splat launch (field: of another kernel) on this workload from
+    the committed counter profile (FETCH_SIZE and WRITE_SIZE, each scaled by a 1 GiB
+    copy measured the same way), or None when the kernel source changed since it was
+    taken."""
     import hashlib
     prof = os.path.join(HERE, "profiles", "k_splat_lidar_hbm_traffic.txt")
     src = os.path.join(HERE, "paper_1909_04631_amd", "csrc", "splat.hip")
@@ -537,9 +538,9 @@ def splat_traffic():
             k, v = line.split("=", 1)
             fields[k.strip()] = v.strip()
     digest = hashlib.sha256(open(src, "rb").read()).hexdigest()
-    if fields.get("splat_hip_sha256") != digest or "hbm_bytes_per_launch" not in fields:
+    if fields.get("splat_hip_sha256") != digest or field not in fields:
         return None
-    return float(fields["hbm_bytes_per_launch"])
+    return float(fields[field])
 
 
 def bench_batched(torch, dev, SemanticMap, town, reps=3):
@@ -657,7 +658,6 @@ def kernel_table(st, p, copy_bw):
         return None
     nh, nf = st["n_hits"], st["n_free"]
     nt = nh + nf
-    V = st["n_updated_voxels"]
     # algorithmic bytes per launch
     alg = {
         "k_count": 16.0 * nh + 12.0 * nh,                  # read xyz+label, write counts/flags
@@ -666,12 +666,13 @@ def kernel_table(st, p, copy_bw):
         "k_hist": 4.0 * nt,                                # one key read per row
         "k_scatter": 16.0 * nt,                            # key + index in and out
         "k_query": 12.0 * nh + 4.0 * (2 * p.K + 2) * nh,   # ijk in; K alpha read, mean out, label, p_occ
-        "k_merge": 8.0 * p.K * V,                          # every updated voxel's alpha read + written
+        # (counted: which classes of a voxel are read and written is known to the merge alone)
+        "k_merge": splat_traffic("merge_hbm_bytes_per_launch"),
     }
     out = {}
     for k, b in alg.items():
         us = dur.get(k) or dur.get(k + "_list")             # (k_merge_list: the merge at B = 4)
-        if us:
+        if us and b:
             out[k] = {"algorithmic_bytes": b, "mean_us": us, "GBps": b / (us * 1e-6) / 1e9,
                       "frac_of_peak": b / (us * 1e-6) / HBM_PEAK,
                       "frac_of_copy": b / (us * 1e-6) / copy_bw}
