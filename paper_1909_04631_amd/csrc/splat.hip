@@ -511,7 +511,7 @@ __global__ void __launch_bounds__(SMKI_WAVE) k_splat(SplatArgs a) {
 // all 64 rows took 11 KB a wavefront (14 a CU), one of 16 rows 4.7 KB (28, by the
 // registers).  Splat at l / res = 1.5, k_splat with two rows a step, this kernel with 64
 // rows in the table, and now: the town's 1.7e8 rows 6.3, 4.5 and 4.0 ms; 2e5 rows in
-// 1.3e5 units 121, 247 and 130 us (region stores; the whole call 484, 568 and 428), in
+// 1.3e5 units 121, 247 and 130 us (region stores; the whole call 484, 568 and 450), in
 // 2.7e4 units 41, 67 and 42.  32 rows in the table: 4.1 ms and 188 us, without the
 // form for few rows (16 without it: 4.2 and 170).
 template <int B, int R, bool W>
